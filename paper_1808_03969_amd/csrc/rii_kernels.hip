@@ -126,6 +126,27 @@ int set_lds0(Kern kern, size_t bytes) { return set_lds_impl(reinterpret_cast<con
     default: { constexpr int MT = 0; __VA_ARGS__; } break;  \
   }
 
+void launch_build_lut(const rii_index* idx, const float* q, int Q, float* lut, hipStream_t st) {
+  // Queries per block: enough blocks to fill the chip first (2048 of four waves are a chip-load),
+  // then up to 16, where reading the code word no longer shows (10^4 queries, M = 16, 164 MB of
+  // tables: 540 us with one query per block, 43 us with 16; at one query the blocks are what counts
+  // and per is 1).
+  const int per = std::min(16, std::max(1, (int)((int64_t)Q * idx->M / 2048)));
+  const dim3 grid((unsigned)idx->M, (unsigned)((Q + per - 1) / per));
+#define RII_LUT(DS) k_build_lut<DS><<<grid, 256, 0, st>>>(idx->d_cb, q, idx->D, idx->M, idx->Ds, Q, per, lut)
+  switch (idx->Ds) {
+    case 2: RII_LUT(2); break;
+    case 3: RII_LUT(3); break;
+    case 4: RII_LUT(4); break;
+    case 6: RII_LUT(6); break;
+    case 8: RII_LUT(8); break;
+    case 12: RII_LUT(12); break;
+    case 16: RII_LUT(16); break;
+    default: RII_LUT(0); break;
+  }
+#undef RII_LUT
+}
+
 // Split max_rows rows per query into equal chunks (one block each): about kWantBlocks blocks
 // in total when the batch is small, never chunks shorter than kMinTiles tiles.
 void scan_chunks(int Q, int64_t max_rows, int64_t* nchunks_out, int64_t* chunk_rows_out) {
@@ -412,7 +433,7 @@ int rii_build_lut(const rii_index_t* idx, const float* q, int Q, float* lut, voi
   if (!idx || !q || !lut || Q < 1) return RII_ERR_INVALID_ARG;
   if (Q > 65535) return RII_ERR_UNSUPPORTED;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  k_build_lut<<<dim3(idx->M, Q), 256, 0, st>>>(idx->d_cb, q, idx->D, idx->M, idx->Ds, lut);
+  launch_build_lut(idx, q, Q, lut, st);
   RII_HIP(hipGetLastError());
   return RII_OK;
 }
@@ -717,7 +738,7 @@ static int check_query_args(const rii_index_t* idx, const float* q, int Q, int t
 static int run_query(const rii_index* idx, const QueryPlan& p, const float* q, int Q, int topk,
                      const int32_t* target_ids, const int64_t* target_offsets, int64_t L, int32_t* ids, float* dist,
                      void* ws, hipStream_t st) {
-  const int M = idx->M, K = idx->K;
+  const int K = idx->K;
   const bool has_lists = K > 0;
   uint8_t* w = static_cast<uint8_t*>(ws);
   float* lut = reinterpret_cast<float*>(w); w += p.lut_b;
@@ -726,7 +747,7 @@ static int run_query(const rii_index* idx, const QueryPlan& p, const float* q, i
   int32_t* probe = reinterpret_cast<int32_t*>(w); w += p.probe_b;
   void* stage_ws = w;
 
-  k_build_lut<<<dim3(M, Q), 256, 0, st>>>(idx->d_cb, q, idx->D, M, idx->Ds, lut);
+  launch_build_lut(idx, q, Q, lut, st);
   k_plan<<<(Q + 255) / 256, 256, 0, st>>>(target_offsets, idx->N, Q, idx->theta, K, L, p.pmax, qmode, nprobe_q);
   int rc = RII_OK;
   // linear-scan branch (mode 0)
