@@ -42,6 +42,7 @@ namespace {
 #include "rii_dev_scan_w.inc"
 #include "rii_dev_scan_batched.inc"
 #include "rii_dev_select.inc"
+#include "rii_dev_coarse.inc"
 #include "rii_dev_ivf.inc"
 #include "rii_dev_offline.inc"
 #include "rii_dev_bench.inc"
@@ -70,6 +71,7 @@ int ensure_ws(const rii_index* idx, size_t bytes) {
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 constexpr int64_t kBatchChunkBytes = (int64_t)384 << 20;  // rows of a large batch are scanned in chunks of about this size
+constexpr int kCoarseSplitQ = 32, kCoarseSplitK = 8192;  // coarse ranking of few queries over many centres: distances first (see coarse_rank)
 constexpr int kSubsetGeneration = RII_SUBSET_GENERATION;  // queries per launch of a subset scan with one block per query
 
 
@@ -578,8 +580,18 @@ int rii_topk(const float* cand_dist, const int32_t* cand_ids, const int64_t* can
   return RII_OK;
 }
 
-// coarse ranking into caller buffers; `ws` must hold what coarse_ws_bytes() says
+// Coarse ranking into caller buffers; `ws` must hold what coarse_ws_bytes() says.  Which way:
+//   n <= RII_MAX_TOPK, K <= kRankMaxRows: k_rank_lists, the distances computed in the kernel --
+//     except for few queries over many centres, where a chip-wide k_adc_all computes them first
+//     (K = 16384, M = 32: 19 us against 32 for one query, 26 against 32 for 32 queries; at K = 4096
+//     the second launch costs what it saves: 14 against 12);
+//   n <= RII_MAX_TOPK, more centres than a block's LDS holds: the scan kernels over the stored form;
+//   n above that: all distances sorted (k_sort_segments, K <= RII_MAX_SORT).
+static bool coarse_in_lds(int K, int nprobe) { return nprobe <= RII_MAX_TOPK && K <= kRankMaxRows; }
+static bool coarse_split(int Q, int K) { return Q <= kCoarseSplitQ && K >= kCoarseSplitK; }
+
 static size_t coarse_ws_bytes(const rii_index* idx, int Q, int nprobe) {
+  if (coarse_in_lds(idx->K, nprobe)) return coarse_split(Q, idx->K) ? align_up((size_t)Q * idx->K * 4, 256) : 256;
   if (nprobe <= RII_MAX_TOPK) return scan_ws_bytes(idx->M, Q, idx->K, nprobe);
   return align_up((size_t)Q * idx->K * 4, 256) + align_up((size_t)(Q + 1) * 8, 256);
 }
@@ -587,17 +599,36 @@ static size_t coarse_ws_bytes(const rii_index* idx, int Q, int nprobe) {
 static int coarse_rank(const rii_index* idx, const float* lut, int Q, int nprobe, int32_t* list_ids, float* list_d0,
                        int out_stride, const int* qmode, int want_mode, void* ws, hipStream_t st) {
   const int M = idx->M, K = idx->K;
-  if (nprobe <= RII_MAX_TOPK) {
+  const bool in_lds = coarse_in_lds(K, nprobe);
+  if (nprobe <= RII_MAX_TOPK && !in_lds) {
     return launch_scan(idx, idx->d_coarse_st, idx->plane_coarse, K, lut, Q, kLinear, nullptr, nullptr, K, nprobe, list_ids, list_d0,
                        out_stride, qmode, want_mode, ws, st);
   }
-  if (K > RII_MAX_SORT) return RII_ERR_UNSUPPORTED;
   float* d0 = static_cast<float*>(ws);
+  const bool split = !in_lds || coarse_split(Q, K);
+  if (split) {
+    const size_t lds = (size_t)M * 1024;
+    const dim3 grid((K + 255) / 256, Q);
+    DISPATCH_M(M, { int rc = set_lds(k_adc_all<MT>, lds); if (rc) return rc;
+                    k_adc_all<MT><<<grid, 256, lds, st>>>(idx->d_coarse, K, M, lut, d0, qmode, want_mode); });
+  }
+  if (in_lds) {
+    const size_t lds = rank_lds(M, K, nprobe, !split);
+    // one block per query: small blocks, several to a CU, when the queries fill the chip
+    const int threads = Q < kWantBlocks ? 1024 : K <= 2048 ? 256 : 512;
+    if (split) {
+      int rc = set_lds(k_rank_lists<0, true>, lds);
+      if (rc) return rc;
+      k_rank_lists<0, true><<<Q, threads, lds, st>>>(nullptr, K, M, nullptr, d0, nprobe, out_stride, list_ids, list_d0, qmode, want_mode);
+    } else {
+      DISPATCH_M(M, { int rc = set_lds(k_rank_lists<MT, false>, lds); if (rc) return rc;
+                      k_rank_lists<MT, false><<<Q, threads, lds, st>>>(idx->d_coarse, K, M, lut, nullptr, nprobe, out_stride,
+                                                                       list_ids, list_d0, qmode, want_mode); });
+    }
+    RII_HIP(hipGetLastError());
+    return RII_OK;
+  }
   int64_t* off = reinterpret_cast<int64_t*>(static_cast<uint8_t*>(ws) + align_up((size_t)Q * K * 4, 256));
-  const size_t lds = (size_t)M * 1024;
-  dim3 grid((K + 255) / 256, Q);
-  DISPATCH_M(M, { int rc = set_lds(k_adc_all<MT>, lds); if (rc) return rc;
-                  k_adc_all<MT><<<grid, 256, lds, st>>>(idx->d_coarse, K, M, lut, d0, qmode, want_mode); });
   k_iota_offsets<<<(Q + 256) / 256, 256, 0, st>>>(off, Q, K);
   SelectArgs s{};
   s.cand_dist = d0; s.cand_offsets = off; s.k = nprobe; s.out_stride = out_stride;
@@ -795,8 +826,9 @@ int rii_index_reserve_workspace(rii_index_t* idx, int Q, int topk, int64_t max_t
   // every stage's need, as bounds that grow with Q and topk (so smaller batches fit as well)
   size_t stage = scan_ws_bound(M, Q, idx->N, topk);
   if (K > 0 && nprobe > 0) {
-    const size_t coarse = nprobe <= RII_MAX_TOPK ? scan_ws_bound(M, Q, K, nprobe)
-                                                 : align_up((size_t)Q * K * 4, 256) + align_up((size_t)(Q + 1) * 8, 256);
+    const size_t coarse = coarse_in_lds(K, nprobe)   ? align_up((size_t)std::min(Q, kCoarseSplitQ) * K * 4, 256) + 256
+                          : nprobe <= RII_MAX_TOPK ? scan_ws_bound(M, Q, K, nprobe)
+                                                   : align_up((size_t)Q * K * 4, 256) + align_up((size_t)(Q + 1) * 8, 256);
     const size_t ivf = kScanArrays * align_up((size_t)Q * 4, 256) + ((size_t)Q + kWantBlocks) * topk * 8 + 256;
     stage = std::max(stage, std::max(coarse, ivf));
   }

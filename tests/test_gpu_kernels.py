@@ -29,3 +29,36 @@ def test_tables_over_widths_and_batches(Ds, M, Q, rii, oracle_lib):
     lut = rii.rii_build_lut(rii.Index(cb), torch.from_numpy(q).cuda())
     torch.cuda.synchronize()
     assert np.array_equal(t2n(lut), oracle_lib.lut(cb, q))
+
+
+def plain_index(rii, oracle, rng, N, M, K, Ds=2, repeat=None):
+    """Random code books and codes with K coarse centres; `repeat`: that many copies of one centre."""
+    cb = rng.normal(size=(M, 256, Ds)).astype(np.float32)
+    codes = rng.integers(0, 256, size=(N, M), dtype=np.uint8)
+    coarse = rng.integers(0, 256, size=(K, M), dtype=np.uint8)
+    if repeat:
+        coarse[rng.permutation(K)[:repeat]] = coarse[0]
+    a = rng.integers(0, K, size=N).astype(np.int32)
+    off, lids = oracle.build_lists(a, K)
+    index = rii.Index(cb)
+    index.add(codes)
+    index.set_lists(coarse, off, lids)
+    return dict(cb=cb, codes=codes, coarse=coarse, off=off, lids=lids, index=index)
+
+
+# few / many queries (one large block or several small ones to a CU), few queries over many centres
+# (distances computed by a kernel of their own), all centres asked for, equal distances at the cut --
+# fewer and more of them than the block can sort
+@pytest.mark.parametrize("M,K,Q,n,repeat", [(8, 1, 3, 1, 0), (16, 97, 300, 97, 0), (12, 1000, 5, 64, 0), (32, 8192, 32, 100, 0),
+                                            (32, 8192, 33, 256, 0), (64, 9000, 2, 1024, 0), (64, 16384, 257, 1000, 0),
+                                            (16, 3000, 300, 10, 200), (8, 4096, 270, 8, 4000), (16, 4096, 7, 300, 4096)])
+def test_ranking_of_lists(M, K, Q, n, repeat, rii, oracle_lib):
+    rng = np.random.default_rng(K + Q)
+    d = plain_index(rii, oracle_lib, rng, 2000, M, K, repeat=repeat)
+    q = rng.normal(size=(Q, 2 * M)).astype(np.float32)
+    ids, d0 = rii.rii_coarse_assign(d["index"], rii.rii_build_lut(d["index"], torch.from_numpy(q).cuda()), n)
+    torch.cuda.synchronize()
+    A = oracle_lib.lut(d["cb"], q)
+    for i in range(0, Q, max(1, Q // 9)):
+        ref = oracle_lib.coarse_rank(A[i], d["coarse"], n)
+        assert np.array_equal(t2n(ids)[i], ref[0]) and np.array_equal(t2n(d0)[i], ref[1]), i
