@@ -883,10 +883,31 @@ int rii_query_noalloc(const rii_index_t* idx, const float* q, int Q, int topk, c
 int rii_encode_device(const rii_index_t* idx, const float* x, int64_t n, uint8_t* codes_out, void* stream) {
   if (!idx || n < 0 || (n > 0 && (!x || !codes_out))) return RII_ERR_INVALID_ARG;
   if (n == 0) return RII_OK;
-  const int Ds = idx->Ds;
+  const int Ds = idx->Ds, M = idx->M;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  // The code book's fragments are 16 ceil(Ds / 4) registers a lane: up to Ds = 16 they and the rest
+  // of k_encode_mfma stay in registers, above that the kernel with the code book in LDS runs.
+  if (Ds <= 16 && (M + 3) / 4 <= 65535) {
+    // a wave keeps its sub-space: two or three blocks of four sub-spaces run on a CU (by its registers), each
+    // over every gridDim.x-th 64 vectors
+    const int64_t tiles = (n + 63) / 64, groups = (M + 3) / 4;
+    const int64_t want = std::max<int64_t>(1, (int64_t)kWantBlocks * (Ds <= 4 ? 3 : 2) / groups);
+    const dim3 grid((unsigned)std::min(tiles, want), (unsigned)groups);
+#define RII_ENCODE(S)                                                                                        \
+  if (Ds == 4 * S) k_encode_mfma<S, true><<<grid, 256, 0, st>>>(idx->d_cb, x, n, idx->D, M, Ds, codes_out);  \
+  else k_encode_mfma<S, false><<<grid, 256, 0, st>>>(idx->d_cb, x, n, idx->D, M, Ds, codes_out)
+    switch ((Ds + 3) / 4) {
+      case 1: RII_ENCODE(1); break;
+      case 2: RII_ENCODE(2); break;
+      case 3: RII_ENCODE(3); break;
+      default: RII_ENCODE(4); break;
+    }
+#undef RII_ENCODE
+    RII_HIP(hipGetLastError());
+    return RII_OK;
+  }
   size_t lds = (size_t)512 * Ds * 4;
   if (lds > 160 * 1024) return RII_ERR_UNSUPPORTED;
-  hipStream_t st = static_cast<hipStream_t>(stream);
   int rc = set_lds(k_encode, lds);
   if (rc) return rc;
   const int64_t max_rows = (int64_t)1 << 30;

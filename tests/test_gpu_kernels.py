@@ -62,3 +62,33 @@ def test_ranking_of_lists(M, K, Q, n, repeat, rii, oracle_lib):
     for i in range(0, Q, max(1, Q // 9)):
         ref = oracle_lib.coarse_rank(A[i], d["coarse"], n)
         assert np.array_equal(t2n(ids)[i], ref[0]) and np.array_equal(t2n(d0)[i], ref[1]), i
+
+
+# every number of matrix steps with and without a coordinate to spare, the width past them; batches below, at
+# and past a wave's 64 vectors and a grid's worth of them; code words that coincide or differ by a
+# rounding (decided by the defined sums), vectors that are code words, that are huge, tiny or infinite
+@pytest.mark.parametrize("Ds,M,n", [(1, 8, 65), (2, 64, 1000), (3, 32, 63), (4, 5, 64), (5, 12, 1), (6, 16, 20011), (8, 16, 50003),
+                                    (12, 8, 129), (13, 3, 700), (16, 8, 40000), (20, 4, 300)])
+def test_encode_over_widths_and_ties(Ds, M, n, rii, oracle_lib):
+    rng = np.random.default_rng(Ds * 1000 + M)
+    cb = rng.normal(size=(M, 256, Ds)).astype(np.float32)
+    cb[:, 200] = cb[:, 17]
+    cb[:, 90] = np.nextafter(cb[:, 91], np.float32(np.inf))
+    cb[0] = np.round(cb[0] * 4)  # a grid: exact ties
+    x = rng.normal(size=(n, M * Ds)).astype(np.float32)
+    x[::7] = np.round(x[::7] * 2) / 2
+    x[::5] = cb[np.arange(M), rng.integers(0, 256, size=((n + 4) // 5, M))].reshape(-1, M * Ds)
+    if n > 40:
+        x[3] *= np.float32(1e18)
+        x[11] *= np.float32(1e-25)
+        x[12] = 0
+        x[22, Ds // 2] = np.inf
+        x[31, :] = -np.inf
+    ref = oracle_lib.encode(cb, x)
+    buf = torch.empty(n * M * Ds + 1, dtype=torch.float32, device="cuda")
+    for shift in (0, 1):  # vectors at an address that is a multiple of 16, and of 4 only
+        xd = buf[shift:shift + n * M * Ds].view(n, M * Ds)
+        xd.copy_(torch.from_numpy(x))
+        got = rii.rii_encode_device(rii.Index(cb), xd)
+        torch.cuda.synchronize()
+        assert np.array_equal(t2n(got), ref), shift
