@@ -92,3 +92,18 @@ def test_encode_over_widths_and_ties(Ds, M, n, rii, oracle_lib):
         got = rii.rii_encode_device(rii.Index(cb), xd)
         torch.cuda.synchronize()
         assert np.array_equal(t2n(got), ref), shift
+
+
+# few rows (below, at and past a block) and many, every number of outputs per thread, inner tiles with and
+# without a remainder, several blocks of outputs
+@pytest.mark.parametrize("D,n", [(1, 5), (16, 32), (17, 33), (64, 1), (128, 1000), (300, 77), (32, 65536), (33, 65500), (90, 66001),
+                                 (128, 65409), (129, 32770), (200, 33000)])
+def test_rotation_over_dimensions(D, n, rii, oracle_lib):
+    rng = np.random.default_rng(D)
+    R = rng.normal(size=(D, D)).astype(np.float32)
+    x = rng.normal(size=(n, D)).astype(np.float32)
+    x[n // 2] = -0.0
+    y = rii.rii_rotate(torch.from_numpy(R).cuda(), torch.from_numpy(x).cuda())
+    torch.cuda.synchronize()
+    ref = oracle_lib.rotate(R, x)
+    assert np.array_equal(t2n(y).view(np.uint32), ref.view(np.uint32))
