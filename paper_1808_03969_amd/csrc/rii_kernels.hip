@@ -44,6 +44,7 @@ namespace {
 #include "rii_dev_select.inc"
 #include "rii_dev_coarse.inc"
 #include "rii_dev_ivf.inc"
+#include "rii_dev_few.inc"
 #include "rii_dev_offline.inc"
 #include "rii_dev_bench.inc"
 
@@ -198,6 +199,69 @@ bool plan_batch(int M, int Q, int64_t rows, int topk, int64_t* nchunks_out, int6
   return true;
 }
 
+// Launch shape of k_few for Q queries of about `rows` rows each.
+struct FewShape {
+  int threads, split, slot, cap;
+};
+// A block hands over at most `slot` keys.  The blocks of a query together stay within the minima that
+// scan_ws_bytes() counts for it (16 KB, 8 KB from four queries on), so that no call needs more scratch for them.
+FewShape few_shape(int M, int Q, int64_t rows, int k, bool capped, bool uneven = false) {
+  FewShape f;
+  // M <= 16: five blocks of four waves share a CU, above that three (M = 32) or two (M = 64) of eight
+  f.threads = capped ? 1024 : M <= 16 ? 256 : 512;
+  const int round = f.threads * (M == 8 || M == 16 ? 4 : 2);
+  f.cap = round + std::max(512, 2 * k);
+  f.slot = (k + std::max(k / 4, 16) + 15) / 16 * 16;
+  const int most = (Q < 4 ? 16384 : 8192) / (f.slot * 8);
+  const int64_t rounds = (rows + round - 1) / round;
+  // Several blocks a query cost about 10 us (a launch that clears, handing over, merging), a round of a
+  // block that has its CU to itself 2.5 us: below four rounds splitting loses, and once the queries
+  // alone give every other CU a block it has to save four rounds (256 queries, M = 16: 2000 rows 41 us
+  // in two blocks, 28 us in one; 32,000 rows 77 and 131 us).  Target sets of very different sizes would
+  // leave the largest to run alone when there are few blocks a CU: those of many rounds are cut up
+  // all the same (500 sets of up to 25,000: 73 -> 55 us).
+  int64_t want = Q <= kWantBlocks / 2 ? (rounds >= 4 ? 2 * kWantBlocks / Q : 1)
+                                      : std::min<int64_t>(rounds / 4, 4 * kWantBlocks / Q);
+  if (uneven && Q < 4 * kWantBlocks && rounds > 16) want = std::max(want, (rounds + 11) / 12);
+  f.split = capped ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(rounds, most), want));
+  return f;
+}
+size_t few_ws_bytes(const FewShape& f, int Q) {
+  return kScanArrays * align_up((size_t)Q * 4, 256) + (f.split > 1 ? (size_t)Q * f.split * f.slot * 8 : 0) + 256;
+}
+
+// `ws` holds few_ws_bytes (looked at only when a query has several blocks).
+template <int SRC>
+int launch_few(FewArgs a, const FewShape& f, int Q, void* ws, hipStream_t st) {
+  a.cap = f.cap;
+  a.slot = f.slot;
+  if (f.split > 1) {
+    const size_t cstride = align_up((size_t)Q * 4, 256) / 4;
+    uint32_t* tau = static_cast<uint32_t*>(ws);
+    a.tau_g = tau; a.cand_cnt = tau + cstride; a.done_cnt = tau + 3 * cstride;
+    a.cand = reinterpret_cast<uint64_t*>(static_cast<uint8_t*>(ws) + kScanArrays * cstride * 4);
+    k_init_scan<<<(Q + 255) / 256, 256, 0, st>>>(tau, Q, (int)cstride, nullptr, 0);
+  }
+  const size_t lds = few_lds(a.M, a.cap, a.nprobe, SRC == kFewCapped);
+  const dim3 grid((unsigned)f.split, (unsigned)Q);
+  DISPATCH_M(a.M, { int rc = set_lds0(k_few<MT, SRC>, lds); if (rc) return rc;
+                    k_few<MT, SRC><<<grid, f.threads, lds, st>>>(a); });
+  RII_HIP(hipGetLastError());
+  return RII_OK;
+}
+
+// Rows per query up to which a scan goes to k_few.  Measured against the streaming kernels (which it
+// would otherwise go to) for batches of 1 .. 4000 queries; microseconds there / here, top-100:
+//   lists     M = 16:  1 query 8,000 rows 45 / 32, 64,000 38 / 37, 128,000 39 / 47; 4000 queries 655 / 255,
+//             1426 / 907, 1976 / 1690;  M = 32:  4000 queries 8,000 rows 786 / 447, 32,000 1323 / 1035, 64,000
+//             1747 / 1833 (its streaming kernel abandons rows half-way)
+//   target sets  M = 16:  1 query 8,000 rows 38 / 24, 64,000 69 / 34; 4000 queries 692 / 221, 2382 / 2446
+//   whole array  M = 16:  1 query 8,000 rows 36 / 23, 64,000 56 / 33, 128,000 45 / 45; 4000 queries 791 / 169,
+//             1193 / 849, 1441 / 1596 (four queries a block);  M = 32:  4000 queries 64,000 rows 1813 / 1713
+bool few_lists(int M, int64_t rows) { return rows <= (M == 32 ? 40000 : 65536); }
+bool few_subset(int64_t rows) { return rows <= 65536; }
+bool few_linear(int M, int64_t rows) { return rows <= (M == 32 ? 65536 : 100000); }
+
 // Scan `nrows_max` rows per query (linear: the whole array) and leave per-block partial keys in
 // the workspace; then select.  Workspace layout: [tau Q u32][partial Q*nchunks*k u64].
 int launch_scan(const rii_index* idx, const uint8_t* codes, int64_t plane, int64_t N, const float* lut, int Q, int mode,
@@ -205,6 +269,19 @@ int launch_scan(const rii_index* idx, const uint8_t* codes, int64_t plane, int64
                 int32_t* ids, float* dist, int out_stride, const int* qmode, int want_mode, void* ws_base,
                 hipStream_t st) {
   const int M = idx->M;
+  if (Q > 65535) return RII_ERR_UNSUPPORTED;
+  const bool timed = mode == kLinear && idx->ev_start && idx->ev_stop && codes == idx->d_codes;
+  if (mode == kLinear ? few_linear(M, max_rows) && !idx->bench_half_table : few_subset(max_rows)) {
+    FewArgs f{};
+    f.codes = codes; f.plane = plane; f.M = M; f.lut = lut; f.N = N; f.target_ids = target_ids; f.target_offsets = target_offsets;
+    f.k = topk; f.ids = ids; f.dist = dist; f.out_stride = out_stride; f.qmode = qmode; f.want_mode = want_mode;
+    const FewShape shape = few_shape(M, Q, max_rows, topk, false, mode == kSubset);
+    if (mode == kSubset) return launch_few<kFewSubset>(f, shape, Q, ws_base, st);
+    if (timed) RII_HIP(hipEventRecord(static_cast<hipEvent_t>(idx->ev_start), st));
+    const int rc = launch_few<kFewLinear>(f, shape, Q, ws_base, st);
+    if (timed && !rc) RII_HIP(hipEventRecord(static_cast<hipEvent_t>(idx->ev_stop), st));
+    return rc;
+  }
   int64_t nchunks, chunk_rows;
   scan_chunks(Q, max_rows, &nchunks, &chunk_rows);
 
@@ -233,8 +310,6 @@ int launch_scan(const rii_index* idx, const uint8_t* codes, int64_t plane, int64
   a.done_cnt = done_cnt; a.ids = ids; a.dist = dist; a.out_stride = out_stride;
   a.qmode = qmode; a.want_mode = want_mode;
   dim3 grid((unsigned)nchunks, (unsigned)Q);
-  if (Q > 65535) return RII_ERR_UNSUPPORTED;
-  const bool timed = mode == kLinear && idx->ev_start && idx->ev_stop && codes == idx->d_codes;
   a.counters = timed ? idx->d_scan_counters : nullptr;
   if (topk <= kWaveK || rot_m(M)) {  // (rotated stored form: k_scan_w up to RII_MAX_TOPK, with a block-level buffer above kWaveK)
     // When a query's rows are split over several blocks, a short first pass over the leading
@@ -445,7 +520,10 @@ int rii_scan_linear_plan(const rii_index_t* idx, int Q, int topk, int* queries_p
   if (topk > RII_MAX_TOPK || !m_supported(idx->M) || Q > 65535) return RII_ERR_UNSUPPORTED;
   int64_t nchunks, chunk_rows, bchunks, brows;
   scan_chunks(Q, idx->N, &nchunks, &chunk_rows);
-  if (topk <= kWaveK && plan_batch(idx->M, Q, idx->N, topk, &bchunks, &brows)) {
+  if (few_linear(idx->M, idx->N)) {
+    *queries_per_block = 1;
+    *row_chunks = few_shape(idx->M, Q, idx->N, topk, false).split;
+  } else if (topk <= kWaveK && plan_batch(idx->M, Q, idx->N, topk, &bchunks, &brows)) {
     *queries_per_block = 4;
     *row_chunks = bchunks;
   } else if (topk <= kWaveK && rot_m(idx->M) && nchunks == 1 && Q >= 2 && topk > kWaveK4) {
@@ -483,13 +561,13 @@ int rii_bench_lds_lookups(int width, int blocks, int threads, int iters, int lds
 int rii_bench_scan_linear_half(rii_index_t* idx, const float* lut, int Q, int topk, int32_t* ids, float* dist,
                                void* stream) {
   if (!idx) return RII_ERR_INVALID_ARG;
-  int qpb = 0;
-  int64_t chunks = 0;
-  int rc = rii_scan_linear_plan(idx, Q, topk, &qpb, &chunks);
-  if (rc) return rc;
-  if (qpb != 4) return RII_ERR_UNSUPPORTED;  // only the four-queries-per-block kernel has the variant
+  if (Q < 1 || topk < 1) return RII_ERR_INVALID_ARG;
+  if (topk > RII_MAX_TOPK || !m_supported(idx->M) || Q > 65535) return RII_ERR_UNSUPPORTED;
+  int64_t chunks = 0, rows = 0;
+  // only the four-queries-per-block kernel has the variant (and it runs at any number of rows that kernel can take)
+  if (topk > kWaveK || !plan_batch(idx->M, Q, idx->N, topk, &chunks, &rows)) return RII_ERR_UNSUPPORTED;
   idx->bench_half_table = true;
-  rc = rii_adc_scan_linear(idx, lut, Q, topk, ids, dist, stream);
+  int rc = rii_adc_scan_linear(idx, lut, Q, topk, ids, dist, stream);
   idx->bench_half_table = false;
   return rc;
 }
@@ -654,6 +732,12 @@ int rii_coarse_assign(const rii_index_t* idx, const float* lut, int Q, int nprob
                      static_cast<hipStream_t>(stream));
 }
 
+// About how many members the `nprobe` lists of a query have, the candidate cap taken into account.
+static int64_t list_rows(const rii_index* idx, int nprobe, int64_t L) {
+  const int64_t rows = idx->N / idx->K * nprobe + (idx->N % idx->K) * nprobe / idx->K;
+  return L > 0 && L < rows ? L : rows;
+}
+
 // Blocks per query of the multi-block inverted-index scan.
 static int ivf_split(int Q, int nprobe) {
   int split = (kWantBlocks + Q - 1) / Q;
@@ -661,8 +745,11 @@ static int ivf_split(int Q, int nprobe) {
   return split < 1 ? 1 : split;
 }
 
-static size_t ivf_ws_bytes(int Q, int nprobe, int topk) {
-  return kScanArrays * align_up((size_t)Q * 4, 256) + (size_t)Q * ivf_split(Q, nprobe) * topk * 8 + 256;
+static size_t ivf_ws_bytes(const rii_index* idx, int Q, int nprobe, int64_t L, int topk, bool targets) {
+  const FewShape f = few_shape(idx->M, Q, list_rows(idx, nprobe, L), topk, targets && L > 0);
+  const size_t few = few_ws_bytes(f, Q);
+  if (topk > kWaveK) return few;
+  return std::max(few, kScanArrays * align_up((size_t)Q * 4, 256) + (size_t)Q * ivf_split(Q, nprobe) * topk * 8 + 256);
 }
 
 static int launch_ivf(const rii_index* idx, const float* lut, int Q, const int32_t* probe, int probe_stride,
@@ -670,12 +757,23 @@ static int launch_ivf(const rii_index* idx, const float* lut, int Q, const int32
                       int64_t L, int topk, int32_t* ids, float* dist, const int* qmode, int want_mode, void* ws,
                       hipStream_t st) {
   const int M = idx->M;
+  const bool capped = L > 0 && target_ids;
+  const int64_t rows = list_rows(idx, nprobe, capped ? 0 : L);
+  if (nprobe <= kIvfMaxProbe && Q <= 65535 && (capped || topk > kWaveK || few_lists(M, rows))) {
+    FewArgs f{};
+    f.codes = idx->d_codes_list; f.plane = idx->plane_list; f.M = M; f.lut = lut; f.N = idx->N;
+    f.target_ids = target_ids; f.target_offsets = target_offsets; f.list_ids = idx->d_list_ids; f.list_off = idx->d_list_off;
+    f.probe = probe; f.probe_stride = probe_stride; f.nprobe = nprobe; f.nprobe_q = nprobe_q; f.Lcap = L;
+    f.k = topk; f.ids = ids; f.dist = dist; f.out_stride = topk; f.qmode = qmode; f.want_mode = want_mode;
+    const FewShape shape = few_shape(M, Q, rows, topk, capped);
+    return capped ? launch_few<kFewCapped>(f, shape, Q, ws, st) : launch_few<kFewLists>(f, shape, Q, ws, st);
+  }
   IvfArgs a{};
   a.codes_list = idx->d_codes_list; a.plane = idx->plane_list; a.list_ids = idx->d_list_ids; a.list_off = idx->d_list_off; a.M = M;
   a.lut = lut; a.probe = probe; a.probe_stride = probe_stride; a.nprobe = nprobe; a.nprobe_q = nprobe_q;
   a.target_ids = target_ids; a.target_offsets = target_offsets; a.Lcap = L; a.k = topk;
   a.ids = ids; a.dist = dist; a.qmode = qmode; a.want_mode = want_mode;
-  if ((L == 0 || !target_ids) && topk <= kWaveK && nprobe <= kIvfMaxProbe && ws && Q <= 65535) {
+  if ((L == 0 || !target_ids) && topk <= kWaveK && nprobe <= kIvfMaxProbe && Q <= 65535) {
     // no candidate cap, or a cap without a target set: who scores which member does not matter,
     // so the members of the probed lists are dealt to the waves of one or more blocks per query
     const int split = ivf_split(Q, nprobe);
@@ -708,14 +806,10 @@ int rii_adc_scan_ivf(const rii_index_t* idx, const float* lut, int Q, const int3
   if ((target_ids == nullptr) != (target_offsets == nullptr)) return RII_ERR_INVALID_ARG;
   if (topk > RII_MAX_TOPK || !m_supported(idx->M)) return RII_ERR_UNSUPPORTED;
   if (L >= idx->N) L = 0;  // such a cap never cuts anything
-  void* ws = nullptr;
-  if ((L == 0 || !target_ids) && topk <= kWaveK) {
-    int rc = ensure_ws(idx, ivf_ws_bytes(Q, nprobe, topk));
-    if (rc) return rc;
-    ws = idx->ws;
-  }
+  int rc = ensure_ws(idx, ivf_ws_bytes(idx, Q, nprobe, L, topk, target_ids != nullptr));
+  if (rc) return rc;
   return launch_ivf(idx, lut, Q, probe_lists, nprobe, nprobe, nullptr, target_ids, target_offsets, L, topk, ids,
-                    dist, nullptr, 0, ws, static_cast<hipStream_t>(stream));
+                    dist, nullptr, 0, idx->ws, static_cast<hipStream_t>(stream));
 }
 
 // Scratch layout of the query procedure: tables, per-query plan, probed lists, then the stage
@@ -750,7 +844,7 @@ static int plan_query(const rii_index* idx, int Q, int topk, bool targets, int64
   p->probe_b = align_up((size_t)Q * p->pmax * 4, 256);
   const size_t scan_b = align_up(scan_ws_bytes(M, Q, p->lin_rows, topk), 256);
   const size_t coarse_b = has_lists ? align_up(coarse_ws_bytes(idx, Q, p->pmax), 256) : 0;
-  p->ivf_b = has_lists && topk <= kWaveK ? align_up(ivf_ws_bytes(Q, p->pmax, topk), 256) : 0;
+  p->ivf_b = has_lists ? align_up(ivf_ws_bytes(idx, Q, p->pmax, L, topk, targets), 256) : 0;
   p->total = p->lut_b + 2 * p->plan_b + p->probe_b + std::max(std::max(scan_b, coarse_b), p->ivf_b);
   return RII_OK;
 }
@@ -795,7 +889,7 @@ static int run_query(const rii_index* idx, const QueryPlan& p, const float* q, i
     rc = coarse_rank(idx, lut, Q, p.pmax, probe, nullptr, p.pmax, qmode, 1, stage_ws, st);
     if (rc) return rc;
     rc = launch_ivf(idx, lut, Q, probe, p.pmax, p.pmax, nprobe_q, target_ids, target_offsets, L, topk, ids, dist, qmode,
-                    1, p.ivf_b ? stage_ws : nullptr, st);
+                    1, stage_ws, st);
     if (rc) return rc;
   }
   RII_HIP(hipGetLastError());

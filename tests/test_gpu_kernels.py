@@ -107,3 +107,54 @@ def test_rotation_over_dimensions(D, n, rii, oracle_lib):
     torch.cuda.synchronize()
     ref = oracle_lib.rotate(R, x)
     assert np.array_equal(t2n(y).view(np.uint32), ref.view(np.uint32))
+
+
+# rounds of 1024 rows: below, at and past one and several; one block a query and several (few queries, and
+# many rounds); all lists of keys the block sorts or ranks; `copies`: that many rows share a code, so that
+# whole keys and not only distances decide what the buffer keeps
+@pytest.mark.parametrize("M,N,Q,topk,copies", [(4, 1, 3, 5, 1), (8, 1023, 300, 10, 1), (16, 1024, 2, 100, 1), (16, 1025, 257, 100, 1),
+                                               (16, 5000, 1, 128, 1), (32, 8193, 5, 1000, 1), (64, 20000, 300, 1, 1),
+                                               (12, 30011, 20, 100, 1), (16, 60000, 130, 300, 1), (8, 9000, 40, 100, 3000),
+                                               (16, 9000, 260, 100, 9000), (32, 7000, 2, 600, 3500)])
+def test_small_scans(M, N, Q, topk, copies, rii, oracle_lib):
+    rng = np.random.default_rng(N + Q)
+    cb = rng.normal(size=(M, 256, 2)).astype(np.float32)
+    codes = rng.integers(0, 256, size=(N, M), dtype=np.uint8)
+    if copies > 1:
+        codes = codes[rng.integers(0, max(1, N // copies), size=N)]
+    K = max(1, min(40, N // 50))
+    coarse = rng.integers(0, 256, size=(K, M), dtype=np.uint8)
+    # lists of very different lengths, the second one empty
+    off, lids = oracle_lib.build_lists(np.where(rng.random(N) < .3, 0, rng.integers(min(2, K - 1), K, size=N)).astype(np.int32), K)
+    index = rii.Index(cb)
+    index.add(codes)
+    index.set_lists(coarse, off, lids)
+    q = rng.normal(size=(Q, 2 * M)).astype(np.float32)
+    qd = torch.from_numpy(q).cuda()
+    lut = rii.rii_build_lut(index, qd)
+    A = oracle_lib.lut(cb, q)
+    # target sets: none, one identifier, all, a few, many; sorted
+    sizes = [[0, 1, N, N // 50, N // 3][i % 5] for i in range(Q)]
+    sets = [np.sort(rng.permutation(N)[:s]).astype(np.int32) for s in sizes]
+    toff = torch.from_numpy(np.concatenate([[0], np.cumsum(sizes)])).cuda()
+    tids = torch.from_numpy(np.concatenate(sets + [np.zeros(1, np.int32)])).cuda()
+    nprobe = (K + 1) // 2
+    probe, _ = rii.rii_coarse_assign(index, lut, nprobe)
+    got = dict(linear=rii.rii_adc_scan_linear(index, lut, topk),
+               subset=rii.rii_adc_scan_subset(index, lut, tids, toff, N, topk),
+               lists=rii.rii_adc_scan_ivf(index, lut, probe, topk),
+               first=rii.rii_adc_scan_ivf(index, lut, probe, topk, L=N // 3 + 1),
+               members=rii.rii_adc_scan_ivf(index, lut, probe, topk, tids, toff),
+               capped=rii.rii_adc_scan_ivf(index, lut, probe, topk, tids, toff, L=N // 9 + 1))
+    index.set_threshold(N // 10)
+    got["query"] = rii.rii_query(index, qd, topk, tids, toff, N, L=max(1, N // K))
+    torch.cuda.synchronize()
+    got = {n: (t2n(i), t2n(d)) for n, (i, d) in got.items()}
+    for i in sorted(set(range(0, Q, max(1, Q // 10))) | {Q - 1}):
+        S = sets[i]
+        iv = lambda L, S: oracle_lib.inverted_index(A[i], codes, coarse, off, lids, topk, nprobe, Lcap=L, S=S)[:2]
+        ref = dict(linear=oracle_lib.linear_scan(A[i], codes, topk), subset=oracle_lib.linear_scan(A[i], codes, topk, S=S),
+                   lists=iv(0, None), first=iv(N // 3 + 1, None), members=iv(0, S), capped=iv(N // 9 + 1, S),
+                   query=oracle_lib.query(cb, q[i], codes, coarse, off, lids, topk, max(1, N // K), N // 10, S=S)[:2])
+        for name, (ids, dist) in ref.items():
+            assert np.array_equal(got[name][0][i], ids) and np.array_equal(got[name][1][i], dist), (name, i)
