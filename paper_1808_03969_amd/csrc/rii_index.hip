@@ -22,6 +22,9 @@ extern "C" int rii_internal_assign_pruned(const rii_index* idx, const uint8_t* c
                                           const uint8_t* super, int G, const float* radius, const uint8_t* coarse_g,
                                           const int32_t* perm_g, const int32_t* group_off, int32_t* assign_out,
                                           unsigned long long* visited_total, hipStream_t st);
+extern "C" size_t rii_internal_assign_matrix_bytes(const rii_index* idx, int64_t n, int K);
+extern "C" int rii_internal_assign_matrix(const rii_index* idx, const uint8_t* codes, int64_t n, int64_t rot_base, int64_t plane,
+                                          const uint8_t* coarse, int K, int32_t* assign_out, void* scratch, hipStream_t st);
 extern "C" int rii_internal_assign_from_lists(const rii_index* idx, int32_t* d_out, hipStream_t st);
 extern "C" int rii_internal_spread_ids(int32_t* ids, int64_t* offsets, int nq, int64_t S, int64_t N, hipStream_t st);
 extern "C" int rii_internal_copy_rows(const uint8_t* in, int64_t in_rot, int64_t in_plane, const int32_t* ids,
@@ -40,6 +43,20 @@ void free_dev(T*& p) {
   if (p) (void)hipFree(p);
   p = nullptr;
 }
+
+struct DevBuf {
+  void* p = nullptr;
+  ~DevBuf() {
+    if (p) (void)hipFree(p);
+  }
+  int alloc(size_t bytes) {
+    if (hipMalloc(&p, bytes ? bytes : 16) == hipSuccess) return RII_OK;
+    (void)hipGetLastError();
+    return RII_ERR_OOM;
+  }
+  template <typename T>
+  T* as() { return static_cast<T*>(p); }
+};
 
 void drop_lists(rii_index* idx) {
   free_dev(idx->d_coarse);
@@ -100,6 +117,7 @@ struct CentreGroups {
 };
 
 constexpr int kPruneMinK = 1024;
+constexpr int64_t kMatrixMinItems = 256;
 
 // Cluster the K coarse codes into G groups in code space (three rounds of the same clustering
 // reconfigure uses) and record each group's radius under d_S.
@@ -177,11 +195,27 @@ int make_groups(rii_index* idx, const uint8_t* coarse, int K, CentreGroups& g) {
 
 // a(n) for n device-resident codes `rows` under the host coarse centres `coarse`; the result
 // stays on the device (d_out, n entries).  rot_base >= 0: `rows` is the base of a stored array with
-// planes `plane` apart and the items are its rows rot_base..; rot_base < 0: plain codes.  Brute
-// force for small K, pruned search (same result) for large K.
+// planes `plane` apart and the items are its rows rot_base..; rot_base < 0: plain codes.  Matrix products
+// for dimensions up to 128 unless the items are few, else brute force for small K and a pruned search
+// for large K (the same result each).
 int assign_rows_dev(rii_index* idx, const uint8_t* rows, int64_t n, int64_t rot_base, int64_t plane,
                     const uint8_t* coarse, int K, int32_t* d_out) {
   if (n == 0) return RII_OK;
+  const int64_t part = std::min<int64_t>(n, (int64_t)1 << 23);  // items per launch: bounds the list of undecided ones
+  const size_t scratch = n >= kMatrixMinItems ? rii_internal_assign_matrix_bytes(idx, part, K) : 0;
+  if (scratch) {
+    DevBuf d_coarse, d_scratch;
+    int rc = d_coarse.alloc((size_t)K * idx->M);
+    if (!rc) rc = d_scratch.alloc(scratch);
+    if (rc) return rc;
+    RII_HIP(hipMemcpy(d_coarse.p, coarse, (size_t)K * idx->M, hipMemcpyHostToDevice));
+    for (int64_t i = 0; i < n && !rc; i += part)
+      rc = rii_internal_assign_matrix(idx, rot_base >= 0 ? rows : rows + i * idx->M, std::min(part, n - i),
+                                      rot_base >= 0 ? rot_base + i : -1, plane, d_coarse.as<uint8_t>(), K, d_out + i, d_scratch.p, nullptr);
+    if (rc) return rc;
+    RII_HIP(hipDeviceSynchronize());
+    return RII_OK;
+  }
   if (K >= kPruneMinK) {
     CentreGroups g;
     int rc = make_groups(idx, coarse, K, g);
@@ -212,21 +246,7 @@ int assign_stored(rii_index* idx, int64_t first, int64_t n, const uint8_t* coars
   return rc;
 }
 
-// helpers of the threshold calibration
-
-struct DevBuf {
-  void* p = nullptr;
-  ~DevBuf() {
-    if (p) (void)hipFree(p);
-  }
-  int alloc(size_t bytes) {
-    if (hipMalloc(&p, bytes ? bytes : 16) == hipSuccess) return RII_OK;
-    (void)hipGetLastError();
-    return RII_ERR_OOM;
-  }
-  template <typename T>
-  T* as() { return static_cast<T*>(p); }
-};
+// helper of the threshold calibration
 
 // median of three timed runs of f() in milliseconds (f launches on the default stream)
 template <typename F>

@@ -1066,7 +1066,7 @@ int rii_internal_assign(const rii_index* idx, const uint8_t* codes, int64_t n, i
   const size_t lds = (size_t)M * 1024;
   int blocks = (int)std::min<int64_t>(n, 256 * 16);
   DISPATCH_M(M, { int rc2 = set_lds(k_assign<MT>, lds); if (rc2) return rc2;
-                  k_assign<MT><<<blocks, 256, lds, st>>>(idx->d_sym, codes, n, rot_base, plane, M, coarse, K, assign_out); });
+                  k_assign<MT><<<blocks, 256, lds, st>>>(idx->d_sym, codes, n, rot_base, plane, M, coarse, K, assign_out, nullptr); });
   RII_HIP(hipGetLastError());
   return RII_OK;
 }
@@ -1075,6 +1075,47 @@ int rii_assign(const rii_index_t* idx, const uint8_t* codes, int64_t n, const ui
                int32_t* assign_out, void* stream) {
   if (!idx || n < 0 || K < 1 || !coarse || (n > 0 && (!codes || !assign_out))) return RII_ERR_INVALID_ARG;
   return rii_internal_assign(idx, codes, n, -1, 0, coarse, K, assign_out, static_cast<hipStream_t>(stream));
+}
+
+// a(n) by matrix products (see k_assign_matrix); all pointers device.  Items as in rii_internal_assign, at most
+// 2^31 of them; scratch: rii_internal_assign_matrix_bytes, or 0 when the dimension is beyond the kernel.
+size_t rii_internal_assign_matrix_bytes(const rii_index* idx, int64_t n, int K) {
+  const int steps = (idx->D + 31) / 32, tiles = (K + 15) / 16;
+  if (steps > 4 || !m_supported(idx->M)) return 0;
+  return (size_t)tiles * steps * 2 * 64 * 16 + align_up((size_t)tiles * 64, 256) + 256 + align_up((size_t)(n + 1) * 4, 256);
+}
+
+int rii_internal_assign_matrix(const rii_index* idx, const uint8_t* codes, int64_t n, int64_t rot_base, int64_t plane,
+                               const uint8_t* coarse, int K, int32_t* assign_out, void* scratch, hipStream_t st) {
+  if (n == 0) return RII_OK;
+  const int M = idx->M, steps = (idx->D + 31) / 32, tiles = (K + 15) / 16;
+  if (!rot_m(M) && rot_base >= 0) { codes += rot_base * M; rot_base = -1; }
+  int rc = rii_internal_sym_table(idx, st);
+  if (rc) return rc;
+  uint8_t* w = static_cast<uint8_t*>(scratch);
+  bf16x8_t* frag = reinterpret_cast<bf16x8_t*>(w); w += (size_t)tiles * steps * 2 * 64 * 16;
+  float* c2 = reinterpret_cast<float*>(w); w += align_up((size_t)tiles * 64, 256);
+  uint32_t* cmax = reinterpret_cast<uint32_t*>(w); w += 256;
+  uint32_t* open = reinterpret_cast<uint32_t*>(w);
+  k_init_scan<<<1, 256, 0, st>>>(nullptr, 0, 0, cmax, 1);
+  k_init_scan<<<1, 256, 0, st>>>(nullptr, 0, 0, open, 1);
+  k_centre_frags<<<tiles, 64, 0, st>>>(idx->d_cb, M, idx->Ds, coarse, K, steps, frag, c2, cmax);
+#define RII_ASSIGN(S, T)                                                                              \
+  k_assign_matrix<S, T><<<(unsigned)((n + 64 * T - 1) / (64 * T)), 256, 0, st>>>(idx->d_cb, M, idx->Ds, codes, n, rot_base, plane, \
+                                                                                 frag, c2, cmax, tiles, assign_out, open)
+  switch (steps) {
+    case 1: RII_ASSIGN(1, 4); break;
+    case 2: RII_ASSIGN(2, 4); break;
+    case 3: RII_ASSIGN(3, 2); break;
+    default: RII_ASSIGN(4, 2); break;
+  }
+#undef RII_ASSIGN
+  const size_t lds = (size_t)M * 1024;
+  const int few = (int)std::min<int64_t>(n, 256 * 8);
+  DISPATCH_M(M, { int rc2 = set_lds(k_assign<MT>, lds); if (rc2) return rc2;
+                  k_assign<MT><<<few, 256, lds, st>>>(idx->d_sym, codes, n, rot_base, plane, M, coarse, K, assign_out, open); });
+  RII_HIP(hipGetLastError());
+  return RII_OK;
 }
 
 // a(n) with pruning (see k_assign_pruned); all pointers device.  visited_total may be NULL.

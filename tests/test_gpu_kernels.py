@@ -158,3 +158,26 @@ def test_small_scans(M, N, Q, topk, copies, rii, oracle_lib):
                    query=oracle_lib.query(cb, q[i], codes, coarse, off, lids, topk, max(1, N // K), N // 10, S=S)[:2])
         for name, (ids, dist) in ref.items():
             assert np.array_equal(got[name][0][i], ids) and np.array_equal(got[name][1][i], dist), (name, i)
+
+
+# a(n) by matrix products: every number of steps over the dimension (and a dimension past them), centres below,
+# at and past a tile of 16, items at and past a block's; repeated centres and items that lie on a
+# centre (ties go to the list of undecided items), code books far from the origin (nearly all do)
+@pytest.mark.parametrize("M,Ds,N,K,shift", [(4, 2, 256, 1, 0), (8, 4, 1000, 16, 0), (8, 5, 257, 17, 0), (12, 8, 5001, 33, 0),
+                                            (16, 6, 20000, 1000, 0), (32, 4, 3001, 1500, 0), (64, 2, 1025, 40, 0), (16, 9, 900, 30, 0),
+                                            (16, 6, 4000, 100, 50)])
+def test_assignment_by_matrix_products(M, Ds, N, K, shift, rii, oracle_lib):
+    rng = np.random.default_rng(N + K)
+    cb = (rng.normal(size=(M, 256, Ds)) + shift).astype(np.float32)
+    codes = rng.integers(0, 256, size=(N, M), dtype=np.uint8)
+    coarse = rng.integers(0, 256, size=(K, M), dtype=np.uint8)
+    coarse[K // 2] = coarse[0]
+    codes[::9] = coarse[rng.integers(0, K, size=len(codes[::9]))]
+    index = rii.Index(cb)
+    index.add(codes[:N - N // 4])
+    index.build_lists(coarse)
+    index.add(codes[N - N // 4:])  # pushed into the lists: rows of a stored array from a row on
+    a = index.get_lists()[3]
+    T = oracle_lib.sym_table(cb)
+    i = np.unique(np.concatenate([np.arange(0, N, max(1, N * K // 4_000_000)), np.arange(N - 70, N)]))
+    assert np.array_equal(a[i], oracle_lib.assign(T, codes[i], coarse))
