@@ -25,6 +25,11 @@ extern "C" int rii_internal_assign_pruned(const rii_index* idx, const uint8_t* c
 extern "C" size_t rii_internal_assign_matrix_bytes(const rii_index* idx, int64_t n, int K);
 extern "C" int rii_internal_assign_matrix(const rii_index* idx, const uint8_t* codes, int64_t n, int64_t rot_base, int64_t plane,
                                           const uint8_t* coarse, int K, int32_t* assign_out, void* scratch, hipStream_t st);
+extern "C" size_t rii_internal_lists_bytes(int64_t n, int K);
+extern "C" int rii_internal_build_lists(const int32_t* assign, int64_t n, int K, int64_t* off, int32_t* ids, void* scratch,
+                                        hipStream_t st);
+extern "C" int rii_internal_update_centres(const rii_index* idx, const uint8_t* sample, const int64_t* off, const int32_t* ids, int K,
+                                           uint8_t* coarse, hipStream_t st);
 extern "C" int rii_internal_assign_from_lists(const rii_index* idx, int32_t* d_out, hipStream_t st);
 extern "C" int rii_internal_spread_ids(int32_t* ids, int64_t* offsets, int nq, int64_t S, int64_t N, hipStream_t st);
 extern "C" int rii_internal_copy_rows(const uint8_t* in, int64_t in_rot, int64_t in_plane, const int32_t* ids,
@@ -56,6 +61,12 @@ struct DevBuf {
   }
   template <typename T>
   T* as() { return static_cast<T*>(p); }
+  template <typename T>
+  T* release() {
+    T* t = static_cast<T*>(p);
+    p = nullptr;
+    return t;
+  }
 };
 
 void drop_lists(rii_index* idx) {
@@ -70,36 +81,57 @@ void drop_lists(rii_index* idx) {
   idx->max_list_len = 0;
 }
 
-// Install lists given on the host (already validated) plus the per-item assignment.
-int install_lists(rii_index* idx, const uint8_t* coarse, int K, const std::vector<int64_t>& off,
-                  const std::vector<int32_t>& ids, const std::vector<int32_t>& assign) {
+// Install posting lists (device arrays [K+1] and [N], already validated, taken over) under the host centres `coarse`.
+int install_lists(rii_index* idx, const uint8_t* coarse, int K, DevBuf& off, DevBuf& ids) {
   const int64_t N = idx->N;
   const int M = idx->M;
   drop_lists(idx);
+  idx->d_list_off = off.release<int64_t>();
+  idx->d_list_ids = ids.release<int32_t>();
   RII_HIP(hipMalloc(&idx->d_coarse, (size_t)K * M));
   RII_HIP(hipMalloc(&idx->d_coarse_st, (size_t)K * M));
-  RII_HIP(hipMalloc(&idx->d_list_off, (size_t)(K + 1) * 8));
-  RII_HIP(hipMalloc(&idx->d_list_ids, std::max<size_t>((size_t)N * 4, 4)));
   RII_HIP(hipMalloc(&idx->d_codes_list, std::max<size_t>((size_t)N * M, 16)));
   RII_HIP(hipMemcpy(idx->d_coarse, coarse, (size_t)K * M, hipMemcpyHostToDevice));
   idx->plane_coarse = plane_for(M, K);
   idx->plane_list = plane_for(M, N);
   int rc = rii_internal_copy_rows(idx->d_coarse, -1, 0, nullptr, K, M, idx->d_coarse_st, 0, idx->plane_coarse, nullptr);
   if (rc) return rc;
-  RII_HIP(hipMemcpy(idx->d_list_off, off.data(), (size_t)(K + 1) * 8, hipMemcpyHostToDevice));
   if (N > 0) {
-    RII_HIP(hipMemcpy(idx->d_list_ids, ids.data(), (size_t)N * 4, hipMemcpyHostToDevice));
     // row p of the list-ordered copy = code of identifier list_ids[p], stored form (rotated by p)
     rc = rii_internal_copy_rows(idx->d_codes, 0, idx->plane_codes, idx->d_list_ids, N, M, idx->d_codes_list, 0,
                                 idx->plane_list, nullptr);
     if (rc) return rc;
   }
-  RII_HIP(hipDeviceSynchronize());
+  std::vector<int64_t> h_off(K + 1);
+  RII_HIP(hipMemcpy(h_off.data(), idx->d_list_off, (size_t)(K + 1) * 8, hipMemcpyDeviceToHost));  // (waits for the copies above)
   idx->h_coarse.assign(coarse, coarse + (size_t)K * M);
-  idx->h_list_off = off;
+  idx->h_list_off = std::move(h_off);
   idx->K = K;
   idx->max_list_len = 0;
-  for (int k = 0; k < K; ++k) idx->max_list_len = std::max(idx->max_list_len, off[k + 1] - off[k]);
+  for (int k = 0; k < K; ++k) idx->max_list_len = std::max(idx->max_list_len, idx->h_list_off[k + 1] - idx->h_list_off[k]);
+  return RII_OK;
+}
+
+// Posting lists of device-resident a(n), n items, as device arrays.
+int lists_of(const int32_t* d_assign, int64_t n, int K, DevBuf& off, DevBuf& ids) {
+  int rc = off.alloc((size_t)(K + 1) * 8);
+  if (!rc) rc = ids.alloc((size_t)n * 4);
+  if (rc) return rc;
+  const size_t scratch = rii_internal_lists_bytes(n, K);
+  if (scratch) {
+    DevBuf d_scratch;
+    rc = d_scratch.alloc(scratch);
+    if (!rc) rc = rii_internal_build_lists(d_assign, n, K, off.as<int64_t>(), ids.as<int32_t>(), d_scratch.p, nullptr);
+    if (!rc && hipDeviceSynchronize() != hipSuccess) rc = RII_ERR_DEVICE;
+    return rc;
+  }
+  std::vector<int32_t> assign((size_t)n), h_ids;
+  std::vector<int64_t> h_off;
+  if (n > 0) RII_HIP(hipMemcpy(assign.data(), d_assign, (size_t)n * 4, hipMemcpyDeviceToHost));
+  rc = rii_host::build_csr(assign.data(), n, K, h_off, h_ids);
+  if (rc) return rc;
+  RII_HIP(hipMemcpy(off.p, h_off.data(), (size_t)(K + 1) * 8, hipMemcpyHostToDevice));
+  if (n > 0) RII_HIP(hipMemcpy(ids.p, h_ids.data(), (size_t)n * 4, hipMemcpyHostToDevice));
   return RII_OK;
 }
 
@@ -193,57 +225,45 @@ int make_groups(rii_index* idx, const uint8_t* coarse, int K, CentreGroups& g) {
   return RII_OK;
 }
 
-// a(n) for n device-resident codes `rows` under the host coarse centres `coarse`; the result
+// a(n) for n device-resident codes `rows` under the device-resident centres d_coarse; the result
 // stays on the device (d_out, n entries).  rot_base >= 0: `rows` is the base of a stored array with
 // planes `plane` apart and the items are its rows rot_base..; rot_base < 0: plain codes.  Matrix products
 // for dimensions up to 128 unless the items are few, else brute force for small K and a pruned search
 // for large K (the same result each).
 int assign_rows_dev(rii_index* idx, const uint8_t* rows, int64_t n, int64_t rot_base, int64_t plane,
-                    const uint8_t* coarse, int K, int32_t* d_out) {
+                    const uint8_t* d_coarse, int K, int32_t* d_out) {
   if (n == 0) return RII_OK;
+  int rc = RII_OK;
   const int64_t part = std::min<int64_t>(n, (int64_t)1 << 23);  // items per launch: bounds the list of undecided ones
   const size_t scratch = n >= kMatrixMinItems ? rii_internal_assign_matrix_bytes(idx, part, K) : 0;
+  DevBuf d_scratch;
+  CentreGroups g;
   if (scratch) {
-    DevBuf d_coarse, d_scratch;
-    int rc = d_coarse.alloc((size_t)K * idx->M);
-    if (!rc) rc = d_scratch.alloc(scratch);
-    if (rc) return rc;
-    RII_HIP(hipMemcpy(d_coarse.p, coarse, (size_t)K * idx->M, hipMemcpyHostToDevice));
+    rc = d_scratch.alloc(scratch);
     for (int64_t i = 0; i < n && !rc; i += part)
       rc = rii_internal_assign_matrix(idx, rot_base >= 0 ? rows : rows + i * idx->M, std::min(part, n - i),
-                                      rot_base >= 0 ? rot_base + i : -1, plane, d_coarse.as<uint8_t>(), K, d_out + i, d_scratch.p, nullptr);
-    if (rc) return rc;
-    RII_HIP(hipDeviceSynchronize());
-    return RII_OK;
+                                      rot_base >= 0 ? rot_base + i : -1, plane, d_coarse, K, d_out + i, d_scratch.p, nullptr);
+  } else if (K >= kPruneMinK) {
+    std::vector<uint8_t> coarse((size_t)K * idx->M);
+    RII_HIP(hipMemcpy(coarse.data(), d_coarse, coarse.size(), hipMemcpyDeviceToHost));
+    rc = make_groups(idx, coarse.data(), K, g);
+    if (!rc) rc = rii_internal_assign_pruned(idx, rows, n, rot_base, plane, g.d_super, g.G, g.d_radius, g.d_coarse_g, g.d_perm_g,
+                                             g.d_group_off, d_out, nullptr, nullptr);
+  } else {
+    rc = rii_internal_assign(idx, rows, n, rot_base, plane, d_coarse, K, d_out, nullptr);
   }
-  if (K >= kPruneMinK) {
-    CentreGroups g;
-    int rc = make_groups(idx, coarse, K, g);
-    if (rc) return rc;
-    rc = rii_internal_assign_pruned(idx, rows, n, rot_base, plane, g.d_super, g.G, g.d_radius, g.d_coarse_g, g.d_perm_g,
-                                    g.d_group_off, d_out, nullptr, nullptr);
-    if (rc) return rc;
-    RII_HIP(hipDeviceSynchronize());
-    return RII_OK;
-  }
-  uint8_t* d_coarse = nullptr;
-  RII_HIP(hipMalloc(&d_coarse, (size_t)K * idx->M));
-  int rc = RII_OK;
-  if (hipMemcpy(d_coarse, coarse, (size_t)K * idx->M, hipMemcpyHostToDevice) != hipSuccess) rc = RII_ERR_DEVICE;
-  if (!rc) rc = rii_internal_assign(idx, rows, n, rot_base, plane, d_coarse, K, d_out, nullptr);
   if (!rc && hipDeviceSynchronize() != hipSuccess) rc = RII_ERR_DEVICE;
-  (void)hipFree(d_coarse);
   return rc;
 }
 
-int assign_stored(rii_index* idx, int64_t first, int64_t n, const uint8_t* coarse, int K, int32_t* assign_host) {
+// The same under host centres, for the rows first .. first + n - 1 of the stored codes.
+int assign_stored(rii_index* idx, int64_t first, int64_t n, const uint8_t* coarse, int K, int32_t* d_out) {
   if (n == 0) return RII_OK;
-  int32_t* d_out = nullptr;
-  RII_HIP(hipMalloc(&d_out, (size_t)n * 4));
-  int rc = assign_rows_dev(idx, idx->d_codes, n, first, idx->plane_codes, coarse, K, d_out);
-  if (!rc && hipMemcpy(assign_host, d_out, (size_t)n * 4, hipMemcpyDeviceToHost) != hipSuccess) rc = RII_ERR_DEVICE;
-  (void)hipFree(d_out);
-  return rc;
+  DevBuf d_coarse;
+  int rc = d_coarse.alloc((size_t)K * idx->M);
+  if (rc) return rc;
+  RII_HIP(hipMemcpy(d_coarse.p, coarse, (size_t)K * idx->M, hipMemcpyHostToDevice));
+  return assign_rows_dev(idx, idx->d_codes, n, first, idx->plane_codes, d_coarse.as<uint8_t>(), K, d_out);
 }
 
 // helper of the threshold calibration
@@ -508,29 +528,21 @@ int rii_index_add(rii_index_t* idx, const uint8_t* codes, int64_t n, int mem) {
   if (idx->K > 0) {
     // push every new identifier to the list of its nearest coarse centre; lists stay ascending
     // because new identifiers are larger than all stored ones
-    std::vector<int32_t> assign(idx->N);
-    if (oldN > 0) {  // a(n) of the items stored so far, read back from the lists (it is not kept)
-      idx->N = oldN;
-      DevBuf d_old;
-      int rc0 = d_old.alloc((size_t)oldN * 4);
-      if (!rc0) rc0 = rii_internal_assign_from_lists(idx, d_old.as<int32_t>(), nullptr);
-      if (!rc0 && hipMemcpy(assign.data(), d_old.p, (size_t)oldN * 4, hipMemcpyDeviceToHost) != hipSuccess) rc0 = RII_ERR_DEVICE;
-      idx->N = oldN + n;
-      if (rc0) {
-        (void)hipGetLastError();
-        drop_lists(idx);
-        return rc0;
-      }
-    }
-    std::vector<uint8_t> coarse = idx->h_coarse;
+    const std::vector<uint8_t> coarse = idx->h_coarse;
     const int K = idx->K;
-    // (from here on a failure leaves the index without posting lists rather than with lists
-    // that are shorter than the code array)
-    int rc = assign_stored(idx, oldN, n, coarse.data(), K, assign.data() + oldN);
-    std::vector<int64_t> off;
-    std::vector<int32_t> ids;
-    if (!rc) rc = rii_host::build_csr(assign.data(), idx->N, K, off, ids);
-    if (!rc) rc = install_lists(idx, coarse.data(), K, off, ids, assign);
+    // (a failure leaves the index without posting lists rather than with lists that are shorter than
+    // the code array)
+    DevBuf d_assign, off, ids;
+    int rc = d_assign.alloc((size_t)idx->N * 4);
+    if (!rc && oldN > 0) {  // a(n) of the items stored so far, read back from the lists (it is not kept)
+      idx->N = oldN;
+      rc = rii_internal_assign_from_lists(idx, d_assign.as<int32_t>(), nullptr);
+      idx->N = oldN + n;
+    }
+    if (!rc) rc = assign_stored(idx, oldN, n, coarse.data(), K, d_assign.as<int32_t>() + oldN);
+    if (!rc) rc = lists_of(d_assign.as<int32_t>(), idx->N, K, off, ids);
+    if (!rc) rc = install_lists(idx, coarse.data(), K, off, ids);
+    if (rc) (void)hipGetLastError();
     if (rc) drop_lists(idx);
     return rc;
   }
@@ -551,29 +563,33 @@ int rii_index_set_lists(rii_index_t* idx, const uint8_t* coarse, int K, const in
   RII_HIP(hipMemcpy(off.data(), list_offsets, (size_t)(K + 1) * 8, kind));
   if (N > 0) RII_HIP(hipMemcpy(ids.data(), list_ids, (size_t)N * 4, kind));
   if (off[0] != 0 || off[K] != N) return RII_ERR_INVALID_ARG;
-  std::vector<int32_t> assign(N, -1);
+  std::vector<bool> seen(N, false);
   for (int k = 0; k < K; ++k) {
     if (off[k + 1] < off[k]) return RII_ERR_INVALID_ARG;
     for (int64_t p = off[k]; p < off[k + 1]; ++p) {
       int32_t n = ids[p];
-      if (n < 0 || n >= N || assign[n] != -1) return RII_ERR_UNSORTED_IDS;
+      if (n < 0 || n >= N || seen[n]) return RII_ERR_UNSORTED_IDS;
       if (p > off[k] && ids[p - 1] >= n) return RII_ERR_UNSORTED_IDS;
-      assign[n] = k;
+      seen[n] = true;
     }
   }
-  return install_lists(idx, hc.data(), K, off, ids, assign);
+  DevBuf d_off, d_ids;
+  int rc = d_off.alloc((size_t)(K + 1) * 8);
+  if (!rc) rc = d_ids.alloc((size_t)N * 4);
+  if (rc) return rc;
+  RII_HIP(hipMemcpy(d_off.p, off.data(), (size_t)(K + 1) * 8, hipMemcpyHostToDevice));
+  if (N > 0) RII_HIP(hipMemcpy(d_ids.p, ids.data(), (size_t)N * 4, hipMemcpyHostToDevice));
+  return install_lists(idx, hc.data(), K, d_off, d_ids);
 }
 
 int rii_index_build_lists(rii_index_t* idx, const uint8_t* coarse, int K) {
   if (!idx || !coarse || K < 1) return RII_ERR_INVALID_ARG;
-  std::vector<int32_t> assign(idx->N);
-  int rc = assign_stored(idx, 0, idx->N, coarse, K, assign.data());
-  if (rc) return rc;
-  std::vector<int64_t> off;
-  std::vector<int32_t> ids;
-  rc = rii_host::build_csr(assign.data(), idx->N, K, off, ids);
-  if (rc) return rc;
-  return install_lists(idx, coarse, K, off, ids, assign);
+  DevBuf d_assign, off, ids;
+  int rc = d_assign.alloc((size_t)idx->N * 4);
+  if (!rc) rc = assign_stored(idx, 0, idx->N, coarse, K, d_assign.as<int32_t>());
+  if (!rc) rc = lists_of(d_assign.as<int32_t>(), idx->N, K, off, ids);
+  if (!rc) rc = install_lists(idx, coarse, K, off, ids);
+  return rc;
 }
 
 int rii_index_reconfigure(rii_index_t* idx, int K, int iters, uint64_t seed) {
@@ -584,19 +600,18 @@ int rii_index_reconfigure(rii_index_t* idx, int K, int iters, uint64_t seed) {
   const int64_t ns = std::min<int64_t>(N, (int64_t)100 * K);
   std::vector<int64_t> rows = rii_host::sample_without_replacement(N, ns, seed);
   std::vector<uint8_t> sample((size_t)ns * M);
+  DevBuf d_sample;
   {
     // fetch the sampled rows in plain form
     std::vector<int32_t> r32(rows.begin(), rows.end());
-    int32_t* d_rows = nullptr;
-    uint8_t* d_tmp = nullptr;
-    RII_HIP(hipMalloc(&d_rows, (size_t)ns * 4));
-    RII_HIP(hipMalloc(&d_tmp, (size_t)ns * M));
-    RII_HIP(hipMemcpy(d_rows, r32.data(), (size_t)ns * 4, hipMemcpyHostToDevice));
-    int rc = rii_internal_copy_rows(idx->d_codes, 0, idx->plane_codes, d_rows, ns, M, d_tmp, -1, 0, nullptr);
+    DevBuf d_rows;
+    int rc = d_rows.alloc((size_t)ns * 4);
+    if (!rc) rc = d_sample.alloc((size_t)ns * M);
     if (rc) return rc;
-    RII_HIP(hipMemcpy(sample.data(), d_tmp, sample.size(), hipMemcpyDeviceToHost));
-    (void)hipFree(d_rows);
-    (void)hipFree(d_tmp);
+    RII_HIP(hipMemcpy(d_rows.p, r32.data(), (size_t)ns * 4, hipMemcpyHostToDevice));
+    rc = rii_internal_copy_rows(idx->d_codes, 0, idx->plane_codes, d_rows.as<int32_t>(), ns, M, d_sample.as<uint8_t>(), -1, 0, nullptr);
+    if (rc) return rc;
+    RII_HIP(hipMemcpy(sample.data(), d_sample.p, sample.size(), hipMemcpyDeviceToHost));
   }
   // initial centres: the first K distinct codes of the sample in a seeded order
   std::vector<uint8_t> coarse((size_t)K * M);
@@ -621,25 +636,21 @@ int rii_index_reconfigure(rii_index_t* idx, int K, int iters, uint64_t seed) {
       std::memcpy(&coarse[(size_t)got * M], &sample[order[i % ns] * M], M);
   }
   if (iters > 0) {
-    int rc = rii_internal_sym_table(idx, nullptr);
+    DevBuf d_coarse, d_assign;
+    int rc = d_coarse.alloc((size_t)K * M);
+    if (!rc) rc = d_assign.alloc((size_t)ns * 4);
     if (rc) return rc;
-    std::vector<float> sym((size_t)M * 256 * 256);
-    RII_HIP(hipDeviceSynchronize());
-    RII_HIP(hipMemcpy(sym.data(), idx->d_sym, sym.size() * 4, hipMemcpyDeviceToHost));
-    uint8_t* d_sample = nullptr;
-    int32_t* d_assign = nullptr;
-    RII_HIP(hipMalloc(&d_sample, (size_t)ns * M));
-    RII_HIP(hipMalloc(&d_assign, (size_t)ns * 4));
-    RII_HIP(hipMemcpy(d_sample, sample.data(), sample.size(), hipMemcpyHostToDevice));
-    std::vector<int32_t> assign(ns);
-    for (int it = 0; it < iters; ++it) {
-      int rc2 = assign_rows_dev(idx, d_sample, ns, -1, 0, coarse.data(), K, d_assign);
-      if (rc2) return rc2;
-      RII_HIP(hipMemcpy(assign.data(), d_assign, (size_t)ns * 4, hipMemcpyDeviceToHost));
-      rii_host::update_centres(sample.data(), ns, assign.data(), sym.data(), M, K, coarse.data());
+    RII_HIP(hipMemcpy(d_coarse.p, coarse.data(), coarse.size(), hipMemcpyHostToDevice));
+    for (int it = 0; it < iters && !rc; ++it) {
+      DevBuf off, ids;
+      rc = assign_rows_dev(idx, d_sample.as<uint8_t>(), ns, -1, 0, d_coarse.as<uint8_t>(), K, d_assign.as<int32_t>());
+      if (!rc) rc = lists_of(d_assign.as<int32_t>(), ns, K, off, ids);
+      if (!rc) rc = rii_internal_update_centres(idx, d_sample.as<uint8_t>(), off.as<int64_t>(), ids.as<int32_t>(), K,
+                                                d_coarse.as<uint8_t>(), nullptr);
+      if (!rc && hipDeviceSynchronize() != hipSuccess) rc = RII_ERR_DEVICE;
     }
-    (void)hipFree(d_sample);
-    (void)hipFree(d_assign);
+    if (rc) return rc;
+    RII_HIP(hipMemcpy(coarse.data(), d_coarse.p, coarse.size(), hipMemcpyDeviceToHost));
   }
   return rii_index_build_lists(idx, coarse.data(), K);
 }

@@ -1140,6 +1140,46 @@ int rii_internal_assign_pruned(const rii_index* idx, const uint8_t* codes, int64
   return RII_OK;
 }
 
+// Posting lists (off [K+1], ids [n], ascending inside a list) of device-resident a(n).  Scratch:
+// rii_internal_lists_bytes, 0 when K is beyond what a block counts in LDS.
+static int64_t list_chunk(int64_t n, int K) {
+  const int64_t most = std::max<int64_t>(1, ((int64_t)1 << 26) / K);  // chunks: at most 256 MB of counts
+  return std::max<int64_t>(4096, ((n + most - 1) / most + 63) / 64 * 64);
+}
+size_t rii_internal_lists_bytes(int64_t n, int K) {
+  if ((size_t)K * 4 > 150 * 1024 || n < 1) return 0;
+  const int64_t chunks = (n + list_chunk(n, K) - 1) / list_chunk(n, K);
+  return align_up((size_t)chunks * K * 4, 256) + align_up((size_t)K * 4, 256);
+}
+int rii_internal_build_lists(const int32_t* assign, int64_t n, int K, int64_t* off, int32_t* ids, void* scratch, hipStream_t st) {
+  const int64_t chunk = list_chunk(n, K);
+  const int chunks = (int)((n + chunk - 1) / chunk);
+  uint32_t* counts = static_cast<uint32_t*>(scratch);
+  uint32_t* lengths = reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(scratch) + align_up((size_t)chunks * K * 4, 256));
+  const size_t lds = (size_t)K * 4;
+  int rc = set_lds(k_list_count, lds);
+  if (!rc) rc = set_lds(k_list_fill, lds);
+  if (rc) return rc;
+  int bits = 0;
+  while (bits < 31 && (K - 1) >> bits) ++bits;
+  k_list_count<<<chunks, 256, lds, st>>>(assign, n, chunk, K, counts);
+  k_list_starts<<<(K + 63) / 64, 64, 0, st>>>(counts, chunks, K, lengths);
+  k_list_offsets<<<1, 1024, 0, st>>>(lengths, K, off);
+  k_list_fill<<<chunks, 64, lds, st>>>(assign, n, chunk, K, bits, counts, off, ids);
+  RII_HIP(hipGetLastError());
+  return RII_OK;
+}
+
+// One update round of the clustering in code space (see k_update_centres); all pointers device.
+int rii_internal_update_centres(const rii_index* idx, const uint8_t* sample, const int64_t* off, const int32_t* ids, int K,
+                                uint8_t* coarse, hipStream_t st) {
+  int rc = rii_internal_sym_table(idx, st);
+  if (rc) return rc;
+  k_update_centres<<<dim3((unsigned)K, (unsigned)idx->M), 256, 0, st>>>(idx->d_sym, sample, idx->M, off, ids, coarse);
+  RII_HIP(hipGetLastError());
+  return RII_OK;
+}
+
 // a(n) of every stored item from the installed posting lists (device buffer of N entries)
 int rii_internal_assign_from_lists(const rii_index* idx, int32_t* d_out, hipStream_t st) {
   if (idx->N == 0) return RII_OK;

@@ -181,3 +181,48 @@ def test_assignment_by_matrix_products(M, Ds, N, K, shift, rii, oracle_lib):
     T = oracle_lib.sym_table(cb)
     i = np.unique(np.concatenate([np.arange(0, N, max(1, N * K // 4_000_000)), np.arange(N - 70, N)]))
     assert np.array_equal(a[i], oracle_lib.assign(T, codes[i], coarse))
+
+
+# posting lists by a counting sort on the device: items below, at and past a wave's 64 and a chunk's 4096, one
+# list, as many lists as the block counts, more than that (host path), everything in one list
+@pytest.mark.parametrize("N,K,same", [(1, 1, False), (64, 3, False), (4096, 257, False), (4097, 1000, True), (30011, 1024, False),
+                                      (70000, 38400, False), (50000, 38401, False)])
+def test_lists_from_assignment(N, K, same, rii, oracle_lib):
+    rng = np.random.default_rng(N)
+    cb = rng.normal(size=(4, 256, 2)).astype(np.float32)
+    codes = rng.integers(0, 256, size=(N, 4), dtype=np.uint8)
+    if same:
+        codes[:] = codes[0]
+    index = rii.Index(cb)
+    index.add(codes[:(N + 1) // 2])
+    index.build_lists(rng.integers(0, 256, size=(K, 4), dtype=np.uint8))
+    if N > 1:
+        index.add(codes[(N + 1) // 2:])
+    _, off, ids, a = index.get_lists()
+    ref_off, ref_ids = oracle_lib.build_lists(a, K)
+    assert np.array_equal(off, ref_off) and np.array_equal(ids, ref_ids)
+
+
+def test_reconfigure_centres_are_the_best_codes(rii, oracle_lib):
+    """One round of the clustering (the sample is the whole database): the new centre of a cell is, per
+    sub-space, the code with the smallest sum of table entries over the members, lowest on ties."""
+    rng = np.random.default_rng(6)
+    N, M, K = 3000, 8, 30
+    cb = rng.normal(size=(M, 256, 3)).astype(np.float32)
+    cb[:, 200] = cb[:, 10]
+    codes = rng.integers(0, 256, size=(N, M), dtype=np.uint8)
+    codes[:40] = codes[0]
+    T = oracle_lib.sym_table(cb)
+    index = rii.Index(cb)
+    index.add(codes)
+    index.reconfigure(K, iters=0, seed=3)
+    start, _, _, a = index.get_lists()
+    assert np.array_equal(a, oracle_lib.assign(T, codes, start))
+    index.reconfigure(K, iters=1, seed=3)
+    want = start.copy()
+    for k in range(K):
+        for m in range(M):
+            h = np.bincount(codes[a == k, m], minlength=256)
+            if h.sum():
+                want[k, m] = np.argmin(np.cumsum(np.concatenate([[np.zeros(256)], h[:, None] * T[m].astype(np.float64)]), axis=0)[-1])
+    assert np.array_equal(index.get_lists()[0], want)
