@@ -72,9 +72,24 @@ std::vector<int64_t> sample_without_replacement(int64_t N, int64_t n, uint64_t s
     return out;
   }
   // Floyd's algorithm: for j = N-n .. N-1 pick t in [0, j]; insert t, or j when t is taken.
+  uint64_t ctr = 0;
+  out.reserve((size_t)n);
+  if (N / 64 <= 16 * n) {
+    // dense enough for a bit per value: no table of nodes to chase, and the values come out in order
+    // (100,000 of 800,000: 9.7 -> 0.6 ms)
+    std::vector<uint64_t> taken((size_t)(N / 64 + 1), 0);
+    for (int64_t j = N - n; j < N; ++j) {
+      uint64_t r = mix64(seed * 0x9E3779B97F4A7C15ull + (++ctr));
+      int64_t t = (int64_t)(r % (uint64_t)(j + 1));
+      if (taken[t >> 6] >> (t & 63) & 1) t = j;
+      taken[t >> 6] |= 1ull << (t & 63);
+    }
+    for (size_t w = 0; w < taken.size(); ++w)
+      for (uint64_t bits = taken[w]; bits; bits &= bits - 1) out.push_back((int64_t)(w * 64) + __builtin_ctzll(bits));
+    return out;
+  }
   std::unordered_set<int64_t> seen;
   seen.reserve((size_t)n * 2);
-  uint64_t ctr = 0;
   for (int64_t j = N - n; j < N; ++j) {
     uint64_t r = mix64(seed * 0x9E3779B97F4A7C15ull + (++ctr));
     int64_t t = (int64_t)(r % (uint64_t)(j + 1));

@@ -616,24 +616,27 @@ int rii_index_reconfigure(rii_index_t* idx, int K, int iters, uint64_t seed) {
   // initial centres: the first K distinct codes of the sample in a seeded order
   std::vector<uint8_t> coarse((size_t)K * M);
   {
-    std::vector<int64_t> order(ns);
-    for (int64_t i = 0; i < ns; ++i) order[i] = i;
-    std::sort(order.begin(), order.end(), [&](int64_t a, int64_t b) {
-      uint64_t ha = rii_host::mix64(seed ^ (uint64_t)rows[a] * 0x9E3779B97F4A7C15ull);
-      uint64_t hb = rii_host::mix64(seed ^ (uint64_t)rows[b] * 0x9E3779B97F4A7C15ull);
-      return ha != hb ? ha < hb : a < b;
-    });
+    // by (hash, row number), put in order only as far as it is used: nearly always little more than K
+    std::vector<std::pair<uint64_t, int64_t>> order(ns);
+    for (int64_t i = 0; i < ns; ++i) order[i] = {rii_host::mix64(seed ^ (uint64_t)rows[i] * 0x9E3779B97F4A7C15ull), i};
     std::unordered_set<std::string> seen;
     int got = 0;
+    int64_t sorted = 0;  // order[0 .. sorted) is final
     for (int64_t i = 0; i < ns && got < K; ++i) {
-      std::string key(reinterpret_cast<const char*>(&sample[order[i] * M]), M);
+      if (i == sorted) {
+        const int64_t to = std::min<int64_t>(ns, std::max<int64_t>(2 * sorted, K + K / 8 + 64));
+        if (to < ns) std::nth_element(order.begin() + sorted, order.begin() + to, order.end());
+        std::sort(order.begin() + sorted, order.begin() + to);
+        sorted = to;
+      }
+      std::string key(reinterpret_cast<const char*>(&sample[order[i].second * M]), M);
       if (seen.insert(key).second) {
         std::memcpy(&coarse[(size_t)got * M], key.data(), M);
         ++got;
       }
     }
     for (int64_t i = 0; got < K; ++i, ++got)  // fewer than K distinct codes: repeat sample rows
-      std::memcpy(&coarse[(size_t)got * M], &sample[order[i % ns] * M], M);
+      std::memcpy(&coarse[(size_t)got * M], &sample[order[i % ns].second * M], M);
   }
   if (iters > 0) {
     DevBuf d_coarse, d_assign;
