@@ -188,7 +188,18 @@ bool plan_batch(int M, int Q, int64_t rows, int topk, int64_t* nchunks_out, int6
     // part of the array and the memory-side cache serves most of them.  With the abandoning
     // tests after every eight look-ups the kernel had become bound by the delivery of the code
     // bytes (10^4 queries over 10^8 rows of 32 bytes: 640 ms in one piece, 545 ms in nine).
-    nchunks = (rows * M + kBatchChunkBytes - 1) / kBatchChunkBytes;
+    // ... or up to three times as many, so that the blocks make whole rounds of the chip: 625 groups over
+    // 960 MB take 8 rounds for 7.3 rounds' worth of blocks in 3 chunks, 10 for 9.8 in 4 (41.7 and 39.5 ms;
+    // half a per cent a chunk is what shorter chunks cost).
+    const int64_t least = (rows * M + kBatchChunkBytes - 1) / kBatchChunkBytes;
+    double best = 0.0;
+    for (int64_t c = least; c <= 3 * least; ++c) {
+      const double t = (double)((groups * c + kWantBlocks - 1) / kWantBlocks) / (double)c * (1.0 + 0.005 * (double)c);
+      if (c == least || t < best) {
+        best = t;
+        nchunks = c;
+      }
+    }
     chunk_rows = (rows + nchunks - 1) / nchunks;
     chunk_rows = (chunk_rows + tile - 1) / tile * tile;
     nchunks = (rows + chunk_rows - 1) / chunk_rows;
@@ -302,7 +313,8 @@ int launch_scan(const rii_index* idx, const uint8_t* codes, int64_t plane, int64
   a.target_ids = target_ids; a.target_offsets = target_offsets;
   a.chunk_rows = chunk_rows; a.k = topk; a.partial = partial; a.tau_g = tau;
   int64_t bchunks, brows;
-  const bool batched = plan_batch(M, Q, max_rows, topk, &bchunks, &brows) && mode == kLinear && !qmode;
+  const bool batched = mode == kLinear && !qmode && plan_batch(M, Q, max_rows, topk, &bchunks, &brows);
+  if (!batched) bchunks = 1;
   a.cand_cnt = cand_cnt; a.cand_cap = std::max(nchunks, bchunks) * topk;
   a.nq = Q;
   // [prepass minima] follow the candidates
@@ -482,11 +494,12 @@ size_t minima_bytes(int Q) {
   return (size_t)std::min(Q, kSeedMaxQ) * blocks * (kScanThreads / 64) * 4;
 }
 
-size_t scan_ws_bytes(int M, int Q, int64_t max_rows, int topk) {
+// batch: the call may take the batched kernel (launch_scan without per-query modes).
+size_t scan_ws_bytes(int M, int Q, int64_t max_rows, int topk, bool batch = true) {
   int64_t nchunks, chunk_rows;
   scan_chunks(Q, max_rows, &nchunks, &chunk_rows);
-  int64_t bchunks, brows;
-  plan_batch(M, Q, max_rows, topk, &bchunks, &brows);
+  int64_t bchunks = 1, brows;
+  if (batch) plan_batch(M, Q, max_rows, topk, &bchunks, &brows);
   const int64_t cap_chunks = std::max(nchunks, bchunks);
   return kScanArrays * align_up((size_t)Q * 4, 256) + (size_t)Q * cap_chunks * topk * 8 + minima_bytes(Q) + 256;
 }
@@ -495,7 +508,7 @@ size_t scan_ws_bytes(int M, int Q, int64_t max_rows, int topk) {
 // a bound that grows with each argument (a batch's blocks per query times its queries stay
 // below Q + 4 kBatchWantBlocks + kWantBlocks whatever the launch shape is).
 size_t scan_ws_bound(int M, int Q, int64_t max_rows, int topk) {
-  const size_t big_chunks = (size_t)(max_rows * M / kBatchChunkBytes + 2);  // chunks of a large batch (see plan_batch)
+  const size_t big_chunks = (size_t)(3 * (max_rows * M / kBatchChunkBytes + 1) + 2);  // chunks of a large batch (see plan_batch)
   return kScanArrays * align_up((size_t)Q * 4, 256) +
          ((size_t)Q * big_chunks + 4 * kBatchWantBlocks + kWantBlocks + 8) * topk * 8 +
          std::max(minima_bytes(Q), minima_bytes(std::min(Q, 3))) + 256;
@@ -818,10 +831,14 @@ struct QueryPlan {
   int pmax = 1;          // most lists any inverted-index query of the batch can ask for
   int64_t lin_rows = 1;  // most rows any linear-scan query of the batch can have
   size_t lut_b = 0, plan_b = 0, probe_b = 0, ivf_b = 0, total = 0;
+  // Without target sets every query has the same |S| = N: the host takes Alg. 3's decision and k_plan and
+  // the per-query modes fall away, which also lets a batch into the batched scan.
+  bool uniform = false;
 };
 
+// `limit` > 0: a plan beyond that many bytes gives up the batched scan where that is what needs them.
 static int plan_query(const rii_index* idx, int Q, int topk, bool targets, int64_t max_targets, int64_t L,
-                      QueryPlan* p) {
+                      QueryPlan* p, size_t limit = 0) {
   const int M = idx->M, K = idx->K;
   const bool has_lists = K > 0;
   // Largest number of lists any inverted-index query of this batch can ask for: such a query
@@ -842,10 +859,17 @@ static int plan_query(const rii_index* idx, int Q, int topk, bool targets, int64
   p->lut_b = align_up((size_t)Q * M * 256 * 4, 256);
   p->plan_b = align_up((size_t)Q * 4, 256);
   p->probe_b = align_up((size_t)Q * p->pmax * 4, 256);
-  const size_t scan_b = align_up(scan_ws_bytes(M, Q, p->lin_rows, topk), 256);
+  p->uniform = !targets;
+  size_t scan_b = align_up(scan_ws_bytes(M, Q, p->lin_rows, topk, p->uniform), 256);
   const size_t coarse_b = has_lists ? align_up(coarse_ws_bytes(idx, Q, p->pmax), 256) : 0;
   p->ivf_b = has_lists ? align_up(ivf_ws_bytes(idx, Q, p->pmax, L, topk, targets), 256) : 0;
-  p->total = p->lut_b + 2 * p->plan_b + p->probe_b + std::max(std::max(scan_b, coarse_b), p->ivf_b);
+  const size_t fixed = p->lut_b + 2 * p->plan_b + p->probe_b, other = std::max(coarse_b, p->ivf_b);
+  p->total = fixed + std::max(scan_b, other);
+  if (limit && p->total > limit && p->uniform) {
+    p->uniform = false;
+    scan_b = align_up(scan_ws_bytes(M, Q, p->lin_rows, topk, false), 256);
+    p->total = fixed + std::max(scan_b, other);
+  }
   return RII_OK;
 }
 
@@ -873,19 +897,21 @@ static int run_query(const rii_index* idx, const QueryPlan& p, const float* q, i
   void* stage_ws = w;
 
   launch_build_lut(idx, q, Q, lut, st);
-  k_plan<<<(Q + 255) / 256, 256, 0, st>>>(target_offsets, idx->N, Q, idx->theta, K, L, p.pmax, qmode, nprobe_q);
+  if (p.uniform) qmode = nprobe_q = nullptr;  // (one branch for all queries; every query's lists are p.pmax then)
+  else k_plan<<<(Q + 255) / 256, 256, 0, st>>>(target_offsets, idx->N, Q, idx->theta, K, L, p.pmax, qmode, nprobe_q);
   int rc = RII_OK;
   // linear-scan branch (mode 0)
+  const bool all_linear = !target_ids && (!has_lists || idx->N < idx->theta);
   if (target_ids) {
     rc = launch_scan(idx, idx->d_codes_rows, idx->plane_rows, idx->N, lut, Q, kSubset, target_ids, target_offsets, p.lin_rows, topk,
                      ids, dist, topk, qmode, 0, stage_ws, st);
-  } else if (!has_lists || idx->N < idx->theta) {
+  } else if (all_linear) {
     rc = launch_scan(idx, idx->d_codes, idx->plane_codes, idx->N, lut, Q, kLinear, nullptr, nullptr, idx->N, topk, ids, dist, topk,
                      qmode, 0, stage_ws, st);
   }
   if (rc) return rc;
   // inverted-index branch (mode 1); the scratch of the scan stage is reused in stream order
-  if (has_lists) {
+  if (has_lists && !all_linear) {
     rc = coarse_rank(idx, lut, Q, p.pmax, probe, nullptr, p.pmax, qmode, 1, stage_ws, st);
     if (rc) return rc;
     rc = launch_ivf(idx, lut, Q, probe, p.pmax, p.pmax, nprobe_q, target_ids, target_offsets, L, topk, ids, dist, qmode,
@@ -965,7 +991,7 @@ int rii_query_noalloc(const rii_index_t* idx, const float* q, int Q, int topk, c
   RII_HIP(hipGetDevice(&dev));
   if (dev != idx->device) return RII_ERR_INVALID_ARG;  // the handle's arrays live on another GPU
   QueryPlan p;
-  rc = plan_query(idx, Q, topk, target_ids != nullptr, max_targets, L, &p);
+  rc = plan_query(idx, Q, topk, target_ids != nullptr, max_targets, L, &p, RII_NOALLOC_SCRATCH_BYTES);
   if (rc) return rc;
   if (p.total > (size_t)RII_NOALLOC_SCRATCH_BYTES) return RII_ERR_UNSUPPORTED;  // beyond the static scratch
   void* ws = nullptr;

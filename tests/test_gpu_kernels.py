@@ -226,3 +226,29 @@ def test_reconfigure_centres_are_the_best_codes(rii, oracle_lib):
             if h.sum():
                 want[k, m] = np.argmin(np.cumsum(np.concatenate([[np.zeros(256)], h[:, None] * T[m].astype(np.float64)]), axis=0)[-1])
     assert np.array_equal(index.get_lists()[0], want)
+
+
+# the query procedure without target sets takes one branch for the whole batch: the batched scan, two queries a
+# block, one query; the lists; and the threshold above the database size
+@pytest.mark.parametrize("M,N,Q,topk,K,theta", [(16, 150_003, 301, 10, 0, 0), (8, 120_001, 2100, 110, 0, 0), (32, 110_000, 3, 100, 0, 0),
+                                                (16, 3000, 9, 20, 12, 0), (16, 3000, 9, 20, 12, 4000)])
+def test_query_without_target_sets(M, N, Q, topk, K, theta, rii, oracle_lib):
+    rng = np.random.default_rng(N)
+    d = plain_index(rii, oracle_lib, rng, N, M, max(K, 1))
+    index = d["index"]
+    if not K:  # an index that has no lists
+        index = rii.Index(d["cb"])
+        index.add(d["codes"])
+    index.set_threshold(theta)
+    q = rng.normal(size=(Q, 2 * M)).astype(np.float32)
+    qd = torch.from_numpy(q).cuda()
+    L = max(1, N // max(K, 1))
+    ids, dist = rii.rii_query(index, qd, topk, L=L)
+    torch.cuda.synchronize()
+    A = oracle_lib.lut(d["cb"], q)
+    for i in range(0, Q, max(1, Q // 8)):
+        if K:
+            ref = oracle_lib.query(d["cb"], q[i], d["codes"], d["coarse"], d["off"], d["lids"], topk, L, theta)
+        else:
+            ref = oracle_lib.linear_scan(A[i], d["codes"], topk)
+        assert np.array_equal(t2n(ids)[i], ref[0]) and np.array_equal(t2n(dist)[i], ref[1]), i
