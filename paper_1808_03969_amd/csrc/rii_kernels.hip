@@ -129,14 +129,16 @@ int set_lds0(Kern kern, size_t bytes) { return set_lds_impl(reinterpret_cast<con
     default: { constexpr int MT = 0; __VA_ARGS__; } break;  \
   }
 
-void launch_build_lut(const rii_index* idx, const float* q, int Q, float* lut, hipStream_t st) {
+// clear: see k_build_lut
+void launch_build_lut(const rii_index* idx, const float* q, int Q, float* lut, hipStream_t st, void* clear = nullptr) {
+  const int stride = (int)(align_up((size_t)Q * 4, 256) / 4);
   // Queries per block: enough blocks to fill the chip first (2048 of four waves are a chip-load),
   // then up to 16, where reading the code word no longer shows (10^4 queries, M = 16, 164 MB of
   // tables: 540 us with one query per block, 43 us with 16; at one query the blocks are what counts
   // and per is 1).
   const int per = std::min(16, std::max(1, (int)((int64_t)Q * idx->M / 2048)));
   const dim3 grid((unsigned)idx->M, (unsigned)((Q + per - 1) / per));
-#define RII_LUT(DS) k_build_lut<DS><<<grid, 256, 0, st>>>(idx->d_cb, q, idx->D, idx->M, idx->Ds, Q, per, lut)
+#define RII_LUT(DS) k_build_lut<DS><<<grid, 256, 0, st>>>(idx->d_cb, q, idx->D, idx->M, idx->Ds, Q, per, lut, static_cast<uint32_t*>(clear), stride)
   switch (idx->Ds) {
     case 2: RII_LUT(2); break;
     case 3: RII_LUT(3); break;
@@ -241,17 +243,18 @@ size_t few_ws_bytes(const FewShape& f, int Q) {
   return kScanArrays * align_up((size_t)Q * 4, 256) + (f.split > 1 ? (size_t)Q * f.split * f.slot * 8 : 0) + 256;
 }
 
-// `ws` holds few_ws_bytes (looked at only when a query has several blocks).
+// `ws` holds few_ws_bytes (looked at only when a query has several blocks); cleared: its bounds and counters
+// are initialised already.
 template <int SRC>
-int launch_few(FewArgs a, const FewShape& f, int Q, void* ws, hipStream_t st) {
+int launch_few(FewArgs a, const FewShape& f, int Q, void* ws, bool cleared, hipStream_t st) {
   a.cap = f.cap;
   a.slot = f.slot;
   if (f.split > 1) {
     const size_t cstride = align_up((size_t)Q * 4, 256) / 4;
     uint32_t* tau = static_cast<uint32_t*>(ws);
-    a.tau_g = tau; a.cand_cnt = tau + cstride; a.done_cnt = tau + 3 * cstride;
+    a.tau_g = tau; a.done_cnt = tau + 3 * cstride;
     a.cand = reinterpret_cast<uint64_t*>(static_cast<uint8_t*>(ws) + kScanArrays * cstride * 4);
-    k_init_scan<<<(Q + 255) / 256, 256, 0, st>>>(tau, Q, (int)cstride, nullptr, 0);
+    if (!cleared) k_init_scan<<<(Q + 255) / 256, 256, 0, st>>>(tau, Q, (int)cstride, nullptr, 0);
   }
   const size_t lds = few_lds(a.M, a.cap, a.nprobe, SRC == kFewCapped);
   const dim3 grid((unsigned)f.split, (unsigned)Q);
@@ -278,7 +281,7 @@ bool few_linear(int M, int64_t rows) { return rows <= (M == 32 ? 65536 : 100000)
 int launch_scan(const rii_index* idx, const uint8_t* codes, int64_t plane, int64_t N, const float* lut, int Q, int mode,
                 const int32_t* target_ids, const int64_t* target_offsets, int64_t max_rows, int topk,
                 int32_t* ids, float* dist, int out_stride, const int* qmode, int want_mode, void* ws_base,
-                hipStream_t st) {
+                hipStream_t st, bool cleared = false) {
   const int M = idx->M;
   if (Q > 65535) return RII_ERR_UNSUPPORTED;
   const bool timed = mode == kLinear && idx->ev_start && idx->ev_stop && codes == idx->d_codes;
@@ -287,9 +290,9 @@ int launch_scan(const rii_index* idx, const uint8_t* codes, int64_t plane, int64
     f.codes = codes; f.plane = plane; f.M = M; f.lut = lut; f.N = N; f.target_ids = target_ids; f.target_offsets = target_offsets;
     f.k = topk; f.ids = ids; f.dist = dist; f.out_stride = out_stride; f.qmode = qmode; f.want_mode = want_mode;
     const FewShape shape = few_shape(M, Q, max_rows, topk, false, mode == kSubset);
-    if (mode == kSubset) return launch_few<kFewSubset>(f, shape, Q, ws_base, st);
+    if (mode == kSubset) return launch_few<kFewSubset>(f, shape, Q, ws_base, cleared, st);
     if (timed) RII_HIP(hipEventRecord(static_cast<hipEvent_t>(idx->ev_start), st));
-    const int rc = launch_few<kFewLinear>(f, shape, Q, ws_base, st);
+    const int rc = launch_few<kFewLinear>(f, shape, Q, ws_base, cleared, st);
     if (timed && !rc) RII_HIP(hipEventRecord(static_cast<hipEvent_t>(idx->ev_stop), st));
     return rc;
   }
@@ -768,7 +771,7 @@ static size_t ivf_ws_bytes(const rii_index* idx, int Q, int nprobe, int64_t L, i
 static int launch_ivf(const rii_index* idx, const float* lut, int Q, const int32_t* probe, int probe_stride,
                       int nprobe, const int* nprobe_q, const int32_t* target_ids, const int64_t* target_offsets,
                       int64_t L, int topk, int32_t* ids, float* dist, const int* qmode, int want_mode, void* ws,
-                      hipStream_t st) {
+                      hipStream_t st, bool cleared = false) {
   const int M = idx->M;
   const bool capped = L > 0 && target_ids;
   const int64_t rows = list_rows(idx, nprobe, capped ? 0 : L);
@@ -779,7 +782,7 @@ static int launch_ivf(const rii_index* idx, const float* lut, int Q, const int32
     f.probe = probe; f.probe_stride = probe_stride; f.nprobe = nprobe; f.nprobe_q = nprobe_q; f.Lcap = L;
     f.k = topk; f.ids = ids; f.dist = dist; f.out_stride = topk; f.qmode = qmode; f.want_mode = want_mode;
     const FewShape shape = few_shape(M, Q, rows, topk, capped);
-    return capped ? launch_few<kFewCapped>(f, shape, Q, ws, st) : launch_few<kFewLists>(f, shape, Q, ws, st);
+    return capped ? launch_few<kFewCapped>(f, shape, Q, ws, cleared, st) : launch_few<kFewLists>(f, shape, Q, ws, cleared, st);
   }
   IvfArgs a{};
   a.codes_list = idx->d_codes_list; a.plane = idx->plane_list; a.list_ids = idx->d_list_ids; a.list_off = idx->d_list_off; a.M = M;
@@ -896,7 +899,7 @@ static int run_query(const rii_index* idx, const QueryPlan& p, const float* q, i
   int32_t* probe = reinterpret_cast<int32_t*>(w); w += p.probe_b;
   void* stage_ws = w;
 
-  launch_build_lut(idx, q, Q, lut, st);
+  launch_build_lut(idx, q, Q, lut, st, p.uniform ? stage_ws : nullptr);
   if (p.uniform) qmode = nprobe_q = nullptr;  // (one branch for all queries; every query's lists are p.pmax then)
   else k_plan<<<(Q + 255) / 256, 256, 0, st>>>(target_offsets, idx->N, Q, idx->theta, K, L, p.pmax, qmode, nprobe_q);
   int rc = RII_OK;
@@ -907,15 +910,16 @@ static int run_query(const rii_index* idx, const QueryPlan& p, const float* q, i
                      ids, dist, topk, qmode, 0, stage_ws, st);
   } else if (all_linear) {
     rc = launch_scan(idx, idx->d_codes, idx->plane_codes, idx->N, lut, Q, kLinear, nullptr, nullptr, idx->N, topk, ids, dist, topk,
-                     qmode, 0, stage_ws, st);
+                     qmode, 0, stage_ws, st, p.uniform);
   }
   if (rc) return rc;
   // inverted-index branch (mode 1); the scratch of the scan stage is reused in stream order
   if (has_lists && !all_linear) {
     rc = coarse_rank(idx, lut, Q, p.pmax, probe, nullptr, p.pmax, qmode, 1, stage_ws, st);
     if (rc) return rc;
+    const bool untouched = coarse_in_lds(K, p.pmax) && !coarse_split(Q, K);  // the ranking leaves the stage scratch alone
     rc = launch_ivf(idx, lut, Q, probe, p.pmax, p.pmax, nprobe_q, target_ids, target_offsets, L, topk, ids, dist, qmode,
-                    1, stage_ws, st);
+                    1, stage_ws, st, p.uniform && untouched);
     if (rc) return rc;
   }
   RII_HIP(hipGetLastError());
