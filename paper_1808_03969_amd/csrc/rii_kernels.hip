@@ -362,7 +362,7 @@ int launch_scan(const rii_index* idx, const uint8_t* codes, int64_t plane, int64
     dim3 pgrid((unsigned)pre_blocks, (unsigned)Q);
     const size_t ldsw = table_bytes(M) + (size_t)(kScanThreads / 64 + 1) * kWaveCap * 8 + kBlockVarsBytes;
     const size_t lds4 = 65536 + 4 * (size_t)(kScanThreads / 64 + 1) * kWaveCap4 * 8 +
-                        (size_t)(kScanThreads / 64) * kRescoreCap * 8 + kBlockVarsBytes + kMthWords * 4;
+                        (size_t)(kScanThreads / 64) * kRescoreCap * 8 + kBlockVarsBytes + 4 * kBins4 * 4;
     const size_t lds2 = 65536 + 2 * (size_t)(kScanThreads / 64 + 1) * kWaveCap * 8 + kBlockVarsBytes;
     if (batched) {
       // Four queries per block with the integer-table filter; the rows are cut into chunks
