@@ -5,9 +5,10 @@
 //
 // Data flow of one query batch:
 //   k_build_lut              q, code books                        -> A [Q][M][256]       (Sec. 3)
+//   k_few                    A in LDS, some 10^4 rows at most     -> top-R per query     (all of the following, small)
 //   k_scan_w4 / k_scan_w     A in LDS, codes streamed             -> top-R per query     (Alg. 1, whole data)
 //   k_scan_w<subset>         A in LDS, codes gathered by id       -> top-R per query     (Alg. 1, target ids)
-//   k_scan_w4 / k_scan_w     the same over the coarse codes       -> nearest lists       (Alg. 2, first block)
+//   k_rank_lists             A in LDS, coarse codes               -> nearest lists       (Alg. 2, first block)
 //   k_ivf_w / k_ivf          A in LDS, probed lists streamed      -> top-R per query     (Alg. 2, second block)
 //   k_scan + k_select, k_sort_segments: R above the per-wave kernels' reach, explicit candidates
 //
