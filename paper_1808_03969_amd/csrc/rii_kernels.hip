@@ -266,16 +266,33 @@ int launch_few(FewArgs a, const FewShape& f, int Q, void* ws, bool cleared, hipS
 }
 
 // Rows per query up to which a scan goes to k_few.  Measured against the streaming kernels (which it
-// would otherwise go to) for batches of 1 .. 4000 queries; microseconds there / here, top-100:
-//   lists     M = 16:  1 query 8,000 rows 45 / 32, 64,000 38 / 37, 128,000 39 / 47; 4000 queries 655 / 255,
-//             1426 / 907, 1976 / 1690;  M = 32:  4000 queries 8,000 rows 786 / 447, 32,000 1323 / 1035, 64,000
-//             1747 / 1833 (its streaming kernel abandons rows half-way)
-//   target sets  M = 16:  1 query 8,000 rows 38 / 24, 64,000 69 / 34; 4000 queries 692 / 221, 2382 / 2446
-//   whole array  M = 16:  1 query 8,000 rows 36 / 23, 64,000 56 / 33, 128,000 45 / 45; 4000 queries 791 / 169,
-//             1193 / 849, 1441 / 1596 (four queries a block);  M = 32:  4000 queries 64,000 rows 1813 / 1713
-bool few_lists(int M, int64_t rows) { return rows <= (M == 32 ? 40000 : 65536); }
-bool few_subset(int64_t rows) { return rows <= 65536; }
-bool few_linear(int M, int64_t rows) { return rows <= (M == 32 ? 65536 : 100000); }
+// would otherwise go to) for batches of 1 .. 4000 queries, M = 16 and 32, top-1, 10 and 100; microseconds
+// there / here.  The streaming kernels lose to their fixed cost and, for many results, to their selection;
+// with few results, many queries or M = 32 (rows abandoned half-way) they catch up early:
+//   whole array  M = 16:  1 query, top-100 64,000 rows 56 / 33;  600 queries, top-100 32,000 158 / 108, 64,000
+//     186 / 188, top-10 16,000 82 / 62, 32,000 92 / 102;  M = 32:  600 queries, top-100 16,000 151 / 108, 32,000 217 / 196
+//   lists        M = 16:  4000 queries, top-100 64,000 members 1431 / 912, top-10 32,000 616 / 514;  64 queries,
+//     top-10 16,000 35 / 38;  M = 32:  4000 queries, top-100 32,000 1346 / 1053, top-10 4,000 406 / 278, 16,000 643 / 676
+//   target sets  M = 16:  64 queries, top-100 64,000 ids 126 / 63;  200 queries, top-100 16,000 72 / 57, 32,000
+//     95 / 105;  4000 queries, top-100 64,000 2396 / 2424, top-10 16,000 787 / 555, 32,000 1289 / 1230
+constexpr int kFewManyResults = 64;
+bool few_linear(int M, int Q, int topk, int64_t rows) {
+  const bool many = topk >= kFewManyResults;
+  if (Q <= 4) return rows <= 65536;
+  if (!rot_m(M)) return rows <= (many ? 65536 : 16000);
+  if (Q <= kWantBlocks) return rows <= (many ? 65536 : M == 32 ? 12000 : 32000);
+  return rows <= (many ? (M == 32 ? 24000 : 40000) : M == 32 ? 10000 : 16000);
+}
+bool few_lists(int M, int Q, int topk, int64_t rows) {
+  if (topk >= kFewManyResults) return rows <= (M == 32 || M == 64 ? 32000 : 65536);
+  return rows <= (Q <= 4 ? 65536 : M == 32 ? 8000 : 16000);
+}
+bool few_subset(int Q, int topk, int64_t rows) {
+  const bool many = topk >= kFewManyResults;
+  if (Q <= 64) return rows <= 65536;
+  if (Q <= 400) return rows <= (many ? 16000 : 12000);
+  return rows <= (many ? 50000 : 24000);
+}
 
 // Scan `nrows_max` rows per query (linear: the whole array) and leave per-block partial keys in
 // the workspace; then select.  Workspace layout: [tau Q u32][partial Q*nchunks*k u64].
@@ -286,7 +303,7 @@ int launch_scan(const rii_index* idx, const uint8_t* codes, int64_t plane, int64
   const int M = idx->M;
   if (Q > 65535) return RII_ERR_UNSUPPORTED;
   const bool timed = mode == kLinear && idx->ev_start && idx->ev_stop && codes == idx->d_codes;
-  if (mode == kLinear ? few_linear(M, max_rows) && !idx->bench_half_table : few_subset(max_rows)) {
+  if (mode == kLinear ? few_linear(M, Q, topk, max_rows) && !idx->bench_half_table : few_subset(Q, topk, max_rows)) {
     FewArgs f{};
     f.codes = codes; f.plane = plane; f.M = M; f.lut = lut; f.N = N; f.target_ids = target_ids; f.target_offsets = target_offsets;
     f.k = topk; f.ids = ids; f.dist = dist; f.out_stride = out_stride; f.qmode = qmode; f.want_mode = want_mode;
@@ -537,7 +554,7 @@ int rii_scan_linear_plan(const rii_index_t* idx, int Q, int topk, int* queries_p
   if (topk > RII_MAX_TOPK || !m_supported(idx->M) || Q > 65535) return RII_ERR_UNSUPPORTED;
   int64_t nchunks, chunk_rows, bchunks, brows;
   scan_chunks(Q, idx->N, &nchunks, &chunk_rows);
-  if (few_linear(idx->M, idx->N)) {
+  if (few_linear(idx->M, Q, topk, idx->N)) {
     *queries_per_block = 1;
     *row_chunks = few_shape(idx->M, Q, idx->N, topk, false).split;
   } else if (topk <= kWaveK && plan_batch(idx->M, Q, idx->N, topk, &bchunks, &brows)) {
@@ -776,7 +793,7 @@ static int launch_ivf(const rii_index* idx, const float* lut, int Q, const int32
   const int M = idx->M;
   const bool capped = L > 0 && target_ids;
   const int64_t rows = list_rows(idx, nprobe, capped ? 0 : L);
-  if (nprobe <= kIvfMaxProbe && Q <= 65535 && (capped || topk > kWaveK || few_lists(M, rows))) {
+  if (nprobe <= kIvfMaxProbe && Q <= 65535 && (capped || topk > kWaveK || few_lists(M, Q, topk, rows))) {
     FewArgs f{};
     f.codes = idx->d_codes_list; f.plane = idx->plane_list; f.M = M; f.lut = lut; f.N = idx->N;
     f.target_ids = target_ids; f.target_offsets = target_offsets; f.list_ids = idx->d_list_ids; f.list_off = idx->d_list_off;
