@@ -252,3 +252,28 @@ def test_query_without_target_sets(M, N, Q, topk, K, theta, rii, oracle_lib):
         else:
             ref = oracle_lib.linear_scan(A[i], d["codes"], topk)
         assert np.array_equal(t2n(ids)[i], ref[0]) and np.array_equal(t2n(dist)[i], ref[1]), i
+
+
+# tables that a caller made: entries of either sign where the scans take any (the sums of 64 and of other numbers of
+# sub-spaces are formed row by row), in every form of the small scan, topk small enough for a bound early on
+@pytest.mark.parametrize("M,N,Q", [(64, 5000, 3), (64, 20000, 2), (12, 5000, 3)])
+def test_small_scans_with_signed_tables(M, N, Q, rii, oracle_lib):
+    rng = np.random.default_rng(N + M)
+    d = plain_index(rii, oracle_lib, rng, N, M, 6)
+    A = rng.normal(size=(Q, M, 256)).astype(np.float32)
+    lut = torch.from_numpy(A).cuda()
+    sets = [np.sort(rng.permutation(N)[:N // 2]).astype(np.int32) for _ in range(Q)]
+    tids = torch.from_numpy(np.concatenate(sets)).cuda()
+    toff = torch.arange(Q + 1).cuda() * (N // 2)
+    probe, _ = rii.rii_coarse_assign(d["index"], lut, 6)
+    got = dict(linear=rii.rii_adc_scan_linear(d["index"], lut, 5),
+               subset=rii.rii_adc_scan_subset(d["index"], lut, tids, toff, N // 2, 5),
+               lists=rii.rii_adc_scan_ivf(d["index"], lut, probe, 5),
+               capped=rii.rii_adc_scan_ivf(d["index"], lut, probe, 5, tids, toff, L=N // 3))
+    torch.cuda.synchronize()
+    for i in range(Q):
+        iv = lambda L, S: oracle_lib.inverted_index(A[i], d["codes"], d["coarse"], d["off"], d["lids"], 5, 6, Lcap=L, S=S)[:2]
+        ref = dict(linear=oracle_lib.linear_scan(A[i], d["codes"], 5), subset=oracle_lib.linear_scan(A[i], d["codes"], 5, S=sets[i]),
+                   lists=iv(0, None), capped=iv(N // 3, sets[i]))
+        for name, (ids, dist) in ref.items():
+            assert np.array_equal(t2n(got[name][0])[i], ids) and np.array_equal(t2n(got[name][1])[i], dist), (name, i)
