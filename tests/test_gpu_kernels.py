@@ -277,3 +277,33 @@ def test_small_scans_with_signed_tables(M, N, Q, rii, oracle_lib):
                    lists=iv(0, None), capped=iv(N // 3, sets[i]))
         for name, (ids, dist) in ref.items():
             assert np.array_equal(t2n(got[name][0])[i], ids) and np.array_equal(t2n(got[name][1])[i], dist), (name, i)
+
+
+# a query that is not a number in one coordinate, beside ordinary ones: at 8, 16 and 32 sub-spaces such distances are no
+# candidates (as in the streaming kernels), else they come after all others with their identifiers in order; one block a
+# query over several rounds (300 queries) and several blocks, the coordinate in the first and in the last sub-space,
+# either sign
+@pytest.mark.parametrize("M,N,Q,topk", [(8, 3000, 4, 10), (16, 9000, 4, 100), (32, 2500, 4, 20), (64, 9000, 4, 100), (64, 5000, 300, 100),
+                                        (12, 9000, 4, 100)])
+def test_small_scans_of_a_query_that_is_not_a_number(M, N, Q, topk, rii, oracle_lib):
+    rng = np.random.default_rng(M)
+    d = plain_index(rii, oracle_lib, rng, N, M, 6)
+    q = rng.normal(size=(Q, 2 * M)).astype(np.float32)
+    q[1, 2 * M - 1], q[2, 0], q[3, M] = np.nan, np.nan, np.inf
+    q[1, 2 * M - 1] = np.copysign(q[1, 2 * M - 1], np.float32(-1 if M in (8, 16, 32) else 1))
+    lut = rii.rii_build_lut(d["index"], torch.from_numpy(q).cuda())
+    got = rii.rii_adc_scan_linear(d["index"], lut, topk)
+    probe = torch.arange(6, dtype=torch.int32).repeat(Q, 1).cuda()
+    lists = rii.rii_adc_scan_ivf(d["index"], lut, probe, topk)
+    torch.cuda.synchronize()
+    A = oracle_lib.lut(d["cb"], q)
+    ref = oracle_lib.linear_scan(A[0], d["codes"], topk)
+    for ids, dist in (got, lists):
+        ids, dist = t2n(ids), t2n(dist)
+        assert np.array_equal(ids[0], ref[0]) and np.array_equal(dist[0], ref[1])
+        for i in (1, 2):
+            if M in (8, 16, 32):
+                assert np.all(ids[i] == -1) and np.all(np.isinf(dist[i])), i
+            else:
+                assert np.array_equal(ids[i], np.arange(topk)) and np.all(np.isnan(dist[i])), i
+        assert np.array_equal(ids[3], np.arange(topk)) and np.all(np.isposinf(dist[3]))
