@@ -307,3 +307,23 @@ def test_small_scans_of_a_query_that_is_not_a_number(M, N, Q, topk, rii, oracle_
             else:
                 assert np.array_equal(ids[i], np.arange(topk)) and np.all(np.isnan(dist[i])), i
         assert np.array_equal(ids[3], np.arange(topk)) and np.all(np.isposinf(dist[3]))
+
+
+# a table that starts at any float of a larger array
+@pytest.mark.parametrize("M", [8, 12, 16, 32, 64])
+def test_small_scans_of_a_table_at_any_float(M, rii, oracle_lib):
+    rng = np.random.default_rng(M)
+    d = plain_index(rii, oracle_lib, rng, 3000, M, 50)
+    A = oracle_lib.lut(d["cb"], rng.normal(size=(2, 2 * M)).astype(np.float32))
+    for shift in (1, 2, 3):
+        buf = torch.empty(A.size + shift, dtype=torch.float32, device="cuda")
+        lut = buf[shift:].view(A.shape)
+        lut.copy_(torch.from_numpy(A))
+        ids, dist = rii.rii_adc_scan_linear(d["index"], lut, 10)
+        lists, d0 = rii.rii_coarse_assign(d["index"], lut, 7)
+        torch.cuda.synchronize()
+        for i in range(2):
+            ref = oracle_lib.linear_scan(A[i], d["codes"], 10)
+            assert np.array_equal(t2n(ids)[i], ref[0]) and np.array_equal(t2n(dist)[i], ref[1]), (shift, i)
+            ref = oracle_lib.coarse_rank(A[i], d["coarse"], 7)
+            assert np.array_equal(t2n(lists)[i], ref[0]) and np.array_equal(t2n(d0)[i], ref[1]), (shift, i)
