@@ -1133,6 +1133,9 @@ size_t rii_internal_assign_matrix_bytes(const rii_index* idx, int64_t n, int K) 
   return (size_t)tiles * steps * 2 * 64 * 16 + align_up((size_t)tiles * 64, 256) + 256 + align_up((size_t)(n + 1) * 4, 256);
 }
 
+// The margin the products are used with, as a share of |x|^2 + max |c|^2 (see assign_margin).
+float rii_internal_assign_margin(int M, int Ds) { return assign_margin((M * Ds + 31) / 32 * 32, M, Ds); }
+
 int rii_internal_assign_matrix(const rii_index* idx, const uint8_t* codes, int64_t n, int64_t rot_base, int64_t plane,
                                const uint8_t* coarse, int K, int32_t* assign_out, void* scratch, hipStream_t st) {
   if (n == 0) return RII_OK;

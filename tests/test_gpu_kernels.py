@@ -327,3 +327,20 @@ def test_small_scans_of_a_table_at_any_float(M, rii, oracle_lib):
             assert np.array_equal(t2n(ids)[i], ref[0]) and np.array_equal(t2n(dist)[i], ref[1]), (shift, i)
             ref = oracle_lib.coarse_rank(A[i], d["coarse"], 7)
             assert np.array_equal(t2n(lists)[i], ref[0]) and np.array_equal(t2n(d0)[i], ref[1]), (shift, i)
+
+
+# centres in pairs whose distances to every item differ by some 10^-4 of them and less, on both sides of what the
+# matrix products may decide; code books of 8, 32 and 128 coordinates
+@pytest.mark.parametrize("M,Ds,N,K", [(4, 2, 3000, 40), (8, 4, 3000, 300), (16, 8, 3000, 600)])
+def test_assignment_between_centres_that_nearly_coincide(M, Ds, N, K, rii, oracle_lib):
+    rng = np.random.default_rng(N + M)
+    cb = rng.normal(size=(M, 256, Ds)).astype(np.float32)
+    cb[:, 1::2] = cb[:, ::2] * (1 + rng.choice([1e-6, 1e-5, 1e-4, 1e-3], size=(M, 128, 1)) * rng.normal(size=(M, 128, Ds)))
+    codes = rng.integers(0, 256, size=(N, M), dtype=np.uint8)
+    coarse = rng.integers(0, 256, size=(K, M), dtype=np.uint8)
+    coarse[1::2] = coarse[::2]
+    coarse[np.arange(1, K, 2), rng.integers(0, M, size=K // 2)] ^= 1
+    index = rii.Index(cb)
+    index.add(codes)
+    index.build_lists(coarse)
+    assert np.array_equal(index.get_lists()[3], oracle_lib.assign(oracle_lib.sym_table(cb), codes, coarse))
