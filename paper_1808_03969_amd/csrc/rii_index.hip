@@ -16,15 +16,16 @@
 
 extern "C" int rii_internal_sym_table(const rii_index* idx, hipStream_t st);
 extern "C" int rii_internal_assign(const rii_index* idx, const uint8_t* codes, int64_t n, int64_t rot_base, int64_t plane,
-                                   const uint8_t* coarse, int K, int32_t* assign_out, hipStream_t st);
+                                   const uint8_t* coarse, int K, int32_t* assign_out, const uint32_t* open, hipStream_t st);
 extern "C" int rii_internal_assign_pruned(const rii_index* idx, const uint8_t* codes, int64_t n, int64_t rot_base,
                                           int64_t plane,
                                           const uint8_t* super, int G, const float* radius, const uint8_t* coarse_g,
                                           const int32_t* perm_g, const int32_t* group_off, int32_t* assign_out,
-                                          unsigned long long* visited_total, hipStream_t st);
+                                          const uint32_t* open, unsigned long long* visited_total, hipStream_t st);
 extern "C" size_t rii_internal_assign_matrix_bytes(const rii_index* idx, int64_t n, int K);
 extern "C" int rii_internal_assign_matrix(const rii_index* idx, const uint8_t* codes, int64_t n, int64_t rot_base, int64_t plane,
-                                          const uint8_t* coarse, int K, int32_t* assign_out, void* scratch, hipStream_t st);
+                                          const uint8_t* coarse, int K, int32_t* assign_out, void* scratch,
+                                          const uint32_t** open_out, hipStream_t st);
 extern "C" size_t rii_internal_lists_bytes(int64_t n, int K);
 extern "C" int rii_internal_build_lists(const int32_t* assign, int64_t n, int K, int64_t* off, int32_t* ids, void* scratch,
                                         hipStream_t st);
@@ -137,7 +138,7 @@ int lists_of(const int32_t* d_assign, int64_t n, int K, DevBuf& off, DevBuf& ids
 
 // Grouping of the coarse centres used to prune the search for a(n) when K is large.
 struct CentreGroups {
-  int G = 0;
+  int G = 0;                     // 0: not made yet
   uint8_t* d_super = nullptr;    // [G][M]
   float* d_radius = nullptr;     // [G]
   uint8_t* d_coarse_g = nullptr; // [K][M] centres, group after group
@@ -150,6 +151,17 @@ struct CentreGroups {
 
 constexpr int kPruneMinK = 1024;
 constexpr int64_t kMatrixMinItems = 256;
+// Undecided items of the matrix products from this many on are worth the pruned search's preparation on the host
+// (46 ns K M: 3 ms at K = 4096, M = 16, 24 ms at K = 16384, M = 32, where k_assign takes 0.22 ps K M an item).
+constexpr int64_t kPruneMinItems = (int64_t)1 << 18;
+// With that many items, kTrialMinK centres (below, the pruned search gains nothing on k_assign) and kTrialWork
+// distances (where waiting for a number no longer shows: 0.05 of 0.9 ms) the undecided ones of the first kTrialItems
+// are counted.  Where they are most of them -- repeated centres, clusters much narrower than they are apart -- the
+// products are of no use and the pruned search takes all items: 2 x 10^6 items, M = 16, K = 4096 with every centre
+// ten times 32.4 -> 15.1 ms, K = 16384 111 -> 32 ms.
+constexpr int kTrialMinK = 2048;
+constexpr int64_t kTrialItems = (int64_t)1 << 17;
+constexpr int64_t kTrialWork = (int64_t)1 << 30;
 
 // Cluster the K coarse codes into G groups in code space (three rounds of the same clustering
 // reconfigure uses) and record each group's radius under d_S.
@@ -159,7 +171,6 @@ int make_groups(rii_index* idx, const uint8_t* coarse, int K, CentreGroups& g) {
   if (G < 64) G = 64;
   if (G > 2048) G = 2048;
   if (G > K) G = K;
-  g.G = G;
   int rc = rii_internal_sym_table(idx, nullptr);
   if (rc) return rc;
   std::vector<float> sym((size_t)M * 256 * 256);
@@ -222,36 +233,55 @@ int make_groups(rii_index* idx, const uint8_t* coarse, int K, CentreGroups& g) {
   RII_HIP(hipMemcpy(g.d_coarse_g, coarse_g.data(), coarse_g.size(), hipMemcpyHostToDevice));
   RII_HIP(hipMemcpy(g.d_perm_g, perm.data(), (size_t)K * 4, hipMemcpyHostToDevice));
   RII_HIP(hipMemcpy(g.d_group_off, off.data(), (size_t)(G + 1) * 4, hipMemcpyHostToDevice));
+  g.G = G;
   return RII_OK;
 }
 
 // a(n) for n device-resident codes `rows` under the device-resident centres d_coarse; the result
 // stays on the device (d_out, n entries).  rot_base >= 0: `rows` is the base of a stored array with
 // planes `plane` apart and the items are its rows rot_base..; rot_base < 0: plain codes.  Matrix products
-// for dimensions up to 128 unless the items are few, else brute force for small K and a pruned search
-// for large K (the same result each).
+// for dimensions up to 128 unless the items are few; what they leave, and everything else, by brute force for
+// small K and by a pruned search for large K (the same result each).
 int assign_rows_dev(rii_index* idx, const uint8_t* rows, int64_t n, int64_t rot_base, int64_t plane,
                     const uint8_t* d_coarse, int K, int32_t* d_out) {
   if (n == 0) return RII_OK;
   int rc = RII_OK;
+  CentreGroups g;
   const int64_t part = std::min<int64_t>(n, (int64_t)1 << 23);  // items per launch: bounds the list of undecided ones
   const size_t scratch = n >= kMatrixMinItems ? rii_internal_assign_matrix_bytes(idx, part, K) : 0;
+  // the defined sums, for the cnt items from `first` on or those of them that are listed (`items` of them)
+  auto decide = [&](int64_t first, int64_t cnt, const uint32_t* open, int64_t items) -> int {
+    const uint8_t* r = rot_base >= 0 ? rows : rows + first * idx->M;
+    const int64_t rot = rot_base >= 0 ? rot_base + first : -1;
+    if (K < kPruneMinK || (scratch && !g.G && items < kPruneMinItems))
+      return rii_internal_assign(idx, r, cnt, rot, plane, d_coarse, K, d_out + first, open, nullptr);
+    if (!g.G) {
+      std::vector<uint8_t> coarse((size_t)K * idx->M);
+      RII_HIP(hipMemcpy(coarse.data(), d_coarse, coarse.size(), hipMemcpyDeviceToHost));
+      const int rc2 = make_groups(idx, coarse.data(), K, g);
+      if (rc2) return rc2;
+    }
+    return rii_internal_assign_pruned(idx, r, cnt, rot, plane, g.d_super, g.G, g.d_radius, g.d_coarse_g, g.d_perm_g,
+                                      g.d_group_off, d_out + first, open, nullptr, nullptr);
+  };
   DevBuf d_scratch;
-  CentreGroups g;
-  if (scratch) {
-    rc = d_scratch.alloc(scratch);
-    for (int64_t i = 0; i < n && !rc; i += part)
-      rc = rii_internal_assign_matrix(idx, rot_base >= 0 ? rows : rows + i * idx->M, std::min(part, n - i),
-                                      rot_base >= 0 ? rot_base + i : -1, plane, d_coarse, K, d_out + i, d_scratch.p, nullptr);
-  } else if (K >= kPruneMinK) {
-    std::vector<uint8_t> coarse((size_t)K * idx->M);
-    RII_HIP(hipMemcpy(coarse.data(), d_coarse, coarse.size(), hipMemcpyDeviceToHost));
-    rc = make_groups(idx, coarse.data(), K, g);
-    if (!rc) rc = rii_internal_assign_pruned(idx, rows, n, rot_base, plane, g.d_super, g.G, g.d_radius, g.d_coarse_g, g.d_perm_g,
-                                             g.d_group_off, d_out, nullptr, nullptr);
-  } else {
-    rc = rii_internal_assign(idx, rows, n, rot_base, plane, d_coarse, K, d_out, nullptr);
+  if (scratch) rc = d_scratch.alloc(scratch);
+  bool counted = K >= kTrialMinK && n >= std::max(kPruneMinItems, kTrialWork / K);
+  int64_t done = 0;
+  while (scratch && done < n && !rc) {
+    const bool trial = counted && done == 0;
+    const int64_t cnt = std::min(trial ? kTrialItems : part, n - done);
+    const uint32_t* open = nullptr;
+    rc = rii_internal_assign_matrix(idx, rot_base >= 0 ? rows : rows + done * idx->M, cnt, rot_base >= 0 ? rot_base + done : -1,
+                                    plane, d_coarse, K, d_out + done, d_scratch.p, &open, nullptr);
+    uint32_t left = 0;
+    if (!rc && counted && hipMemcpy(&left, open, 4, hipMemcpyDeviceToHost) != hipSuccess) rc = RII_ERR_DEVICE;
+    if (trial && 2 * (int64_t)left > cnt) break;
+    if (trial && 64 * (int64_t)left < cnt) counted = false;  // few: not worth counting in the parts that follow
+    if (!rc) rc = decide(done, cnt, open, left);
+    done += cnt;
   }
+  if (!rc && done < n) rc = decide(done, n - done, nullptr, n - done);
   if (!rc && hipDeviceSynchronize() != hipSuccess) rc = RII_ERR_DEVICE;
   return rc;
 }

@@ -1102,9 +1102,10 @@ int rii_internal_sym_table(const rii_index* cidx, hipStream_t st) {
 }
 
 // a(n) by brute force.  rot_base >= 0: `codes` is the base of a stored array (planes `plane`
-// apart) and the items are its rows rot_base .. rot_base+n-1; rot_base < 0: n plain codes.
+// apart) and the items are its rows rot_base .. rot_base+n-1; rot_base < 0: n plain codes.  `open` not NULL:
+// only those of the items that it lists (see k_assign).
 int rii_internal_assign(const rii_index* idx, const uint8_t* codes, int64_t n, int64_t rot_base, int64_t plane,
-                        const uint8_t* coarse, int K, int32_t* assign_out, hipStream_t st) {
+                        const uint8_t* coarse, int K, int32_t* assign_out, const uint32_t* open, hipStream_t st) {
   if (!m_supported(idx->M)) return RII_ERR_UNSUPPORTED;
   if (n == 0) return RII_OK;
   if (!rot_m(idx->M) && rot_base >= 0) { codes += rot_base * idx->M; rot_base = -1; }
@@ -1112,9 +1113,9 @@ int rii_internal_assign(const rii_index* idx, const uint8_t* codes, int64_t n, i
   if (rc) return rc;
   const int M = idx->M;
   const size_t lds = (size_t)M * 1024;
-  int blocks = (int)std::min<int64_t>(n, 256 * 16);
+  int blocks = (int)std::min<int64_t>(n, open ? 256 * 8 : 256 * 16);
   DISPATCH_M(M, { int rc2 = set_lds(k_assign<MT>, lds); if (rc2) return rc2;
-                  k_assign<MT><<<blocks, 256, lds, st>>>(idx->d_sym, codes, n, rot_base, plane, M, coarse, K, assign_out, nullptr); });
+                  k_assign<MT><<<blocks, 256, lds, st>>>(idx->d_sym, codes, n, rot_base, plane, M, coarse, K, assign_out, open); });
   RII_HIP(hipGetLastError());
   return RII_OK;
 }
@@ -1122,37 +1123,37 @@ int rii_internal_assign(const rii_index* idx, const uint8_t* codes, int64_t n, i
 int rii_assign(const rii_index_t* idx, const uint8_t* codes, int64_t n, const uint8_t* coarse, int K,
                int32_t* assign_out, void* stream) {
   if (!idx || n < 0 || K < 1 || !coarse || (n > 0 && (!codes || !assign_out))) return RII_ERR_INVALID_ARG;
-  return rii_internal_assign(idx, codes, n, -1, 0, coarse, K, assign_out, static_cast<hipStream_t>(stream));
+  return rii_internal_assign(idx, codes, n, -1, 0, coarse, K, assign_out, nullptr, static_cast<hipStream_t>(stream));
 }
 
-// a(n) by matrix products (see k_assign_matrix); all pointers device.  Items as in rii_internal_assign, at most
-// 2^31 of them; scratch: rii_internal_assign_matrix_bytes, or 0 when the dimension is beyond the kernel.
+// a(n) by matrix products (see k_assign_matrix), as far as they decide it; all pointers device.  Items as in
+// rii_internal_assign, at most 2^31 of them; scratch: rii_internal_assign_matrix_bytes, or 0 when the dimension is
+// beyond the kernel.  *open_out: the undecided items, for rii_internal_assign or rii_internal_assign_pruned.
 size_t rii_internal_assign_matrix_bytes(const rii_index* idx, int64_t n, int K) {
   const int steps = (idx->D + 31) / 32, tiles = (K + 15) / 16;
   if (steps > 4 || !m_supported(idx->M)) return 0;
-  return (size_t)tiles * steps * 2 * 64 * 16 + align_up((size_t)tiles * 64, 256) + 256 + align_up((size_t)(n + 1) * 4, 256);
+  return (size_t)tiles * steps * 2 * 64 * 16 + align_up((size_t)tiles * 64, 256) + align_up((size_t)idx->D * 1024, 256) + 256 +
+         align_up((size_t)(n + 1) * 4, 256);
 }
 
 // The margin the products are used with, as a share of |x|^2 + max |c|^2 (see assign_margin).
 float rii_internal_assign_margin(int M, int Ds) { return assign_margin((M * Ds + 31) / 32 * 32, M, Ds); }
 
 int rii_internal_assign_matrix(const rii_index* idx, const uint8_t* codes, int64_t n, int64_t rot_base, int64_t plane,
-                               const uint8_t* coarse, int K, int32_t* assign_out, void* scratch, hipStream_t st) {
-  if (n == 0) return RII_OK;
-  const int M = idx->M, steps = (idx->D + 31) / 32, tiles = (K + 15) / 16;
+                               const uint8_t* coarse, int K, int32_t* assign_out, void* scratch, const uint32_t** open_out,
+                               hipStream_t st) {
+  const int M = idx->M, Ds = idx->Ds, steps = (idx->D + 31) / 32, tiles = (K + 15) / 16;
   if (!rot_m(M) && rot_base >= 0) { codes += rot_base * M; rot_base = -1; }
-  int rc = rii_internal_sym_table(idx, st);
-  if (rc) return rc;
   uint8_t* w = static_cast<uint8_t*>(scratch);
   bf16x8_t* frag = reinterpret_cast<bf16x8_t*>(w); w += (size_t)tiles * steps * 2 * 64 * 16;
   float* c2 = reinterpret_cast<float*>(w); w += align_up((size_t)tiles * 64, 256);
+  float* books = reinterpret_cast<float*>(w); w += align_up((size_t)idx->D * 1024, 256);
   uint32_t* cmax = reinterpret_cast<uint32_t*>(w); w += 256;
   uint32_t* open = reinterpret_cast<uint32_t*>(w);
-  k_init_scan<<<1, 256, 0, st>>>(nullptr, 0, 0, cmax, 1);
-  k_init_scan<<<1, 256, 0, st>>>(nullptr, 0, 0, open, 1);
-  k_centre_frags<<<tiles, 64, 0, st>>>(idx->d_cb, M, idx->Ds, coarse, K, steps, frag, c2, cmax);
+  k_centred_books<<<dim3((unsigned)M, (unsigned)Ds), 256, 0, st>>>(idx->d_cb, M, Ds, coarse, K, books, cmax, open);
+  k_centre_frags<<<tiles, 64, 0, st>>>(books, M, Ds, coarse, K, steps, frag, c2, cmax);
 #define RII_ASSIGN(S, T)                                                                              \
-  k_assign_matrix<S, T><<<(unsigned)((n + 64 * T - 1) / (64 * T)), 256, 0, st>>>(idx->d_cb, M, idx->Ds, codes, n, rot_base, plane, \
+  k_assign_matrix<S, T><<<(unsigned)((n + 64 * T - 1) / (64 * T)), 256, 0, st>>>(books, M, Ds, codes, n, rot_base, plane, \
                                                                                  frag, c2, cmax, tiles, assign_out, open)
   switch (steps) {
     case 1: RII_ASSIGN(1, 4); break;
@@ -1161,20 +1162,17 @@ int rii_internal_assign_matrix(const rii_index* idx, const uint8_t* codes, int64
     default: RII_ASSIGN(4, 2); break;
   }
 #undef RII_ASSIGN
-  const size_t lds = (size_t)M * 1024;
-  const int few = (int)std::min<int64_t>(n, 256 * 8);
-  DISPATCH_M(M, { int rc2 = set_lds(k_assign<MT>, lds); if (rc2) return rc2;
-                  k_assign<MT><<<few, 256, lds, st>>>(idx->d_sym, codes, n, rot_base, plane, M, coarse, K, assign_out, open); });
   RII_HIP(hipGetLastError());
+  *open_out = open;
   return RII_OK;
 }
 
-// a(n) with pruning (see k_assign_pruned); all pointers device.  visited_total may be NULL.
+// a(n) with pruning (see k_assign_pruned); all pointers device; `open` as in rii_internal_assign.  visited_total may be NULL.
 int rii_internal_assign_pruned(const rii_index* idx, const uint8_t* codes, int64_t n, int64_t rot_base, int64_t plane,
                                const uint8_t* super, int G,
                                const float* radius, const uint8_t* coarse_g, const int32_t* perm_g,
-                               const int32_t* group_off, int32_t* assign_out, unsigned long long* visited_total,
-                               hipStream_t st) {
+                               const int32_t* group_off, int32_t* assign_out, const uint32_t* open,
+                               unsigned long long* visited_total, hipStream_t st) {
   if (n == 0) return RII_OK;
   if (!rot_m(idx->M) && rot_base >= 0) { codes += rot_base * idx->M; rot_base = -1; }
   int rc = rii_internal_sym_table(idx, st);
@@ -1186,7 +1184,7 @@ int rii_internal_assign_pruned(const rii_index* idx, const uint8_t* codes, int64
   DISPATCH_M(M, { int rc2 = set_lds(k_assign_pruned<MT>, lds); if (rc2) return rc2;
                   k_assign_pruned<MT><<<blocks, 256, lds, st>>>(idx->d_sym, codes, n, rot_base, plane, M, super, G, radius,
                                                                coarse_g,
-                                                               perm_g, group_off, assign_out, visited_total); });
+                                                               perm_g, group_off, assign_out, open, visited_total); });
   RII_HIP(hipGetLastError());
   return RII_OK;
 }

@@ -37,4 +37,5 @@ def test_margin_covers_every_rounding(M, Ds, left_out):
     partial = max(np.sin(t) ** 2 + 2 * (1 + 2 * lo) * np.sin(t) * np.cos(t) for t in np.linspace(0, np.pi / 2, 100001))
     score = 2 * share * 0.5 + 3 * Dp * 2 * U * partial + (Dp / 4 + 3) * U
     defined = 2 * (Ds + M + 2) * U
-    assert f(M, Ds) * (1 - 1e-5) >= 2 * (score + defined)
+    moved = 4.01 * U  # both sides' coordinates, rounded once more when the origin is moved: 2 |x - c| u (X + C)
+    assert f(M, Ds) * (1 - 1e-5) >= 2 * (score + defined + moved)

@@ -344,3 +344,43 @@ def test_assignment_between_centres_that_nearly_coincide(M, Ds, N, K, rii, oracl
     index.add(codes)
     index.build_lists(coarse)
     assert np.array_equal(index.get_lists()[3], oracle_lib.assign(oracle_lib.sym_table(cb), codes, coarse))
+
+
+# enough items and centres for the undecided ones to be counted, and centres of which none, some or all occur twice: few
+# items undecided (by the defined sums one by one), many (by the pruned search), most (which takes all items then); the
+# same with too few centres to be counted.  Code books away from the origin.
+@pytest.mark.parametrize("N,K,twice", [(530_000, 2050, 0.0), (1_700_000, 2050, 0.4), (530_000, 2050, 1.0), (530_000, 560, 1.0)])
+def test_assignment_with_many_undecided_items(N, K, twice, rii, oracle_lib):
+    rng = np.random.default_rng(K)
+    M = 16
+    cb = (rng.normal(size=(M, 256, 2)) + 30).astype(np.float32)
+    codes = rng.integers(0, 256, size=(N, M), dtype=np.uint8)
+    coarse = rng.integers(0, 256, size=(K, M), dtype=np.uint8)
+    n2 = int(twice * K) // 2
+    coarse[K - n2:] = coarse[:n2]
+    index = rii.Index(cb)
+    index.add(codes)
+    index.build_lists(coarse)
+    a = index.get_lists()[3]
+    brute = rii.rii_assign(index, torch.from_numpy(codes).cuda(), torch.from_numpy(coarse).cuda())
+    torch.cuda.synchronize()
+    assert np.array_equal(a, t2n(brute))
+    some = rng.integers(0, N, size=500)
+    assert np.array_equal(a[some], oracle_lib.assign(oracle_lib.sym_table(cb), codes[some], coarse))
+
+
+# the pruned search on its own: dimensions past the matrix products', and a few items added to many lists
+@pytest.mark.parametrize("M,Ds,K,few", [(16, 9, 1100, 0), (32, 6, 1500, 3), (12, 12, 1024, 0), (16, 6, 1024, 200), (64, 2, 2000, 255)])
+def test_pruned_assignment(M, Ds, K, few, rii, oracle_lib):
+    rng = np.random.default_rng(K)
+    N = 3000
+    cb = rng.normal(size=(M, 256, Ds)).astype(np.float32)
+    codes = rng.integers(0, 16, size=(N, M), dtype=np.uint8) + np.repeat(rng.integers(0, 15, size=(N // 50, M), dtype=np.uint8) * 16, 50, axis=0)
+    coarse = codes[rng.permutation(N)[:K]].copy()
+    coarse[7] = coarse[3]
+    index = rii.Index(cb)
+    index.add(codes[:N - few])
+    index.build_lists(coarse)
+    if few:
+        index.add(codes[N - few:])
+    assert np.array_equal(index.get_lists()[3], oracle_lib.assign(oracle_lib.sym_table(cb), codes, coarse))
