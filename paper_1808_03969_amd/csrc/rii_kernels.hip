@@ -217,27 +217,51 @@ bool plan_batch(int M, int Q, int64_t rows, int topk, int64_t* nchunks_out, int6
 struct FewShape {
   int threads, split, slot, cap;
 };
-// A block hands over at most `slot` keys.  The blocks of a query together stay within the minima that
-// scan_ws_bytes() counts for it (16 KB, 8 KB from four queries on), so that no call needs more scratch for them.
-FewShape few_shape(int M, int Q, int64_t rows, int k, bool capped, bool uneven = false) {
+// A block hands over at most `slot` keys.  All of them together stay within kFewHandOver bytes; `tight` (scratch of a
+// fixed size that would be exceeded): those of a query within the minima that scan_ws_bytes() counts for it (16 KB,
+// 8 KB from four queries on), whatever the rows are.
+constexpr int64_t kFewHandOver = (int64_t)16 << 20;
+enum class FewRows { linear, targets, lists, capped };
+FewShape few_shape(int M, int Q, int64_t rows, int k, FewRows kind, bool tight) {
   FewShape f;
-  // M <= 16: five blocks of four waves share a CU, above that three (M = 32) or two (M = 64) of eight
-  f.threads = capped ? 1024 : M <= 16 ? 256 : 512;
+  // By registers four blocks of four waves share a CU (M <= 16), two of eight above that; by LDS fewer for many
+  // results (M = 64: one from 500 results on).
+  f.threads = kind == FewRows::capped ? 1024 : M <= 16 ? 256 : 512;
   const int round = f.threads * (M == 8 || M == 16 ? 4 : 2);
   f.cap = round + std::max(512, 2 * k);
   f.slot = (k + std::max(k / 4, 16) + 15) / 16 * 16;
-  const int most = (Q < 4 ? 16384 : 8192) / (f.slot * 8);
+  f.split = 1;
   const int64_t rounds = (rows + round - 1) / round;
+  if (kind == FewRows::capped || rounds < 4) return f;
   // Several blocks a query cost about 10 us (a launch that clears, handing over, merging), a round of a
-  // block that has its CU to itself 2.5 us: below four rounds splitting loses, and once the queries
+  // block that has its CU to itself 2 us: below four rounds splitting loses, and once the queries
   // alone give every other CU a block it has to save four rounds (256 queries, M = 16: 2000 rows 41 us
   // in two blocks, 28 us in one; 32,000 rows 77 and 131 us).  Target sets of very different sizes would
   // leave the largest to run alone when there are few blocks a CU: those of many rounds are cut up
   // all the same (500 sets of up to 25,000: 73 -> 55 us).
-  int64_t want = Q <= kWantBlocks / 2 ? (rounds >= 4 ? 2 * kWantBlocks / Q : 1)
-                                      : std::min<int64_t>(rounds / 4, 4 * kWantBlocks / Q);
-  if (uneven && Q < 4 * kWantBlocks && rounds > 16) want = std::max(want, (rounds + 11) / 12);
-  f.split = capped ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(rounds, most), want));
+  const bool full = Q > kWantBlocks / 2;
+  const int64_t per_cu = std::min<int64_t>(M <= 16 ? 4 : 2, (int64_t)(160 * 1024 / few_lds(M, f.cap, 0, false)));
+  int64_t want = full ? std::min<int64_t>(rounds / 4, per_cu * kWantBlocks / Q) : std::min<int64_t>(2, per_cu) * kWantBlocks / Q;
+  const int64_t least = (Q < 4 ? 16384 : 8192) / (f.slot * 8);  // (few where many results make a block dear)
+  if (kind == FewRows::targets && Q < 4 * kWantBlocks && rounds > 16) want = std::max(want, std::min(least, (rounds + 11) / 12));
+  want = std::min(std::min(want, rounds), tight ? least : kFewHandOver / ((int64_t)Q * f.slot * 8));
+  // A block more takes rounds off the others and gives the last one `slot` keys more to merge, about 1 us a thousand
+  // (one query, M = 16, 65,536 rows, top-1000: 94, 82, 85, 102, 142 us in 4, 8, 16, 32, 64 blocks; 10^6 members,
+  // top-300: 629, 343, 198, 130, 100 us in 4 .. 64); on a full chip the blocks also take turns at selecting
+  // (256 sets of 16,000, M = 8, top-1000: 71 us in one block each, 90 in four; top-300: 61 in two, 80 in four).  The
+  // best of the numbers of blocks whose rounds come out even.
+  const float per_key = full ? 1.2e-2f : 1e-3f;
+  const uint32_t all = (uint32_t)rounds;
+  float best = 2.f * (float)all - 3.f;
+  for (uint32_t n = 2; n <= (uint32_t)std::max<int64_t>(want, 1); ++n) {
+    const uint32_t each = (all + n - 1) / n;
+    if ((all + each - 1) / each != n) continue;  // fewer blocks have as many rounds
+    const float t = 2.f * (float)each + per_key * (float)n * (float)f.slot;
+    if (t < best) {
+      best = t;
+      f.split = (int)n;
+    }
+  }
   return f;
 }
 size_t few_ws_bytes(const FewShape& f, int Q) {
@@ -294,20 +318,24 @@ bool few_subset(int Q, int topk, int64_t rows) {
   return rows <= (many ? 50000 : 24000);
 }
 
+bool few_scan(int mode, int M, int Q, int topk, int64_t rows) {
+  return mode == kLinear ? few_linear(M, Q, topk, rows) : few_subset(Q, topk, rows);
+}
+
 // Scan `nrows_max` rows per query (linear: the whole array) and leave per-block partial keys in
 // the workspace; then select.  Workspace layout: [tau Q u32][partial Q*nchunks*k u64].
 int launch_scan(const rii_index* idx, const uint8_t* codes, int64_t plane, int64_t N, const float* lut, int Q, int mode,
                 const int32_t* target_ids, const int64_t* target_offsets, int64_t max_rows, int topk,
                 int32_t* ids, float* dist, int out_stride, const int* qmode, int want_mode, void* ws_base,
-                hipStream_t st, bool cleared = false) {
+                hipStream_t st, bool cleared = false, bool tight = false) {
   const int M = idx->M;
   if (Q > 65535) return RII_ERR_UNSUPPORTED;
   const bool timed = mode == kLinear && idx->ev_start && idx->ev_stop && codes == idx->d_codes;
-  if (mode == kLinear ? few_linear(M, Q, topk, max_rows) && !idx->bench_half_table : few_subset(Q, topk, max_rows)) {
+  if (few_scan(mode, M, Q, topk, max_rows) && !idx->bench_half_table) {
     FewArgs f{};
     f.codes = codes; f.plane = plane; f.M = M; f.lut = lut; f.N = N; f.target_ids = target_ids; f.target_offsets = target_offsets;
     f.k = topk; f.ids = ids; f.dist = dist; f.out_stride = out_stride; f.qmode = qmode; f.want_mode = want_mode;
-    const FewShape shape = few_shape(M, Q, max_rows, topk, false, mode == kSubset);
+    const FewShape shape = few_shape(M, Q, max_rows, topk, mode == kSubset ? FewRows::targets : FewRows::linear, tight);
     if (mode == kSubset) return launch_few<kFewSubset>(f, shape, Q, ws_base, cleared, st);
     if (timed) RII_HIP(hipEventRecord(static_cast<hipEvent_t>(idx->ev_start), st));
     const int rc = launch_few<kFewLinear>(f, shape, Q, ws_base, cleared, st);
@@ -515,14 +543,16 @@ size_t minima_bytes(int Q) {
   return (size_t)std::min(Q, kSeedMaxQ) * blocks * (kScanThreads / 64) * 4;
 }
 
-// batch: the call may take the batched kernel (launch_scan without per-query modes).
-size_t scan_ws_bytes(int M, int Q, int64_t max_rows, int topk, bool batch = true) {
+// What launch_scan needs.  batch: the call may take the batched kernel (no per-query modes); tight: see few_shape.
+size_t scan_ws_bytes(int mode, int M, int Q, int64_t max_rows, int topk, bool batch = true, bool tight = false) {
   int64_t nchunks, chunk_rows;
   scan_chunks(Q, max_rows, &nchunks, &chunk_rows);
   int64_t bchunks = 1, brows;
   if (batch) plan_batch(M, Q, max_rows, topk, &bchunks, &brows);
   const int64_t cap_chunks = std::max(nchunks, bchunks);
-  return kScanArrays * align_up((size_t)Q * 4, 256) + (size_t)Q * cap_chunks * topk * 8 + minima_bytes(Q) + 256;
+  const size_t few = few_scan(mode, M, Q, topk, max_rows)
+                         ? few_ws_bytes(few_shape(M, Q, max_rows, topk, mode == kSubset ? FewRows::targets : FewRows::linear, tight), Q) : 0;
+  return std::max(few, kScanArrays * align_up((size_t)Q * 4, 256) + (size_t)Q * cap_chunks * topk * 8 + minima_bytes(Q) + 256);
 }
 
 // The same for every batch of at most Q queries, at most max_rows rows and at most topk results:
@@ -531,8 +561,9 @@ size_t scan_ws_bytes(int M, int Q, int64_t max_rows, int topk, bool batch = true
 size_t scan_ws_bound(int M, int Q, int64_t max_rows, int topk) {
   const size_t big_chunks = (size_t)(3 * (max_rows * M / kBatchChunkBytes + 1) + 2);  // chunks of a large batch (see plan_batch)
   return kScanArrays * align_up((size_t)Q * 4, 256) +
-         ((size_t)Q * big_chunks + 4 * kBatchWantBlocks + kWantBlocks + 8) * topk * 8 +
-         std::max(minima_bytes(Q), minima_bytes(std::min(Q, 3))) + 256;
+         std::max(((size_t)Q * big_chunks + 4 * kBatchWantBlocks + kWantBlocks + 8) * topk * 8 +
+                      std::max(minima_bytes(Q), minima_bytes(std::min(Q, 3))),
+                  (size_t)kFewHandOver) + 256;
 }
 
 }  // namespace
@@ -556,7 +587,7 @@ int rii_scan_linear_plan(const rii_index_t* idx, int Q, int topk, int* queries_p
   scan_chunks(Q, idx->N, &nchunks, &chunk_rows);
   if (few_linear(idx->M, Q, topk, idx->N)) {
     *queries_per_block = 1;
-    *row_chunks = few_shape(idx->M, Q, idx->N, topk, false).split;
+    *row_chunks = few_shape(idx->M, Q, idx->N, topk, FewRows::linear, false).split;
   } else if (topk <= kWaveK && plan_batch(idx->M, Q, idx->N, topk, &bchunks, &brows)) {
     *queries_per_block = 4;
     *row_chunks = bchunks;
@@ -633,7 +664,7 @@ int rii_adc_scan_linear(const rii_index_t* idx, const float* lut, int Q, int top
   if (!idx || !lut || !ids || !dist || Q < 1 || topk < 1) return RII_ERR_INVALID_ARG;
   if (topk > RII_MAX_TOPK || !m_supported(idx->M) || Q > 65535) return RII_ERR_UNSUPPORTED;
   if (idx->N < 1) return RII_ERR_INVALID_ARG;
-  int rc = ensure_ws(idx, scan_ws_bytes(idx->M, Q, idx->N, topk));
+  int rc = ensure_ws(idx, scan_ws_bytes(kLinear, idx->M, Q, idx->N, topk));
   if (rc) return rc;
   return launch_scan(idx, idx->d_codes, idx->plane_codes, idx->N, lut, Q, kLinear, nullptr, nullptr, idx->N, topk, ids, dist, topk,
                      nullptr, 0, idx->ws, static_cast<hipStream_t>(stream));
@@ -666,7 +697,7 @@ int rii_adc_scan_subset(const rii_index_t* idx, const float* lut, int Q, const i
   if (topk > RII_MAX_TOPK || !m_supported(idx->M) || Q > 65535) return RII_ERR_UNSUPPORTED;
   if (max_targets > idx->N) max_targets = idx->N;
   int64_t rows = std::max<int64_t>(max_targets, 1);
-  int rc = ensure_ws(idx, scan_ws_bytes(idx->M, Q, rows, topk));
+  int rc = ensure_ws(idx, scan_ws_bytes(kSubset, idx->M, Q, rows, topk));
   if (rc) return rc;
   return launch_scan(idx, idx->d_codes_rows, idx->plane_rows, idx->N, lut, Q, kSubset, target_ids, target_offsets, rows, topk, ids, dist,
                      topk, nullptr, 0, idx->ws, static_cast<hipStream_t>(stream));
@@ -702,19 +733,19 @@ int rii_topk(const float* cand_dist, const int32_t* cand_ids, const int64_t* can
 static bool coarse_in_lds(int K, int nprobe) { return nprobe <= RII_MAX_TOPK && K <= kRankMaxRows; }
 static bool coarse_split(int Q, int K) { return Q <= kCoarseSplitQ && K >= kCoarseSplitK; }
 
-static size_t coarse_ws_bytes(const rii_index* idx, int Q, int nprobe) {
+static size_t coarse_ws_bytes(const rii_index* idx, int Q, int nprobe, bool tight = false) {
   if (coarse_in_lds(idx->K, nprobe)) return coarse_split(Q, idx->K) ? align_up((size_t)Q * idx->K * 4, 256) : 256;
-  if (nprobe <= RII_MAX_TOPK) return scan_ws_bytes(idx->M, Q, idx->K, nprobe);
+  if (nprobe <= RII_MAX_TOPK) return scan_ws_bytes(kLinear, idx->M, Q, idx->K, nprobe, true, tight);
   return align_up((size_t)Q * idx->K * 4, 256) + align_up((size_t)(Q + 1) * 8, 256);
 }
 
 static int coarse_rank(const rii_index* idx, const float* lut, int Q, int nprobe, int32_t* list_ids, float* list_d0,
-                       int out_stride, const int* qmode, int want_mode, void* ws, hipStream_t st) {
+                       int out_stride, const int* qmode, int want_mode, void* ws, hipStream_t st, bool tight = false) {
   const int M = idx->M, K = idx->K;
   const bool in_lds = coarse_in_lds(K, nprobe);
   if (nprobe <= RII_MAX_TOPK && !in_lds) {
     return launch_scan(idx, idx->d_coarse_st, idx->plane_coarse, K, lut, Q, kLinear, nullptr, nullptr, K, nprobe, list_ids, list_d0,
-                       out_stride, qmode, want_mode, ws, st);
+                       out_stride, qmode, want_mode, ws, st, false, tight);
   }
   float* d0 = static_cast<float*>(ws);
   const bool split = !in_lds || coarse_split(Q, K);
@@ -779,8 +810,8 @@ static int ivf_split(int Q, int nprobe) {
   return split < 1 ? 1 : split;
 }
 
-static size_t ivf_ws_bytes(const rii_index* idx, int Q, int nprobe, int64_t L, int topk, bool targets) {
-  const FewShape f = few_shape(idx->M, Q, list_rows(idx, nprobe, L), topk, targets && L > 0);
+static size_t ivf_ws_bytes(const rii_index* idx, int Q, int nprobe, int64_t L, int topk, bool targets, bool tight = false) {
+  const FewShape f = few_shape(idx->M, Q, list_rows(idx, nprobe, L), topk, targets && L > 0 ? FewRows::capped : FewRows::lists, tight);
   const size_t few = few_ws_bytes(f, Q);
   if (topk > kWaveK) return few;
   return std::max(few, kScanArrays * align_up((size_t)Q * 4, 256) + (size_t)Q * ivf_split(Q, nprobe) * topk * 8 + 256);
@@ -789,7 +820,7 @@ static size_t ivf_ws_bytes(const rii_index* idx, int Q, int nprobe, int64_t L, i
 static int launch_ivf(const rii_index* idx, const float* lut, int Q, const int32_t* probe, int probe_stride,
                       int nprobe, const int* nprobe_q, const int32_t* target_ids, const int64_t* target_offsets,
                       int64_t L, int topk, int32_t* ids, float* dist, const int* qmode, int want_mode, void* ws,
-                      hipStream_t st, bool cleared = false) {
+                      hipStream_t st, bool cleared = false, bool tight = false) {
   const int M = idx->M;
   const bool capped = L > 0 && target_ids;
   const int64_t rows = list_rows(idx, nprobe, capped ? 0 : L);
@@ -799,7 +830,7 @@ static int launch_ivf(const rii_index* idx, const float* lut, int Q, const int32
     f.target_ids = target_ids; f.target_offsets = target_offsets; f.list_ids = idx->d_list_ids; f.list_off = idx->d_list_off;
     f.probe = probe; f.probe_stride = probe_stride; f.nprobe = nprobe; f.nprobe_q = nprobe_q; f.Lcap = L;
     f.k = topk; f.ids = ids; f.dist = dist; f.out_stride = topk; f.qmode = qmode; f.want_mode = want_mode;
-    const FewShape shape = few_shape(M, Q, rows, topk, capped);
+    const FewShape shape = few_shape(M, Q, rows, topk, capped ? FewRows::capped : FewRows::lists, tight);
     return capped ? launch_few<kFewCapped>(f, shape, Q, ws, cleared, st) : launch_few<kFewLists>(f, shape, Q, ws, cleared, st);
   }
   IvfArgs a{};
@@ -851,13 +882,14 @@ int rii_adc_scan_ivf(const rii_index_t* idx, const float* lut, int Q, const int3
 struct QueryPlan {
   int pmax = 1;          // most lists any inverted-index query of the batch can ask for
   int64_t lin_rows = 1;  // most rows any linear-scan query of the batch can have
-  size_t lut_b = 0, plan_b = 0, probe_b = 0, ivf_b = 0, total = 0;
+  size_t lut_b = 0, plan_b = 0, probe_b = 0, total = 0;
   // Without target sets every query has the same |S| = N: the host takes Alg. 3's decision and k_plan and
   // the per-query modes fall away, which also lets a batch into the batched scan.
   bool uniform = false;
+  bool tight = false;  // small scans get the least scratch (see few_shape)
 };
 
-// `limit` > 0: a plan beyond that many bytes gives up the batched scan where that is what needs them.
+// `limit` > 0: a plan beyond that many bytes gives up the small scans' room, then the batched scan.
 static int plan_query(const rii_index* idx, int Q, int topk, bool targets, int64_t max_targets, int64_t L,
                       QueryPlan* p, size_t limit = 0) {
   const int M = idx->M, K = idx->K;
@@ -880,17 +912,18 @@ static int plan_query(const rii_index* idx, int Q, int topk, bool targets, int64
   p->lut_b = align_up((size_t)Q * M * 256 * 4, 256);
   p->plan_b = align_up((size_t)Q * 4, 256);
   p->probe_b = align_up((size_t)Q * p->pmax * 4, 256);
-  p->uniform = !targets;
-  size_t scan_b = align_up(scan_ws_bytes(M, Q, p->lin_rows, topk, p->uniform), 256);
-  const size_t coarse_b = has_lists ? align_up(coarse_ws_bytes(idx, Q, p->pmax), 256) : 0;
-  p->ivf_b = has_lists ? align_up(ivf_ws_bytes(idx, Q, p->pmax, L, topk, targets), 256) : 0;
-  const size_t fixed = p->lut_b + 2 * p->plan_b + p->probe_b, other = std::max(coarse_b, p->ivf_b);
-  p->total = fixed + std::max(scan_b, other);
-  if (limit && p->total > limit && p->uniform) {
-    p->uniform = false;
-    scan_b = align_up(scan_ws_bytes(M, Q, p->lin_rows, topk, false), 256);
-    p->total = fixed + std::max(scan_b, other);
-  }
+  const int scan_mode = targets ? kSubset : kLinear;
+  auto size = [&](bool uniform, bool tight) {
+    p->uniform = uniform;
+    p->tight = tight;
+    const size_t scan_b = align_up(scan_ws_bytes(scan_mode, M, Q, p->lin_rows, topk, uniform, tight), 256);
+    const size_t coarse_b = has_lists ? align_up(coarse_ws_bytes(idx, Q, p->pmax, tight), 256) : 0;
+    const size_t ivf_b = has_lists ? align_up(ivf_ws_bytes(idx, Q, p->pmax, L, topk, targets, tight), 256) : 0;
+    p->total = p->lut_b + 2 * p->plan_b + p->probe_b + std::max(scan_b, std::max(coarse_b, ivf_b));
+  };
+  size(!targets, false);
+  if (limit && p->total > limit) size(!targets, true);
+  if (limit && p->total > limit) size(false, true);
   return RII_OK;
 }
 
@@ -925,19 +958,19 @@ static int run_query(const rii_index* idx, const QueryPlan& p, const float* q, i
   const bool all_linear = !target_ids && (!has_lists || idx->N < idx->theta);
   if (target_ids) {
     rc = launch_scan(idx, idx->d_codes_rows, idx->plane_rows, idx->N, lut, Q, kSubset, target_ids, target_offsets, p.lin_rows, topk,
-                     ids, dist, topk, qmode, 0, stage_ws, st);
+                     ids, dist, topk, qmode, 0, stage_ws, st, false, p.tight);
   } else if (all_linear) {
     rc = launch_scan(idx, idx->d_codes, idx->plane_codes, idx->N, lut, Q, kLinear, nullptr, nullptr, idx->N, topk, ids, dist, topk,
-                     qmode, 0, stage_ws, st, p.uniform);
+                     qmode, 0, stage_ws, st, p.uniform, p.tight);
   }
   if (rc) return rc;
   // inverted-index branch (mode 1); the scratch of the scan stage is reused in stream order
   if (has_lists && !all_linear) {
-    rc = coarse_rank(idx, lut, Q, p.pmax, probe, nullptr, p.pmax, qmode, 1, stage_ws, st);
+    rc = coarse_rank(idx, lut, Q, p.pmax, probe, nullptr, p.pmax, qmode, 1, stage_ws, st, p.tight);
     if (rc) return rc;
     const bool untouched = coarse_in_lds(K, p.pmax) && !coarse_split(Q, K);  // the ranking leaves the stage scratch alone
     rc = launch_ivf(idx, lut, Q, probe, p.pmax, p.pmax, nprobe_q, target_ids, target_offsets, L, topk, ids, dist, qmode,
-                    1, stage_ws, st, p.uniform && untouched);
+                    1, stage_ws, st, p.uniform && untouched, p.tight);
     if (rc) return rc;
   }
   RII_HIP(hipGetLastError());

@@ -384,3 +384,49 @@ def test_pruned_assignment(M, Ds, K, few, rii, oracle_lib):
     if few:
         index.add(codes[N - few:])
     assert np.array_equal(index.get_lists()[3], oracle_lib.assign(oracle_lib.sym_table(cb), codes, coarse))
+
+
+# many results from few rows: the blocks of a query hand over as many keys as the batch's scratch has room for, also
+# where the scratch has a fixed size; one query in many blocks, many queries in few, every way to the rows
+@pytest.mark.parametrize("M,N,Q,topk", [(16, 60000, 1, 1000), (64, 60000, 3, 700), (12, 65536, 70, 300), (32, 50001, 16, 1024), (8, 65000, 200, 500)])
+def test_small_scans_with_many_results(M, N, Q, topk, rii, oracle_lib):
+    from paper_1808_03969_amd import binding
+    rng = np.random.default_rng(N + M)
+    d = plain_index(rii, oracle_lib, rng, N, M, 4)
+    index = d["index"]
+    assert Q > 64 or binding.rii_scan_linear_plan(index, Q, topk)[1] >= 4  # (one block a query leaves the chip idle)
+    q = rng.normal(size=(Q, 2 * M)).astype(np.float32)
+    qd = torch.from_numpy(q).cuda()
+    lut = rii.rii_build_lut(index, qd)
+    sets = [np.sort(rng.permutation(N)[:N - 7 * i]).astype(np.int32) for i in range(Q)]
+    tids = torch.from_numpy(np.concatenate(sets)).cuda()
+    toff = torch.from_numpy(np.concatenate([[0], np.cumsum([len(s) for s in sets])])).cuda()
+    probe, _ = rii.rii_coarse_assign(index, lut, 4)
+    index.reserve_workspace(Q, topk, N, 4)
+    held = index.info()["device_bytes"]
+    got = dict(linear=rii.rii_adc_scan_linear(index, lut, topk), subset=rii.rii_adc_scan_subset(index, lut, tids, toff, N, topk),
+               lists=rii.rii_adc_scan_ivf(index, lut, probe, topk), query=rii.rii_query(index, qd, topk, L=N),
+               fixed=rii.rii_query_noalloc(index, qd, topk, L=N))
+    torch.cuda.synchronize()
+    assert index.info()["device_bytes"] == held
+    A = oracle_lib.lut(d["cb"], q)
+    for i in sorted({0, Q // 2, Q - 1}):
+        whole = oracle_lib.linear_scan(A[i], d["codes"], topk)
+        for name, (ids, dist) in got.items():
+            ref = oracle_lib.linear_scan(A[i], d["codes"], topk, S=sets[i]) if name == "subset" else whole
+            assert np.array_equal(t2n(ids)[i], ref[0]) and np.array_equal(t2n(dist)[i], ref[1]), (name, i)
+
+
+# a batch whose small scans' room would exceed the scratch of a fixed size: they get less of it
+def test_small_scans_in_a_scratch_of_a_fixed_size(rii, oracle_lib):
+    rng = np.random.default_rng(77)
+    M, N, Q, topk = 64, 30000, 760, 100  # 50 MB of tables, 62 MB with the hand-over area of its size
+    d = plain_index(rii, oracle_lib, rng, N, M, 3)
+    index = rii.Index(d["cb"])
+    index.add(d["codes"])
+    q = rng.normal(size=(Q, 2 * M)).astype(np.float32)
+    ids, dist = rii.rii_query_noalloc(index, torch.from_numpy(q).cuda(), topk)
+    torch.cuda.synchronize()
+    for i in (0, 400, Q - 1):
+        ref = oracle_lib.linear_scan(oracle_lib.lut(d["cb"], q[i:i + 1])[0], d["codes"], topk)
+        assert np.array_equal(t2n(ids)[i], ref[0]) and np.array_equal(t2n(dist)[i], ref[1]), i
