@@ -80,6 +80,7 @@ void drop_lists(rii_index* idx) {
   idx->h_list_off.clear();
   idx->K = 0;
   idx->max_list_len = 0;
+  idx->member_list_len = 0;
 }
 
 // Install posting lists (device arrays [K+1] and [N], already validated, taken over) under the host centres `coarse`.
@@ -109,7 +110,13 @@ int install_lists(rii_index* idx, const uint8_t* coarse, int K, DevBuf& off, Dev
   idx->h_list_off = std::move(h_off);
   idx->K = K;
   idx->max_list_len = 0;
-  for (int k = 0; k < K; ++k) idx->max_list_len = std::max(idx->max_list_len, idx->h_list_off[k + 1] - idx->h_list_off[k]);
+  double squares = 0.0;
+  for (int k = 0; k < K; ++k) {
+    const int64_t len = idx->h_list_off[k + 1] - idx->h_list_off[k];
+    idx->max_list_len = std::max(idx->max_list_len, len);
+    squares += (double)len * (double)len;
+  }
+  idx->member_list_len = N > 0 ? (int64_t)(squares / (double)N) : 0;
   return RII_OK;
 }
 

@@ -40,6 +40,7 @@ struct rii_index {
   std::vector<uint8_t> h_coarse;    // host mirror of the coarse centres
   std::vector<int64_t> h_list_off;  // host mirror of the list offsets
   int64_t max_list_len = 0;
+  int64_t member_list_len = 0;      // length of the list a member is in, averaged over the members
 
   // scratch reused by the online calls (grown on demand)
   mutable void* ws = nullptr;

@@ -289,14 +289,19 @@ int launch_few(FewArgs a, const FewShape& f, int Q, void* ws, bool cleared, hipS
   return RII_OK;
 }
 
-// Rows per query up to which a scan goes to k_few.  Measured against the streaming kernels (which it
-// would otherwise go to) for batches of 1 .. 4000 queries, M = 16 and 32, top-1, 10 and 100; microseconds
-// there / here.  The streaming kernels lose to their fixed cost and, for many results, to their selection;
-// with few results, many queries or M = 32 (rows abandoned half-way) they catch up early:
-//   whole array  M = 16:  1 query, top-100 64,000 rows 56 / 33;  600 queries, top-100 32,000 158 / 108, 64,000
-//     186 / 188, top-10 16,000 82 / 62, 32,000 92 / 102;  M = 32:  600 queries, top-100 16,000 151 / 108, 32,000 217 / 196
-//   lists        M = 16:  4000 queries, top-100 64,000 members 1431 / 912, top-10 32,000 616 / 514;  64 queries,
-//     top-10 16,000 35 / 38;  M = 32:  4000 queries, top-100 32,000 1346 / 1053, top-10 4,000 406 / 278, 16,000 643 / 676
+// Rows per query up to which a scan goes to k_few (of lists: what list_rows() says, which for clustered data is about
+// twice the mean).  Measured against the streaming kernels (which it would otherwise go to) for batches of 1 .. 4000
+// queries, every M, top-1 to top-1000; microseconds there / here.  The streaming kernels lose to their fixed cost and,
+// for many results, to their selection; with few results, many queries or M = 32 (rows abandoned half-way) they catch
+// up early:
+//   whole array  M = 16:  1 query, top-100 64,000 rows 56 / 33, top-1000 200 / 82;  600 queries, top-100 32,000 158 /
+//     108, 64,000 186 / 188, top-10 16,000 82 / 62, 32,000 92 / 102;  M = 32:  600 queries, top-100 16,000 151 / 108,
+//     32,000 217 / 196
+//   lists (mean lengths)  M = 16:  4000 queries, top-100 64,000 members 1431 / 912, top-10 32,000 616 / 514;  1 query,
+//     top-300 10^6 1683 / 100;  M = 32:  4000 queries, top-100 32,000 1346 / 1053, top-10 4,000 406 / 278, 16,000
+//     643 / 676.  Where the queries make whole rounds of the chip in the streaming kernel it is ahead before the
+//     line: M = 16, top-10, 16,000 members, 64 queries 33 / 34, 256 queries 43 / 48 (but 130 queries 59 / 43).
+//     Zipf-like lengths, M = 16, 256 queries, two lists, top-1 283 / 969: beyond the line by list_rows()
 //   target sets  M = 16:  64 queries, top-100 64,000 ids 126 / 63;  200 queries, top-100 16,000 72 / 57, 32,000
 //     95 / 105;  4000 queries, top-100 64,000 2396 / 2424, top-10 16,000 787 / 555, 32,000 1289 / 1230
 constexpr int kFewManyResults = 64;
@@ -308,8 +313,8 @@ bool few_linear(int M, int Q, int topk, int64_t rows) {
   return rows <= (many ? (M == 32 ? 24000 : 40000) : M == 32 ? 10000 : 16000);
 }
 bool few_lists(int M, int Q, int topk, int64_t rows) {
-  if (topk >= kFewManyResults) return rows <= (M == 32 || M == 64 ? 32000 : 65536);
-  return rows <= (Q <= 4 ? 65536 : M == 32 ? 8000 : 16000);
+  if (topk >= kFewManyResults) return rows <= (M == 32 || M == 64 ? 58000 : 110000);
+  return rows <= (Q <= 4 ? 120000 : M == 32 ? 20000 : 40000);
 }
 bool few_subset(int Q, int topk, int64_t rows) {
   const bool many = topk >= kFewManyResults;
@@ -797,9 +802,14 @@ int rii_coarse_assign(const rii_index_t* idx, const float* lut, int Q, int nprob
                      static_cast<hipStream_t>(stream));
 }
 
-// About how many members the `nprobe` lists of a query have, the candidate cap taken into account.
+// How many members the `nprobe` lists of a query may well have, the candidate cap taken into account.  Queries come
+// from where the data are, so a list is probed about in proportion to its length, and the lists count with the
+// length that a member's list has; one of them may be the longest, and a batch waits for its longest query.  (Lists
+// by Zipf's law, M = 16, 256 queries, two lists of 2 x 10^6 members in 1000, top-1: 283 us in the streaming kernel, 969
+// in k_few, where the mean length alone sent them.)
 static int64_t list_rows(const rii_index* idx, int nprobe, int64_t L) {
-  const int64_t rows = idx->N / idx->K * nprobe + (idx->N % idx->K) * nprobe / idx->K;
+  const int64_t mean = idx->N / idx->K * nprobe + (idx->N % idx->K) * nprobe / idx->K;
+  const int64_t rows = std::min(idx->N, std::max(mean, idx->member_list_len * nprobe) + idx->max_list_len);
   return L > 0 && L < rows ? L : rows;
 }
 

@@ -430,3 +430,30 @@ def test_small_scans_in_a_scratch_of_a_fixed_size(rii, oracle_lib):
     for i in (0, 400, Q - 1):
         ref = oracle_lib.linear_scan(oracle_lib.lut(d["cb"], q[i:i + 1])[0], d["codes"], topk)
         assert np.array_equal(t2n(ids)[i], ref[0]) and np.array_equal(t2n(dist)[i], ref[1]), i
+
+
+# lists of very different lengths: half of all members in one, a quarter in another, the rest short or empty; queries
+# that probe none, one or both of the long ones, in one block a query and in several, on both sides of the lines
+@pytest.mark.parametrize("M,N,Q,topk", [(16, 60000, 200, 10), (16, 200000, 300, 100), (64, 30000, 5, 1), (32, 30000, 260, 10), (12, 50000, 3, 300)])
+def test_scans_of_uneven_lists(M, N, Q, topk, rii, oracle_lib):
+    rng = np.random.default_rng(N)
+    K = 60
+    cb = rng.normal(size=(M, 256, 2)).astype(np.float32)
+    codes = rng.integers(0, 256, size=(N, M), dtype=np.uint8)
+    coarse = rng.integers(0, 256, size=(K, M), dtype=np.uint8)
+    u = rng.random(N)
+    off, lids = oracle_lib.build_lists(np.where(u < .5, 7, np.where(u < .75, 31, rng.integers(10, K, size=N))).astype(np.int32), K)
+    index = rii.Index(cb)
+    index.add(codes)
+    index.set_lists(coarse, off, lids)
+    q = rng.normal(size=(Q, 2 * M)).astype(np.float32)
+    q[::3] = np.concatenate([cb[m][coarse[7, m]] for m in range(M)]) + 0.1 * q[::3]  # the longest list is the nearest
+    lut = rii.rii_build_lut(index, torch.from_numpy(q).cuda())
+    A = oracle_lib.lut(cb, q)
+    for P in (1, 2, 20):
+        probe, _ = rii.rii_coarse_assign(index, lut, P)
+        ids, dist = rii.rii_adc_scan_ivf(index, lut, probe, topk)
+        torch.cuda.synchronize()
+        for i in range(0, Q, max(1, Q // 7)):
+            ref = oracle_lib.inverted_index(A[i], codes, coarse, off, lids, topk, P)[:2]
+            assert np.array_equal(t2n(ids)[i], ref[0]) and np.array_equal(t2n(dist)[i], ref[1]), (P, i)
