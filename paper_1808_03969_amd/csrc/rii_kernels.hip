@@ -562,13 +562,14 @@ size_t scan_ws_bytes(int mode, int M, int Q, int64_t max_rows, int topk, bool ba
 
 // The same for every batch of at most Q queries, at most max_rows rows and at most topk results:
 // a bound that grows with each argument (a batch's blocks per query times its queries stay
-// below Q + 4 kBatchWantBlocks + kWantBlocks whatever the launch shape is).
+// below Q + 4 kBatchWantBlocks + kWantBlocks whatever the launch shape is, but for the chunks of a large batch over a
+// large array, which only the kernel for up to kWaveK4 results makes).
 size_t scan_ws_bound(int M, int Q, int64_t max_rows, int topk) {
-  const size_t big_chunks = (size_t)(3 * (max_rows * M / kBatchChunkBytes + 1) + 2);  // chunks of a large batch (see plan_batch)
+  const size_t big_chunks = (size_t)(3 * (max_rows * M / kBatchChunkBytes + 1) + 2);  // (see plan_batch)
+  const size_t keys = std::max((size_t)Q * big_chunks * std::min(topk, kWaveK4), (size_t)Q * topk) +
+                      (size_t)(4 * kBatchWantBlocks + kWantBlocks + 8) * topk;
   return kScanArrays * align_up((size_t)Q * 4, 256) +
-         std::max(((size_t)Q * big_chunks + 4 * kBatchWantBlocks + kWantBlocks + 8) * topk * 8 +
-                      std::max(minima_bytes(Q), minima_bytes(std::min(Q, 3))),
-                  (size_t)kFewHandOver) + 256;
+         std::max(keys * 8 + std::max(minima_bytes(Q), minima_bytes(std::min(Q, 3))), (size_t)kFewHandOver) + 256;
 }
 
 }  // namespace

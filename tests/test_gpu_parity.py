@@ -328,6 +328,32 @@ def test_reserve_workspace_then_no_growth(rii, oracle_lib, idx16):
         check_topk(t2n(ids)[i], t2n(dist)[i], ref[0], ref[1])
 
 
+def test_reserved_scratch_of_many_results_over_a_large_array(rii, oracle_lib):
+    """Row chunks of a large batch are made for up to 100 results only: reserving for 1024 results holds room for
+    their candidates once, not once a chunk; no call within the reservation grows it."""
+    N, M, Q = 52_000_000, 8, 8000  # two chunks' worth of rows
+    rng = np.random.default_rng(3)
+    cb = rng.normal(size=(M, 256, 1)).astype(np.float32)
+    index = rii.Index(cb)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    codes = torch.randint(0, 256, (N, M), generator=g, device="cuda", dtype=torch.uint8)
+    index.add(codes)
+    before = index.info()["device_bytes"]
+    index.reserve_workspace(Q, 1024)
+    held = index.info()["device_bytes"]
+    # tables, candidates once, the bound-seeding pass' minima, room for the blocks of smaller batches; a quarter to spare
+    assert held - before <= 1.25 * (Q * M * 1024 + Q * 1024 * 8 + 2048 * 8192 + 4400 * 1024 * 8) + (1 << 20)
+    q = torch.randn((2100, M), generator=g, device="cuda")
+    lut = rii.rii_build_lut(index, q)
+    ids, dist = rii.rii_adc_scan_linear(index, lut, 100)
+    torch.cuda.synchronize()
+    assert index.info()["device_bytes"] == held
+    A = oracle_lib.lut(cb, t2n(q[:1]))
+    ref = oracle_lib.linear_scan(A[0], t2n(codes), 100)
+    assert np.array_equal(t2n(ids)[0], ref[0]) and np.array_equal(t2n(dist)[0], ref[1])
+
+
 @pytest.mark.parametrize("M", [16, 32])
 def test_linear_scan_large_topk_block_buffer(M, rii, oracle_lib):
     """topk above the per-wave buffers' reach: the waves of a block share one candidate buffer and
