@@ -94,6 +94,9 @@ int rii_index_create(const float* codebooks, int D, int M, int Ks, rii_index_t**
  * Device memory held per code: M bytes, 2 M for M = 32 (which keeps the codes in two layouts, one
  * for sequential and one for gathered scans, unless RII_OPT_GATHER_COPY is 0), plus M + 4 once
  * posting lists are installed (list-ordered copy, identifier); rii_index_info reports the total.
+ * While lists are rebuilt the device also holds a(n) (4 bytes a code) and, where there is room, up to
+ * 256 MB of counts and some 50 MB of other scratch; the old lists make way for the new ones (here) or stay
+ * until those are complete (rii_index_build_lists, rii_index_reconfigure: 4 bytes a code more).
  * Synchronous.  If the codes were stored but re-listing them failed (RII_ERR_OOM, RII_ERR_DEVICE), the
  * index keeps the codes and is left without posting lists. */
 int rii_index_add(rii_index_t* index, const uint8_t* codes, int64_t n, int mem);

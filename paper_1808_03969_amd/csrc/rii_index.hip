@@ -126,10 +126,9 @@ int lists_of(const int32_t* d_assign, int64_t n, int K, DevBuf& off, DevBuf& ids
   if (!rc) rc = ids.alloc((size_t)n * 4);
   if (rc) return rc;
   const size_t scratch = rii_internal_lists_bytes(n, K);
-  if (scratch) {
-    DevBuf d_scratch;
-    rc = d_scratch.alloc(scratch);
-    if (!rc) rc = rii_internal_build_lists(d_assign, n, K, off.as<int64_t>(), ids.as<int32_t>(), d_scratch.p, nullptr);
+  DevBuf d_scratch;
+  if (scratch && d_scratch.alloc(scratch) == RII_OK) {  // (no room for the counts: on the host)
+    rc = rii_internal_build_lists(d_assign, n, K, off.as<int64_t>(), ids.as<int32_t>(), d_scratch.p, nullptr);
     if (!rc && hipDeviceSynchronize() != hipSuccess) rc = RII_ERR_DEVICE;
     return rc;
   }
@@ -255,7 +254,9 @@ int assign_rows_dev(rii_index* idx, const uint8_t* rows, int64_t n, int64_t rot_
   int rc = RII_OK;
   CentreGroups g;
   const int64_t part = std::min<int64_t>(n, (int64_t)1 << 23);  // items per launch: bounds the list of undecided ones
-  const size_t scratch = n >= kMatrixMinItems ? rii_internal_assign_matrix_bytes(idx, part, K) : 0;
+  size_t scratch = n >= kMatrixMinItems ? rii_internal_assign_matrix_bytes(idx, part, K) : 0;
+  DevBuf d_scratch;
+  if (scratch && d_scratch.alloc(scratch)) scratch = 0;  // (no room for them: without the products)
   // the defined sums, for the cnt items from `first` on or those of them that are listed (`items` of them)
   auto decide = [&](int64_t first, int64_t cnt, const uint32_t* open, int64_t items) -> int {
     const uint8_t* r = rot_base >= 0 ? rows : rows + first * idx->M;
@@ -271,8 +272,6 @@ int assign_rows_dev(rii_index* idx, const uint8_t* rows, int64_t n, int64_t rot_
     return rii_internal_assign_pruned(idx, r, cnt, rot, plane, g.d_super, g.G, g.d_radius, g.d_coarse_g, g.d_perm_g,
                                       g.d_group_off, d_out + first, open, nullptr, nullptr);
   };
-  DevBuf d_scratch;
-  if (scratch) rc = d_scratch.alloc(scratch);
   bool counted = K >= kTrialMinK && n >= std::max(kPruneMinItems, kTrialWork / K);
   int64_t done = 0;
   while (scratch && done < n && !rc) {
@@ -575,6 +574,10 @@ int rii_index_add(rii_index_t* idx, const uint8_t* codes, int64_t n, int mem) {
       idx->N = oldN;
       rc = rii_internal_assign_from_lists(idx, d_assign.as<int32_t>(), nullptr);
       idx->N = oldN + n;
+    }
+    if (!rc) {  // the old lists are not needed any more: their room is (waits for the read-back)
+      free_dev(idx->d_codes_list);
+      free_dev(idx->d_list_ids);
     }
     if (!rc) rc = assign_stored(idx, oldN, n, coarse.data(), K, d_assign.as<int32_t>() + oldN);
     if (!rc) rc = lists_of(d_assign.as<int32_t>(), idx->N, K, off, ids);
