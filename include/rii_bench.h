@@ -20,7 +20,8 @@ extern "C" {
 int rii_index_set_scan_events(rii_index_t* index, void* start_event, void* stop_event);
 
 #define RII_SCAN_COUNTERS 8
-/* While the scan events are set, the kernels of Alg. 1 over the whole database keep tallies.
+/* While the scan events are set, the streaming kernels of Alg. 1 over the whole database keep tallies (the
+ * kernel that scans arrays of up to some ten thousand codes fetches every row whole and keeps none).
  * This call returns them (counters_out[RII_SCAN_COUNTERS], host) as accumulated since the last
  * call and resets them.  Synchronous (waits for the device).
  *   [0] batched scan: slices (64 rows x one group of four queries, i.e. 64 x M table look-ups) scored
@@ -57,8 +58,8 @@ int rii_bench_lds_lookups(int width, int blocks, int threads, int iters, int lds
  * precision of the distance table open; the library's batched kernel filters with a 15-bit integer
  * table, this variant with fp16 entries and packed fp16 sums; both re-score the rows that pass in
  * fp32, so the results are the same -- what differs is the time).  Same arguments as
- * rii_adc_scan_linear; RII_ERR_UNSUPPORTED when the batch would not take the four-queries-per-block
- * kernel (see rii_scan_linear_plan). */
+ * rii_adc_scan_linear; RII_ERR_UNSUPPORTED when the four-queries-per-block kernel cannot take the batch (at
+ * least four queries, enough of them or of rows to fill a quarter of the chip, at most 100 results). */
 int rii_bench_scan_linear_half(rii_index_t* index, const float* lut, int Q, int topk, int32_t* ids, float* dist,
                                void* stream);
 

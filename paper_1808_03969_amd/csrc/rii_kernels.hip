@@ -268,6 +268,12 @@ size_t few_ws_bytes(const FewShape& f, int Q) {
   return kScanArrays * align_up((size_t)Q * 4, 256) + (f.split > 1 ? (size_t)Q * f.split * f.slot * 8 : 0) + 256;
 }
 
+// The bounds and counters of a scan in several blocks a query, at the start of its scratch.
+void clear_few(const FewShape& f, int Q, void* ws, hipStream_t st) {
+  const size_t cstride = align_up((size_t)Q * 4, 256) / 4;
+  if (f.split > 1) k_init_scan<<<(Q + 255) / 256, 256, 0, st>>>(static_cast<uint32_t*>(ws), Q, (int)cstride, nullptr, 0);
+}
+
 // `ws` holds few_ws_bytes (looked at only when a query has several blocks); cleared: its bounds and counters
 // are initialised already.
 template <int SRC>
@@ -279,7 +285,7 @@ int launch_few(FewArgs a, const FewShape& f, int Q, void* ws, bool cleared, hipS
     uint32_t* tau = static_cast<uint32_t*>(ws);
     a.tau_g = tau; a.done_cnt = tau + 3 * cstride;
     a.cand = reinterpret_cast<uint64_t*>(static_cast<uint8_t*>(ws) + kScanArrays * cstride * 4);
-    if (!cleared) k_init_scan<<<(Q + 255) / 256, 256, 0, st>>>(tau, Q, (int)cstride, nullptr, 0);
+    if (!cleared) clear_few(f, Q, ws, st);
   }
   const size_t lds = few_lds(a.M, a.cap, a.nprobe, SRC == kFewCapped);
   const dim3 grid((unsigned)f.split, (unsigned)Q);
@@ -342,8 +348,9 @@ int launch_scan(const rii_index* idx, const uint8_t* codes, int64_t plane, int64
     f.k = topk; f.ids = ids; f.dist = dist; f.out_stride = out_stride; f.qmode = qmode; f.want_mode = want_mode;
     const FewShape shape = few_shape(M, Q, max_rows, topk, mode == kSubset ? FewRows::targets : FewRows::linear, tight);
     if (mode == kSubset) return launch_few<kFewSubset>(f, shape, Q, ws_base, cleared, st);
+    if (!cleared) clear_few(shape, Q, ws_base, st);
     if (timed) RII_HIP(hipEventRecord(static_cast<hipEvent_t>(idx->ev_start), st));
-    const int rc = launch_few<kFewLinear>(f, shape, Q, ws_base, cleared, st);
+    const int rc = launch_few<kFewLinear>(f, shape, Q, ws_base, true, st);
     if (timed && !rc) RII_HIP(hipEventRecord(static_cast<hipEvent_t>(idx->ev_stop), st));
     return rc;
   }

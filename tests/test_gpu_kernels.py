@@ -457,3 +457,24 @@ def test_scans_of_uneven_lists(M, N, Q, topk, rii, oracle_lib):
         for i in range(0, Q, max(1, Q // 7)):
             ref = oracle_lib.inverted_index(A[i], codes, coarse, off, lids, topk, P)[:2]
             assert np.array_equal(t2n(ids)[i], ref[0]) and np.array_equal(t2n(dist)[i], ref[1]), (P, i)
+
+
+# a small scan in several blocks with the scan events set: they are recorded around its kernel, which keeps no tallies,
+# and the results are the usual ones
+def test_scan_events_of_a_small_scan(rii, oracle_lib):
+    from paper_1808_03969_amd import binding
+    rng = np.random.default_rng(2)
+    d = plain_index(rii, oracle_lib, rng, 60000, 16, 4)
+    q = rng.normal(size=(1, 32)).astype(np.float32)
+    lut = rii.rii_build_lut(d["index"], torch.from_numpy(q).cuda())
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    for e in ev:
+        e.record()  # (makes the handles)
+    binding.rii_index_set_scan_events(d["index"], ev[0].cuda_event, ev[1].cuda_event)
+    ids, dist = rii.rii_adc_scan_linear(d["index"], lut, 10)
+    torch.cuda.synchronize()
+    binding.rii_index_set_scan_events(d["index"], None, None)
+    assert 0 < ev[0].elapsed_time(ev[1]) < 5
+    assert binding.rii_index_read_scan_counters(d["index"]) == [0] * 8
+    ref = oracle_lib.linear_scan(oracle_lib.lut(d["cb"], q)[0], d["codes"], 10)
+    assert np.array_equal(t2n(ids)[0], ref[0]) and np.array_equal(t2n(dist)[0], ref[1])
