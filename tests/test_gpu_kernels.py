@@ -478,3 +478,80 @@ def test_scan_events_of_a_small_scan(rii, oracle_lib):
     assert binding.rii_index_read_scan_counters(d["index"]) == [0] * 8
     ref = oracle_lib.linear_scan(oracle_lib.lut(d["cb"], q)[0], d["codes"], 10)
     assert np.array_equal(t2n(ids)[0], ref[0]) and np.array_equal(t2n(dist)[0], ref[1])
+
+
+# ---- the streaming kernels past the small scans' lines
+# every code some 3,200 times: buffers full of equal distances in the kernels for four, two and one query a block,
+# whose common bound counts them (four) or that fall back to sorting, and in the block's buffer for many results
+@pytest.mark.parametrize("Q,topk,per_block", [(300, 100, 4), (1027, 17, 4), (521, 128, 2), (6, 100, 1), (3, 128, 1), (5, 700, 1)])
+def test_streaming_scans_of_repeated_codes(Q, topk, per_block, rii, oracle_lib):
+    from paper_1808_03969_amd import binding
+    rng = np.random.default_rng(topk)
+    M, N = 8, 120_003
+    cb = rng.normal(size=(M, 256, 4)).astype(np.float32)
+    codes = rng.integers(0, 256, size=(37, M), dtype=np.uint8)[rng.integers(0, 37, size=N)]
+    index = rii.Index(cb)
+    index.add(codes)
+    assert binding.rii_scan_linear_plan(index, Q, topk)[0] == per_block
+    q = rng.normal(size=(Q, 4 * M)).astype(np.float32)
+    ids, dist = rii.rii_adc_scan_linear(index, rii.rii_build_lut(index, torch.from_numpy(q).cuda()), topk)
+    torch.cuda.synchronize()
+    A = oracle_lib.lut(cb, q)
+    for i in sorted(set(range(0, Q, max(1, Q // 9))) | {Q - 1}):
+        ref = oracle_lib.linear_scan(A[i], codes, topk)
+        assert np.array_equal(t2n(ids)[i], ref[0]) and np.array_equal(t2n(dist)[i], ref[1]), i
+
+
+# numbers of sub-spaces without a rotated form, and a block's buffer over short shares (16,500 rows, top-1024)
+@pytest.mark.parametrize("M,N,Q,topk", [(12, 150_001, 3, 20), (12, 150_001, 40, 128), (12, 100_000, 5, 300), (64, 150_001, 3, 50),
+                                        (64, 100_003, 20, 128), (64, 100_003, 5, 400), (16, 66_000, 64, 1024), (32, 66_000, 64, 129)])
+def test_streaming_scans_past_the_lines(M, N, Q, topk, rii, oracle_lib):
+    rng = np.random.default_rng(N + topk)
+    cb = rng.normal(size=(M, 256, 2)).astype(np.float32)
+    codes = rng.integers(0, 256, size=(N, M), dtype=np.uint8)
+    index = rii.Index(cb)
+    index.add(codes)
+    q = rng.normal(size=(Q, 2 * M)).astype(np.float32)
+    lut = rii.rii_build_lut(index, torch.from_numpy(q).cuda())
+    S = np.sort(rng.permutation(N)[:N - 9]).astype(np.int32)
+    tids = torch.from_numpy(np.tile(S, 2)).cuda()
+    lin = rii.rii_adc_scan_linear(index, lut, topk)
+    sub = rii.rii_adc_scan_subset(index, lut[:2].contiguous(), tids, torch.arange(3).cuda() * len(S), len(S), topk)
+    torch.cuda.synchronize()
+    A = oracle_lib.lut(cb, q)
+    for i in sorted({0, 1, Q // 2, Q - 1}):
+        ref = oracle_lib.linear_scan(A[i], codes, topk)
+        assert np.array_equal(t2n(lin[0])[i], ref[0]) and np.array_equal(t2n(lin[1])[i], ref[1]), i
+        if i < 2:
+            ref = oracle_lib.linear_scan(A[i], codes, topk, S=S)
+            assert np.array_equal(t2n(sub[0])[i], ref[0]) and np.array_equal(t2n(sub[1])[i], ref[1]), ("subset", i)
+
+
+# many short lists and empty ones, more members than the small scans take (the streaming kernel for lists) and more lists
+# than either keeps prefix sums for (the kernel that walks them one by one); with a target set, with a cap, with both
+@pytest.mark.parametrize("M,N,K,P,L,topk", [(8, 400_000, 900, 500, 150_000, 20), (12, 300_000, 900, 700, 150_000, 128),
+                                            (64, 300_000, 900, 700, 150_000, 5), (16, 300_000, 900, 600, 130_001, 100),
+                                            (8, 40_000, 4_700, 4_300, 9_000, 20), (12, 40_000, 4_700, 4_097, 20_000, 300),
+                                            (32, 40_000, 4_700, 4_700, 1_000, 1_000), (64, 30_000, 4_400, 4_200, 9_000, 10)])
+def test_scans_of_many_lists(M, N, K, P, L, topk, rii, oracle_lib):
+    rng = np.random.default_rng(K + M)
+    cb = rng.normal(size=(M, 256, 2)).astype(np.float32)
+    codes = rng.integers(0, 256, size=(N, M), dtype=np.uint8)
+    coarse = rng.integers(0, 256, size=(K, M), dtype=np.uint8)
+    off, lids = oracle_lib.build_lists((rng.integers(0, K // 2, size=N) * 2).astype(np.int32), K)  # every other one is empty
+    index = rii.Index(cb)
+    index.add(codes)
+    index.set_lists(coarse, off, lids)
+    Q = 4
+    q = rng.normal(size=(Q, 2 * M)).astype(np.float32)
+    lut = rii.rii_build_lut(index, torch.from_numpy(q).cuda())
+    S = np.sort(rng.permutation(N)[:N // 2]).astype(np.int32)
+    tids, toff = torch.from_numpy(np.tile(S, Q)).cuda(), torch.arange(Q + 1).cuda() * len(S)
+    probe, _ = rii.rii_coarse_assign(index, lut, P)
+    A = oracle_lib.lut(cb, q)
+    for use_S, cap in ((False, 0), (True, 0), (False, L), (True, L // 3)):
+        ids, dist = rii.rii_adc_scan_ivf(index, lut, probe, topk, tids if use_S else None, toff if use_S else None, L=cap)
+        torch.cuda.synchronize()
+        for i in range(Q):
+            ref = oracle_lib.inverted_index(A[i], codes, coarse, off, lids, topk, P, S=S if use_S else None, Lcap=cap)[:2]
+            assert np.array_equal(t2n(ids)[i], ref[0]) and np.array_equal(t2n(dist)[i], ref[1]), (use_S, cap, i)

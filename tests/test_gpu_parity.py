@@ -181,7 +181,8 @@ def test_scans_over_random_shapes(rii, oracle_lib):
 
 
 def test_linear_scan_ties_and_padding(rii, oracle_lib):
-    """Many identical codes (exact distance ties) and fewer rows than topk."""
+    """Many identical codes (exact distance ties) and fewer rows than topk, in the kernel for small scans (the
+    streaming kernels meet such codes in test_gpu_kernels.py)."""
     rng = np.random.default_rng(5)
     cb = rng.normal(size=(8, 256, 4)).astype(np.float32)
     base = rng.integers(0, 256, size=(37, 8)).astype(np.uint8)
@@ -196,15 +197,14 @@ def test_linear_scan_ties_and_padding(rii, oracle_lib):
     for i in range(6):
         ref = oracle_lib.linear_scan(A[i], codes, 700)
         assert np.array_equal(t2n(ids)[i], ref[0]) and np.array_equal(t2n(dist)[i], ref[1])
-    # the same ties against the per-wave buffers (topk <= 128): a full buffer of equal distances
-    # cannot make room by a distance bound alone and falls back to sorting; one query per block ...
+    # a full buffer of equal distances cannot make room by a distance bound alone and falls back to whole keys ...
     for topk in (100, 128):
         ids, dist = rii.rii_adc_scan_linear(index, lut, topk)
         torch.cuda.synchronize()
         for i in range(6):
             ref = oracle_lib.linear_scan(A[i], codes, topk)
             assert np.array_equal(t2n(ids)[i], ref[0]) and np.array_equal(t2n(dist)[i], ref[1]), (topk, i)
-    # ... and four queries per block (a batch large enough for that kernel)
+    # ... also with one block a query (a larger batch)
     qb = rng.normal(size=(300, 32)).astype(np.float32)
     lutb = rii.rii_build_lut(index, torch.from_numpy(qb).cuda())
     Ab = oracle_lib.lut(cb, qb)
@@ -473,7 +473,7 @@ def test_linear_scan_large_batch_in_row_chunks(M, Q, topk, rii, oracle_lib):
 
 
 def test_generic_m(rii, oracle_lib):
-    """M = 12 takes the run-time-M code path."""
+    """M = 12 takes the run-time-M code path (of the kernel for small scans)."""
     d = make_index(rii, oracle_lib, N=9000, D=48, M=12, K=0, seed=7, Q=5)
     ids, dist = rii.rii_adc_scan_linear(d["index"], lut_dev(rii, d), 20)
     torch.cuda.synchronize()
@@ -567,8 +567,8 @@ def test_ivf_scan(name, rii, oracle_lib, request):
 @pytest.mark.parametrize("M", [12, 8])
 def test_ivf_scan_short_and_empty_lists(M, rii, oracle_lib):
     """Many short posting lists, some of them empty (more coarse centres than distinct nearest
-    ones), probed in every combination of target set and candidate cap; M = 12 takes the
-    run-time-M code path.  The cap cuts inside a list, lies beyond all members, or is 1."""
+    ones), probed in every combination of target set and candidate cap by the kernel for small scans; M = 12
+    takes the run-time-M code path.  The cap cuts inside a list, lies beyond all members, or is 1."""
     d = make_index(rii, oracle_lib, N=5000, D=48, M=M, K=700, seed=9, Q=7)
     N, K, Q = d["N"], d["K"], len(d["q"])
     # every seventh centre becomes a copy of centre 0: ties go to the smaller index, so the copies' lists are empty
@@ -811,8 +811,8 @@ def test_determinism(rii, idx32):
 
 
 def test_pruned_assignment_equals_brute_force(rii, oracle_lib):
-    """K >= 1024 takes the grouped, bound-pruned search for a(n); the lists must be the ones
-    brute force gives, on clustered data (pruning active) and on unclustered data (little pruning)."""
+    """a(n) among many centres; the lists must be the ones brute force gives, on clustered and on unclustered data.
+    (At 96 dimensions the matrix products decide most of it; test_gpu_kernels.py has the pruned search by itself.)"""
     for kind, seed in (("mixture", 21), ("gaussian", 22)):
         d = make_index(rii, oracle_lib, N=30000, D=96, M=16, K=0, kind=kind, seed=seed, Q=2)
         coarse = d["codes"][t2n(synth.sample_rows(9, 30000, 1500))].copy()
