@@ -14,6 +14,8 @@
 #include "rii_internal.h"
 #include "rii_bench.h"
 
+extern "C" size_t rii_internal_matrix_bytes(int M, int Ds);
+extern "C" int rii_internal_matrix_books(rii_index* idx, void* where);
 extern "C" int rii_internal_sym_table(const rii_index* idx, hipStream_t st);
 extern "C" int rii_internal_assign(const rii_index* idx, const uint8_t* codes, int64_t n, int64_t rot_base, int64_t plane,
                                    const uint8_t* coarse, int K, int32_t* assign_out, const uint32_t* open, hipStream_t st);
@@ -343,9 +345,12 @@ int rii_index_create(const float* codebooks, int D, int M, int Ks, rii_index_t**
     delete idx;
     return RII_ERR_DEVICE;
   }
-  size_t bytes = (size_t)M * Ks * idx->Ds * sizeof(float);
-  if (hipMalloc(&idx->d_cb, bytes) != hipSuccess ||
-      hipMemcpy(idx->d_cb, codebooks, bytes, hipMemcpyHostToDevice) != hipSuccess) {
+  const size_t bytes = (size_t)M * Ks * idx->Ds * sizeof(float);
+  // the tables of the scan by matrix products behind the code books (0.6 MB at D = 128, M = 16)
+  const size_t books = (bytes + 255) / 256 * 256, more = rii_internal_matrix_bytes(M, idx->Ds);
+  if (hipMalloc(&idx->d_cb, books + more) != hipSuccess ||
+      hipMemcpy(idx->d_cb, codebooks, bytes, hipMemcpyHostToDevice) != hipSuccess ||
+      (more && rii_internal_matrix_books(idx, reinterpret_cast<uint8_t*>(idx->d_cb) + books) != RII_OK)) {
     (void)hipGetLastError();
     rii_index_destroy(idx);
     return RII_ERR_DEVICE;
@@ -497,7 +502,7 @@ int rii_index_info(const rii_index_t* idx, int64_t* info) {
   const int64_t N = idx->N, M = idx->M, K = idx->K;
   info[0] = N; info[1] = idx->D; info[2] = M; info[3] = idx->Ks; info[4] = K; info[5] = idx->theta;
   info[6] = (N + K) * M + 4 * N;
-  int64_t dev = (int64_t)M * 256 * idx->Ds * 4 + idx->cap * M * (idx->d_codes_rows != idx->d_codes ? 2 : 1) + (int64_t)idx->ws_bytes;
+  int64_t dev = (int64_t)M * 256 * idx->Ds * 4 + (int64_t)rii_internal_matrix_bytes(M, idx->Ds) + idx->cap * M * (idx->d_codes_rows != idx->d_codes ? 2 : 1) + (int64_t)idx->ws_bytes;
   if (idx->d_sym) dev += M * 256 * 256 * 4;
   if (K > 0) dev += 2 * K * M + (K + 1) * 8 + N * 4 /*ids*/ + N * M /*list-ordered codes*/;
   info[7] = dev;

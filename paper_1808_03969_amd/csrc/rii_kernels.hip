@@ -20,6 +20,7 @@
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -46,6 +47,7 @@ namespace {
 #include "rii_dev_coarse.inc"
 #include "rii_dev_ivf.inc"
 #include "rii_dev_few.inc"
+#include "rii_dev_matrix.inc"
 #include "rii_dev_offline.inc"
 #include "rii_dev_bench.inc"
 
@@ -333,15 +335,17 @@ bool few_scan(int mode, int M, int Q, int topk, int64_t rows) {
   return mode == kLinear ? few_linear(M, Q, topk, rows) : few_subset(Q, topk, rows);
 }
 
+// qmode, want_mode: only the queries in that mode are done.  leftover: they are what the scan by matrix products has left,
+// few or none, and the kernels for several queries a block may do a group's other queries once more.
 // Scan `nrows_max` rows per query (linear: the whole array) and leave per-block partial keys in
 // the workspace; then select.  Workspace layout: [tau Q u32][partial Q*nchunks*k u64].
 int launch_scan(const rii_index* idx, const uint8_t* codes, int64_t plane, int64_t N, const float* lut, int Q, int mode,
                 const int32_t* target_ids, const int64_t* target_offsets, int64_t max_rows, int topk,
                 int32_t* ids, float* dist, int out_stride, const int* qmode, int want_mode, void* ws_base,
-                hipStream_t st, bool cleared = false, bool tight = false) {
+                hipStream_t st, bool cleared = false, bool tight = false, bool leftover = false) {
   const int M = idx->M;
   if (Q > 65535) return RII_ERR_UNSUPPORTED;
-  const bool timed = mode == kLinear && idx->ev_start && idx->ev_stop && codes == idx->d_codes;
+  const bool timed = !leftover && mode == kLinear && idx->ev_start && idx->ev_stop && codes == idx->d_codes;
   if (few_scan(mode, M, Q, topk, max_rows) && !idx->bench_half_table) {
     FewArgs f{};
     f.codes = codes; f.plane = plane; f.M = M; f.lut = lut; f.N = N; f.target_ids = target_ids; f.target_offsets = target_offsets;
@@ -374,7 +378,7 @@ int launch_scan(const rii_index* idx, const uint8_t* codes, int64_t plane, int64
   a.target_ids = target_ids; a.target_offsets = target_offsets;
   a.chunk_rows = chunk_rows; a.k = topk; a.partial = partial; a.tau_g = tau;
   int64_t bchunks, brows;
-  const bool batched = mode == kLinear && !qmode && plan_batch(M, Q, max_rows, topk, &bchunks, &brows);
+  const bool batched = mode == kLinear && (!qmode || leftover) && plan_batch(M, Q, max_rows, topk, &bchunks, &brows);
   if (!batched) bchunks = 1;
   a.cand_cnt = cand_cnt; a.cand_cap = std::max(nchunks, bchunks) * topk;
   a.nq = Q;
@@ -461,13 +465,14 @@ int launch_scan(const rii_index* idx, const uint8_t* codes, int64_t plane, int64
                      k_scan_w4<32><<<g4, kScanThreads, lds4, st>>>(a4); } break;
         }
       }
-    } else if (mode == kLinear && rot_m(M) && nchunks == 1 && !qmode && Q >= 2 && topk > kWaveK4 && topk <= kWaveK) {
+    } else if (mode == kLinear && rot_m(M) && nchunks == 1 && (!qmode || leftover) && Q >= 2 && topk > kWaveK4 && topk <= kWaveK) {
       // Large batch with topk beyond the four-query kernel's reach: two queries per block
       // (k_scan_w2), every block owning its queries' whole scan, and a single-query block for an
       // odd one left over, addressed as query 0 of argument arrays shifted by Q - 1.
       auto shifted = [&](int o) {
         ScanArgs b = a;
         b.lut = lut + (size_t)o * M * 256;
+        b.qmode = qmode ? qmode + o : nullptr;
         b.partial = partial + (size_t)o * a.cand_cap;
         b.tau_g = tau + o; b.cand_cnt = cand_cnt + o; b.done_cnt = done_cnt + o;
         b.ids = ids + (size_t)o * out_stride;
@@ -579,6 +584,141 @@ size_t scan_ws_bound(int M, int Q, int64_t max_rows, int topk) {
          std::max(keys * 8 + std::max(minima_bytes(Q), minima_bytes(std::min(Q, 3))), (size_t)kFewHandOver) + 256;
 }
 
+// ------------------------------------------------------------------ the batched scan by matrix products
+// Which calls: see matrix_applies.  Scratch behind launch_scan's own (which the left-over queries need).
+struct MatrixPlan {
+  int nf, Qp, cap;
+  size_t qfrag, cq, lo, hi, mode, cnt, dist, cand, minima, total;  // byte offsets, size
+};
+constexpr int kMatrixMinQ = 64;
+constexpr int64_t kMatrixMinRows = (int64_t)1 << 18;
+constexpr double kMatrixGrowth = 5.0;  // rows of a round against those before it
+bool matrix_applies(const rii_index* idx, int Q, int topk, int64_t rows) {
+  (void)topk;
+  return idx->mx_book && Q >= kMatrixMinQ && rows >= kMatrixMinRows && !idx->bench_half_table;
+}
+MatrixPlan matrix_plan(int D, int Q, int topk) {
+  MatrixPlan p;
+  p.nf = (D + 31) / 32 * 2;
+  p.Qp = (Q + 31) / 32 * 32;
+  p.cap = 16 * topk + 1024;
+  size_t at = 0;
+  auto take = [&](size_t bytes) { const size_t o = at; at += align_up(bytes, 256); return o; };
+  p.qfrag = take((size_t)p.Qp * p.nf * 32);
+  p.cq = take((size_t)p.Qp * 4);
+  p.lo = take((size_t)p.Qp * 4);
+  p.hi = take((size_t)p.Qp * 4);
+  p.mode = take((size_t)p.Qp * 4);
+  p.cnt = take((size_t)p.Qp * kMxCntStride * 4);
+  p.dist = take((size_t)Q * topk * 4);
+  p.cand = take((size_t)Q * p.cap * 4);
+  p.minima = take((size_t)kMxSeedGroups * p.Qp * 4);
+  p.total = at;
+  return p;
+}
+
+// Room for the scan by matrix products?  A call that is being captured and could do with the scratch there is without it
+// must not allocate, and where the device has no room the look-up kernels' need may still fit.
+bool matrix_room(const rii_index* idx, size_t with, size_t without, hipStream_t st) {
+  if (idx->ws_bytes >= with) return true;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (idx->ws_bytes >= without && (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return ensure_ws(idx, with) == RII_OK;
+}
+
+template <int NF, bool SEED>
+int launch_matrix_round(const MatrixArgs& a, dim3 grid, hipStream_t st) {
+  const int rc = set_lds(k_matrix_scan<NF, SEED>, mx_lds<NF>());
+  if (rc) return rc;
+  k_matrix_scan<NF, SEED><<<grid, 64 * kMxWaves, mx_lds<NF>(), st>>>(a);
+  return RII_OK;
+}
+
+int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int topk, int32_t* ids, float* dist, int out_stride,
+                       void* scan_ws, size_t scan_bytes, hipStream_t st) {
+  const int M = idx->M;
+  const MatrixPlan p = matrix_plan(idx->D, Q, topk);
+  uint8_t* w = static_cast<uint8_t*>(scan_ws) + align_up(scan_bytes, 256);
+  float* cq = reinterpret_cast<float*>(w + p.cq);
+  float* lo = reinterpret_cast<float*>(w + p.lo);
+  float* hi = reinterpret_cast<float*>(w + p.hi);
+  int* mode = reinterpret_cast<int*>(w + p.mode);
+  const bool timed = idx->ev_start && idx->ev_stop;
+  if (timed) RII_HIP(hipEventRecord(static_cast<hipEvent_t>(idx->ev_start), st));
+  MatrixArgs a{};
+  a.codes = idx->d_codes; a.plane = idx->plane_codes; a.N = idx->N; a.M = M; a.Ds = idx->Ds; a.D = idx->D;
+  a.book = idx->mx_book; a.b = idx->mx_b;
+  a.qfrag = reinterpret_cast<const mx_u32x4*>(w + p.qfrag); a.cq = cq; a.nq = Q; a.Qp = p.Qp;
+  a.tiles = (idx->N + kMxRows - 1) / kMxRows;
+  // tiles in an order that spreads every round over the whole array (rows may be stored in some order of their own)
+  a.step = (int64_t)((double)a.tiles * 0.6180339887) | 1;
+  auto gcd = [](int64_t x, int64_t y) { while (y) { const int64_t t = x % y; x = y; y = t; } return x; };
+  while (gcd(a.step, a.tiles) != 1) ++a.step;
+  a.minima = reinterpret_cast<float*>(w + p.minima);
+  a.cnt = reinterpret_cast<uint32_t*>(w + p.cnt);
+  a.cand = reinterpret_cast<int32_t*>(w + p.cand);
+  a.cap = p.cap;
+  uint16_t* qfrag = reinterpret_cast<uint16_t*>(w + p.qfrag);
+#define RII_FIT(DSP) k_fit_tables<DSP><<<p.Qp, 256, 0, st>>>(lut, idx->mx_fit, idx->mx_ch, idx->mx_b, M, idx->Ds, p.nf, Q, qfrag, cq, lo, hi, mode, a.cnt)
+  switch (idx->mx_dsp) {
+    case 4: RII_FIT(4); break;
+    case 8: RII_FIT(8); break;
+    case 16: RII_FIT(16); break;
+    default: RII_FIT(32); break;
+  }
+#undef RII_FIT
+  auto scan = [&](bool seed, int64_t first, int64_t last) {
+    a.first = first;
+    const int qtiles = p.Qp / 32;
+    const int64_t n = last - first;
+    int splits = (int)std::max<int64_t>(1, std::min<int64_t>((8 * kWantBlocks + n - 1) / n, qtiles / 32));
+    a.per_split = (int)align_up((size_t)(qtiles + splits - 1) / splits, kMxStage);
+    const dim3 grid((unsigned)n, (unsigned)((qtiles + a.per_split - 1) / a.per_split));
+    switch (p.nf * 2 + (seed ? 1 : 0)) {
+      case 4: return launch_matrix_round<2, false>(a, grid, st);
+      case 5: return launch_matrix_round<2, true>(a, grid, st);
+      case 8: return launch_matrix_round<4, false>(a, grid, st);
+      case 9: return launch_matrix_round<4, true>(a, grid, st);
+      case 12: return launch_matrix_round<6, false>(a, grid, st);
+      case 13: return launch_matrix_round<6, true>(a, grid, st);
+      case 16: return launch_matrix_round<8, false>(a, grid, st);
+      default: return launch_matrix_round<8, true>(a, grid, st);
+    }
+  };
+  int rc = scan(true, 0, kMxSeedTiles);
+  if (rc) return rc;
+  k_matrix_seed<<<p.Qp / 32, 512, 0, st>>>(a.minima, kMxSeedGroups, Q, p.Qp, topk, lo, hi, mode, cq);
+  const double ratio = (double)a.tiles / kMxSeedTiles;
+  const int rounds = std::max(1, (int)std::ceil(std::log(ratio) / std::log(kMatrixGrowth)));
+  int64_t from = 0;
+  for (int r = 1; r <= rounds; ++r) {
+    const int64_t to = r == rounds ? a.tiles : std::min<int64_t>(a.tiles, (int64_t)(kMxSeedTiles * std::pow(ratio, (double)r / rounds)));
+    rc = scan(false, from, to);
+    if (rc) return rc;
+    from = to;
+    // what is listed, scored as defined: the k best so far
+    FewArgs f{};
+    f.codes = idx->d_codes_rows; f.plane = idx->plane_rows; f.M = M; f.lut = lut; f.N = idx->N;
+    f.target_ids = a.cand; f.target_cnt = a.cnt; f.target_cap = p.cap; f.target_cnt_stride = kMxCntStride;
+    f.k = topk; f.ids = ids; f.out_stride = out_stride; f.qmode = mode; f.want_mode = 0;
+    f.dist = dist ? dist : reinterpret_cast<float*>(w + p.dist);
+    FewShape shape = few_shape(M, Q, p.cap, topk, FewRows::targets, false);
+    shape.split = 1;
+    rc = launch_few<kFewSubset>(f, shape, Q, nullptr, true, st);
+    if (rc) return rc;
+    k_matrix_next<<<(Q + 3) / 4, 256, 0, st>>>(ids, f.dist, Q, topk, out_stride, p.cap, lo, cq, a.cnt, a.cand, mode);
+  }
+  rc = launch_scan(idx, idx->d_codes, idx->plane_codes, idx->N, lut, Q, kLinear, nullptr, nullptr, idx->N, topk, ids, dist, out_stride,
+                   mode, 1, scan_ws, st, false, false, true);
+  if (rc) return rc;
+  if (timed) RII_HIP(hipEventRecord(static_cast<hipEvent_t>(idx->ev_stop), st));
+  RII_HIP(hipGetLastError());
+  return RII_OK;
+}
+
 }  // namespace
 
 // ====================================================================== entry points
@@ -598,7 +738,10 @@ int rii_scan_linear_plan(const rii_index_t* idx, int Q, int topk, int* queries_p
   if (topk > RII_MAX_TOPK || !m_supported(idx->M) || Q > 65535) return RII_ERR_UNSUPPORTED;
   int64_t nchunks, chunk_rows, bchunks, brows;
   scan_chunks(Q, idx->N, &nchunks, &chunk_rows);
-  if (few_linear(idx->M, Q, topk, idx->N)) {
+  if (matrix_applies(idx, Q, topk, idx->N)) {
+    *queries_per_block = 32;  // (a tile of them at a time, past a block's rows)
+    *row_chunks = (idx->N + kMxRows - 1) / kMxRows;
+  } else if (few_linear(idx->M, Q, topk, idx->N)) {
     *queries_per_block = 1;
     *row_chunks = few_shape(idx->M, Q, idx->N, topk, FewRows::linear, false).split;
   } else if (topk <= kWaveK && plan_batch(idx->M, Q, idx->N, topk, &bchunks, &brows)) {
@@ -677,7 +820,11 @@ int rii_adc_scan_linear(const rii_index_t* idx, const float* lut, int Q, int top
   if (!idx || !lut || !ids || !dist || Q < 1 || topk < 1) return RII_ERR_INVALID_ARG;
   if (topk > RII_MAX_TOPK || !m_supported(idx->M) || Q > 65535) return RII_ERR_UNSUPPORTED;
   if (idx->N < 1) return RII_ERR_INVALID_ARG;
-  int rc = ensure_ws(idx, scan_ws_bytes(kLinear, idx->M, Q, idx->N, topk));
+  const size_t need = scan_ws_bytes(kLinear, idx->M, Q, idx->N, topk);
+  if (matrix_applies(idx, Q, topk, idx->N) &&
+      matrix_room(idx, align_up(need, 256) + matrix_plan(idx->D, Q, topk).total, need, static_cast<hipStream_t>(stream)))
+    return launch_matrix_scan(idx, lut, Q, topk, ids, dist, topk, idx->ws, need, static_cast<hipStream_t>(stream));
+  int rc = ensure_ws(idx, need);
   if (rc) return rc;
   return launch_scan(idx, idx->d_codes, idx->plane_codes, idx->N, lut, Q, kLinear, nullptr, nullptr, idx->N, topk, ids, dist, topk,
                      nullptr, 0, idx->ws, static_cast<hipStream_t>(stream));
@@ -905,11 +1052,14 @@ struct QueryPlan {
   // the per-query modes fall away, which also lets a batch into the batched scan.
   bool uniform = false;
   bool tight = false;  // small scans get the least scratch (see few_shape)
+  bool matrix = false;  // the linear scan goes by matrix products
+  size_t scan_b = 0;    // scratch of the scan without them
 };
 
-// `limit` > 0: a plan beyond that many bytes gives up the small scans' room, then the batched scan.
+// `limit` > 0: a plan beyond that many bytes gives up the scan by matrix products (which `matrix` = false does without
+// anyway), the small scans' room, then the batched scan.
 static int plan_query(const rii_index* idx, int Q, int topk, bool targets, int64_t max_targets, int64_t L,
-                      QueryPlan* p, size_t limit = 0) {
+                      QueryPlan* p, size_t limit = 0, bool matrix = true) {
   const int M = idx->M, K = idx->K;
   const bool has_lists = K > 0;
   // Largest number of lists any inverted-index query of this batch can ask for: such a query
@@ -931,17 +1081,21 @@ static int plan_query(const rii_index* idx, int Q, int topk, bool targets, int64
   p->plan_b = align_up((size_t)Q * 4, 256);
   p->probe_b = align_up((size_t)Q * p->pmax * 4, 256);
   const int scan_mode = targets ? kSubset : kLinear;
-  auto size = [&](bool uniform, bool tight) {
+  const bool all_linear = !targets && (!has_lists || idx->N < idx->theta);
+  auto size = [&](bool uniform, bool tight, bool matrix) {
     p->uniform = uniform;
     p->tight = tight;
-    const size_t scan_b = align_up(scan_ws_bytes(scan_mode, M, Q, p->lin_rows, topk, uniform, tight), 256);
+    p->matrix = matrix;
+    p->scan_b = align_up(scan_ws_bytes(scan_mode, M, Q, p->lin_rows, topk, uniform, tight), 256);
+    const size_t scan_b = p->scan_b + (matrix ? matrix_plan(idx->D, Q, topk).total : 0);
     const size_t coarse_b = has_lists ? align_up(coarse_ws_bytes(idx, Q, p->pmax, tight), 256) : 0;
     const size_t ivf_b = has_lists ? align_up(ivf_ws_bytes(idx, Q, p->pmax, L, topk, targets, tight), 256) : 0;
     p->total = p->lut_b + 2 * p->plan_b + p->probe_b + std::max(scan_b, std::max(coarse_b, ivf_b));
   };
-  size(!targets, false);
-  if (limit && p->total > limit) size(!targets, true);
-  if (limit && p->total > limit) size(false, true);
+  size(!targets, false, matrix && all_linear && matrix_applies(idx, Q, topk, idx->N));
+  if (limit && p->matrix && p->total > limit) size(!targets, false, false);
+  if (limit && p->total > limit) size(!targets, true, false);
+  if (limit && p->total > limit) size(false, true, false);
   return RII_OK;
 }
 
@@ -977,6 +1131,8 @@ static int run_query(const rii_index* idx, const QueryPlan& p, const float* q, i
   if (target_ids) {
     rc = launch_scan(idx, idx->d_codes_rows, idx->plane_rows, idx->N, lut, Q, kSubset, target_ids, target_offsets, p.lin_rows, topk,
                      ids, dist, topk, qmode, 0, stage_ws, st, false, p.tight);
+  } else if (all_linear && p.matrix) {
+    rc = launch_matrix_scan(idx, lut, Q, topk, ids, dist, topk, stage_ws, p.scan_b, st);
   } else if (all_linear) {
     rc = launch_scan(idx, idx->d_codes, idx->plane_codes, idx->N, lut, Q, kLinear, nullptr, nullptr, idx->N, topk, ids, dist, topk,
                      qmode, 0, stage_ws, st, p.uniform, p.tight);
@@ -1006,6 +1162,11 @@ int rii_query(const rii_index_t* idx, const float* q, int Q, int topk, const int
   QueryPlan p;
   rc = plan_query(idx, Q, topk, target_ids != nullptr, max_targets, L, &p);
   if (rc) return rc;
+  if (p.matrix) {
+    const size_t with = p.total;
+    plan_query(idx, Q, topk, target_ids != nullptr, max_targets, L, &p, 0, false);
+    if (matrix_room(idx, with, p.total, static_cast<hipStream_t>(stream))) plan_query(idx, Q, topk, target_ids != nullptr, max_targets, L, &p);
+  }
   rc = ensure_ws(idx, p.total);
   if (rc) return rc;
   return run_query(idx, p, q, Q, topk, target_ids, target_offsets, L, ids, dist, idx->ws, static_cast<hipStream_t>(stream));
@@ -1018,6 +1179,7 @@ int rii_index_reserve_workspace(rii_index_t* idx, int Q, int topk, int64_t max_t
   nprobe = std::min(nprobe, std::max(K, 1));
   // every stage's need, as bounds that grow with Q and topk (so smaller batches fit as well)
   size_t stage = scan_ws_bound(M, Q, idx->N, topk);
+  if (matrix_applies(idx, Q, topk, idx->N)) stage = align_up(stage, 256) + matrix_plan(idx->D, Q, topk).total;
   if (K > 0 && nprobe > 0) {
     const size_t coarse = coarse_in_lds(K, nprobe)   ? align_up((size_t)std::min(Q, kCoarseSplitQ) * K * 4, 256) + 256
                           : nprobe <= RII_MAX_TOPK ? scan_ws_bound(M, Q, K, nprobe)
@@ -1143,6 +1305,24 @@ int rii_rotate(const float* R, int D, const float* x, int64_t n, float* y, void*
 }
 
 // lazily build the symmetric table
+static int matrix_dsp(int Ds) { return Ds <= 4 ? 4 : Ds <= 8 ? 8 : Ds <= 16 ? 16 : 32; }
+size_t rii_internal_matrix_bytes(int M, int Ds) {
+  if (!m_supported(M) || M * Ds > kMxMaxD || Ds > kMxMaxDs) return 0;
+  return (size_t)M * 256 * (mx_entry_bytes(Ds) + 2 * matrix_dsp(Ds) * 4 + 4);
+}
+int rii_internal_matrix_books(rii_index* idx, void* where) {
+  const int M = idx->M, Ds = idx->Ds;
+  idx->mx_dsp = matrix_dsp(Ds);
+  idx->mx_book = static_cast<uint8_t*>(where);
+  idx->mx_fit = reinterpret_cast<float*>(idx->mx_book + (size_t)M * 256 * mx_entry_bytes(Ds));
+  idx->mx_ch = idx->mx_fit + (size_t)M * idx->mx_dsp * 256;
+  idx->mx_b = idx->mx_ch + (size_t)M * idx->mx_dsp * 256;
+  k_matrix_books<<<M, 256, 0, nullptr>>>(idx->d_cb, Ds, idx->mx_dsp, idx->mx_book, idx->mx_fit, idx->mx_ch, idx->mx_b);
+  RII_HIP(hipGetLastError());
+  RII_HIP(hipStreamSynchronize(nullptr));
+  return RII_OK;
+}
+
 int rii_internal_sym_table(const rii_index* cidx, hipStream_t st) {
   rii_index* idx = const_cast<rii_index*>(cidx);
   if (idx->d_sym) return RII_OK;

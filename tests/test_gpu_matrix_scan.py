@@ -1,0 +1,125 @@
+"""The batched linear scan by matrix products against the CPU oracle.  The products only decide which rows are scored;
+what is returned comes from the defined sums, so identifiers and distances must be the oracle's bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import t2n
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rii():
+    import paper_1808_03969_amd as r
+    r.load_library()
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    return r
+
+
+def check(rii, oracle, index, lut, codes, topk, at):
+    ids, dist = rii.rii_adc_scan_linear(index, lut, topk)
+    torch.cuda.synchronize()
+    A, ids, dist = t2n(lut), t2n(ids), t2n(dist)
+    for i in at:
+        ref = oracle.linear_scan(A[i], codes, topk)
+        assert np.array_equal(ids[i], ref[0]) and np.array_equal(dist[i], ref[1]), i
+
+
+# every number of matrix steps and every width of the fit, sub-spaces with and without a rotated stored form, two planes,
+# the fewest rows and rows that leave the last tile of 512 nearly empty or full, query tiles short and full, one result
+# to the most; code words far from the origin, of one value, clustered codes
+@pytest.mark.parametrize("M,Ds,N,Q,topk,kind", [
+    (16, 8, 262144, 64, 100, "normal"), (16, 8, 262145, 97, 1, "far"), (32, 3, 300_000, 128, 128, "normal"),
+    (32, 3, 400_127, 65, 10, "clustered"), (64, 2, 263_000, 129, 100, "normal"), (12, 8, 270_001, 64, 1000, "normal"),
+    (8, 16, 262_655, 161, 50, "flat"), (8, 4, 524_289, 64, 300, "normal"), (4, 32, 262_144, 70, 1024, "normal"),
+    (8, 1, 262_200, 66, 100, "normal"), (16, 6, 1_400_003, 256, 100, "clustered"), (12, 5, 262_500, 64, 20, "far")])
+def test_matrix_scan(M, Ds, N, Q, topk, kind, rii, oracle_lib):
+    from paper_1808_03969_amd import binding
+    rng = np.random.default_rng(N + M)
+    cb = rng.normal(size=(M, 256, Ds)).astype(np.float32)
+    q = rng.normal(size=(Q, M * Ds)).astype(np.float32)
+    codes = rng.integers(0, 256, size=(N, M), dtype=np.uint8)
+    if kind == "far":
+        cb += 300.0
+        q += 300.0
+    if kind == "flat":
+        cb[1] = cb[1, :1]          # a sub-space whose code words are all the same
+        cb[2, :, 1:] = 0.5         # one that varies in one coordinate only
+    if kind == "clustered":        # rows in the order of their clusters
+        proto = rng.integers(0, 256, size=(500, M), dtype=np.uint8)
+        codes = np.where(rng.random((N, M)) < 0.2, codes, proto[np.sort(rng.integers(0, 500, size=N))])
+    index = rii.Index(cb)
+    index.add(codes)
+    assert binding.rii_scan_linear_plan(index, Q, topk)[0] == 32
+    lut = rii.rii_build_lut(index, torch.from_numpy(q).cuda())
+    check(rii, oracle_lib, index, lut, codes, topk, sorted(set(range(0, Q, max(1, Q // 6))) | {Q - 1}))
+
+
+# tables that no query made, in a batch with others: random entries, of both signs, all equal, not finite, infinite,
+# huge and tiny; and queries far from every code word
+@pytest.mark.parametrize("M,topk", [(16, 100), (16, 120), (32, 10), (12, 50), (64, 200)])
+def test_tables_that_no_query_made(M, topk, rii, oracle_lib):
+    rng = np.random.default_rng(M)
+    N, Q = 262_777, 80
+    cb = rng.normal(size=(M, 256, 2)).astype(np.float32)
+    codes = rng.integers(0, 256, size=(N, M), dtype=np.uint8)
+    index = rii.Index(cb)
+    index.add(codes)
+    q = rng.normal(size=(Q, 2 * M)).astype(np.float32)
+    q[3] *= 1e4
+    q[4] *= 1e-4
+    lut = rii.rii_build_lut(index, torch.from_numpy(q).cuda())
+    lut[7] = torch.rand_like(lut[7])
+    lut[9] = 3.0
+    lut[11] *= 1e20
+    lut[12] *= 1e-20
+    lut[14] = torch.rand_like(lut[14]) * 100
+    lut[15, 0, 7:9] = float("inf")
+    lut[16, 1] += 50.0
+    check(rii, oracle_lib, index, lut, codes, topk, [0, 3, 4, 6, 7, 8, 9, 10, 11, 12, 14, 15, 16, 17, Q - 1])
+
+
+# one row over and over: more rows within every query's bound than its list holds
+@pytest.mark.parametrize("M,topk", [(8, 100), (32, 128), (64, 10)])
+def test_lists_that_overflow(M, topk, rii, oracle_lib):
+    rng = np.random.default_rng(M)
+    N, Q = 262_144 + 700, 67
+    cb = rng.normal(size=(M, 256, 2)).astype(np.float32)
+    codes = rng.integers(0, 256, size=(5, M), dtype=np.uint8)[rng.integers(0, 5, size=N)]
+    index = rii.Index(cb)
+    index.add(codes)
+    q = rng.normal(size=(Q, 2 * M)).astype(np.float32)
+    lut = rii.rii_build_lut(index, torch.from_numpy(q).cuda())
+    check(rii, oracle_lib, index, lut, codes, topk, [0, 1, 33, Q - 1])
+
+
+# the query procedure takes the same way, within scratch that was reserved, and in a captured graph that is replayed
+def test_query_reserved_and_captured(rii, oracle_lib):
+    rng = np.random.default_rng(5)
+    M, N, Q, topk = 16, 262_999, 70, 20
+    cb = rng.normal(size=(M, 256, 2)).astype(np.float32)
+    codes = rng.integers(0, 256, size=(N, M), dtype=np.uint8)
+    index = rii.Index(cb)
+    index.add(codes)
+    index.reserve_workspace(100, 50)
+    before = index.info()["device_bytes"]
+    q = torch.from_numpy(rng.normal(size=(Q, 2 * M)).astype(np.float32)).cuda()
+    want = rii.rii_query(index, q, topk)
+    torch.cuda.synchronize()
+    assert index.info()["device_bytes"] == before
+    for i in (0, 33, Q - 1):
+        ref = oracle_lib.linear_scan(oracle_lib.lut(cb, t2n(q[i:i + 1]))[0], codes, topk)
+        assert np.array_equal(t2n(want[0])[i], ref[0]) and np.array_equal(t2n(want[1])[i], ref[1])
+    out = (torch.empty_like(want[0]), torch.empty_like(want[1]))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        rii.rii_query(index, q, topk, out=out)
+    for _ in range(3):
+        out[0].zero_()
+        out[1].zero_()
+        rii.rii_query(index, q[:3], topk)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out[0], want[0]) and torch.equal(out[1], want[1])
