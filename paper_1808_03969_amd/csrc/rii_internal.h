@@ -21,9 +21,10 @@ struct rii_index {
   // What the batched scan by matrix products reads (see rii_dev_matrix.inc), behind the code books in the same
   // allocation; NULL where that scan does not apply (D > 128, Ds > 32)
   int mx_dsp = 0;                 // coordinates a sub-space has in mx_fit and mx_ch
-  uint8_t* mx_book = nullptr;        // [M][256] bf16 code words from the book's mean (entries: mx_entry_bytes)
+  uint8_t* mx_book = nullptr;        // [M][256] fp16 code words from the book's mean (entries: mx_entry_bytes)
   float* mx_fit = nullptr;  // [M][mx_dsp][256] -1/2 of the centred code words' pseudo-inverse
-  float* mx_ch = nullptr;   // [M][mx_dsp][256] the bf16 code words as floats
+  float* mx_ch = nullptr;   // [M][mx_dsp][256] the fp16 code words as floats
+  float* mx_scale = nullptr;      // what the coordinates and the distances are multiplied with
   float* mx_b = nullptr;    // [M][256] |c|^2
   float* d_sym = nullptr;         // [M][256][256] code-word-to-code-word squared distances (lazy)
   // "Stored" code arrays (d_codes, d_codes_list, d_coarse_st) keep row r rotated by r bytes when

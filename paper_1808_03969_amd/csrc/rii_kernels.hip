@@ -588,20 +588,28 @@ size_t scan_ws_bound(int M, int Q, int64_t max_rows, int topk) {
 // Which calls: see matrix_applies.  Scratch behind launch_scan's own (which the left-over queries need).
 struct MatrixPlan {
   int nf, Qp, cap;
-  size_t qfrag, cq, lo, hi, mode, cnt, dist, cand, minima, total;  // byte offsets, size
+  size_t qfrag, cq, lo, hi, mode, cnt, dist, cand, minima, part, total;  // byte offsets, size
 };
-constexpr int kMatrixMinQ = 64;
 constexpr int64_t kMatrixMinRows = (int64_t)1 << 18;
 constexpr double kMatrixGrowth = 5.0;  // rows of a round against those before it
+// From so many queries and rows on (microseconds of the look-up kernels / here; M = 16 unless said): the launches of its
+// rounds are 80 us that few queries do not bring back, and it looks at 32 queries at a time.
+//   64 queries, 4 x 10^6 rows, top-10 318 / 446, top-100 408 / 489;  128 queries, top-10 516 / 495, top-100 600 / 549,
+//   270,000 rows top-100 251 / 136;  256 queries, top-10 207 / 115, 10^6 rows 405 / 216;  2048, top-100 1242 / 848
+//   many results are scored one query a block: 256 queries, 270,000 rows, top-1000 466 / 459 (M = 8 392 / 453), 10^6 rows
+//   863 / 675;  512 queries 887 / 609
+//   without a look-up kernel for several queries a block:  M = 64, 64 queries, 270,000 rows 320 / 149, 512 queries,
+//   10^6 rows 5673 / 394;  M = 12, 64 queries, 270,000 rows 138 / 105, top-1000 275 / 324
 bool matrix_applies(const rii_index* idx, int Q, int topk, int64_t rows) {
-  (void)topk;
-  return idx->mx_book && Q >= kMatrixMinQ && rows >= kMatrixMinRows && !idx->bench_half_table;
+  if (!idx->mx_book || idx->bench_half_table || rows < kMatrixMinRows) return false;
+  if (topk > kWaveK && Q < 512 && rows < 2 * kMatrixMinRows) return false;
+  return Q >= (!rot_m(idx->M) ? 64 : topk >= kFewManyResults ? 128 : 256);
 }
-MatrixPlan matrix_plan(int D, int Q, int topk) {
+MatrixPlan matrix_plan(int D, int M, int Q, int topk) {
   MatrixPlan p;
   p.nf = (D + 31) / 32 * 2;
   p.Qp = (Q + 31) / 32 * 32;
-  p.cap = 16 * topk + 1024;
+  p.cap = 16 * topk + 4096;  // (a round is expected to list five to ten times topk rows; clusters many more)
   size_t at = 0;
   auto take = [&](size_t bytes) { const size_t o = at; at += align_up(bytes, 256); return o; };
   p.qfrag = take((size_t)p.Qp * p.nf * 32);
@@ -612,7 +620,8 @@ MatrixPlan matrix_plan(int D, int Q, int topk) {
   p.cnt = take((size_t)p.Qp * kMxCntStride * 4);
   p.dist = take((size_t)Q * topk * 4);
   p.cand = take((size_t)Q * p.cap * 4);
-  p.minima = take((size_t)kMxSeedGroups * p.Qp * 4);
+  // (the fit's partial results are read before the groups' maxima are written)
+  p.minima = p.part = take(std::max((size_t)kMxSeedGroups * 4, (size_t)M * 16) * p.Qp);
   p.total = at;
   return p;
 }
@@ -640,7 +649,7 @@ int launch_matrix_round(const MatrixArgs& a, dim3 grid, hipStream_t st) {
 int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int topk, int32_t* ids, float* dist, int out_stride,
                        void* scan_ws, size_t scan_bytes, hipStream_t st) {
   const int M = idx->M;
-  const MatrixPlan p = matrix_plan(idx->D, Q, topk);
+  const MatrixPlan p = matrix_plan(idx->D, idx->M, Q, topk);
   uint8_t* w = static_cast<uint8_t*>(scan_ws) + align_up(scan_bytes, 256);
   float* cq = reinterpret_cast<float*>(w + p.cq);
   float* lo = reinterpret_cast<float*>(w + p.lo);
@@ -662,7 +671,11 @@ int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int topk, 
   a.cand = reinterpret_cast<int32_t*>(w + p.cand);
   a.cap = p.cap;
   uint16_t* qfrag = reinterpret_cast<uint16_t*>(w + p.qfrag);
-#define RII_FIT(DSP) k_fit_tables<DSP><<<p.Qp, 256, 0, st>>>(lut, idx->mx_fit, idx->mx_ch, idx->mx_b, M, idx->Ds, p.nf, Q, qfrag, cq, lo, hi, mode, a.cnt)
+  // queries a wave of the fit goes through: enough waves to fill the chip first
+  const int per = std::min(8, std::max(1, (int)((int64_t)Q * M / (16 * kWantBlocks))));
+  float4* part = reinterpret_cast<float4*>(w + p.part);
+  const dim3 fgrid((unsigned)((p.Qp + per - 1) / per), (unsigned)(M / 4));
+#define RII_FIT(DSP) k_fit_tables<DSP><<<fgrid, 256, 0, st>>>(lut, idx->mx_fit, idx->mx_ch, idx->mx_b, idx->mx_scale, M, idx->Ds, p.nf, Q, p.Qp, per, qfrag, part)
   switch (idx->mx_dsp) {
     case 4: RII_FIT(4); break;
     case 8: RII_FIT(8); break;
@@ -670,6 +683,7 @@ int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int topk, 
     default: RII_FIT(32); break;
   }
 #undef RII_FIT
+  k_fit_sums<<<(p.Qp + 255) / 256, 256, 0, st>>>(part, M, p.nf, Q, p.Qp, cq, lo, hi, mode, a.cnt);
   auto scan = [&](bool seed, int64_t first, int64_t last) {
     a.first = first;
     const int qtiles = p.Qp / 32;
@@ -690,7 +704,13 @@ int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int topk, 
   };
   int rc = scan(true, 0, kMxSeedTiles);
   if (rc) return rc;
-  k_matrix_seed<<<p.Qp / 32, 512, 0, st>>>(a.minima, kMxSeedGroups, Q, p.Qp, topk, lo, hi, mode, cq);
+  const int spare = kMxSeedGroups / (8 * topk);  // groups to a result, in eights
+#define RII_SEED(FOLD) k_matrix_seed<FOLD><<<p.Qp / 32, 512, 0, st>>>(a.minima, Q, p.Qp, topk, lo, hi, mode, cq)
+  if (spare >= 8) RII_SEED(8);
+  else if (spare >= 4) RII_SEED(4);
+  else if (spare >= 2) RII_SEED(2);
+  else RII_SEED(1);
+#undef RII_SEED
   const double ratio = (double)a.tiles / kMxSeedTiles;
   const int rounds = std::max(1, (int)std::ceil(std::log(ratio) / std::log(kMatrixGrowth)));
   int64_t from = 0;
@@ -709,7 +729,7 @@ int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int topk, 
     shape.split = 1;
     rc = launch_few<kFewSubset>(f, shape, Q, nullptr, true, st);
     if (rc) return rc;
-    k_matrix_next<<<(Q + 3) / 4, 256, 0, st>>>(ids, f.dist, Q, topk, out_stride, p.cap, lo, cq, a.cnt, a.cand, mode);
+    k_matrix_next<<<(Q + 3) / 4, 256, 0, st>>>(ids, f.dist, Q, topk, out_stride, p.cap, idx->mx_scale, lo, cq, a.cnt, a.cand, mode);
   }
   rc = launch_scan(idx, idx->d_codes, idx->plane_codes, idx->N, lut, Q, kLinear, nullptr, nullptr, idx->N, topk, ids, dist, out_stride,
                    mode, 1, scan_ws, st, false, false, true);
@@ -822,7 +842,7 @@ int rii_adc_scan_linear(const rii_index_t* idx, const float* lut, int Q, int top
   if (idx->N < 1) return RII_ERR_INVALID_ARG;
   const size_t need = scan_ws_bytes(kLinear, idx->M, Q, idx->N, topk);
   if (matrix_applies(idx, Q, topk, idx->N) &&
-      matrix_room(idx, align_up(need, 256) + matrix_plan(idx->D, Q, topk).total, need, static_cast<hipStream_t>(stream)))
+      matrix_room(idx, align_up(need, 256) + matrix_plan(idx->D, idx->M, Q, topk).total, need, static_cast<hipStream_t>(stream)))
     return launch_matrix_scan(idx, lut, Q, topk, ids, dist, topk, idx->ws, need, static_cast<hipStream_t>(stream));
   int rc = ensure_ws(idx, need);
   if (rc) return rc;
@@ -1087,7 +1107,7 @@ static int plan_query(const rii_index* idx, int Q, int topk, bool targets, int64
     p->tight = tight;
     p->matrix = matrix;
     p->scan_b = align_up(scan_ws_bytes(scan_mode, M, Q, p->lin_rows, topk, uniform, tight), 256);
-    const size_t scan_b = p->scan_b + (matrix ? matrix_plan(idx->D, Q, topk).total : 0);
+    const size_t scan_b = p->scan_b + (matrix ? matrix_plan(idx->D, idx->M, Q, topk).total : 0);
     const size_t coarse_b = has_lists ? align_up(coarse_ws_bytes(idx, Q, p->pmax, tight), 256) : 0;
     const size_t ivf_b = has_lists ? align_up(ivf_ws_bytes(idx, Q, p->pmax, L, topk, targets, tight), 256) : 0;
     p->total = p->lut_b + 2 * p->plan_b + p->probe_b + std::max(scan_b, std::max(coarse_b, ivf_b));
@@ -1179,7 +1199,7 @@ int rii_index_reserve_workspace(rii_index_t* idx, int Q, int topk, int64_t max_t
   nprobe = std::min(nprobe, std::max(K, 1));
   // every stage's need, as bounds that grow with Q and topk (so smaller batches fit as well)
   size_t stage = scan_ws_bound(M, Q, idx->N, topk);
-  if (matrix_applies(idx, Q, topk, idx->N)) stage = align_up(stage, 256) + matrix_plan(idx->D, Q, topk).total;
+  if (matrix_applies(idx, Q, topk, idx->N)) stage = align_up(stage, 256) + matrix_plan(idx->D, idx->M, Q, topk).total;
   if (K > 0 && nprobe > 0) {
     const size_t coarse = coarse_in_lds(K, nprobe)   ? align_up((size_t)std::min(Q, kCoarseSplitQ) * K * 4, 256) + 256
                           : nprobe <= RII_MAX_TOPK ? scan_ws_bound(M, Q, K, nprobe)
@@ -1308,7 +1328,7 @@ int rii_rotate(const float* R, int D, const float* x, int64_t n, float* y, void*
 static int matrix_dsp(int Ds) { return Ds <= 4 ? 4 : Ds <= 8 ? 8 : Ds <= 16 ? 16 : 32; }
 size_t rii_internal_matrix_bytes(int M, int Ds) {
   if (!m_supported(M) || M * Ds > kMxMaxD || Ds > kMxMaxDs) return 0;
-  return (size_t)M * 256 * (mx_entry_bytes(Ds) + 2 * matrix_dsp(Ds) * 4 + 4);
+  return (size_t)M * 256 * (mx_entry_bytes(Ds) + 2 * matrix_dsp(Ds) * 4 + 4) + 256;
 }
 int rii_internal_matrix_books(rii_index* idx, void* where) {
   const int M = idx->M, Ds = idx->Ds;
@@ -1317,7 +1337,9 @@ int rii_internal_matrix_books(rii_index* idx, void* where) {
   idx->mx_fit = reinterpret_cast<float*>(idx->mx_book + (size_t)M * 256 * mx_entry_bytes(Ds));
   idx->mx_ch = idx->mx_fit + (size_t)M * idx->mx_dsp * 256;
   idx->mx_b = idx->mx_ch + (size_t)M * idx->mx_dsp * 256;
-  k_matrix_books<<<M, 256, 0, nullptr>>>(idx->d_cb, Ds, idx->mx_dsp, idx->mx_book, idx->mx_fit, idx->mx_ch, idx->mx_b);
+  idx->mx_scale = idx->mx_b + (size_t)M * 256;
+  k_matrix_scale<<<1, 1024, 0, nullptr>>>(idx->d_cb, M, Ds, idx->mx_scale);
+  k_matrix_books<<<M, 256, 0, nullptr>>>(idx->d_cb, idx->mx_scale, Ds, idx->mx_dsp, idx->mx_book, idx->mx_fit, idx->mx_ch, idx->mx_b);
   RII_HIP(hipGetLastError());
   RII_HIP(hipStreamSynchronize(nullptr));
   return RII_OK;

@@ -30,10 +30,11 @@ def check(rii, oracle, index, lut, codes, topk, at):
 # the fewest rows and rows that leave the last tile of 512 nearly empty or full, query tiles short and full, one result
 # to the most; code words far from the origin, of one value, clustered codes
 @pytest.mark.parametrize("M,Ds,N,Q,topk,kind", [
-    (16, 8, 262144, 64, 100, "normal"), (16, 8, 262145, 97, 1, "far"), (32, 3, 300_000, 128, 128, "normal"),
-    (32, 3, 400_127, 65, 10, "clustered"), (64, 2, 263_000, 129, 100, "normal"), (12, 8, 270_001, 64, 1000, "normal"),
-    (8, 16, 262_655, 161, 50, "flat"), (8, 4, 524_289, 64, 300, "normal"), (4, 32, 262_144, 70, 1024, "normal"),
-    (8, 1, 262_200, 66, 100, "normal"), (16, 6, 1_400_003, 256, 100, "clustered"), (12, 5, 262_500, 64, 20, "far")])
+    (16, 8, 262144, 128, 100, "normal"), (16, 8, 262145, 257, 1, "far"), (32, 3, 300_000, 129, 128, "normal"),
+    (32, 3, 400_127, 280, 10, "clustered"), (64, 2, 263_000, 129, 100, "normal"), (12, 8, 524_288, 64, 1000, "normal"),
+    (8, 16, 262_655, 261, 50, "flat"), (8, 4, 524_289, 159, 300, "normal"), (4, 32, 524_800, 70, 1024, "normal"),
+    (8, 1, 262_200, 130, 100, "normal"), (16, 6, 1_400_003, 256, 100, "clustered"), (12, 5, 262_500, 64, 20, "far"),
+    (16, 2, 270_000, 513, 200, "tiny"), (32, 4, 262_200, 160, 64, "huge")])
 def test_matrix_scan(M, Ds, N, Q, topk, kind, rii, oracle_lib):
     from paper_1808_03969_amd import binding
     rng = np.random.default_rng(N + M)
@@ -43,6 +44,10 @@ def test_matrix_scan(M, Ds, N, Q, topk, kind, rii, oracle_lib):
     if kind == "far":
         cb += 300.0
         q += 300.0
+    if kind in ("tiny", "huge"):   # magnitudes at the ends of what the scaling reaches and past it
+        cb *= 1e-12 if kind == "tiny" else 1e9
+        q *= 1e-12 if kind == "tiny" else 1e9
+        q[1] *= 50.0
     if kind == "flat":
         cb[1] = cb[1, :1]          # a sub-space whose code words are all the same
         cb[2, :, 1:] = 0.5         # one that varies in one coordinate only
@@ -58,10 +63,10 @@ def test_matrix_scan(M, Ds, N, Q, topk, kind, rii, oracle_lib):
 
 # tables that no query made, in a batch with others: random entries, of both signs, all equal, not finite, infinite,
 # huge and tiny; and queries far from every code word
-@pytest.mark.parametrize("M,topk", [(16, 100), (16, 120), (32, 10), (12, 50), (64, 200)])
+@pytest.mark.parametrize("M,topk", [(16, 100), (16, 120), (32, 10), (12, 50), (64, 100)])
 def test_tables_that_no_query_made(M, topk, rii, oracle_lib):
     rng = np.random.default_rng(M)
-    N, Q = 262_777, 80
+    N, Q = 262_777, 300
     cb = rng.normal(size=(M, 256, 2)).astype(np.float32)
     codes = rng.integers(0, 256, size=(N, M), dtype=np.uint8)
     index = rii.Index(cb)
@@ -84,7 +89,7 @@ def test_tables_that_no_query_made(M, topk, rii, oracle_lib):
 @pytest.mark.parametrize("M,topk", [(8, 100), (32, 128), (64, 10)])
 def test_lists_that_overflow(M, topk, rii, oracle_lib):
     rng = np.random.default_rng(M)
-    N, Q = 262_144 + 700, 67
+    N, Q = 262_144 + 700, 270
     cb = rng.normal(size=(M, 256, 2)).astype(np.float32)
     codes = rng.integers(0, 256, size=(5, M), dtype=np.uint8)[rng.integers(0, 5, size=N)]
     index = rii.Index(cb)
@@ -97,12 +102,12 @@ def test_lists_that_overflow(M, topk, rii, oracle_lib):
 # the query procedure takes the same way, within scratch that was reserved, and in a captured graph that is replayed
 def test_query_reserved_and_captured(rii, oracle_lib):
     rng = np.random.default_rng(5)
-    M, N, Q, topk = 16, 262_999, 70, 20
+    M, N, Q, topk = 16, 262_999, 270, 20
     cb = rng.normal(size=(M, 256, 2)).astype(np.float32)
     codes = rng.integers(0, 256, size=(N, M), dtype=np.uint8)
     index = rii.Index(cb)
     index.add(codes)
-    index.reserve_workspace(100, 50)
+    index.reserve_workspace(300, 50)
     before = index.info()["device_bytes"]
     q = torch.from_numpy(rng.normal(size=(Q, 2 * M)).astype(np.float32)).cuda()
     want = rii.rii_query(index, q, topk)
