@@ -355,6 +355,16 @@ def main():
         }
         del out_h
 
+    elif qpb == 32:
+        # The batched launches go by matrix products: a multiply-add per coordinate, query and row decides which rows are scored.
+        flops = 2.0 * Q * N * cfg.D
+        batched = {
+            "bound": "mfma", "kernel": f"k_matrix_scan, {Q} queries, {row_chunks} row tiles of 512, all its launches and the scoring between them",
+            "achieved": round(flops / (scan_avg_ms * 1e-3) / 1e12, 1), "peak": 2500.0, "unit": "TFLOP/s (fp16, dense)",
+            "frac": round(flops / (scan_avg_ms * 1e-3) / 2.5e15, 4), "flops_per_launch": flops,
+            "algorithmic_lookups_per_launch": float(Q) * N * M, "launch_ms": round(scan_avg_ms, 3),
+        }
+
     # The subset scan gathers rows of M bytes out of 128-byte memory lines: bytes it needs against
     # the bytes of the lines they lie in (counted from the identifiers of a sample of the queries).
     toff_h = toff[:17].cpu().numpy()

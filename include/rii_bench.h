@@ -36,7 +36,8 @@ int rii_index_set_scan_events(rii_index_t* index, void* start_event, void* stop_
 int rii_index_read_scan_counters(rii_index_t* index, uint64_t* counters_out);
 
 /* Launch shape rii_adc_scan_linear uses for a batch of Q queries on this index (so that a
- * benchmark can name the kernel it timed): *queries_per_block = 4, 2 or 1 queries sharing one
+ * benchmark can name the kernel it timed): *queries_per_block = 32 (the scan by matrix products: a
+ * tile of queries; *row_chunks = row tiles), or 4, 2 or 1 queries sharing one
  * pass over the codes (Alg. 1 run for several queries at once; results are per query);
  * *row_chunks = blocks that share one query group's rows.  Host call, no GPU work. */
 int rii_scan_linear_plan(const rii_index_t* index, int Q, int topk, int* queries_per_block, int64_t* row_chunks);

@@ -6,6 +6,7 @@
 // Data flow of one query batch:
 //   k_build_lut              q, code books                        -> A [Q][M][256]       (Sec. 3)
 //   k_few                    A in LDS, some 10^4 rows at most     -> top-R per query     (all of the following, small)
+//   k_matrix_scan + k_few    A as a vector, codes decoded, MFMA   -> top-R per query     (Alg. 1, whole data, batches)
 //   k_scan_w4 / k_scan_w     A in LDS, codes streamed             -> top-R per query     (Alg. 1, whole data)
 //   k_scan_w<subset>         A in LDS, codes gathered by id       -> top-R per query     (Alg. 1, target ids)
 //   k_rank_lists             A in LDS, coarse codes               -> nearest lists       (Alg. 2, first block)
@@ -595,7 +596,7 @@ constexpr double kMatrixGrowth = 5.0;  // rows of a round against those before i
 // From so many queries and rows on (microseconds of the look-up kernels / here; M = 16 unless said): the launches of its
 // rounds are 80 us that few queries do not bring back, and it looks at 32 queries at a time.
 //   64 queries, 4 x 10^6 rows, top-10 318 / 446, top-100 408 / 489;  128 queries, top-10 516 / 495, top-100 600 / 549,
-//   270,000 rows top-100 251 / 136;  256 queries, top-10 207 / 115, 10^6 rows 405 / 216;  2048, top-100 1242 / 848
+//   270,000 rows top-100 251 / 136, 1.6 x 10^7 rows top-100 1553 / 1616;  256 queries, top-10 207 / 115, 10^6 rows 405 / 216;  2048, top-100 1242 / 848
 //   many results are scored one query a block: 256 queries, 270,000 rows, top-1000 466 / 459 (M = 8 392 / 453), 10^6 rows
 //   863 / 675;  512 queries 887 / 609
 //   without a look-up kernel for several queries a block:  M = 64, 64 queries, 270,000 rows 320 / 149, 512 queries,
@@ -603,13 +604,17 @@ constexpr double kMatrixGrowth = 5.0;  // rows of a round against those before i
 bool matrix_applies(const rii_index* idx, int Q, int topk, int64_t rows) {
   if (!idx->mx_book || idx->bench_half_table || rows < kMatrixMinRows) return false;
   if (topk > kWaveK && Q < 512 && rows < 2 * kMatrixMinRows) return false;
-  return Q >= (!rot_m(idx->M) ? 64 : topk >= kFewManyResults ? 128 : 256);
+  return Q >= (!rot_m(idx->M) ? 64 : topk >= kFewManyResults && rows <= 32 * kMatrixMinRows ? 128 : 256);
 }
-MatrixPlan matrix_plan(int D, int M, int Q, int topk) {
+MatrixPlan matrix_plan(const rii_index* idx, int Q, int topk) {
+  const int D = idx->D, M = idx->M;
   MatrixPlan p;
   p.nf = (D + 31) / 32 * 2;
   p.Qp = (Q + 31) / 32 * 32;
-  p.cap = 16 * topk + 4096;  // (a round is expected to list five to ten times topk rows; clusters many more)
+  // A round is expected to list five to ten times topk rows; where clusters have collapsed onto few codes, all
+  // rows that share the bound's distance with them (1000 clusters, 1.6 x 10^7 rows: 12,000; 2048 queries 13.7 ms with the
+  // lists of two queries in three too short).  1 GB for such lists at most.
+  p.cap = 16 * topk + 4096 + (int)std::min<int64_t>(idx->N / 1024, ((int64_t)1 << 28) / Q);
   size_t at = 0;
   auto take = [&](size_t bytes) { const size_t o = at; at += align_up(bytes, 256); return o; };
   p.qfrag = take((size_t)p.Qp * p.nf * 32);
@@ -649,7 +654,7 @@ int launch_matrix_round(const MatrixArgs& a, dim3 grid, hipStream_t st) {
 int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int topk, int32_t* ids, float* dist, int out_stride,
                        void* scan_ws, size_t scan_bytes, hipStream_t st) {
   const int M = idx->M;
-  const MatrixPlan p = matrix_plan(idx->D, idx->M, Q, topk);
+  const MatrixPlan p = matrix_plan(idx, Q, topk);
   uint8_t* w = static_cast<uint8_t*>(scan_ws) + align_up(scan_bytes, 256);
   float* cq = reinterpret_cast<float*>(w + p.cq);
   float* lo = reinterpret_cast<float*>(w + p.lo);
@@ -842,7 +847,7 @@ int rii_adc_scan_linear(const rii_index_t* idx, const float* lut, int Q, int top
   if (idx->N < 1) return RII_ERR_INVALID_ARG;
   const size_t need = scan_ws_bytes(kLinear, idx->M, Q, idx->N, topk);
   if (matrix_applies(idx, Q, topk, idx->N) &&
-      matrix_room(idx, align_up(need, 256) + matrix_plan(idx->D, idx->M, Q, topk).total, need, static_cast<hipStream_t>(stream)))
+      matrix_room(idx, align_up(need, 256) + matrix_plan(idx, Q, topk).total, need, static_cast<hipStream_t>(stream)))
     return launch_matrix_scan(idx, lut, Q, topk, ids, dist, topk, idx->ws, need, static_cast<hipStream_t>(stream));
   int rc = ensure_ws(idx, need);
   if (rc) return rc;
@@ -1107,7 +1112,7 @@ static int plan_query(const rii_index* idx, int Q, int topk, bool targets, int64
     p->tight = tight;
     p->matrix = matrix;
     p->scan_b = align_up(scan_ws_bytes(scan_mode, M, Q, p->lin_rows, topk, uniform, tight), 256);
-    const size_t scan_b = p->scan_b + (matrix ? matrix_plan(idx->D, idx->M, Q, topk).total : 0);
+    const size_t scan_b = p->scan_b + (matrix ? matrix_plan(idx, Q, topk).total : 0);
     const size_t coarse_b = has_lists ? align_up(coarse_ws_bytes(idx, Q, p->pmax, tight), 256) : 0;
     const size_t ivf_b = has_lists ? align_up(ivf_ws_bytes(idx, Q, p->pmax, L, topk, targets, tight), 256) : 0;
     p->total = p->lut_b + 2 * p->plan_b + p->probe_b + std::max(scan_b, std::max(coarse_b, ivf_b));
@@ -1199,7 +1204,8 @@ int rii_index_reserve_workspace(rii_index_t* idx, int Q, int topk, int64_t max_t
   nprobe = std::min(nprobe, std::max(K, 1));
   // every stage's need, as bounds that grow with Q and topk (so smaller batches fit as well)
   size_t stage = scan_ws_bound(M, Q, idx->N, topk);
-  if (matrix_applies(idx, Q, topk, idx->N)) stage = align_up(stage, 256) + matrix_plan(idx->D, idx->M, Q, topk).total;
+  // (calls with fewer results may go by matrix products where these do not)
+  if (matrix_applies(idx, Q, std::min(topk, kWaveK), idx->N)) stage = align_up(stage, 256) + matrix_plan(idx, Q, topk).total;
   if (K > 0 && nprobe > 0) {
     const size_t coarse = coarse_in_lds(K, nprobe)   ? align_up((size_t)std::min(Q, kCoarseSplitQ) * K * 4, 256) + 256
                           : nprobe <= RII_MAX_TOPK ? scan_ws_bound(M, Q, K, nprobe)

@@ -107,7 +107,7 @@ def test_query_reserved_and_captured(rii, oracle_lib):
     codes = rng.integers(0, 256, size=(N, M), dtype=np.uint8)
     index = rii.Index(cb)
     index.add(codes)
-    index.reserve_workspace(300, 50)
+    index.reserve_workspace(300, 200)  # (200 results of 300 queries go by look-ups, fewer by products)
     before = index.info()["device_bytes"]
     q = torch.from_numpy(rng.normal(size=(Q, 2 * M)).astype(np.float32)).cuda()
     want = rii.rii_query(index, q, topk)
