@@ -53,6 +53,7 @@ struct rii_index {
   // scratch reused by the online calls (grown on demand)
   mutable void* ws = nullptr;
   mutable size_t ws_bytes = 0;
+  bool ws_reserved = false;       // sized by rii_index_reserve_workspace: calls within it must not grow it
 
   bool bench_half_table = false;  // set around one launch by rii_bench_scan_linear_half only
   // optional measurement aid: events recorded right before / after the linear-scan kernel

@@ -613,8 +613,8 @@ MatrixPlan matrix_plan(const rii_index* idx, int Q, int topk) {
   p.Qp = (Q + 31) / 32 * 32;
   // A round is expected to list five to ten times topk rows; where clusters have collapsed onto few codes, all
   // rows that share the bound's distance with them (1000 clusters, 1.6 x 10^7 rows: 12,000; 2048 queries 13.7 ms with the
-  // lists of two queries in three too short).  1 GB for such lists at most.
-  p.cap = 16 * topk + 4096 + (int)std::min<int64_t>(idx->N / 1024, ((int64_t)1 << 28) / Q);
+  // lists of two queries in three too short).
+  p.cap = 16 * topk + 4096 + (int)std::min<int64_t>(idx->N / 1024, 32768);
   size_t at = 0;
   auto take = [&](size_t bytes) { const size_t o = at; at += align_up(bytes, 256); return o; };
   p.qfrag = take((size_t)p.Qp * p.nf * 32);
@@ -631,16 +631,35 @@ MatrixPlan matrix_plan(const rii_index* idx, int Q, int topk) {
   return p;
 }
 
-// Room for the scan by matrix products?  A call that is being captured and could do with the scratch there is without it
-// must not allocate, and where the device has no room the look-up kernels' need may still fit.
-bool matrix_room(const rii_index* idx, size_t with, size_t without, hipStream_t st) {
-  if (idx->ws_bytes >= with) return true;
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (idx->ws_bytes >= without && (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)) {
-    (void)hipGetLastError();
-    return false;
+// What `q` queries of a batch of Q need, the last piece's left-over queries included (launch_scan may want more for fewer).
+size_t matrix_need(const rii_index* idx, int Q, int q, int topk) {
+  const int tail = Q % q ? Q % q : q;
+  const size_t scan = std::max(scan_ws_bytes(kLinear, idx->M, q, idx->N, topk), scan_ws_bytes(kLinear, idx->M, tail, idx->N, topk));
+  return align_up(scan, 256) + matrix_plan(idx, q, topk).total;
+}
+
+// Queries the scan by matrix products takes at a time, its scratch `lead` bytes into the handle's; 0: it is not taken.
+// Scratch that was reserved, or is there when a call is captured, is not grown as long as it holds the `without` bytes
+// that the look-up kernels need: the batch is then cut into pieces that fit, if they are worth it.  Otherwise pieces of 1 GB.
+constexpr size_t kMatrixScratch = (size_t)1 << 30;
+int matrix_queries(const rii_index* idx, int Q, int topk, size_t lead, size_t without, hipStream_t st) {
+  if (!matrix_applies(idx, Q, topk, idx->N)) return 0;
+  bool fixed = idx->ws_reserved;
+  if (!fixed) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    fixed = hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
+    if (fixed) (void)hipGetLastError();
   }
-  return ensure_ws(idx, with) == RII_OK;
+  fixed = fixed && idx->ws_bytes >= without;
+  const size_t room = fixed ? idx->ws_bytes : std::max(idx->ws_bytes, lead + kMatrixScratch);
+  for (int pieces = 1;; ++pieces) {
+    const int q = std::min(Q, ((Q + pieces - 1) / pieces + 31) / 32 * 32);
+    if (!matrix_applies(idx, q, topk, idx->N)) return 0;
+    const size_t need = lead + matrix_need(idx, Q, q, topk);
+    if (need > room) continue;
+    if (need <= idx->ws_bytes || ensure_ws(idx, std::max(need, without)) == RII_OK) return q;
+    return 0;  // (no room on the device; without the products there may be)
+  }
 }
 
 template <int NF, bool SEED>
@@ -660,8 +679,6 @@ int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int topk, 
   float* lo = reinterpret_cast<float*>(w + p.lo);
   float* hi = reinterpret_cast<float*>(w + p.hi);
   int* mode = reinterpret_cast<int*>(w + p.mode);
-  const bool timed = idx->ev_start && idx->ev_stop;
-  if (timed) RII_HIP(hipEventRecord(static_cast<hipEvent_t>(idx->ev_start), st));
   MatrixArgs a{};
   a.codes = idx->d_codes; a.plane = idx->plane_codes; a.N = idx->N; a.M = M; a.Ds = idx->Ds; a.D = idx->D;
   a.book = idx->mx_book; a.b = idx->mx_b;
@@ -739,8 +756,22 @@ int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int topk, 
   rc = launch_scan(idx, idx->d_codes, idx->plane_codes, idx->N, lut, Q, kLinear, nullptr, nullptr, idx->N, topk, ids, dist, out_stride,
                    mode, 1, scan_ws, st, false, false, true);
   if (rc) return rc;
-  if (timed) RII_HIP(hipEventRecord(static_cast<hipEvent_t>(idx->ev_stop), st));
   RII_HIP(hipGetLastError());
+  return RII_OK;
+}
+
+// The whole batch, q queries (what matrix_queries said) at a time in the same scratch.
+int launch_matrix_batches(const rii_index* idx, const float* lut, int Q, int q, int topk, int32_t* ids, float* dist, int out_stride,
+                          void* ws, hipStream_t st) {
+  const bool timed = idx->ev_start && idx->ev_stop;
+  const size_t scan_bytes = matrix_need(idx, Q, q, topk) - matrix_plan(idx, q, topk).total;
+  if (timed) RII_HIP(hipEventRecord(static_cast<hipEvent_t>(idx->ev_start), st));
+  for (int o = 0; o < Q; o += q) {
+    const int rc = launch_matrix_scan(idx, lut + (size_t)o * idx->M * 256, std::min(q, Q - o), topk, ids + (size_t)o * out_stride,
+                                      dist ? dist + (size_t)o * out_stride : nullptr, out_stride, ws, scan_bytes, st);
+    if (rc) return rc;
+  }
+  if (timed) RII_HIP(hipEventRecord(static_cast<hipEvent_t>(idx->ev_stop), st));
   return RII_OK;
 }
 
@@ -846,9 +877,8 @@ int rii_adc_scan_linear(const rii_index_t* idx, const float* lut, int Q, int top
   if (topk > RII_MAX_TOPK || !m_supported(idx->M) || Q > 65535) return RII_ERR_UNSUPPORTED;
   if (idx->N < 1) return RII_ERR_INVALID_ARG;
   const size_t need = scan_ws_bytes(kLinear, idx->M, Q, idx->N, topk);
-  if (matrix_applies(idx, Q, topk, idx->N) &&
-      matrix_room(idx, align_up(need, 256) + matrix_plan(idx, Q, topk).total, need, static_cast<hipStream_t>(stream)))
-    return launch_matrix_scan(idx, lut, Q, topk, ids, dist, topk, idx->ws, need, static_cast<hipStream_t>(stream));
+  if (const int some = matrix_queries(idx, Q, topk, 0, need, static_cast<hipStream_t>(stream)))
+    return launch_matrix_batches(idx, lut, Q, some, topk, ids, dist, topk, idx->ws, static_cast<hipStream_t>(stream));
   int rc = ensure_ws(idx, need);
   if (rc) return rc;
   return launch_scan(idx, idx->d_codes, idx->plane_codes, idx->N, lut, Q, kLinear, nullptr, nullptr, idx->N, topk, ids, dist, topk,
@@ -1077,14 +1107,12 @@ struct QueryPlan {
   // the per-query modes fall away, which also lets a batch into the batched scan.
   bool uniform = false;
   bool tight = false;  // small scans get the least scratch (see few_shape)
-  bool matrix = false;  // the linear scan goes by matrix products
-  size_t scan_b = 0;    // scratch of the scan without them
+  int matrix_q = 0;    // queries at a time of the linear scan by matrix products; 0: it goes by look-ups
 };
 
-// `limit` > 0: a plan beyond that many bytes gives up the scan by matrix products (which `matrix` = false does without
-// anyway), the small scans' room, then the batched scan.
+// `limit` > 0: a plan beyond that many bytes gives up the small scans' room, then the batched scan.
 static int plan_query(const rii_index* idx, int Q, int topk, bool targets, int64_t max_targets, int64_t L,
-                      QueryPlan* p, size_t limit = 0, bool matrix = true) {
+                      QueryPlan* p, size_t limit = 0) {
   const int M = idx->M, K = idx->K;
   const bool has_lists = K > 0;
   // Largest number of lists any inverted-index query of this batch can ask for: such a query
@@ -1106,21 +1134,17 @@ static int plan_query(const rii_index* idx, int Q, int topk, bool targets, int64
   p->plan_b = align_up((size_t)Q * 4, 256);
   p->probe_b = align_up((size_t)Q * p->pmax * 4, 256);
   const int scan_mode = targets ? kSubset : kLinear;
-  const bool all_linear = !targets && (!has_lists || idx->N < idx->theta);
-  auto size = [&](bool uniform, bool tight, bool matrix) {
+  auto size = [&](bool uniform, bool tight) {
     p->uniform = uniform;
     p->tight = tight;
-    p->matrix = matrix;
-    p->scan_b = align_up(scan_ws_bytes(scan_mode, M, Q, p->lin_rows, topk, uniform, tight), 256);
-    const size_t scan_b = p->scan_b + (matrix ? matrix_plan(idx, Q, topk).total : 0);
+    const size_t scan_b = align_up(scan_ws_bytes(scan_mode, M, Q, p->lin_rows, topk, uniform, tight), 256);
     const size_t coarse_b = has_lists ? align_up(coarse_ws_bytes(idx, Q, p->pmax, tight), 256) : 0;
     const size_t ivf_b = has_lists ? align_up(ivf_ws_bytes(idx, Q, p->pmax, L, topk, targets, tight), 256) : 0;
     p->total = p->lut_b + 2 * p->plan_b + p->probe_b + std::max(scan_b, std::max(coarse_b, ivf_b));
   };
-  size(!targets, false, matrix && all_linear && matrix_applies(idx, Q, topk, idx->N));
-  if (limit && p->matrix && p->total > limit) size(!targets, false, false);
-  if (limit && p->total > limit) size(!targets, true, false);
-  if (limit && p->total > limit) size(false, true, false);
+  size(!targets, false);
+  if (limit && p->total > limit) size(!targets, true);
+  if (limit && p->total > limit) size(false, true);
   return RII_OK;
 }
 
@@ -1156,8 +1180,8 @@ static int run_query(const rii_index* idx, const QueryPlan& p, const float* q, i
   if (target_ids) {
     rc = launch_scan(idx, idx->d_codes_rows, idx->plane_rows, idx->N, lut, Q, kSubset, target_ids, target_offsets, p.lin_rows, topk,
                      ids, dist, topk, qmode, 0, stage_ws, st, false, p.tight);
-  } else if (all_linear && p.matrix) {
-    rc = launch_matrix_scan(idx, lut, Q, topk, ids, dist, topk, stage_ws, p.scan_b, st);
+  } else if (all_linear && p.matrix_q) {
+    rc = launch_matrix_batches(idx, lut, Q, p.matrix_q, topk, ids, dist, topk, stage_ws, st);
   } else if (all_linear) {
     rc = launch_scan(idx, idx->d_codes, idx->plane_codes, idx->N, lut, Q, kLinear, nullptr, nullptr, idx->N, topk, ids, dist, topk,
                      qmode, 0, stage_ws, st, p.uniform, p.tight);
@@ -1187,11 +1211,8 @@ int rii_query(const rii_index_t* idx, const float* q, int Q, int topk, const int
   QueryPlan p;
   rc = plan_query(idx, Q, topk, target_ids != nullptr, max_targets, L, &p);
   if (rc) return rc;
-  if (p.matrix) {
-    const size_t with = p.total;
-    plan_query(idx, Q, topk, target_ids != nullptr, max_targets, L, &p, 0, false);
-    if (matrix_room(idx, with, p.total, static_cast<hipStream_t>(stream))) plan_query(idx, Q, topk, target_ids != nullptr, max_targets, L, &p);
-  }
+  if (!target_ids && (idx->K == 0 || idx->N < idx->theta))
+    p.matrix_q = matrix_queries(idx, Q, topk, p.lut_b + 2 * p.plan_b + p.probe_b, p.total, static_cast<hipStream_t>(stream));
   rc = ensure_ws(idx, p.total);
   if (rc) return rc;
   return run_query(idx, p, q, Q, topk, target_ids, target_offsets, L, ids, dist, idx->ws, static_cast<hipStream_t>(stream));
@@ -1204,8 +1225,6 @@ int rii_index_reserve_workspace(rii_index_t* idx, int Q, int topk, int64_t max_t
   nprobe = std::min(nprobe, std::max(K, 1));
   // every stage's need, as bounds that grow with Q and topk (so smaller batches fit as well)
   size_t stage = scan_ws_bound(M, Q, idx->N, topk);
-  // (calls with fewer results may go by matrix products where these do not)
-  if (matrix_applies(idx, Q, std::min(topk, kWaveK), idx->N)) stage = align_up(stage, 256) + matrix_plan(idx, Q, topk).total;
   if (K > 0 && nprobe > 0) {
     const size_t coarse = coarse_in_lds(K, nprobe)   ? align_up((size_t)std::min(Q, kCoarseSplitQ) * K * 4, 256) + 256
                           : nprobe <= RII_MAX_TOPK ? scan_ws_bound(M, Q, K, nprobe)
@@ -1215,6 +1234,7 @@ int rii_index_reserve_workspace(rii_index_t* idx, int Q, int topk, int64_t max_t
   }
   const size_t query = align_up((size_t)Q * M * 256 * 4, 256) + 2 * align_up((size_t)Q * 4, 256) +
                        align_up((size_t)Q * std::max(nprobe, 1) * 4, 256) + align_up(stage, 256);
+  idx->ws_reserved = true;
   return ensure_ws(idx, query);
 }
 
