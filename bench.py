@@ -22,7 +22,9 @@ launches: first plane streamed, second-plane lines fetched on demand or streamed
 `roofline_no_pruning` -- the same kernel over N independent uniform code bytes, where nearly every
 128-byte line of second halves has a row that is still open half-way, so the kernel ends up
 fetching (nearly) every byte: moved = algorithmic.
-`roofline_batched` -- the batched launch of the timed steps (k_scan_w4: four queries share each
+`roofline_batched` -- the batched launches of the timed steps: by matrix products (two operations per
+coordinate, query and row, over the whole call, against the dense fp16 rate), or, for batches that do not
+go that way, those of k_scan_w4 (four queries share each
 code byte, so the bound is the LDS look-up rate; `achieved` counts the look-ups the kernel really
 made -- it abandons part of them -- and `peak` is the best rate of conflict-free 8-byte LDS reads
 over several occupancies, measured in the same run; the rate of the scan's inner loop alone at the

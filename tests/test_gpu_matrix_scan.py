@@ -99,21 +99,23 @@ def test_lists_that_overflow(M, topk, rii, oracle_lib):
     check(rii, oracle_lib, index, lut, codes, topk, [0, 1, 33, Q - 1])
 
 
-# the query procedure takes the same way, within scratch that was reserved, and in a captured graph that is replayed
-def test_query_reserved_and_captured(rii, oracle_lib):
+# the query procedure takes the same way, within scratch that was reserved (in pieces where it is short: 700 queries' tables
+# leave room for half of them), and in a captured graph that is replayed
+@pytest.mark.parametrize("Q,topk,reserve", [(270, 20, (300, 200)), (700, 100, (700, 100))])
+def test_query_reserved_and_captured(Q, topk, reserve, rii, oracle_lib):
     rng = np.random.default_rng(5)
-    M, N, Q, topk = 16, 262_999, 270, 20
+    M, N = 16, 262_999
     cb = rng.normal(size=(M, 256, 2)).astype(np.float32)
     codes = rng.integers(0, 256, size=(N, M), dtype=np.uint8)
     index = rii.Index(cb)
     index.add(codes)
-    index.reserve_workspace(300, 200)  # (200 results of 300 queries go by look-ups, fewer by products)
+    index.reserve_workspace(*reserve)
     before = index.info()["device_bytes"]
     q = torch.from_numpy(rng.normal(size=(Q, 2 * M)).astype(np.float32)).cuda()
     want = rii.rii_query(index, q, topk)
     torch.cuda.synchronize()
     assert index.info()["device_bytes"] == before
-    for i in (0, 33, Q - 1):
+    for i in (0, 33, Q // 2 + 40, Q - 1):
         ref = oracle_lib.linear_scan(oracle_lib.lut(cb, t2n(q[i:i + 1]))[0], codes, topk)
         assert np.array_equal(t2n(want[0])[i], ref[0]) and np.array_equal(t2n(want[1])[i], ref[1])
     out = (torch.empty_like(want[0]), torch.empty_like(want[1]))
