@@ -20,6 +20,7 @@ struct rii_index {
   std::vector<float> h_cb;        // host mirror of the codebooks
   // What the batched scan by matrix products reads (see rii_dev_matrix.inc), behind the code books in the same
   // allocation; NULL where that scan does not apply (D > 128, Ds > 32)
+  mutable bool mx_ready = false;  // the tables are made (by the first call that reads them)
   int mx_dsp = 0;                 // coordinates a sub-space has in mx_fit and mx_ch
   uint8_t* mx_book = nullptr;        // [M][256] fp16 code words from the book's mean (entries: mx_entry_bytes)
   float* mx_fit = nullptr;  // [M][mx_dsp][256] -1/2 of the centred code words' pseudo-inverse

@@ -119,9 +119,16 @@ def test_query_reserved_and_captured(Q, topk, reserve, rii, oracle_lib):
         ref = oracle_lib.linear_scan(oracle_lib.lut(cb, t2n(q[i:i + 1]))[0], codes, topk)
         assert np.array_equal(t2n(want[0])[i], ref[0]) and np.array_equal(t2n(want[1])[i], ref[1])
     out = (torch.empty_like(want[0]), torch.empty_like(want[1]))
+    if reserve[0] != Q:  # an index whose first call of this kind is the captured one
+        index = rii.Index(cb)
+        index.add(codes)
+        index.reserve_workspace(*reserve)
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         rii.rii_query(index, q, topk, out=out)
+    first = rii.rii_query(index, q, topk)  # before any replay
+    torch.cuda.synchronize()
+    assert torch.equal(first[0], want[0]) and torch.equal(first[1], want[1])
     for _ in range(3):
         out[0].zero_()
         out[1].zero_()
