@@ -744,12 +744,12 @@ int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int topk, 
     // what is listed, scored as defined: the k best so far
     FewArgs f{};
     f.codes = idx->d_codes_rows; f.plane = idx->plane_rows; f.M = M; f.lut = lut; f.N = idx->N;
-    f.target_ids = a.cand; f.target_cnt = a.cnt; f.target_cap = p.cap; f.target_cnt_stride = kMxCntStride;
+    f.listed = a.cand; f.listed_cnt = a.cnt; f.listed_cap = p.cap; f.listed_cnt_stride = kMxCntStride;
     f.k = topk; f.ids = ids; f.out_stride = out_stride; f.qmode = mode; f.want_mode = 0;
     f.dist = dist ? dist : reinterpret_cast<float*>(w + p.dist);
     FewShape shape = few_shape(M, Q, p.cap, topk, FewRows::targets, false);
     shape.split = 1;
-    rc = launch_few<kFewSubset>(f, shape, Q, nullptr, true, st);
+    rc = launch_few<kFewListed>(f, shape, Q, nullptr, true, st);
     if (rc) return rc;
     k_matrix_next<<<(Q + 3) / 4, 256, 0, st>>>(ids, f.dist, Q, topk, out_stride, p.cap, idx->mx_scale, lo, cq, a.cnt, a.cand, mode);
   }
