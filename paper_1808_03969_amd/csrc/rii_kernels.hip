@@ -336,17 +336,15 @@ bool few_scan(int mode, int M, int Q, int topk, int64_t rows) {
   return mode == kLinear ? few_linear(M, Q, topk, rows) : few_subset(Q, topk, rows);
 }
 
-// qmode, want_mode: only the queries in that mode are done.  leftover: they are what the scan by matrix products has left,
-// few or none, and the kernels for several queries a block may do a group's other queries once more.
 // Scan `nrows_max` rows per query (linear: the whole array) and leave per-block partial keys in
 // the workspace; then select.  Workspace layout: [tau Q u32][partial Q*nchunks*k u64].
 int launch_scan(const rii_index* idx, const uint8_t* codes, int64_t plane, int64_t N, const float* lut, int Q, int mode,
                 const int32_t* target_ids, const int64_t* target_offsets, int64_t max_rows, int topk,
                 int32_t* ids, float* dist, int out_stride, const int* qmode, int want_mode, void* ws_base,
-                hipStream_t st, bool cleared = false, bool tight = false, bool leftover = false) {
+                hipStream_t st, bool cleared = false, bool tight = false) {
   const int M = idx->M;
   if (Q > 65535) return RII_ERR_UNSUPPORTED;
-  const bool timed = !leftover && mode == kLinear && idx->ev_start && idx->ev_stop && codes == idx->d_codes;
+  const bool timed = mode == kLinear && idx->ev_start && idx->ev_stop && codes == idx->d_codes;
   if (few_scan(mode, M, Q, topk, max_rows) && !idx->bench_half_table) {
     FewArgs f{};
     f.codes = codes; f.plane = plane; f.M = M; f.lut = lut; f.N = N; f.target_ids = target_ids; f.target_offsets = target_offsets;
@@ -379,7 +377,7 @@ int launch_scan(const rii_index* idx, const uint8_t* codes, int64_t plane, int64
   a.target_ids = target_ids; a.target_offsets = target_offsets;
   a.chunk_rows = chunk_rows; a.k = topk; a.partial = partial; a.tau_g = tau;
   int64_t bchunks, brows;
-  const bool batched = mode == kLinear && (!qmode || leftover) && plan_batch(M, Q, max_rows, topk, &bchunks, &brows);
+  const bool batched = mode == kLinear && !qmode && plan_batch(M, Q, max_rows, topk, &bchunks, &brows);
   if (!batched) bchunks = 1;
   a.cand_cnt = cand_cnt; a.cand_cap = std::max(nchunks, bchunks) * topk;
   a.nq = Q;
@@ -466,14 +464,13 @@ int launch_scan(const rii_index* idx, const uint8_t* codes, int64_t plane, int64
                      k_scan_w4<32><<<g4, kScanThreads, lds4, st>>>(a4); } break;
         }
       }
-    } else if (mode == kLinear && rot_m(M) && nchunks == 1 && (!qmode || leftover) && Q >= 2 && topk > kWaveK4 && topk <= kWaveK) {
+    } else if (mode == kLinear && rot_m(M) && nchunks == 1 && !qmode && Q >= 2 && topk > kWaveK4 && topk <= kWaveK) {
       // Large batch with topk beyond the four-query kernel's reach: two queries per block
       // (k_scan_w2), every block owning its queries' whole scan, and a single-query block for an
       // odd one left over, addressed as query 0 of argument arrays shifted by Q - 1.
       auto shifted = [&](int o) {
         ScanArgs b = a;
         b.lut = lut + (size_t)o * M * 256;
-        b.qmode = qmode ? qmode + o : nullptr;
         b.partial = partial + (size_t)o * a.cand_cap;
         b.tau_g = tau + o; b.cand_cnt = cand_cnt + o; b.done_cnt = done_cnt + o;
         b.ids = ids + (size_t)o * out_stride;
@@ -545,7 +542,7 @@ int launch_scan(const rii_index* idx, const uint8_t* codes, int64_t plane, int64
     SelectArgs s{};
     s.keys = partial; s.nkeys = a.cand_cap; s.key_cnt = cand_cnt; s.k = topk; s.out_stride = out_stride;
     s.ids = ids; s.dist = dist; s.qmode = qmode; s.want_mode = want_mode;
-    k_select<<<Q, kScanThreads, 0, st>>>(s);
+    k_select<><<<Q, kScanThreads, 0, st>>>(s);
   }
   RII_HIP(hipGetLastError());
   return RII_OK;
@@ -586,10 +583,10 @@ size_t scan_ws_bound(int M, int Q, int64_t max_rows, int topk) {
 }
 
 // ------------------------------------------------------------------ the batched scan by matrix products
-// Which calls: see matrix_applies.  Scratch behind launch_scan's own (which the left-over queries need).
+// Which calls: see matrix_applies.  Scratch behind launch_left's.
 struct MatrixPlan {
   int nf, Qp, cap;
-  size_t qfrag, cq, lo, hi, mode, cnt, dist, cand, minima, part, total;  // byte offsets, size
+  size_t qfrag, cq, lo, hi, mode, cnt, left, dist, cand, minima, part, total;  // byte offsets, size
 };
 constexpr int64_t kMatrixMinRows = (int64_t)1 << 18;
 constexpr double kMatrixGrowth = 5.0;  // rows of a round against those before it
@@ -623,6 +620,7 @@ MatrixPlan matrix_plan(const rii_index* idx, int Q, int topk) {
   p.hi = take((size_t)p.Qp * 4);
   p.mode = take((size_t)p.Qp * 4);
   p.cnt = take((size_t)p.Qp * kMxCntStride * 4);
+  p.left = take(256 + (size_t)Q * 4);
   p.dist = take((size_t)Q * topk * 4);
   p.cand = take((size_t)Q * p.cap * 4);
   // (the fit's partial results are read before the groups' maxima are written)
@@ -631,11 +629,84 @@ MatrixPlan matrix_plan(const rii_index* idx, int Q, int topk) {
   return p;
 }
 
-// What `q` queries of a batch of Q need, the last piece's left-over queries included (launch_scan may want more for fewer).
-size_t matrix_need(const rii_index* idx, int Q, int q, int topk) {
-  const int tail = Q % q ? Q % q : q;
-  const size_t scan = std::max(scan_ws_bytes(kLinear, idx->M, q, idx->N, topk), scan_ws_bytes(kLinear, idx->M, tail, idx->N, topk));
-  return align_up(scan, 256) + matrix_plan(idx, q, topk).total;
+// ---- what it leaves
+// Row chunks of two rounds' groups of four and more (as plan_batch has them for the whole batch), 1 where there are none.
+int64_t left_big(const rii_index* idx, int Q, int topk) {
+  int64_t chunks = 1, rows;
+  const bool many = (Q + 3) / 4 >= 2 * kWantBlocks;
+  return rot_m(idx->M) && topk <= kWaveK4 && many && plan_batch(idx->M, Q, idx->N, topk, &chunks, &rows) ? chunks : 1;
+}
+// Bounds and counters by place, then candidates: of at most kBatchWantBlocks groups of four in chunks, or of a large batch's
+// chunks, or (one query a block) of kWantBlocks blocks or a block a query.
+size_t left_ws_bytes(const rii_index* idx, int Q, int topk) {
+  const size_t lists = std::max<size_t>((size_t)Q * left_big(idx, Q, topk), 4 * kBatchWantBlocks);
+  return kScanArrays * align_up((size_t)Q * 4, 256) + lists * topk * 8;
+}
+// The linear scan for the queries that are entered in `left` (up to Q; their number is known on the device only, and usually
+// 0): by the kernels of launch_scan, spread over the chip as their number asks for.  A launch of the whole batch's shape
+// with the other queries' blocks gone left a query to one block, or dragged in its group's others (whole call, that way / here):
+// one of 512 queries over 10^6 rows, M = 64, top-100 3240 / 507 us (none left: 392);  16 of 256 over 10^7, M = 16 2441 / 1332;
+// 512 of 2048 over 10^6, M = 16 1906 / 1278, all of them 1751 / 1751;  one of 1024, top-300 1168 / 701.
+int launch_left(const rii_index* idx, const float* lut, int Q, int topk, int32_t* ids, float* dist, int out_stride,
+                const LeftOut& left, hipStream_t st) {
+  const int M = idx->M;
+  ScanArgs a{};
+  a.codes = idx->d_codes; a.plane = idx->plane_codes; a.N = idx->N; a.M = M; a.lut = lut; a.k = topk;
+  a.tau_g = left.arrays; a.cand_cnt = left.arrays + left.stride; a.done_cnt = left.arrays + 3 * left.stride;
+  a.partial = reinterpret_cast<uint64_t*>(left.arrays + kScanArrays * left.stride);
+  a.ids = ids; a.dist = dist; a.out_stride = out_stride;
+  a.left_n = left.n; a.left_q = left.q; a.left_big = (int)left_big(idx, Q, topk); a.left_most = 0xFFFFFFFFu;
+  auto blocks = [&](int per) { return (unsigned)left_blocks(per, Q, a.left_big); };
+  const size_t ldsw = table_bytes(M) + (size_t)(kScanThreads / 64 + 1) * kWaveCap * 8 + kBlockVarsBytes;
+  if (rot_m(M) && topk <= kWaveK4) {
+    const size_t lds4 = 65536 + 4 * (size_t)(kScanThreads / 64 + 1) * kWaveCap4 * 8 +
+                        (size_t)(kScanThreads / 64) * kRescoreCap * 8 + kBlockVarsBytes + 4 * kBins4 * 4;
+#define RII_LEFT4(MT) { int rc = set_lds0(k_scan_w4<MT, false, true>, lds4); if (rc) return rc; \
+                        k_scan_w4<MT, false, true><<<blocks(4), kScanThreads, lds4, st>>>(a); } break
+    switch (M) {
+      case 8: RII_LEFT4(8);
+      case 16: RII_LEFT4(16);
+      default: RII_LEFT4(32);
+    }
+#undef RII_LEFT4
+  } else if (topk <= kWaveK || rot_m(M)) {
+    if (rot_m(M) && topk <= kWaveK && Q > kWantBlocks) {  // more than a round of single queries: two a block
+      a.left_most = kWantBlocks;
+      const size_t lds2 = 65536 + 2 * (size_t)(kScanThreads / 64 + 1) * kWaveCap * 8 + kBlockVarsBytes;
+#define RII_LEFT2(MT) { int rc = set_lds0(k_scan_w2<MT, true>, lds2); if (rc) return rc; \
+                        k_scan_w2<MT, true><<<blocks(2), kScanThreads, lds2, st>>>(a); } break
+      switch (M) {
+        case 8: RII_LEFT2(8);
+        case 16: RII_LEFT2(16);
+        default: RII_LEFT2(32);
+      }
+#undef RII_LEFT2
+    }
+    DISPATCH_M(M, { int rc = set_lds0(k_scan_w<MT, kLeft>, ldsw); if (rc) return rc;
+                    k_scan_w<MT, kLeft><<<blocks(1), kScanThreads, ldsw, st>>>(a); });
+  } else {
+    const size_t lds = (size_t)M * 1024 + (size_t)kSelCap * 8;
+    if (M == 64) {
+      int rc = set_lds(k_scan<64, kLeft>, lds); if (rc) return rc;
+      k_scan<64, kLeft><<<blocks(1), kScanThreads, lds, st>>>(a);
+    } else {
+      int rc = set_lds(k_scan<0, kLeft>, lds); if (rc) return rc;
+      k_scan<0, kLeft><<<blocks(1), kScanThreads, lds, st>>>(a);
+    }
+  }
+  if (topk > kWaveK) {
+    SelectArgs s{};
+    s.keys = a.partial; s.key_cnt = a.cand_cnt; s.k = topk; s.out_stride = out_stride; s.ids = ids; s.dist = dist;
+    s.left_n = left.n; s.left_q = left.q; s.left_rows = idx->N;
+    k_select<true><<<Q, kScanThreads, 0, st>>>(s);
+  }
+  RII_HIP(hipGetLastError());
+  return RII_OK;
+}
+
+// What `q` queries of a batch need, what is left of them included.
+size_t matrix_need(const rii_index* idx, int q, int topk) {
+  return align_up(left_ws_bytes(idx, q, topk), 256) + matrix_plan(idx, q, topk).total;
 }
 
 // Queries the scan by matrix products takes at a time, its scratch `lead` bytes into the handle's; 0: it is not taken.
@@ -655,7 +726,7 @@ int matrix_queries(const rii_index* idx, int Q, int topk, size_t lead, size_t wi
   for (int pieces = 1;; ++pieces) {
     const int q = std::min(Q, ((Q + pieces - 1) / pieces + 31) / 32 * 32);
     if (!matrix_applies(idx, q, topk, idx->N)) return 0;
-    const size_t need = lead + matrix_need(idx, Q, q, topk);
+    const size_t need = lead + matrix_need(idx, q, topk);
     if (need > room) continue;
     if (need <= idx->ws_bytes || ensure_ws(idx, std::max(need, without)) == RII_OK) return q;
     return 0;  // (no room on the device; without the products there may be)
@@ -696,8 +767,12 @@ int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int topk, 
   // queries a wave of the fit goes through: enough waves to fill the chip first
   const int per = std::min(8, std::max(1, (int)((int64_t)Q * M / (16 * kWantBlocks))));
   float4* part = reinterpret_cast<float4*>(w + p.part);
+  LeftOut left{};
+  left.n = reinterpret_cast<uint32_t*>(w + p.left); left.q = reinterpret_cast<int32_t*>(w + p.left + 256);
+  left.arrays = static_cast<uint32_t*>(scan_ws); left.stride = (int64_t)(align_up((size_t)Q * 4, 256) / 4);
+  left.counters = idx->ev_start && idx->ev_stop ? idx->d_scan_counters : nullptr;
   const dim3 fgrid((unsigned)((p.Qp + per - 1) / per), (unsigned)(M / 4));
-#define RII_FIT(DSP) k_fit_tables<DSP><<<fgrid, 256, 0, st>>>(lut, idx->mx_fit, idx->mx_ch, idx->mx_b, idx->mx_scale, M, idx->Ds, p.nf, Q, p.Qp, per, qfrag, part)
+#define RII_FIT(DSP) k_fit_tables<DSP><<<fgrid, 256, 0, st>>>(lut, idx->mx_fit, idx->mx_ch, idx->mx_b, idx->mx_scale, M, idx->Ds, p.nf, Q, p.Qp, per, qfrag, part, left.n)
   switch (idx->mx_dsp) {
     case 4: RII_FIT(4); break;
     case 8: RII_FIT(8); break;
@@ -705,7 +780,7 @@ int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int topk, 
     default: RII_FIT(32); break;
   }
 #undef RII_FIT
-  k_fit_sums<<<(p.Qp + 255) / 256, 256, 0, st>>>(part, M, p.nf, Q, p.Qp, cq, lo, hi, mode, a.cnt);
+  k_fit_sums<<<(p.Qp + 255) / 256, 256, 0, st>>>(part, M, p.nf, Q, p.Qp, cq, lo, hi, mode, a.cnt, left);
   auto scan = [&](bool seed, int64_t first, int64_t last) {
     a.first = first;
     const int qtiles = p.Qp / 32;
@@ -727,7 +802,7 @@ int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int topk, 
   int rc = scan(true, 0, kMxSeedTiles);
   if (rc) return rc;
   const int spare = kMxSeedGroups / (8 * topk);  // groups to a result, in eights
-#define RII_SEED(FOLD) k_matrix_seed<FOLD><<<p.Qp / 32, 512, 0, st>>>(a.minima, Q, p.Qp, topk, lo, hi, mode, cq)
+#define RII_SEED(FOLD) k_matrix_seed<FOLD><<<p.Qp / 32, 512, 0, st>>>(a.minima, Q, p.Qp, topk, lo, hi, mode, cq, left)
   if (spare >= 8) RII_SEED(8);
   else if (spare >= 4) RII_SEED(4);
   else if (spare >= 2) RII_SEED(2);
@@ -751,20 +826,16 @@ int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int topk, 
     shape.split = 1;
     rc = launch_few<kFewListed>(f, shape, Q, nullptr, true, st);
     if (rc) return rc;
-    k_matrix_next<<<(Q + 3) / 4, 256, 0, st>>>(ids, f.dist, Q, topk, out_stride, p.cap, idx->mx_scale, lo, cq, a.cnt, a.cand, mode);
+    k_matrix_next<<<(Q + 3) / 4, 256, 0, st>>>(ids, f.dist, Q, topk, out_stride, p.cap, idx->mx_scale, lo, cq, a.cnt, a.cand, mode, left);
   }
-  rc = launch_scan(idx, idx->d_codes, idx->plane_codes, idx->N, lut, Q, kLinear, nullptr, nullptr, idx->N, topk, ids, dist, out_stride,
-                   mode, 1, scan_ws, st, false, false, true);
-  if (rc) return rc;
-  RII_HIP(hipGetLastError());
-  return RII_OK;
+  return launch_left(idx, lut, Q, topk, ids, dist, out_stride, left, st);
 }
 
 // The whole batch, q queries (what matrix_queries said) at a time in the same scratch.
 int launch_matrix_batches(const rii_index* idx, const float* lut, int Q, int q, int topk, int32_t* ids, float* dist, int out_stride,
                           void* ws, hipStream_t st) {
   const bool timed = idx->ev_start && idx->ev_stop;
-  const size_t scan_bytes = matrix_need(idx, Q, q, topk) - matrix_plan(idx, q, topk).total;
+  const size_t scan_bytes = matrix_need(idx, q, topk) - matrix_plan(idx, q, topk).total;
   // The index's tables are made by the first call that reads them, on its own stream (35 us; at the index's creation, with
   // the wait for them, they were 4 to 7 % of building one of 100,000 codes).  A call that is being captured makes them
   // for itself at every replay: nothing has run when the next call is issued.
@@ -938,7 +1009,7 @@ int rii_topk(const float* cand_dist, const int32_t* cand_ids, const int64_t* can
   s.cand_dist = cand_dist; s.cand_ids = cand_ids; s.cand_offsets = cand_offsets;
   s.k = topk; s.out_stride = topk; s.ids = ids; s.dist = dist;
   if (topk <= RII_MAX_TOPK) {
-    k_select<<<Q, kScanThreads, 0, st>>>(s);
+    k_select<><<<Q, kScanThreads, 0, st>>>(s);
   } else {
     if (topk > RII_MAX_SORT || max_segment < 1 || max_segment > RII_MAX_SORT) return RII_ERR_UNSUPPORTED;
     size_t lds = (size_t)RII_MAX_SORT * 8;

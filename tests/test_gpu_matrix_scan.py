@@ -26,6 +26,29 @@ def check(rii, oracle, index, lut, codes, topk, at):
         assert np.array_equal(ids[i], ref[0]) and np.array_equal(dist[i], ref[1]), i
 
 
+def counted(rii, index, call):
+    """The call's results and the scan counters it leaves."""
+    from paper_1808_03969_amd import binding
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    for e in ev:
+        e.record()
+    binding.rii_index_set_scan_events(index, ev[0].cuda_event, ev[1].cuda_event)
+    binding.rii_index_read_scan_counters(index)
+    out = call()
+    torch.cuda.synchronize()
+    counters = binding.rii_index_read_scan_counters(index)
+    binding.rii_index_set_scan_events(index, None, None)
+    return out, counters
+
+
+def by_look_ups(rii, index, lut, topk):
+    """The same queries by the look-up kernels: batches that are too small for the matrix products."""
+    from paper_1808_03969_amd import binding
+    assert binding.rii_scan_linear_plan(index, 32, topk)[0] != 32
+    parts = [rii.rii_adc_scan_linear(index, lut[i:i + 32], topk) for i in range(0, lut.shape[0], 32)]
+    return torch.cat([p[0] for p in parts]), torch.cat([p[1] for p in parts])
+
+
 # every number of matrix steps and every width of the fit, sub-spaces with and without a rotated stored form, two planes,
 # the fewest rows and rows that leave the last tile of 512 nearly empty or full, query tiles short and full, one result
 # to the most; code words far from the origin, of one value, clustered codes
@@ -137,3 +160,26 @@ def test_query_reserved_and_captured(Q, topk, reserve, rii, oracle_lib):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out[0], want[0]) and torch.equal(out[1], want[1])
+
+
+# queries that are left to the look-up kernels: none, one, a part of a group of four, some, more than a round of blocks,
+# half, all; every kernel that takes them (four, two and one a block, in row chunks and whole, with and without k_select)
+@pytest.mark.parametrize("M,Ds,topk,N", [(16, 2, 100, 262_777), (8, 4, 10, 900_001), (32, 3, 100, 1_200_000), (8, 2, 120, 262_777), (32, 3, 128, 300_000),
+                                         (32, 2, 300, 270_001), (64, 2, 100, 262_777), (64, 1, 200, 400_000), (12, 5, 100, 262_777),
+                                         (12, 3, 500, 900_001)])
+def test_left_over_queries(M, Ds, topk, N, rii):
+    rng = np.random.default_rng(M + topk)
+    Q = 600
+    cb = rng.normal(size=(M, 256, Ds)).astype(np.float32)
+    index = rii.Index(cb)
+    index.add(rng.integers(0, 256, size=(N, M), dtype=np.uint8))
+    lut = rii.rii_build_lut(index, torch.from_numpy(rng.normal(size=(Q, M * Ds)).astype(np.float32)).cuda())
+    foreign = torch.from_numpy(rng.random((Q, M, 256)).astype(np.float32)).cuda() * lut.mean() * 2
+    for left in (0, 1, 3, 70, 290, 600):
+        mixed = lut.clone()
+        at = torch.from_numpy(np.sort(rng.permutation(Q)[:left])).cuda()
+        mixed[at] = foreign[at]
+        (ids, dist), counters = counted(rii, index, lambda: rii.rii_adc_scan_linear(index, mixed, topk))
+        assert counters[5] == left
+        want = by_look_ups(rii, index, mixed, topk)
+        assert torch.equal(ids, want[0]) and torch.equal(dist, want[1]), left
