@@ -180,6 +180,8 @@ def test_left_over_queries(M, Ds, topk, N, rii):
         at = torch.from_numpy(np.sort(rng.permutation(Q)[:left])).cuda()
         mixed[at] = foreign[at]
         (ids, dist), counters = counted(rii, index, lambda: rii.rii_adc_scan_linear(index, mixed, topk))
-        assert counters[5] == left
+        # (with more than 3/8 or 3/4 of the tables foreign, the others are left with them and nothing is multiplied)
+        given_up = left > Q * (3 if topk <= 100 and M in (8, 16, 32) else 6) // 8
+        assert counters[5] == (Q if given_up else left) and (counters[6] == 0) == given_up
         want = by_look_ups(rii, index, mixed, topk)
         assert torch.equal(ids, want[0]) and torch.equal(dist, want[1]), left
