@@ -636,18 +636,17 @@ int64_t left_big(const rii_index* idx, int Q, int topk) {
   const bool many = (Q + 3) / 4 >= 2 * kWantBlocks;
   return rot_m(idx->M) && topk <= kWaveK4 && many && plan_batch(idx->M, Q, idx->N, topk, &chunks, &rows) ? chunks : 1;
 }
-// Bounds and counters by place, then candidates: of at most kBatchWantBlocks groups of four in chunks, or of a large batch's
-// chunks, or (one query a block) of kWantBlocks blocks or a block a query.
+// Bounds and counters by place, then candidates.
 size_t left_ws_bytes(const rii_index* idx, int Q, int topk) {
-  const size_t lists = std::max<size_t>((size_t)Q * left_big(idx, Q, topk), 4 * kBatchWantBlocks);
-  return kScanArrays * align_up((size_t)Q * 4, 256) + lists * topk * 8;
+  return kScanArrays * align_up((size_t)Q * 4, 256) + (size_t)left_lists(Q, left_big(idx, Q, topk)) * topk * 8;
 }
 // The linear scan for the queries that are entered in `left` (up to Q; their number is known on the device only, and usually
 // 0): by the kernels of launch_scan, spread over the chip as their number asks for.  A launch of the whole batch's shape
 // with the other queries' blocks gone left a query to one block, or dragged in its group's others (whole call, that way / here):
 // one of 512 queries over 10^6 rows, M = 64, top-100 3240 / 507 us (none left: 392);  16 of 256 over 10^7, M = 16 2441 / 1332;
 // 512 of 2048 over 10^6, M = 16 1906 / 1278, all of them 1751 / 1751;  one of 1024, top-300 1168 / 701.
-int launch_left(const rii_index* idx, const float* lut, int Q, int topk, int32_t* ids, float* dist, int out_stride,
+// `big`: left_big of the batch that the scratch was sized for (a smaller one, its last piece, may ask for more chunks).
+int launch_left(const rii_index* idx, const float* lut, int Q, int64_t big, int topk, int32_t* ids, float* dist, int out_stride,
                 const LeftOut& left, hipStream_t st) {
   const int M = idx->M;
   ScanArgs a{};
@@ -655,7 +654,7 @@ int launch_left(const rii_index* idx, const float* lut, int Q, int topk, int32_t
   a.tau_g = left.arrays; a.cand_cnt = left.arrays + left.stride; a.done_cnt = left.arrays + 3 * left.stride;
   a.partial = reinterpret_cast<uint64_t*>(left.arrays + kScanArrays * left.stride);
   a.ids = ids; a.dist = dist; a.out_stride = out_stride;
-  a.left_n = left.n; a.left_q = left.q; a.left_big = (int)left_big(idx, Q, topk); a.left_most = 0xFFFFFFFFu;
+  a.left_n = left.n; a.left_q = left.q; a.left_big = (int)big; a.left_most = 0xFFFFFFFFu;
   auto blocks = [&](int per) { return (unsigned)left_blocks(per, Q, a.left_big); };
   const size_t ldsw = table_bytes(M) + (size_t)(kScanThreads / 64 + 1) * kWaveCap * 8 + kBlockVarsBytes;
   if (rot_m(M) && topk <= kWaveK4) {
@@ -741,7 +740,7 @@ int launch_matrix_round(const MatrixArgs& a, dim3 grid, hipStream_t st) {
   return RII_OK;
 }
 
-int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int topk, int32_t* ids, float* dist, int out_stride,
+int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int64_t big, int topk, int32_t* ids, float* dist, int out_stride,
                        void* scan_ws, size_t scan_bytes, hipStream_t st) {
   const int M = idx->M;
   const MatrixPlan p = matrix_plan(idx, Q, topk);
@@ -833,7 +832,7 @@ int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int topk, 
     if (rc) return rc;
     k_matrix_next<<<(Q + 3) / 4, 256, 0, st>>>(ids, f.dist, Q, topk, out_stride, p.cap, idx->mx_scale, lo, cq, a.cnt, a.cand, mode, left);
   }
-  return launch_left(idx, lut, Q, topk, ids, dist, out_stride, left, st);
+  return launch_left(idx, lut, Q, big, topk, ids, dist, out_stride, left, st);
 }
 
 // The whole batch, q queries (what matrix_queries said) at a time in the same scratch.
@@ -855,7 +854,7 @@ int launch_matrix_batches(const rii_index* idx, const float* lut, int Q, int q, 
   }
   if (timed) RII_HIP(hipEventRecord(static_cast<hipEvent_t>(idx->ev_start), st));
   for (int o = 0; o < Q; o += q) {
-    const int rc = launch_matrix_scan(idx, lut + (size_t)o * idx->M * 256, std::min(q, Q - o), topk, ids + (size_t)o * out_stride,
+    const int rc = launch_matrix_scan(idx, lut + (size_t)o * idx->M * 256, std::min(q, Q - o), left_big(idx, q, topk), topk, ids + (size_t)o * out_stride,
                                       dist ? dist + (size_t)o * out_stride : nullptr, out_stride, ws, scan_bytes, st);
     if (rc) return rc;
   }
@@ -1501,6 +1500,11 @@ size_t rii_internal_assign_matrix_bytes(const rii_index* idx, int64_t n, int K) 
 
 // The margin the products are used with, as a share of |x|^2 + max |c|^2 (see assign_margin).
 float rii_internal_assign_margin(int M, int Ds) { return assign_margin((M * Ds + 31) / 32 * 32, M, Ds); }
+
+// What the launches for left-over queries ask for (see left_chunks).
+int64_t rii_internal_left_chunks(int per, int64_t groups, int64_t rows, int64_t big) { return left_chunks(per, groups, rows, big); }
+int64_t rii_internal_left_blocks(int per, int64_t Q, int64_t big) { return left_blocks(per, Q, big); }
+int64_t rii_internal_left_lists(int64_t Q, int64_t big) { return left_lists(Q, big); }
 
 int rii_internal_assign_matrix(const rii_index* idx, const uint8_t* codes, int64_t n, int64_t rot_base, int64_t plane,
                                const uint8_t* coarse, int K, int32_t* assign_out, void* scratch, const uint32_t** open_out,
