@@ -25,7 +25,10 @@
  *     scratch memory that the online calls reuse, so calls on one handle must be issued on
  *     one stream at a time.  A call that needs more scratch than the handle holds frees and
  *     re-allocates it first, which waits for the device; rii_index_reserve_workspace sizes it
- *     ahead of time.
+ *     ahead of time.  Large batches over the whole database (from 64 to 512 queries on, 2^18 codes and more) are faster
+ *     with up to 1 GB beside it, which the first such call asks the device for: not in a handle that was reserved, not
+ *     while its stream is being captured, nor once a captured graph holds it, and a refusal is no error (the call then
+ *     makes do with the scratch there is).
  *   - Results are ordered by (distance, identifier) ascending; distances are squared
  *     (Eq. (2)), fp32, accumulated over sub-spaces in ascending order.  When fewer than R
  *     candidates exist the tail is filled with identifier -1 and distance +infinity.

@@ -55,6 +55,12 @@ struct rii_index {
   mutable void* ws = nullptr;
   mutable size_t ws_bytes = 0;
   bool ws_reserved = false;       // sized by rii_index_reserve_workspace: calls within it must not grow it
+  // scratch of the batched scan by matrix products, where `ws` has no room for it (see matrix_scratch)
+  mutable void* mx_ws = nullptr;
+  mutable size_t mx_ws_bytes = 0;
+  mutable bool mx_held = false;   // a captured graph holds it: it stays
+  mutable int mx_wait = 0;        // calls that go without before the device is asked again
+  size_t mx_most = SIZE_MAX;      // more than that the device has no room for
 
   bool bench_half_table = false;  // set around one launch by rii_bench_scan_linear_half only
   // optional measurement aid: events recorded right before / after the linear-scan kernel

@@ -708,28 +708,56 @@ size_t matrix_need(const rii_index* idx, int q, int topk) {
   return align_up(left_ws_bytes(idx, q, topk), 256) + matrix_plan(idx, q, topk).total;
 }
 
-// Queries the scan by matrix products takes at a time, its scratch `lead` bytes into the handle's; 0: it is not taken.
-// Scratch that was reserved, or is there when a call is captured, is not grown as long as it holds the `without` bytes
-// that the look-up kernels need: the batch is then cut into pieces that fit, if they are worth it.  Otherwise pieces of 1 GB.
-constexpr size_t kMatrixScratch = (size_t)1 << 30;
-int matrix_queries(const rii_index* idx, int Q, int topk, size_t lead, size_t without, hipStream_t st) {
-  if (!matrix_applies(idx, Q, topk, idx->N)) return 0;
-  bool fixed = idx->ws_reserved;
-  if (!fixed) {
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    fixed = hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
-    if (fixed) (void)hipGetLastError();
-  }
-  fixed = fixed && idx->ws_bytes >= without;
-  const size_t room = fixed ? idx->ws_bytes : std::max(idx->ws_bytes, lead + kMatrixScratch);
+// Where a batch's products have their scratch, and how many queries fit it at a time; q = 0: the batch goes by look-ups.
+struct MatrixScratch {
+  int q = 0;
+  void* at = nullptr;
+};
+// Queries at a time in `room` bytes: pieces of equal size, as long as they are worth it; 0: none.
+int matrix_fit(const rii_index* idx, int Q, int topk, size_t room) {
   for (int pieces = 1;; ++pieces) {
     const int q = std::min(Q, ((Q + pieces - 1) / pieces + 31) / 32 * 32);
     if (!matrix_applies(idx, q, topk, idx->N)) return 0;
-    const size_t need = lead + matrix_need(idx, q, topk);
-    if (need > room) continue;
-    if (need <= idx->ws_bytes || ensure_ws(idx, std::max(need, without)) == RII_OK) return q;
-    return 0;  // (no room on the device; without the products there may be)
+    if (matrix_need(idx, q, topk) <= room) return q;
   }
+}
+// The handle holds the `lead` bytes in front and what the look-up kernels need (`reserved`: and held them before the call, by
+// rii_index_reserve_workspace); the products' scratch is an allocation of its own of 1 GB at most, so that asking for it, or
+// asking in vain, leaves alone what served the look-ups, and what a captured graph of theirs reads.  It is not asked for in a
+// reserved handle or while a graph is captured, and not moved once a graph holds it: pieces that fit what is there, or
+// look-ups.  A device without room is asked for half as long as that is enough, and then for nothing in the next 64 calls.
+constexpr size_t kMatrixScratch = (size_t)1 << 30;
+constexpr int kMatrixPatience = 64;
+MatrixScratch matrix_scratch(const rii_index* idx, int Q, int topk, size_t lead, bool reserved, hipStream_t st) {
+  MatrixScratch s;
+  if (!matrix_applies(idx, Q, topk, idx->N)) return s;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const bool capturing = hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
+  if (capturing) (void)hipGetLastError();
+  const size_t behind = idx->ws_bytes - lead;
+  if (!reserved && !capturing && !idx->mx_held && idx->mx_wait == 0) {
+    for (size_t room = kMatrixScratch;; room /= 2) {
+      const int q = matrix_fit(idx, Q, topk, room);
+      const size_t need = q ? matrix_need(idx, q, topk) : 0;
+      if (need <= std::max(behind, idx->mx_ws_bytes)) break;
+      void* bigger = nullptr;
+      if (need <= idx->mx_most && hipMalloc(&bigger, need) == hipSuccess) {
+        if (idx->mx_ws) (void)hipFree(idx->mx_ws);  // (waits for the device)
+        idx->mx_ws = bigger;
+        idx->mx_ws_bytes = need;
+        break;
+      }
+      (void)hipGetLastError();
+      idx->mx_wait = kMatrixPatience;
+    }
+  } else if (idx->mx_wait > 0) {
+    --idx->mx_wait;
+  }
+  const bool own = idx->mx_ws_bytes > behind;
+  s.q = matrix_fit(idx, Q, topk, own ? idx->mx_ws_bytes : behind);
+  s.at = own ? idx->mx_ws : static_cast<uint8_t*>(idx->ws) + lead;
+  if (s.q && own && capturing) idx->mx_held = true;
+  return s;
 }
 
 template <int NF, bool SEED>
@@ -835,9 +863,10 @@ int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int64_t bi
   return launch_left(idx, lut, Q, big, topk, ids, dist, out_stride, left, st);
 }
 
-// The whole batch, q queries (what matrix_queries said) at a time in the same scratch.
-int launch_matrix_batches(const rii_index* idx, const float* lut, int Q, int q, int topk, int32_t* ids, float* dist, int out_stride,
-                          void* ws, hipStream_t st) {
+// The whole batch, as many queries at a time as the scratch is for.
+int launch_matrix_batches(const rii_index* idx, const float* lut, int Q, const MatrixScratch& scratch, int topk, int32_t* ids, float* dist,
+                          int out_stride, hipStream_t st) {
+  const int q = scratch.q;
   const bool timed = idx->ev_start && idx->ev_stop;
   const size_t scan_bytes = matrix_need(idx, q, topk) - matrix_plan(idx, q, topk).total;
   // The index's tables are made by the first call that reads them, on its own stream (35 us; at the index's creation, with
@@ -855,7 +884,7 @@ int launch_matrix_batches(const rii_index* idx, const float* lut, int Q, int q, 
   if (timed) RII_HIP(hipEventRecord(static_cast<hipEvent_t>(idx->ev_start), st));
   for (int o = 0; o < Q; o += q) {
     const int rc = launch_matrix_scan(idx, lut + (size_t)o * idx->M * 256, std::min(q, Q - o), left_big(idx, q, topk), topk, ids + (size_t)o * out_stride,
-                                      dist ? dist + (size_t)o * out_stride : nullptr, out_stride, ws, scan_bytes, st);
+                                      dist ? dist + (size_t)o * out_stride : nullptr, out_stride, scratch.at, scan_bytes, st);
     if (rc) return rc;
   }
   if (timed) RII_HIP(hipEventRecord(static_cast<hipEvent_t>(idx->ev_stop), st));
@@ -964,10 +993,11 @@ int rii_adc_scan_linear(const rii_index_t* idx, const float* lut, int Q, int top
   if (topk > RII_MAX_TOPK || !m_supported(idx->M) || Q > 65535) return RII_ERR_UNSUPPORTED;
   if (idx->N < 1) return RII_ERR_INVALID_ARG;
   const size_t need = scan_ws_bytes(kLinear, idx->M, Q, idx->N, topk);
-  if (const int some = matrix_queries(idx, Q, topk, 0, need, static_cast<hipStream_t>(stream)))
-    return launch_matrix_batches(idx, lut, Q, some, topk, ids, dist, topk, idx->ws, static_cast<hipStream_t>(stream));
+  const bool reserved = idx->ws_reserved && idx->ws_bytes >= need;
   int rc = ensure_ws(idx, need);
   if (rc) return rc;
+  const MatrixScratch products = matrix_scratch(idx, Q, topk, 0, reserved, static_cast<hipStream_t>(stream));
+  if (products.q) return launch_matrix_batches(idx, lut, Q, products, topk, ids, dist, topk, static_cast<hipStream_t>(stream));
   return launch_scan(idx, idx->d_codes, idx->plane_codes, idx->N, lut, Q, kLinear, nullptr, nullptr, idx->N, topk, ids, dist, topk,
                      nullptr, 0, idx->ws, static_cast<hipStream_t>(stream));
 }
@@ -1194,7 +1224,7 @@ struct QueryPlan {
   // the per-query modes fall away, which also lets a batch into the batched scan.
   bool uniform = false;
   bool tight = false;  // small scans get the least scratch (see few_shape)
-  int matrix_q = 0;    // queries at a time of the linear scan by matrix products; 0: it goes by look-ups
+  MatrixScratch products;  // of the linear scan by matrix products, where it goes that way
 };
 
 // `limit` > 0: a plan beyond that many bytes gives up the small scans' room, then the batched scan.
@@ -1267,8 +1297,8 @@ static int run_query(const rii_index* idx, const QueryPlan& p, const float* q, i
   if (target_ids) {
     rc = launch_scan(idx, idx->d_codes_rows, idx->plane_rows, idx->N, lut, Q, kSubset, target_ids, target_offsets, p.lin_rows, topk,
                      ids, dist, topk, qmode, 0, stage_ws, st, false, p.tight);
-  } else if (all_linear && p.matrix_q) {
-    rc = launch_matrix_batches(idx, lut, Q, p.matrix_q, topk, ids, dist, topk, stage_ws, st);
+  } else if (all_linear && p.products.q) {
+    rc = launch_matrix_batches(idx, lut, Q, p.products, topk, ids, dist, topk, st);
   } else if (all_linear) {
     rc = launch_scan(idx, idx->d_codes, idx->plane_codes, idx->N, lut, Q, kLinear, nullptr, nullptr, idx->N, topk, ids, dist, topk,
                      qmode, 0, stage_ws, st, p.uniform, p.tight);
@@ -1298,10 +1328,11 @@ int rii_query(const rii_index_t* idx, const float* q, int Q, int topk, const int
   QueryPlan p;
   rc = plan_query(idx, Q, topk, target_ids != nullptr, max_targets, L, &p);
   if (rc) return rc;
-  if (!target_ids && (idx->K == 0 || idx->N < idx->theta))
-    p.matrix_q = matrix_queries(idx, Q, topk, p.lut_b + 2 * p.plan_b + p.probe_b, p.total, static_cast<hipStream_t>(stream));
+  const bool reserved = idx->ws_reserved && idx->ws_bytes >= p.total;
   rc = ensure_ws(idx, p.total);
   if (rc) return rc;
+  if (!target_ids && (idx->K == 0 || idx->N < idx->theta))
+    p.products = matrix_scratch(idx, Q, topk, p.lut_b + 2 * p.plan_b + p.probe_b, reserved, static_cast<hipStream_t>(stream));
   return run_query(idx, p, q, Q, topk, target_ids, target_offsets, L, ids, dist, idx->ws, static_cast<hipStream_t>(stream));
 }
 
@@ -1500,6 +1531,12 @@ size_t rii_internal_assign_matrix_bytes(const rii_index* idx, int64_t n, int K) 
 
 // The margin the products are used with, as a share of |x|^2 + max |c|^2 (see assign_margin).
 float rii_internal_assign_margin(int M, int Ds) { return assign_margin((M * Ds + 31) / 32 * 32, M, Ds); }
+
+// What the device is taken to have room for at the most, for the products' scratch (tests of a full device).
+void rii_internal_matrix_room(rii_index* idx, size_t most) {
+  idx->mx_most = most;
+  idx->mx_wait = 0;
+}
 
 // What the launches for left-over queries ask for (see left_chunks).
 int64_t rii_internal_left_chunks(int per, int64_t groups, int64_t rows, int64_t big) { return left_chunks(per, groups, rows, big); }

@@ -1,5 +1,7 @@
 """The batched linear scan by matrix products against the CPU oracle.  The products only decide which rows are scored;
 what is returned comes from the defined sums, so identifiers and distances must be the oracle's bit for bit."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -185,3 +187,82 @@ def test_left_over_queries(M, Ds, topk, N, rii):
         assert counters[5] == (Q if given_up else left) and (counters[6] == 0) == given_up
         want = by_look_ups(rii, index, mixed, topk)
         assert torch.equal(ids, want[0]) and torch.equal(dist, want[1]), left
+
+
+def device_room(index, most):
+    """The products' scratch: the device is taken to have room for `most` bytes."""
+    from paper_1808_03969_amd import binding
+    f = binding.load_library().rii_internal_matrix_room
+    f.restype, f.argtypes = None, [ctypes.c_void_p, ctypes.c_size_t]
+    f(index.handle, most)
+
+
+def scratch_case(rii, Q, topk, N=300_000, M=16, Ds=2, seed=3):
+    rng = np.random.default_rng(seed)
+    index = rii.Index(rng.normal(size=(M, 256, Ds)).astype(np.float32))
+    index.add(rng.integers(0, 256, size=(N, M), dtype=np.uint8))
+    lut = rii.rii_build_lut(index, torch.from_numpy(rng.normal(size=(Q, M * Ds)).astype(np.float32)).cuda())
+    return index, lut, by_look_ups(rii, index, lut, topk)
+
+
+# a device without room for the products' scratch (pieces within what the look-ups have), with room for a part of it, with room
+# for all: larger pieces each time, over all rows; what the look-ups have is kept, and further calls ask for nothing
+def test_device_without_room(rii):
+    Q, topk = 1100, 100
+    index, lut, want = scratch_case(rii, Q, topk)
+
+    def scan():
+        (ids, dist), counters = counted(rii, index, lambda: rii.rii_adc_scan_linear(index, lut, topk))
+        assert torch.equal(ids, want[0]) and torch.equal(dist, want[1])
+        return index.info()["device_bytes"], counters[6]
+
+    start, before = None, 1 << 62
+    for most in (0, 24 << 20, 1 << 62):
+        device_room(index, most)
+        held, blocks = scan()
+        start = held if start is None else start
+        assert held - start <= min(most, 1 << 30) and (most == 0 or held > start)
+        assert 0 < blocks < before
+        assert scan() == (held, blocks)
+        before = blocks
+
+
+# a graph of a call by look-ups reads the handle's scratch: the next call with the same arguments, which gets the products'
+# scratch, leaves that alone.  A graph of a call by products holds theirs: a larger call does not move it.
+def test_graphs_keep_their_scratch(rii):
+    Q, topk = 300, 50
+    index, lut, want = scratch_case(rii, 1500, topk)
+    part, first = lut[:Q].contiguous(), (want[0][:Q], want[1][:Q])
+    device_room(index, 0)
+    assert counted(rii, index, lambda: rii.rii_adc_scan_linear(index, part, topk))[1][6] == 0
+    held = index.info()["device_bytes"]
+
+    def capture():
+        out = (torch.empty_like(first[0]), torch.empty_like(first[1]))
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            rii.rii_adc_scan_linear(index, part, topk, out=out)
+        return graph, out
+
+    def replay(graph, out):
+        for _ in range(3):
+            out[0].zero_()
+            out[1].zero_()
+            got, counters = counted(rii, index, lambda: rii.rii_adc_scan_linear(index, part, topk))
+            assert torch.equal(got[0], first[0]) and torch.equal(got[1], first[1]) and counters[6] > 0
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out[0], first[0]) and torch.equal(out[1], first[1])
+
+    graphs = [capture()]
+    device_room(index, 1 << 62)
+    assert index.info()["device_bytes"] == held
+    replay(*graphs[0])
+    held = index.info()["device_bytes"]
+    graphs.append(capture())
+    got = rii.rii_adc_scan_linear(index, lut, topk)
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    small = 8 * 1500 * (topk + 64 * 128)  # (the look-ups' scratch grew, as it always did, and with it the first graph's went)
+    assert index.info()["device_bytes"] <= held + 2 * small
+    replay(*graphs[1])
