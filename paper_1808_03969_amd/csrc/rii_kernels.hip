@@ -603,15 +603,24 @@ bool matrix_applies(const rii_index* idx, int Q, int topk, int64_t rows) {
   if (topk > kWaveK && Q < 512 && rows < 2 * kMatrixMinRows) return false;
   return Q >= (!rot_m(idx->M) ? 64 : topk >= kFewManyResults && rows <= 32 * kMatrixMinRows ? 128 : 256);
 }
-MatrixPlan matrix_plan(const rii_index* idx, int Q, int topk) {
+// Places of a query's list.  A round is expected to list five to ten times topk rows; where clusters have collapsed onto few
+// codes, all rows that share the bound's distance with them, which is what the places above the least are for: as many
+// as 512 MB of lists allow, an eighth of the rows at most.  Microseconds by look-ups / with lists of
+// the least and N / 1024 places / here (M = 16, top-100):  250 clusters of 1.6 x 10^7 rows, 2048 queries 26,700 / 35,200 /
+// 14,100, 256 queries 4240 / 5840 / 3080;  1000 clusters of 10^8, 1024 queries 53,900 / 73,300 / 30,500;  100 clusters of
+// 10^6, 256 queries 750 / 930 / 570.
+constexpr size_t kMatrixLists = (size_t)512 << 20;
+int matrix_least(const rii_index* idx, int topk) { return 16 * topk + 4096 + (int)std::min<int64_t>(idx->N / 1024, 32768); }
+int matrix_most(const rii_index* idx, int Q, int topk) {
+  const int64_t least = matrix_least(idx, topk);
+  return (int)std::max(least, std::min<int64_t>(least + idx->N / 8, kMatrixLists / 4 / Q));
+}
+MatrixPlan matrix_plan(const rii_index* idx, int Q, int topk, int cap) {
   const int D = idx->D, M = idx->M;
   MatrixPlan p;
   p.nf = (D + 31) / 32 * 2;
   p.Qp = (Q + 31) / 32 * 32;
-  // A round is expected to list five to ten times topk rows; where clusters have collapsed onto few codes, all
-  // rows that share the bound's distance with them (1000 clusters, 1.6 x 10^7 rows: 12,000; 2048 queries 13.7 ms with the
-  // lists of two queries in three too short).
-  p.cap = 16 * topk + 4096 + (int)std::min<int64_t>(idx->N / 1024, 32768);
+  p.cap = cap;
   size_t at = 0;
   auto take = [&](size_t bytes) { const size_t o = at; at += align_up(bytes, 256); return o; };
   p.qfrag = take((size_t)p.Qp * p.nf * 32);
@@ -704,21 +713,28 @@ int launch_left(const rii_index* idx, const float* lut, int Q, int64_t big, int 
 }
 
 // What `q` queries of a batch need, what is left of them included.
-size_t matrix_need(const rii_index* idx, int q, int topk) {
-  return align_up(left_ws_bytes(idx, q, topk), 256) + matrix_plan(idx, q, topk).total;
+size_t matrix_need(const rii_index* idx, int q, int topk, int cap) {
+  return align_up(left_ws_bytes(idx, q, topk), 256) + matrix_plan(idx, q, topk, cap).total;
 }
 
 // Where a batch's products have their scratch, and how many queries fit it at a time; q = 0: the batch goes by look-ups.
 struct MatrixScratch {
-  int q = 0;
+  int q = 0;    // queries at a time
+  int cap = 0;  // places of a list
   void* at = nullptr;
 };
-// Queries at a time in `room` bytes: pieces of equal size, as long as they are worth it; 0: none.
-int matrix_fit(const rii_index* idx, int Q, int topk, size_t room) {
+// Queries at a time in `room` bytes, pieces of equal size as long as they are worth it, and the places that there is room for.
+MatrixScratch matrix_fit(const rii_index* idx, int Q, int topk, size_t room) {
+  MatrixScratch s;
+  const int least = matrix_least(idx, topk);
   for (int pieces = 1;; ++pieces) {
     const int q = std::min(Q, ((Q + pieces - 1) / pieces + 31) / 32 * 32);
-    if (!matrix_applies(idx, q, topk, idx->N)) return 0;
-    if (matrix_need(idx, q, topk) <= room) return q;
+    if (!matrix_applies(idx, q, topk, idx->N)) return s;
+    const size_t need = matrix_need(idx, q, topk, least);
+    if (need > room) continue;
+    s.q = q;
+    s.cap = (int)std::min<size_t>(matrix_most(idx, q, topk), least + (room - need) / 256 * 256 / 4 / q);  // (areas are multiples of 256)
+    return s;
   }
 }
 // The handle holds the `lead` bytes in front and what the look-up kernels need (`reserved`: and held them before the call, by
@@ -737,8 +753,8 @@ MatrixScratch matrix_scratch(const rii_index* idx, int Q, int topk, size_t lead,
   const size_t behind = idx->ws_bytes - lead;
   if (!reserved && !capturing && !idx->mx_held && idx->mx_wait == 0) {
     for (size_t room = kMatrixScratch;; room /= 2) {
-      const int q = matrix_fit(idx, Q, topk, room);
-      const size_t need = q ? matrix_need(idx, q, topk) : 0;
+      const MatrixScratch fit = matrix_fit(idx, Q, topk, room);
+      const size_t need = fit.q ? matrix_need(idx, fit.q, topk, fit.cap) : 0;
       if (need <= std::max(behind, idx->mx_ws_bytes)) break;
       void* bigger = nullptr;
       if (need <= idx->mx_most && hipMalloc(&bigger, need) == hipSuccess) {
@@ -754,7 +770,7 @@ MatrixScratch matrix_scratch(const rii_index* idx, int Q, int topk, size_t lead,
     --idx->mx_wait;
   }
   const bool own = idx->mx_ws_bytes > behind;
-  s.q = matrix_fit(idx, Q, topk, own ? idx->mx_ws_bytes : behind);
+  s = matrix_fit(idx, Q, topk, own ? idx->mx_ws_bytes : behind);
   s.at = own ? idx->mx_ws : static_cast<uint8_t*>(idx->ws) + lead;
   if (s.q && own && capturing) idx->mx_held = true;
   return s;
@@ -768,10 +784,10 @@ int launch_matrix_round(const MatrixArgs& a, dim3 grid, hipStream_t st) {
   return RII_OK;
 }
 
-int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int64_t big, int topk, int32_t* ids, float* dist, int out_stride,
+int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int cap, int64_t big, int topk, int32_t* ids, float* dist, int out_stride,
                        void* scan_ws, size_t scan_bytes, hipStream_t st) {
   const int M = idx->M;
-  const MatrixPlan p = matrix_plan(idx, Q, topk);
+  const MatrixPlan p = matrix_plan(idx, Q, topk, cap);
   uint8_t* w = static_cast<uint8_t*>(scan_ws) + align_up(scan_bytes, 256);
   float* cq = reinterpret_cast<float*>(w + p.cq);
   float* lo = reinterpret_cast<float*>(w + p.lo);
@@ -868,7 +884,7 @@ int launch_matrix_batches(const rii_index* idx, const float* lut, int Q, const M
                           int out_stride, hipStream_t st) {
   const int q = scratch.q;
   const bool timed = idx->ev_start && idx->ev_stop;
-  const size_t scan_bytes = matrix_need(idx, q, topk) - matrix_plan(idx, q, topk).total;
+  const size_t scan_bytes = matrix_need(idx, q, topk, scratch.cap) - matrix_plan(idx, q, topk, scratch.cap).total;
   // The index's tables are made by the first call that reads them, on its own stream (35 us; at the index's creation, with
   // the wait for them, they were 4 to 7 % of building one of 100,000 codes).  A call that is being captured makes them
   // for itself at every replay: nothing has run when the next call is issued.
@@ -883,7 +899,7 @@ int launch_matrix_batches(const rii_index* idx, const float* lut, int Q, const M
   }
   if (timed) RII_HIP(hipEventRecord(static_cast<hipEvent_t>(idx->ev_start), st));
   for (int o = 0; o < Q; o += q) {
-    const int rc = launch_matrix_scan(idx, lut + (size_t)o * idx->M * 256, std::min(q, Q - o), left_big(idx, q, topk), topk, ids + (size_t)o * out_stride,
+    const int rc = launch_matrix_scan(idx, lut + (size_t)o * idx->M * 256, std::min(q, Q - o), scratch.cap, left_big(idx, q, topk), topk, ids + (size_t)o * out_stride,
                                       dist ? dist + (size_t)o * out_stride : nullptr, out_stride, scratch.at, scan_bytes, st);
     if (rc) return rc;
   }

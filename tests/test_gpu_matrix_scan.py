@@ -266,3 +266,26 @@ def test_graphs_keep_their_scratch(rii):
     small = 8 * 1500 * (topk + 64 * 128)  # (the look-ups' scratch grew, as it always did, and with it the first graph's went)
     assert index.info()["device_bytes"] <= held + 2 * small
     replay(*graphs[1])
+
+
+# Rows that collapsed onto few codes: as many as an eighth of the rows share the distance of the bound, and the lists hold them;
+# a quarter of them do, and the lists of the queries there run over in a round that is not the first.
+@pytest.mark.parametrize("share,left", [(0.02, 0), (0.25, 60)])
+def test_collapsed_clusters(share, left, rii):
+    M, N, Q, topk, copies = 16, 1_400_003, 260, 10, 2
+    rng = np.random.default_rng(8)
+    cb = rng.normal(size=(M, 256, 2)).astype(np.float32)
+    codes = rng.integers(0, 256, size=(N, M), dtype=np.uint8)
+    place = rng.random(N)
+    for c in range(copies):
+        codes[(place >= c * share) & (place < (c + 1) * share)] = codes[c]
+    q = rng.normal(size=(Q, 2 * M)).astype(np.float32)
+    for i in range(60):  # queries at the two rows
+        q[4 * i] = np.concatenate([cb[m][codes[i % copies][m]] for m in range(M)]) + 0.01 * q[4 * i]
+    index = rii.Index(cb)
+    index.add(codes)
+    lut = rii.rii_build_lut(index, torch.from_numpy(q).cuda())
+    (ids, dist), counters = counted(rii, index, lambda: rii.rii_adc_scan_linear(index, lut, topk))
+    assert counters[5] == left and counters[6] > 0
+    want = by_look_ups(rii, index, lut, topk)
+    assert torch.equal(ids, want[0]) and torch.equal(dist, want[1])
