@@ -590,18 +590,39 @@ struct MatrixPlan {
 };
 constexpr int64_t kMatrixMinRows = (int64_t)1 << 18;
 constexpr double kMatrixGrowth = 5.0;  // rows of a round against those before it
-// From so many queries and rows on (microseconds of the look-up kernels / here; M = 16 unless said): the launches of its
-// rounds are 80 us that few queries do not bring back, and it looks at 32 queries at a time.
+// From so many queries and rows on (microseconds by look-ups / here, M = 16 and D = 128 unless said; "clustered": rows
+// collapsed onto 1000 codes, which list more): the launches of its rounds are 80 us that few queries do not bring back, and it
+// looks at 32 queries at a time.
 //   64 queries, 4 x 10^6 rows, top-10 318 / 446, top-100 408 / 489;  128 queries, top-10 516 / 495, top-100 600 / 549,
-//   270,000 rows top-100 251 / 136, 1.6 x 10^7 rows top-100 1553 / 1616;  256 queries, top-10 207 / 115, 10^6 rows 405 / 216;  2048, top-100 1242 / 848
+//   270,000 rows top-100 251 / 122, clustered 251 / 141, 1.6 x 10^7 rows top-100 1553 / 1616;  256 queries over 270,000, top-10
+//   206 / 107, clustered 230 / 140;  256 over 1.6 x 10^7, top-100 clustered 3122 / 2043;  2048 over 10^6, top-100 1242 / 848
 //   many results are scored one query a block: 256 queries, 270,000 rows, top-1000 466 / 459 (M = 8 392 / 453), 10^6 rows
 //   863 / 675;  512 queries 887 / 609
-//   without a look-up kernel for several queries a block:  M = 64, 64 queries, 270,000 rows 320 / 149, 512 queries,
-//   10^6 rows 5673 / 394;  M = 12, 64 queries, 270,000 rows 138 / 105, top-1000 275 / 324
+//   without a look-up kernel for several queries a block:  M = 64, 512 queries, 10^6 rows 5668 / 392, 64 queries ahead by 1.7
+//   from 262,144 rows on;  M = 20 by 1.03;  M = 12, D = 96, 400,000 rows, 64 queries top-10 102 / 118, top-100 157 / 161, 80
+//   queries ahead by 1.14, 10^6 rows, 64 queries by 1.2 (D = 48: 0.90 to 1.04 and 1.3 with 64);  M = 4 has so few look-ups that it takes, with D = 128,
+//   384 queries below 786,432 rows (256: 0.81 to 1.3, 384: 1.5 and more), 192 from there (128: 0.83, 192: 1.38), 96 from 2^21
+//   (2.5 x 10^6: 64 queries 253 / 362, 96 ahead by 1.17), with D = 64 half of each.  (More than 512 results and M = 4, D = 128: from
+//   0.75, 70 queries over 524,800 rows 332 / 440, to 1.5, 192 over 10^6.)
+//   A batch that fills one round of the four-query kernel's blocks, M = 8, 400,000 rows:  top-10 640 queries 0.97 times as
+//   fast here, 1024 0.77;  top-100 768 1.01, 1024 0.87;  M = 16 top-10 900 0.97.  (D = 64 and less: 0.97 and more.)
 bool matrix_applies(const rii_index* idx, int Q, int topk, int64_t rows) {
+  const int M = idx->M, D = idx->D;
   if (!idx->mx_book || idx->bench_half_table || rows < kMatrixMinRows) return false;
   if (topk > kWaveK && Q < 512 && rows < 2 * kMatrixMinRows) return false;
-  return Q >= (!rot_m(idx->M) ? 64 : topk >= kFewManyResults && rows <= 32 * kMatrixMinRows ? 128 : 256);
+  const bool many = topk >= kFewManyResults;
+  if (!rot_m(M)) {
+    int least = 64;
+    if (M == 4 && topk <= 512) least = std::max(80, (D > 64 ? 384 : 192) >> (rows >= 8 * kMatrixMinRows ? 2 : rows >= 3 * kMatrixMinRows ? 1 : 0));
+    else if (M <= 12 && topk <= kWaveK && D > 64 && rows < 4 * kMatrixMinRows) least = 80;
+    return Q >= least;
+  }
+  if (Q < (many && rows <= 32 * kMatrixMinRows ? 128 : 256)) return false;
+  int64_t chunks, chunk_rows;
+  if (M <= 16 && D > 64 && topk <= kWaveK4 && Q <= 4 * kWantBlocks && rows < 3 * kMatrixMinRows &&
+      plan_batch(M, Q, rows, topk, &chunks, &chunk_rows) && chunks == 1)
+    return Q <= (M == 8 ? (many ? 800 : 576) : many || D <= 96 ? 4 * kWantBlocks : 864);
+  return true;
 }
 // Places of a query's list.  A round is expected to list five to ten times topk rows; where clusters have collapsed onto few
 // codes, all rows that share the bound's distance with them, which is what the places above the least are for: as many
