@@ -16,6 +16,8 @@ extern "C" {
 /* While two hipEvent_t (passed as void*) are set, every rii_adc_scan_linear call (and the
  * linear-scan branch of rii_query) records `start_event` right before and `stop_event` right
  * after the kernel that streams the code array (Alg. 1, the loop over s), on the call's stream.
+ * A batch that goes by matrix products has no one such kernel: its events stand around all its launches (fit of the
+ * tables, first bounds, rounds of products and of scoring, and the look-ups of what was left).
  * Pass NULL, NULL to switch it off.  The caller owns the events. */
 int rii_index_set_scan_events(rii_index_t* index, void* start_event, void* stop_event);
 
@@ -24,7 +26,7 @@ int rii_index_set_scan_events(rii_index_t* index, void* start_event, void* stop_
  * kernel that scans arrays of up to some ten thousand codes fetches every row whole and keeps none).
  * This call returns them (counters_out[RII_SCAN_COUNTERS], host) as accumulated since the last
  * call and resets them.  Synchronous (waits for the device).
- *   [0] batched scan: slices (64 rows x one group of four queries, i.e. 64 x M table look-ups) scored
+ *   [0] batched scan by look-ups: slices (64 rows x one group of four queries, i.e. 64 x M table look-ups) scored
  *   [1] batched scan: slices abandoned after M/2 look-ups at the latest
  *   [3] batched scan, M = 32: those of [1] that were abandoned after M/4 look-ups already
  *   [4] batched scan, M = 32: slices abandoned after 3M/4 look-ups
@@ -43,7 +45,9 @@ int rii_index_read_scan_counters(rii_index_t* index, uint64_t* counters_out);
  * benchmark can name the kernel it timed): *queries_per_block = 32 (the scan by matrix products: a
  * tile of queries; *row_chunks = row tiles), or 4, 2 or 1 queries sharing one
  * pass over the codes (Alg. 1 run for several queries at once; results are per query);
- * *row_chunks = blocks that share one query group's rows.  Host call, no GPU work. */
+ * *row_chunks = blocks that share one query group's rows.  Where the handle's scratch is settled (reserved, held by a
+ * graph, more refused by the device) the answer is for that scratch; rii_query has its tables in it as well and may
+ * go by look-ups where this call says 32.  Host call, no GPU work. */
 int rii_scan_linear_plan(const rii_index_t* index, int Q, int topk, int* queries_per_block, int64_t* row_chunks);
 
 /* LDS look-up ceiling of the scan kernels' inner loop, for the roofline of the batched scan

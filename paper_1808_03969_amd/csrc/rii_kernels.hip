@@ -797,6 +797,14 @@ MatrixScratch matrix_scratch(const rii_index* idx, int Q, int topk, size_t lead,
   return s;
 }
 
+// Whether rii_adc_scan_linear takes the products for such a batch (a device that has not refused is taken to have room).
+bool matrix_taken(const rii_index* idx, int Q, int topk) {
+  if (!matrix_applies(idx, Q, topk, idx->N)) return false;
+  const size_t look_ups = scan_ws_bytes(kLinear, idx->M, Q, idx->N, topk);
+  const bool fixed = (idx->ws_reserved && idx->ws_bytes >= look_ups) || idx->mx_held || idx->mx_wait > 0;
+  return !fixed || matrix_fit(idx, Q, topk, std::max(std::max(idx->ws_bytes, look_ups), idx->mx_ws_bytes)).q > 0;
+}
+
 template <int NF, bool SEED>
 int launch_matrix_round(const MatrixArgs& a, dim3 grid, hipStream_t st) {
   const int rc = set_lds(k_matrix_scan<NF, SEED>, mx_lds<NF>());
@@ -947,7 +955,7 @@ int rii_scan_linear_plan(const rii_index_t* idx, int Q, int topk, int* queries_p
   if (topk > RII_MAX_TOPK || !m_supported(idx->M) || Q > 65535) return RII_ERR_UNSUPPORTED;
   int64_t nchunks, chunk_rows, bchunks, brows;
   scan_chunks(Q, idx->N, &nchunks, &chunk_rows);
-  if (matrix_applies(idx, Q, topk, idx->N)) {
+  if (matrix_taken(idx, Q, topk)) {
     *queries_per_block = 32;  // (a tile of them at a time, past a block's rows)
     *row_chunks = (idx->N + kMxRows - 1) / kMxRows;
   } else if (few_linear(idx->M, Q, topk, idx->N)) {

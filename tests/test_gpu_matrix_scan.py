@@ -289,3 +289,20 @@ def test_collapsed_clusters(share, left, rii):
     assert counters[5] == left and counters[6] > 0
     want = by_look_ups(rii, index, lut, topk)
     assert torch.equal(ids, want[0]) and torch.equal(dist, want[1])
+
+
+# reserved scratch: the plan names what the call does, in scratch for a few queries (look-ups), for the batch and for a larger one
+@pytest.mark.parametrize("reserve,products", [((130, 50), False), ((40, 1024), True), ((600, 1024), True)])
+def test_plan_within_reserved_scratch(reserve, products, rii):
+    from paper_1808_03969_amd import binding
+    Q, topk = 600, 300
+    index, lut, want = scratch_case(rii, Q, topk)
+    again = rii.Index(np.zeros((16, 256, 2), dtype=np.float32))  # (nothing has sized its scratch)
+    again.add(index.get_codes())
+    again.reserve_workspace(*reserve)
+    held = again.info()["device_bytes"]
+    assert (binding.rii_scan_linear_plan(again, Q, topk)[0] == 32) == products
+    # (an index of another code book: tables that no query made, all left to the look-up kernels)
+    (ids, dist), counters = counted(rii, again, lambda: rii.rii_adc_scan_linear(again, lut, topk))
+    assert counters[5] == (Q if products else 0) and again.info()["device_bytes"] == held
+    assert torch.equal(ids, want[0]) and torch.equal(dist, want[1])
