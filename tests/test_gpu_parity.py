@@ -330,10 +330,20 @@ def test_reserve_workspace_then_no_growth(rii, oracle_lib, idx16):
 
 def test_reserved_scratch_of_many_results_over_a_large_array(rii, oracle_lib):
     """Row chunks of a large batch are made for up to 100 results only: reserving for 1024 results holds room for
-    their candidates once, not once a chunk; no call within the reservation grows it."""
-    N, M, Q = 52_000_000, 8, 8000  # two chunks' worth of rows
+    their candidates once, not once a chunk; no call within the reservation grows it.  (The batch goes by matrix products.)"""
+    reserved_scratch_over_a_large_array(52_000_000, 1, 32, 1024, rii, oracle_lib)
+
+
+def test_reserved_scratch_over_a_large_array_by_look_ups(rii, oracle_lib):
+    """The same with more than 128 coordinates and enough rows: the row chunks themselves (eleven at most, of 100 candidates)."""
+    reserved_scratch_over_a_large_array(101_000_000, 17, 4, 1100, rii, oracle_lib)
+
+
+def reserved_scratch_over_a_large_array(N, Ds, group, lists, rii, oracle_lib):
+    from paper_1808_03969_amd import binding
+    M, Q = 8, 8000
     rng = np.random.default_rng(3)
-    cb = rng.normal(size=(M, 256, 1)).astype(np.float32)
+    cb = rng.normal(size=(M, 256, Ds)).astype(np.float32)
     index = rii.Index(cb)
     g = torch.Generator(device="cuda")
     g.manual_seed(1)
@@ -343,8 +353,10 @@ def test_reserved_scratch_of_many_results_over_a_large_array(rii, oracle_lib):
     index.reserve_workspace(Q, 1024)
     held = index.info()["device_bytes"]
     # tables, candidates once, the bound-seeding pass' minima, room for the blocks of smaller batches; a quarter to spare
-    assert held - before <= 1.25 * (Q * M * 1024 + Q * 1024 * 8 + 2048 * 8192 + 4400 * 1024 * 8) + (1 << 20)
-    q = torch.randn((2100, M), generator=g, device="cuda")
+    assert held - before <= 1.25 * (Q * M * 1024 + Q * lists * 8 + 2048 * 8192 + 4400 * 1024 * 8) + (1 << 20)
+    q = torch.randn((2100, M * Ds), generator=g, device="cuda")
+    plan = binding.rii_scan_linear_plan(index, 2100, 100)
+    assert plan[0] == group and plan[1] > 1
     lut = rii.rii_build_lut(index, q)
     ids, dist = rii.rii_adc_scan_linear(index, lut, 100)
     torch.cuda.synchronize()
@@ -447,21 +459,34 @@ def test_half_precision_table_variant(M, kind, rii, oracle_lib):
 
 @pytest.mark.parametrize("M,Q,topk", [(8, 263, 100), (16, 258, 10)])
 def test_linear_scan_large_batch_in_row_chunks(M, Q, topk, rii, oracle_lib):
-    """A batch that takes the several-queries-per-block kernel, over a code array long enough to
+    """As the next test, with so few coordinates that the batch goes by matrix products."""
+    large_batch_in_row_chunks(M, Q, topk, 2, 32, rii, oracle_lib)
+
+
+@pytest.mark.parametrize("M,Q,topk,Ds", [(8, 263, 100, 17), (16, 258, 10, 9)])
+def test_linear_scan_large_batch_in_row_chunks_by_look_ups(M, Q, topk, Ds, rii, oracle_lib):
+    """A batch that takes the several-queries-per-block kernel (more than 128 coordinates), over a code array long enough to
     be cut into row chunks; Q is not a multiple of four (short last group).  Codes are uniform
     bytes; copies of row 5 sit on both sides of every fifth tile boundary (the chunks here come
     out 65 tiles long, so every chunk boundary has them) and query 0 is row 5's own
     reconstruction, so its top-100 is a run of exact ties that crosses several chunks."""
+    large_batch_in_row_chunks(M, Q, topk, Ds, 4, rii, oracle_lib)
+
+
+def large_batch_in_row_chunks(M, Q, topk, Ds, group, rii, oracle_lib):
+    from paper_1808_03969_amd import binding
     N = 2 * 2097152 + 3 * 4096 + 77
     rng = np.random.default_rng(11 + M)
-    cb = rng.normal(size=(M, 256, 2)).astype(np.float32)
+    cb = rng.normal(size=(M, 256, Ds)).astype(np.float32)
     codes = rng.integers(0, 256, size=(N, M), dtype=np.uint8)
     for b in range(4096, N, 4096 * 5):
         codes[b - 1:b + 1] = codes[5]
-    q = rng.normal(size=(Q, 2 * M)).astype(np.float32)
+    q = rng.normal(size=(Q, Ds * M)).astype(np.float32)
     q[0] = np.concatenate([cb[m][codes[5][m]] for m in range(M)])
     index = rii.Index(cb)
     index.add(codes)
+    plan = binding.rii_scan_linear_plan(index, Q, topk)
+    assert plan[0] == group and plan[1] > 1
     lut = rii.rii_build_lut(index, torch.from_numpy(q).cuda())
     ids, dist = rii.rii_adc_scan_linear(index, lut, topk)
     torch.cuda.synchronize()
