@@ -1577,6 +1577,9 @@ size_t rii_internal_assign_matrix_bytes(const rii_index* idx, int64_t n, int K) 
 // The margin the products are used with, as a share of |x|^2 + max |c|^2 (see assign_margin).
 float rii_internal_assign_margin(int M, int Ds) { return assign_margin((M * Ds + 31) / 32 * 32, M, Ds); }
 
+// The margin of the scan's filter by matrix products, as a share of its magnitudes (see k_fit_sums).
+float rii_internal_matrix_margin(int M, int Ds) { return mx_margin((M * Ds + 31) / 32 * 2, M); }
+
 // What the device is taken to have room for at the most, for the products' scratch (tests of a full device).
 void rii_internal_matrix_room(rii_index* idx, size_t most) {
   idx->mx_most = most;

@@ -54,13 +54,15 @@ def by_look_ups(rii, index, lut, topk):
 # every number of matrix steps and every width of the fit, sub-spaces with and without a rotated stored form, two planes,
 # the fewest rows and rows that leave the last tile of 512 nearly empty or full, query tiles short and full, one result
 # to the most; code words far from the origin, of one value, clustered codes
-@pytest.mark.parametrize("M,Ds,N,Q,topk,kind", [
+MATRIX_CASES = [
     (16, 8, 262144, 128, 100, "normal"), (16, 8, 262145, 257, 1, "far"), (32, 3, 300_000, 129, 128, "normal"),
     (32, 3, 400_127, 280, 10, "clustered"), (64, 2, 263_000, 129, 100, "normal"), (12, 8, 524_288, 64, 1000, "normal"),
     (8, 16, 262_655, 261, 50, "flat"), (8, 4, 524_289, 159, 300, "normal"), (4, 32, 524_800, 70, 1024, "normal"),
     (8, 1, 262_200, 130, 100, "normal"), (16, 6, 1_400_003, 256, 100, "clustered"), (12, 5, 262_500, 64, 20, "far"),
-    (16, 2, 270_000, 513, 200, "tiny"), (32, 4, 262_200, 160, 64, "huge")])
-def test_matrix_scan(M, Ds, N, Q, topk, kind, rii, oracle_lib):
+    (16, 2, 270_000, 513, 200, "tiny"), (32, 4, 262_200, 160, 64, "huge")]
+
+
+def matrix_case(rii, M, Ds, N, Q, topk, kind):
     from paper_1808_03969_amd import binding
     rng = np.random.default_rng(N + M)
     cb = rng.normal(size=(M, 256, Ds)).astype(np.float32)
@@ -69,9 +71,10 @@ def test_matrix_scan(M, Ds, N, Q, topk, kind, rii, oracle_lib):
     if kind == "far":
         cb += 300.0
         q += 300.0
-    if kind in ("tiny", "huge"):   # magnitudes at the ends of what the scaling reaches and past it
-        cb *= 1e-12 if kind == "tiny" else 1e9
-        q *= 1e-12 if kind == "tiny" else 1e9
+    size = {"tiny": 1e-12, "huge": 1e9, "small": 1e-8}.get(kind)
+    if size:                       # magnitudes at the ends of what the scaling reaches and past it
+        cb *= size
+        q *= size
         q[1] *= 50.0
     if kind == "flat":
         cb[1] = cb[1, :1]          # a sub-space whose code words are all the same
@@ -82,8 +85,25 @@ def test_matrix_scan(M, Ds, N, Q, topk, kind, rii, oracle_lib):
     index = rii.Index(cb)
     index.add(codes)
     assert binding.rii_scan_linear_plan(index, Q, topk)[0] == 32
-    lut = rii.rii_build_lut(index, torch.from_numpy(q).cuda())
+    return index, codes, rii.rii_build_lut(index, torch.from_numpy(q).cuda())
+
+
+@pytest.mark.parametrize("M,Ds,N,Q,topk,kind", MATRIX_CASES)
+def test_matrix_scan(M, Ds, N, Q, topk, kind, rii, oracle_lib):
+    index, codes, lut = matrix_case(rii, M, Ds, N, Q, topk, kind)
     check(rii, oracle_lib, index, lut, codes, topk, sorted(set(range(0, Q, max(1, Q // 6))) | {Q - 1}))
+
+
+# the products decide for every query of these batches (a query that the fit or an empty list handed to the look-up kernels
+# would have the right results whatever the products say), and no query's results are another's
+@pytest.mark.parametrize("M,Ds,N,Q,topk,kind", MATRIX_CASES + [(16, 2, 270_000, 513, 200, "small")])
+def test_products_do_the_work(M, Ds, N, Q, topk, kind, rii):
+    index, _, lut = matrix_case(rii, M, Ds, N, Q, topk, kind)
+    (ids, dist), counters = counted(rii, index, lambda: rii.rii_adc_scan_linear(index, lut, topk))
+    # (1e-12: below what the scaling reaches, nothing is left of the code words in fp16)
+    assert (counters[5], counters[6] > 0) == ((Q, False) if kind == "tiny" else (0, True))
+    want = by_look_ups(rii, index, lut, topk)
+    assert torch.equal(ids, want[0]) and torch.equal(dist, want[1])
 
 
 # tables that no query made, in a batch with others: random entries, of both signs, all equal, not finite, infinite,
