@@ -283,6 +283,8 @@ template <int SRC>
 int launch_few(FewArgs a, const FewShape& f, int Q, void* ws, bool cleared, hipStream_t st) {
   a.cap = f.cap;
   a.slot = f.slot;
+  a.filter_ids = a.target_ids;
+  a.filter_offsets = a.target_offsets;
   if (f.split > 1) {
     const size_t cstride = align_up((size_t)Q * 4, 256) / 4;
     uint32_t* tau = static_cast<uint32_t*>(ws);
@@ -825,7 +827,7 @@ int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int cap, i
   MatrixArgs a{};
   a.codes = idx->d_codes; a.plane = idx->plane_codes; a.N = idx->N; a.M = M; a.Ds = idx->Ds; a.D = idx->D;
   a.book = idx->mx_book; a.b = idx->mx_b;
-  a.qfrag = reinterpret_cast<const mx_u32x4*>(w + p.qfrag); a.cq = cq; a.nq = Q; a.Qp = p.Qp;
+  a.qfrag = reinterpret_cast<const mx_u32x4*>(w + p.qfrag); a.cq = cq; a.Qp = p.Qp;
   a.tiles = (idx->N + kMxRows - 1) / kMxRows;
   // tiles in an order that spreads every round over the whole array (rows may be stored in some order of their own)
   a.step = (int64_t)((double)a.tiles * 0.6180339887) | 1;
@@ -1513,7 +1515,7 @@ int rii_rotate(const float* R, int D, const float* x, int64_t n, float* y, void*
   return RII_OK;
 }
 
-// lazily build the symmetric table
+// The tables of the scan by matrix products: their place behind the code books (made by launch_matrix_batches).
 static int matrix_dsp(int Ds) { return Ds <= 4 ? 4 : Ds <= 8 ? 8 : Ds <= 16 ? 16 : 32; }
 size_t rii_internal_matrix_bytes(int M, int Ds) {
   if (!m_supported(M) || M * Ds > kMxMaxD || Ds > kMxMaxDs) return 0;
@@ -1530,6 +1532,7 @@ int rii_internal_matrix_books(rii_index* idx, void* where) {
   return RII_OK;
 }
 
+// lazily build the symmetric table
 int rii_internal_sym_table(const rii_index* cidx, hipStream_t st) {
   rii_index* idx = const_cast<rii_index*>(cidx);
   if (idx->d_sym) return RII_OK;
