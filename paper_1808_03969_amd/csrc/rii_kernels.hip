@@ -807,6 +807,22 @@ bool matrix_taken(const rii_index* idx, int Q, int topk) {
   return !fixed || matrix_fit(idx, Q, topk, std::max(std::max(idx->ws_bytes, look_ups), idx->mx_ws_bytes)).q > 0;
 }
 
+void launch_fit(const rii_index* idx, const float* lut, int Q, int Qp, int nf, uint16_t* qfrag, float4* part, uint32_t* left_n,
+                hipStream_t st) {
+  const int M = idx->M;
+  // groups of 16 queries a wave goes through: one round of blocks (three a CU by their registers)
+  const int per = std::max(1, (int)(((int64_t)(Qp / 16) * M + 12 * kWantBlocks - 1) / (12 * kWantBlocks)));
+  const dim3 grid((unsigned)((Qp / 16 + 4 * per - 1) / (4 * per)), (unsigned)M);
+#define RII_FIT(DSP) k_fit_tables<DSP><<<grid, 256, 0, st>>>(lut, idx->mx_fit, idx->mx_ch, idx->mx_b, idx->mx_scale, M, idx->Ds, nf, Q, Qp, per, qfrag, part, left_n)
+  switch (idx->mx_dsp) {
+    case 4: RII_FIT(4); break;
+    case 8: RII_FIT(8); break;
+    case 16: RII_FIT(16); break;
+    default: RII_FIT(32); break;
+  }
+#undef RII_FIT
+}
+
 template <int NF, bool SEED>
 int launch_matrix_round(const MatrixArgs& a, dim3 grid, hipStream_t st) {
   const int rc = set_lds(k_matrix_scan<NF, SEED>, mx_lds<NF>());
@@ -838,22 +854,12 @@ int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int cap, i
   a.cand = reinterpret_cast<int32_t*>(w + p.cand);
   a.cap = p.cap;
   uint16_t* qfrag = reinterpret_cast<uint16_t*>(w + p.qfrag);
-  // queries a wave of the fit goes through: enough waves to fill the chip first
-  const int per = std::min(8, std::max(1, (int)((int64_t)Q * M / (16 * kWantBlocks))));
   float4* part = reinterpret_cast<float4*>(w + p.part);
   LeftOut left{};
   left.n = reinterpret_cast<uint32_t*>(w + p.left); left.q = reinterpret_cast<int32_t*>(w + p.left + 256);
   left.arrays = static_cast<uint32_t*>(scan_ws); left.stride = (int64_t)(align_up((size_t)Q * 4, 256) / 4);
   left.counters = idx->ev_start && idx->ev_stop ? idx->d_scan_counters : nullptr;
-  const dim3 fgrid((unsigned)((p.Qp + per - 1) / per), (unsigned)(M / 4));
-#define RII_FIT(DSP) k_fit_tables<DSP><<<fgrid, 256, 0, st>>>(lut, idx->mx_fit, idx->mx_ch, idx->mx_b, idx->mx_scale, M, idx->Ds, p.nf, Q, p.Qp, per, qfrag, part, left.n)
-  switch (idx->mx_dsp) {
-    case 4: RII_FIT(4); break;
-    case 8: RII_FIT(8); break;
-    case 16: RII_FIT(16); break;
-    default: RII_FIT(32); break;
-  }
-#undef RII_FIT
+  launch_fit(idx, lut, Q, p.Qp, p.nf, qfrag, part, left.n, st);
   k_fit_sums<<<(p.Qp + 255) / 256, 256, 0, st>>>(part, M, p.nf, Q, p.Qp, cq, lo, hi, mode, a.cnt, left);
   // Tables that no query made are known after the fit: with many of them the products are not worth it, and all queries go by look-ups.
   // (2048 queries over 10^6 rows, M = 16, top-100: products 0.7 of the look-ups' time; 512 over 10^6, M = 64: 0.07)

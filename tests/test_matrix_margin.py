@@ -20,7 +20,7 @@ def test_margin_covers_every_rounding(M, Ds):
     entry, dot2 = r + n + 2.01 * b, n + 1.01 * b
     steps = (M * Ds + 31) // 32 * 32 + 1  # additions of the products and the start value, 2 u each (rounded or cut off), halved scale
     products = 2 * steps * (entry + r + dot2)        # twice (|tau - lo| / 2 + sum |qh ch|), 2 u
-    residual = (Ds + 2) * (entry + b + dot2)         # entry - b, then a product and an addition per coordinate
+    residual = (2 * Ds + 2) * (entry + b + dot2)     # entry - b, then an addition per coordinate, 2 u (the products are exact)
     extremes = (M + 1) * r                           # lo and hi: M additions, and the margin's own
     distance = M * entry                             # the defined sum
     row = M * b                                      # B
