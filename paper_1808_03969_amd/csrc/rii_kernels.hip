@@ -11,6 +11,7 @@
 //   k_scan_w<subset>         A in LDS, codes gathered by id       -> top-R per query     (Alg. 1, target ids)
 //   k_rank_lists             A in LDS, coarse codes               -> nearest lists       (Alg. 2, first block)
 //   k_ivf_w / k_ivf          A in LDS, probed lists streamed      -> top-R per query     (Alg. 2, second block)
+//   k_list_products          A as a vector, lists decoded, MFMA   -> top-R per query     (Alg. 2, second block, batches)
 //   k_scan + k_select, k_sort_segments: R above the per-wave kernels' reach, explicit candidates
 //
 // A candidate is one 64-bit key: order-preserving image of the fp32 distance in the high word,
@@ -49,6 +50,7 @@ namespace {
 #include "rii_dev_ivf.inc"
 #include "rii_dev_few.inc"
 #include "rii_dev_matrix.inc"
+#include "rii_dev_lists.inc"
 #include "rii_dev_offline.inc"
 #include "rii_dev_bench.inc"
 
@@ -807,13 +809,13 @@ bool matrix_taken(const rii_index* idx, int Q, int topk) {
   return !fixed || matrix_fit(idx, Q, topk, std::max(std::max(idx->ws_bytes, look_ups), idx->mx_ws_bytes)).q > 0;
 }
 
-void launch_fit(const rii_index* idx, const float* lut, int Q, int Qp, int nf, uint16_t* qfrag, float4* part, uint32_t* left_n,
+void launch_fit(const rii_index* idx, const float* lut, int Q, int Qp, int nf, bool by_query, uint16_t* qfrag, float4* part, uint32_t* left_n,
                 hipStream_t st) {
   const int M = idx->M;
   // groups of 16 queries a wave goes through: one round of blocks (three a CU by their registers)
   const int per = std::max(1, (int)(((int64_t)(Qp / 16) * M + 12 * kWantBlocks - 1) / (12 * kWantBlocks)));
   const dim3 grid((unsigned)((Qp / 16 + 4 * per - 1) / (4 * per)), (unsigned)M);
-#define RII_FIT(DSP) k_fit_tables<DSP><<<grid, 256, 0, st>>>(lut, idx->mx_fit, idx->mx_ch, idx->mx_b, idx->mx_scale, M, idx->Ds, nf, Q, Qp, per, qfrag, part, left_n)
+#define RII_FIT(DSP) k_fit_tables<DSP><<<grid, 256, 0, st>>>(lut, idx->mx_fit, idx->mx_ch, idx->mx_b, idx->mx_scale, M, idx->Ds, nf, Q, Qp, per, by_query, qfrag, part, left_n)
   switch (idx->mx_dsp) {
     case 4: RII_FIT(4); break;
     case 8: RII_FIT(8); break;
@@ -859,8 +861,8 @@ int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int cap, i
   left.n = reinterpret_cast<uint32_t*>(w + p.left); left.q = reinterpret_cast<int32_t*>(w + p.left + 256);
   left.arrays = static_cast<uint32_t*>(scan_ws); left.stride = (int64_t)(align_up((size_t)Q * 4, 256) / 4);
   left.counters = idx->ev_start && idx->ev_stop ? idx->d_scan_counters : nullptr;
-  launch_fit(idx, lut, Q, p.Qp, p.nf, qfrag, part, left.n, st);
-  k_fit_sums<<<(p.Qp + 255) / 256, 256, 0, st>>>(part, M, p.nf, Q, p.Qp, cq, lo, hi, mode, a.cnt, left);
+  launch_fit(idx, lut, Q, p.Qp, p.nf, false, qfrag, part, left.n, st);
+  k_fit_sums<<<(p.Qp + 255) / 256, 256, 0, st>>>(part, M, p.nf, Q, p.Qp, cq, lo, hi, mode, a.cnt, left, nullptr, 0);
   // Tables that no query made are known after the fit: with many of them the products are not worth it, and all queries go by look-ups.
   // (2048 queries over 10^6 rows, M = 16, top-100: products 0.7 of the look-ups' time; 512 over 10^6, M = 64: 0.07)
   const uint32_t most_left = rot_m(M) && topk <= kWaveK4 ? (uint32_t)Q * 3 / 8 : (uint32_t)Q * 3 / 4;
@@ -916,32 +918,189 @@ int launch_matrix_scan(const rii_index* idx, const float* lut, int Q, int cap, i
   return launch_left(idx, lut, Q, big, topk, ids, dist, out_stride, left, st);
 }
 
+// The index's tables are made by the first call that reads them, on its own stream (35 us; at the index's creation, with
+// the wait for them, they were 4 to 7 % of building one of 100,000 codes).  A call that is being captured makes them
+// for itself at every replay: nothing has run when the next call is issued.
+int matrix_books(const rii_index* idx, hipStream_t st) {
+  if (idx->mx_ready) return RII_OK;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const bool known = hipStreamIsCapturing(st, &capture) == hipSuccess;
+  if (!known) (void)hipGetLastError();
+  k_matrix_scale<<<1, 1024, 0, st>>>(idx->d_cb, idx->M, idx->Ds, idx->mx_scale);
+  k_matrix_books<<<idx->M, 256, 0, st>>>(idx->d_cb, idx->mx_scale, idx->Ds, idx->mx_dsp, idx->mx_book, idx->mx_fit, idx->mx_ch, idx->mx_b);
+  RII_HIP(hipGetLastError());
+  idx->mx_ready = known && capture == hipStreamCaptureStatusNone;
+  return RII_OK;
+}
+
 // The whole batch, as many queries at a time as the scratch is for.
 int launch_matrix_batches(const rii_index* idx, const float* lut, int Q, const MatrixScratch& scratch, int topk, int32_t* ids, float* dist,
                           int out_stride, hipStream_t st) {
   const int q = scratch.q;
   const bool timed = idx->ev_start && idx->ev_stop;
   const size_t scan_bytes = matrix_need(idx, q, topk, scratch.cap) - matrix_plan(idx, q, topk, scratch.cap).total;
-  // The index's tables are made by the first call that reads them, on its own stream (35 us; at the index's creation, with
-  // the wait for them, they were 4 to 7 % of building one of 100,000 codes).  A call that is being captured makes them
-  // for itself at every replay: nothing has run when the next call is issued.
-  if (!idx->mx_ready) {
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    const bool known = hipStreamIsCapturing(st, &capture) == hipSuccess;
-    if (!known) (void)hipGetLastError();
-    k_matrix_scale<<<1, 1024, 0, st>>>(idx->d_cb, idx->M, idx->Ds, idx->mx_scale);
-    k_matrix_books<<<idx->M, 256, 0, st>>>(idx->d_cb, idx->mx_scale, idx->Ds, idx->mx_dsp, idx->mx_book, idx->mx_fit, idx->mx_ch, idx->mx_b);
-    RII_HIP(hipGetLastError());
-    idx->mx_ready = known && capture == hipStreamCaptureStatusNone;
-  }
+  int rc = matrix_books(idx, st);
+  if (rc) return rc;
   if (timed) RII_HIP(hipEventRecord(static_cast<hipEvent_t>(idx->ev_start), st));
   for (int o = 0; o < Q; o += q) {
-    const int rc = launch_matrix_scan(idx, lut + (size_t)o * idx->M * 256, std::min(q, Q - o), scratch.cap, left_big(idx, q, topk), topk, ids + (size_t)o * out_stride,
+    rc = launch_matrix_scan(idx, lut + (size_t)o * idx->M * 256, std::min(q, Q - o), scratch.cap, left_big(idx, q, topk), topk, ids + (size_t)o * out_stride,
                                       dist ? dist + (size_t)o * out_stride : nullptr, out_stride, scratch.at, scan_bytes, st);
     if (rc) return rc;
   }
   if (timed) RII_HIP(hipEventRecord(static_cast<hipEvent_t>(idx->ev_stop), st));
   return RII_OK;
+}
+
+// ------------------------------------------------------------------ lists by matrix products
+// Scratch of a batch (rii_dev_lists.inc), from `at` on: byte offsets.
+struct ListPlan {
+  int nf, Qp, cap;
+  int64_t items;  // most work items
+  size_t query, cq, lo, hi, mode, cnt, left, part, counts, starts, groups_n, pairs, by_list, items_at, groups, cand, total;
+};
+bool list_shape(int M, int Ds) {
+#define RII_SHAPE(MT, DS) if (M == MT && Ds == DS) return true;
+  RII_LIST_SHAPES(RII_SHAPE)
+#undef RII_SHAPE
+  return false;
+}
+ListPlan list_plan(const rii_index* idx, int Q, int nprobe) {
+  const int M = idx->M, K = idx->K;
+  ListPlan p;
+  p.nf = lp_frags(M, idx->Ds);
+  p.Qp = (Q + 31) / 32 * 32;
+  const int64_t pairs = (int64_t)Q * nprobe;
+  p.items = idx->N / kLpRows + K + pairs / kLpQueries * (idx->max_list_len / kLpRows + 1);
+  size_t at = 0;
+  auto take = [&](size_t bytes) { const size_t o = at; at += align_up(bytes, 256); return o; };
+  p.query = take((size_t)p.Qp * p.nf * 32);
+  p.cq = take((size_t)p.Qp * 4);
+  p.lo = take((size_t)p.Qp * 4);
+  p.hi = take((size_t)p.Qp * 4);
+  p.mode = take((size_t)p.Qp * 4);
+  p.cnt = take((size_t)p.Qp * kMxCntStride * 4);
+  p.left = take(256 + (size_t)(1 + kScanArrays) * p.Qp * 4);
+  p.part = take((size_t)M * p.Qp * 16);
+  p.counts = take((size_t)(K + 2) * 4);
+  p.starts = take((size_t)K * 4);
+  p.groups_n = take((size_t)Q * 4);
+  p.pairs = take((size_t)pairs * sizeof(ListPair));
+  p.by_list = take((size_t)pairs * sizeof(ListPair));
+  p.items_at = take((size_t)p.items * sizeof(ListItem));
+  p.groups = take((size_t)Q * kLpGroups * 4);
+  // (an eighth of the scratch there may be)
+  p.cap = (int)std::min<int64_t>(std::max<int64_t>((int64_t)kMatrixScratch / 8 / 4 / Q, kLpLeast), kLpMost);
+  p.cand = take((size_t)Q * p.cap * 4);
+  p.total = at;
+  return p;
+}
+// Which batches: from so many members on, all queries together, as pay for the launches (90 us) and for decoding the lists twice.
+// Microseconds query by query / here (lists of 1000 and nprobe 8 unless said; mixture: rows in 1000 clusters):
+//   M = 16, N = 10^6, 1500 queries 107 / 109, 4000 top-10 210 / 153, top-100 244 / 178, mixture 251 / 234 and 290 / 264, 4000 with 32
+//   lists 769 / 251 and 732 / 330;  N = 100,000, 4000 queries 164 / 122;  D = 96, N = 4 x 10^6, 2048 lists of 1953, 4000 queries 241 / 264,
+//   1500 with 32 lists 322 / 262;  M = 32, D = 96, N = 10^6, 4000 queries 249 / 176 and 272 / 220
+//   M = 8, where clusters share few codes and their members are listed by thousands:  10^6, 4000 queries 199 / 147, mixture 232 / 229;
+//   8 x 10^6, 500 lists, mixture, 32 of them, 500 queries 1227 / 1403, 1500 2935 / 2165
+//   kernels of two blocks a CU or less lose earlier:  M = 64, N = 500,000, 500 queries 142 / 142, 1500 339 / 167, N = 10^6, mixture, 1500
+//   182 / 202, 4000 457 / 335;  M = 12, N = 500,000, 1500 queries 243 / 146
+bool list_products_apply(const rii_index* idx, int Q, int nprobe, int64_t L, int topk) {
+  const int M = idx->M;
+  if (!idx->mx_book || !list_shape(M, idx->Ds) || topk > kWaveK || nprobe > kIvfMaxProbe || idx->K > kLpMaxLists || Q > 65535) return false;
+  int64_t rows = idx->N / idx->K * nprobe;
+  if (L > 0 && L < rows) rows = L;
+  if (rows < 32 * (int64_t)topk) return false;  // (a bound is taken of groups of four and more members)
+  const double share = M == 8 ? 1.5 : rot_m(M) ? 1.0 : M == 64 ? 0.6 : 0.5;
+  return (double)Q * (double)rows >= share * (16e6 + 18.0 * (double)idx->N);
+}
+// Their scratch: behind the `lead` bytes of the handle's, else an allocation of its own, the one that the linear scan's
+// products have (see matrix_scratch for when it is asked for); NULL: query by query.
+void* list_scratch(const rii_index* idx, int Q, int nprobe, int64_t L, int topk, size_t lead, bool reserved, hipStream_t st) {
+  if (!list_products_apply(idx, Q, nprobe, L, topk)) return nullptr;
+  const size_t need = list_plan(idx, Q, nprobe).total;
+  if (need > kMatrixScratch) return nullptr;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const bool capturing = hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
+  if (capturing) (void)hipGetLastError();
+  const size_t behind = idx->ws_bytes > lead ? idx->ws_bytes - lead : 0;
+  if (need <= behind) return static_cast<uint8_t*>(idx->ws) + lead;
+  if (need > idx->mx_ws_bytes) {
+    if (reserved || capturing || idx->mx_held) return nullptr;
+    if (idx->mx_wait > 0) {
+      --idx->mx_wait;
+      return nullptr;
+    }
+    void* bigger = nullptr;
+    if (need > idx->mx_most || hipMalloc(&bigger, need) != hipSuccess) {
+      (void)hipGetLastError();
+      idx->mx_wait = kMatrixPatience;
+      return nullptr;
+    }
+    if (idx->mx_ws) (void)hipFree(idx->mx_ws);  // (waits for the device)
+    idx->mx_ws = bigger;
+    idx->mx_ws_bytes = need;
+  }
+  if (capturing) idx->mx_held = true;
+  return idx->mx_ws;
+}
+template <int M, int DS, bool SEED>
+int launch_list_round(const ListProductsArgs& a, hipStream_t st) {
+  const int rc = set_lds0(k_list_products<M, DS, SEED>, lp_lds(M, DS));
+  if (rc) return rc;
+  k_list_products<M, DS, SEED><<<kWantBlocks, 64 * kLpWaves, lp_lds(M, DS), st>>>(a);
+  return RII_OK;
+}
+// All but the queries that are left: their mode is 1 afterwards, the others' 0.
+int launch_list_products(const rii_index* idx, const float* lut, int Q, const int32_t* probe, int probe_stride, int nprobe, int64_t L,
+                         int topk, int32_t* ids, float* dist, void* scratch, int** mode_out, hipStream_t st) {
+  int rc = matrix_books(idx, st);
+  if (rc) return rc;
+  const int M = idx->M, K = idx->K;
+  const ListPlan p = list_plan(idx, Q, nprobe);
+  uint8_t* w = static_cast<uint8_t*>(scratch);
+  auto floats = [&](size_t o) { return reinterpret_cast<float*>(w + o); };
+  auto words = [&](size_t o) { return reinterpret_cast<uint32_t*>(w + o); };
+  int* mode = reinterpret_cast<int*>(w + p.mode);
+  float4* part = reinterpret_cast<float4*>(w + p.part);
+  LeftOut left{};
+  left.n = words(p.left); left.q = reinterpret_cast<int32_t*>(w + p.left + 256);
+  left.arrays = words(p.left + 256) + p.Qp; left.stride = p.Qp;
+  launch_fit(idx, lut, Q, p.Qp, p.nf, true, reinterpret_cast<uint16_t*>(w + p.query), part, left.n, st);
+  uint32_t* counts = words(p.counts);
+  k_fit_sums<<<(p.Qp + 255) / 256, 256, 0, st>>>(part, M, p.nf, Q, p.Qp, floats(p.cq), floats(p.lo), floats(p.hi), mode, words(p.cnt), left, counts, K + 2);
+  ListPair* pairs = reinterpret_cast<ListPair*>(w + p.pairs);
+  ListPair* by_list = reinterpret_cast<ListPair*>(w + p.by_list);
+  ListItem* items = reinterpret_cast<ListItem*>(w + p.items_at);
+  const int per_block = std::max(16, (Q + kWantBlocks / 2 - 1) / (kWantBlocks / 2));
+  rc = set_lds(k_pair_count, (size_t)K * 4);
+  if (rc) return rc;
+  k_pair_count<<<(Q + per_block - 1) / per_block, 1024, (size_t)K * 4, st>>>(probe, probe_stride, nprobe, idx->d_list_off, K, Q, per_block, L, counts, pairs, words(p.groups_n));
+  k_pair_place<<<(K + 63) / 64, 256, 0, st>>>(counts, idx->d_list_off, K, words(p.starts), counts + K, items);
+  const int64_t n = (int64_t)Q * nprobe;
+  k_pair_fill<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(pairs, n, nprobe, words(p.starts), by_list);
+  ListProductsArgs a{};
+  a.codes = idx->d_codes_list; a.plane = idx->plane_list; a.book = idx->mx_book;
+  a.query = reinterpret_cast<const uint16_t*>(w + p.query); a.cq = floats(p.cq); a.pairs = by_list;
+  a.list_ids = idx->d_list_ids; a.items = items; a.n_items = counts + K + 1; a.groups = floats(p.groups); a.cnt = words(p.cnt); a.cand = reinterpret_cast<int32_t*>(w + p.cand); a.cap = p.cap;
+  a.left_n = left.n; a.left_most = (uint32_t)Q * 3 / 8;
+#define RII_SEED_ROUND(MT, DS) if (M == MT && idx->Ds == DS) rc = launch_list_round<MT, DS, true>(a, st);
+#define RII_LIST_ROUND(MT, DS) if (M == MT && idx->Ds == DS) rc = launch_list_round<MT, DS, false>(a, st);
+  RII_LIST_SHAPES(RII_SEED_ROUND)
+  if (rc) return rc;
+  k_list_bound<<<(Q + 3) / 4, 256, 0, st>>>(a.groups, words(p.groups_n), Q, topk, floats(p.lo), floats(p.hi), mode, floats(p.cq), left.n, a.left_most);
+  RII_LIST_SHAPES(RII_LIST_ROUND)
+#undef RII_SEED_ROUND
+#undef RII_LIST_ROUND
+  if (rc) return rc;
+  DISPATCH_M(M, k_list_score<MT><<<Q, kLpRanked, 0, st>>>(idx->d_codes_rows, idx->plane_rows, M, lut, a.cnt, a.cand, p.cap, topk, ids, dist, mode));
+  FewArgs f{};
+  f.codes = idx->d_codes_rows; f.plane = idx->plane_rows; f.M = M; f.lut = lut; f.N = idx->N;
+  f.listed = a.cand; f.listed_cnt = a.cnt; f.listed_cap = p.cap; f.listed_cnt_stride = kMxCntStride;
+  f.k = topk; f.ids = ids; f.dist = dist; f.out_stride = topk; f.qmode = mode; f.want_mode = 2;
+  FewShape shape = few_shape(M, Q, p.cap, topk, FewRows::targets, false);
+  shape.split = 1;
+  rc = launch_few<kFewListed>(f, shape, Q, nullptr, true, st);
+  *mode_out = mode;
+  return rc;
 }
 
 }  // namespace
@@ -1210,9 +1369,16 @@ static size_t ivf_ws_bytes(const rii_index* idx, int Q, int nprobe, int64_t L, i
 static int launch_ivf(const rii_index* idx, const float* lut, int Q, const int32_t* probe, int probe_stride,
                       int nprobe, const int* nprobe_q, const int32_t* target_ids, const int64_t* target_offsets,
                       int64_t L, int topk, int32_t* ids, float* dist, const int* qmode, int want_mode, void* ws,
-                      hipStream_t st, bool cleared = false, bool tight = false) {
+                      hipStream_t st, bool cleared = false, bool tight = false, void* products = nullptr) {
   const int M = idx->M;
   const bool capped = L > 0 && target_ids;
+  int* left = nullptr;
+  if (products) {  // (no target sets, one branch and one number of lists for all queries); below: what it leaves
+    const int rc = launch_list_products(idx, lut, Q, probe, probe_stride, nprobe, L, topk, ids, dist, products, &left, st);
+    if (rc) return rc;
+    qmode = left;
+    want_mode = 1;
+  }
   const int64_t rows = list_rows(idx, nprobe, capped ? 0 : L);
   if (nprobe <= kIvfMaxProbe && Q <= 65535 && (capped || topk > kWaveK || few_lists(M, Q, topk, rows))) {
     FewArgs f{};
@@ -1261,10 +1427,14 @@ int rii_adc_scan_ivf(const rii_index_t* idx, const float* lut, int Q, const int3
   if ((target_ids == nullptr) != (target_offsets == nullptr)) return RII_ERR_INVALID_ARG;
   if (topk > RII_MAX_TOPK || !m_supported(idx->M)) return RII_ERR_UNSUPPORTED;
   if (L >= idx->N) L = 0;  // such a cap never cuts anything
-  int rc = ensure_ws(idx, ivf_ws_bytes(idx, Q, nprobe, L, topk, target_ids != nullptr));
+  const size_t need = ivf_ws_bytes(idx, Q, nprobe, L, topk, target_ids != nullptr);
+  const bool reserved = idx->ws_reserved && idx->ws_bytes >= need;
+  int rc = ensure_ws(idx, need);
   if (rc) return rc;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  void* products = target_ids ? nullptr : list_scratch(idx, Q, nprobe, L, topk, align_up(need, 256), reserved, st);
   return launch_ivf(idx, lut, Q, probe_lists, nprobe, nprobe, nullptr, target_ids, target_offsets, L, topk, ids,
-                    dist, nullptr, 0, idx->ws, static_cast<hipStream_t>(stream));
+                    dist, nullptr, 0, idx->ws, st, false, false, products);
 }
 
 // Scratch layout of the query procedure: tables, per-query plan, probed lists, then the stage
@@ -1278,6 +1448,7 @@ struct QueryPlan {
   bool uniform = false;
   bool tight = false;  // small scans get the least scratch (see few_shape)
   MatrixScratch products;  // of the linear scan by matrix products, where it goes that way
+  void* lists = nullptr;   // the same of the inverted index
 };
 
 // `limit` > 0: a plan beyond that many bytes gives up the small scans' room, then the batched scan.
@@ -1363,7 +1534,7 @@ static int run_query(const rii_index* idx, const QueryPlan& p, const float* q, i
     if (rc) return rc;
     const bool untouched = coarse_in_lds(K, p.pmax) && !coarse_split(Q, K);  // the ranking leaves the stage scratch alone
     rc = launch_ivf(idx, lut, Q, probe, p.pmax, p.pmax, nprobe_q, target_ids, target_offsets, L, topk, ids, dist, qmode,
-                    1, stage_ws, st, p.uniform && untouched, p.tight);
+                    1, stage_ws, st, p.uniform && untouched, p.tight, p.lists);
     if (rc) return rc;
   }
   RII_HIP(hipGetLastError());
@@ -1386,6 +1557,8 @@ int rii_query(const rii_index_t* idx, const float* q, int Q, int topk, const int
   if (rc) return rc;
   if (!target_ids && (idx->K == 0 || idx->N < idx->theta))
     p.products = matrix_scratch(idx, Q, topk, p.lut_b + 2 * p.plan_b + p.probe_b, reserved, static_cast<hipStream_t>(stream));
+  else if (!target_ids)
+    p.lists = list_scratch(idx, Q, p.pmax, L, topk, p.total, reserved, static_cast<hipStream_t>(stream));
   return run_query(idx, p, q, Q, topk, target_ids, target_offsets, L, ids, dist, idx->ws, static_cast<hipStream_t>(stream));
 }
 

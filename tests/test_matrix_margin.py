@@ -23,7 +23,8 @@ def test_margin_covers_every_rounding(M, Ds):
     residual = (2 * Ds + 2) * (entry + b + dot2)     # entry - b, then an addition per coordinate, 2 u (the products are exact)
     extremes = (M + 1) * r                           # lo and hi: M additions, and the margin's own
     distance = M * entry                             # the defined sum
-    row = M * b                                      # B
+    row = M * b                                      # B: M additions of the book's numbers, or
+    row = np.maximum(row, 2 * steps * 1.01 * b + Ds * b)  # the squares of the row's coordinates added up, 2 u, against the book's sums of Ds
     start = 2 * (entry + r)                          # (tau - lo) / 2 and its factor
     worst = products + residual + extremes + distance + row + start
     share = float(np.max(worst / np.array([2, 4.1, 7.1]))) * U
