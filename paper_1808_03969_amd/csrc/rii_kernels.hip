@@ -6,6 +6,7 @@
 // Data flow of one query batch:
 //   k_build_lut              q, code books                        -> A [Q][M][256]       (Sec. 3)
 //   k_few                    A in LDS, some 10^4 rows at most     -> top-R per query     (all of the following, small)
+//   k_pick_members + k_few   lists' members in a target set       -> top-R per query     (Alg. 2, target ids and cap)
 //   k_matrix_scan + k_few    A as a vector, codes decoded, MFMA   -> top-R per query     (Alg. 1, whole data, batches)
 //   k_scan_w4 / k_scan_w     A in LDS, codes streamed             -> top-R per query     (Alg. 1, whole data)
 //   k_scan_w<subset>         A in LDS, codes gathered by id       -> top-R per query     (Alg. 1, target ids)
@@ -801,6 +802,35 @@ MatrixScratch matrix_scratch(const rii_index* idx, int Q, int topk, size_t lead,
   return s;
 }
 
+// Scratch that a call can do without: behind the `lead` bytes of the handle's, else an allocation of its own, the one that the
+// linear scan's products have (see matrix_scratch for when it is asked for); NULL: there is none.
+void* extra_scratch(const rii_index* idx, size_t need, size_t lead, bool reserved, hipStream_t st) {
+  if (need > kMatrixScratch) return nullptr;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const bool capturing = hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
+  if (capturing) (void)hipGetLastError();
+  const size_t behind = idx->ws_bytes > lead ? idx->ws_bytes - lead : 0;
+  if (need <= behind) return static_cast<uint8_t*>(idx->ws) + lead;
+  if (need > idx->mx_ws_bytes) {
+    if (reserved || capturing || idx->mx_held) return nullptr;
+    if (idx->mx_wait > 0) {
+      --idx->mx_wait;
+      return nullptr;
+    }
+    void* bigger = nullptr;
+    if (need > idx->mx_most || hipMalloc(&bigger, need) != hipSuccess) {
+      (void)hipGetLastError();
+      idx->mx_wait = kMatrixPatience;
+      return nullptr;
+    }
+    if (idx->mx_ws) (void)hipFree(idx->mx_ws);  // (waits for the device)
+    idx->mx_ws = bigger;
+    idx->mx_ws_bytes = need;
+  }
+  if (capturing) idx->mx_held = true;
+  return idx->mx_ws;
+}
+
 // Whether rii_adc_scan_linear takes the products for such a batch (a device that has not refused is taken to have room).
 bool matrix_taken(const rii_index* idx, int Q, int topk) {
   if (!matrix_applies(idx, Q, topk, idx->N)) return false;
@@ -1012,35 +1042,10 @@ bool list_products_apply(const rii_index* idx, int Q, int nprobe, int64_t L, int
   const double share = M == 8 ? 1.5 : rot_m(M) ? 1.0 : M == 64 ? 0.6 : 0.5;
   return (double)Q * (double)rows >= share * (16e6 + 18.0 * (double)idx->N);
 }
-// Their scratch: behind the `lead` bytes of the handle's, else an allocation of its own, the one that the linear scan's
-// products have (see matrix_scratch for when it is asked for); NULL: query by query.
+// Their scratch; NULL: query by query.
 void* list_scratch(const rii_index* idx, int Q, int nprobe, int64_t L, int topk, size_t lead, bool reserved, hipStream_t st) {
   if (!list_products_apply(idx, Q, nprobe, L, topk)) return nullptr;
-  const size_t need = list_plan(idx, Q, nprobe).total;
-  if (need > kMatrixScratch) return nullptr;
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  const bool capturing = hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
-  if (capturing) (void)hipGetLastError();
-  const size_t behind = idx->ws_bytes > lead ? idx->ws_bytes - lead : 0;
-  if (need <= behind) return static_cast<uint8_t*>(idx->ws) + lead;
-  if (need > idx->mx_ws_bytes) {
-    if (reserved || capturing || idx->mx_held) return nullptr;
-    if (idx->mx_wait > 0) {
-      --idx->mx_wait;
-      return nullptr;
-    }
-    void* bigger = nullptr;
-    if (need > idx->mx_most || hipMalloc(&bigger, need) != hipSuccess) {
-      (void)hipGetLastError();
-      idx->mx_wait = kMatrixPatience;
-      return nullptr;
-    }
-    if (idx->mx_ws) (void)hipFree(idx->mx_ws);  // (waits for the device)
-    idx->mx_ws = bigger;
-    idx->mx_ws_bytes = need;
-  }
-  if (capturing) idx->mx_held = true;
-  return idx->mx_ws;
+  return extra_scratch(idx, list_plan(idx, Q, nprobe).total, lead, reserved, st);
 }
 template <int M, int DS, bool SEED>
 int launch_list_round(const ListProductsArgs& a, hipStream_t st) {
@@ -1101,6 +1106,49 @@ int launch_list_products(const rii_index* idx, const float* lut, int Q, const in
   rc = launch_few<kFewListed>(f, shape, Q, nullptr, true, st);
   *mode_out = mode;
   return rc;
+}
+
+// ------------------------------------------------------------------ lists with target set and candidate cap
+// Scratch of k_pick_members, then that of the scan that follows.
+struct PickPlan {
+  int cap;              // most members that are scored
+  bool joint;
+  FewShape few;
+  size_t cnt, few_ws, total;
+};
+// lin_rows: identifiers that the batch's other queries may have; they are done in the same launch where all of it is a small scan
+// (joint), 0: there are none.
+PickPlan pick_plan(const rii_index* idx, int Q, int nprobe, int64_t L, int64_t lin_rows, int topk) {
+  PickPlan p;
+  p.cap = (int)std::min(L, (int64_t)nprobe * idx->max_list_len);
+  p.joint = lin_rows > 0 && few_scan(kSubset, idx->M, Q, topk, std::max<int64_t>(lin_rows, p.cap));
+  p.few = few_shape(idx->M, Q, std::max<int64_t>(p.joint ? lin_rows : 1, p.cap), topk, FewRows::targets, false);
+  p.cnt = align_up((size_t)Q * p.cap * 4, 256);
+  p.few_ws = p.cnt + align_up((size_t)Q * 4, 256);
+  p.total = p.few_ws + few_ws_bytes(p.few, Q);
+  return p;
+}
+bool pick_applies(const rii_index* idx, int Q, int nprobe, int64_t L, int topk) {
+  return nprobe <= kIvfMaxProbe && Q <= 65535 && few_scan(kSubset, idx->M, Q, topk, std::min(L, idx->N));
+}
+int launch_pick(const rii_index* idx, const PickPlan& p, int Q, const int32_t* probe, int probe_stride, int nprobe, const int* nprobe_q,
+                const int32_t* target_ids, const int64_t* target_offsets, int64_t L, const int* qmode, void* scratch, FewArgs* f,
+                hipStream_t st) {
+  uint8_t* w = static_cast<uint8_t*>(scratch);
+  PickArgs a{};
+  a.list_ids = idx->d_list_ids; a.list_off = idx->d_list_off; a.probe = probe; a.probe_stride = probe_stride; a.nprobe = nprobe;
+  a.nprobe_q = nprobe_q; a.target_ids = target_ids; a.target_offsets = target_offsets; a.qmode = qmode; a.Lcap = L;
+  a.cand = reinterpret_cast<int32_t*>(w); a.cnt = reinterpret_cast<uint32_t*>(w + p.cnt); a.cap = p.cap;
+  // as many bits as there are identifiers, 128 KB of them at most, half of it where more than 1000 lists want their place in LDS
+  const int64_t bits = std::min<int64_t>((idx->N + 127) / 128 * 128, nprobe <= 1000 ? 1 << 20 : 1 << 19);
+  a.words = (int)(bits / 32);
+  while (((idx->N - 1) >> a.shift) >= bits) ++a.shift;
+  const size_t lds = pick_lds(a.words, nprobe);
+  const int rc = set_lds(k_pick_members, lds);
+  if (rc) return rc;
+  k_pick_members<<<Q, kPickThreads, lds, st>>>(a);
+  f->listed = a.cand; f->listed_cnt = a.cnt; f->listed_cap = p.cap; f->listed_cnt_stride = 1;
+  return RII_OK;
 }
 
 }  // namespace
@@ -1432,6 +1480,17 @@ int rii_adc_scan_ivf(const rii_index_t* idx, const float* lut, int Q, const int3
   int rc = ensure_ws(idx, need);
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (target_ids && L > 0 && pick_applies(idx, Q, nprobe, L, topk)) {
+    const PickPlan p = pick_plan(idx, Q, nprobe, L, 0, topk);
+    if (void* pick = extra_scratch(idx, p.total, align_up(need, 256), reserved, st)) {
+      FewArgs f{};
+      rc = launch_pick(idx, p, Q, probe_lists, nprobe, nprobe, nullptr, target_ids, target_offsets, L, nullptr, pick, &f, st);
+      if (rc) return rc;
+      f.codes = idx->d_codes_rows; f.plane = idx->plane_rows; f.M = idx->M; f.lut = lut; f.N = idx->N;
+      f.k = topk; f.ids = ids; f.dist = dist; f.out_stride = topk;
+      return launch_few<kFewListed>(f, p.few, Q, static_cast<uint8_t*>(pick) + p.few_ws, false, st);
+    }
+  }
   void* products = target_ids ? nullptr : list_scratch(idx, Q, nprobe, L, topk, align_up(need, 256), reserved, st);
   return launch_ivf(idx, lut, Q, probe_lists, nprobe, nprobe, nullptr, target_ids, target_offsets, L, topk, ids,
                     dist, nullptr, 0, idx->ws, st, false, false, products);
@@ -1449,6 +1508,7 @@ struct QueryPlan {
   bool tight = false;  // small scans get the least scratch (see few_shape)
   MatrixScratch products;  // of the linear scan by matrix products, where it goes that way
   void* lists = nullptr;   // the same of the inverted index
+  void* pick = nullptr;    // of lists with target sets, whose members are found first
 };
 
 // `limit` > 0: a plan beyond that many bytes gives up the small scans' room, then the batched scan.
@@ -1513,9 +1573,34 @@ static int run_query(const rii_index* idx, const QueryPlan& p, const float* q, i
   void* stage_ws = w;
 
   launch_build_lut(idx, q, Q, lut, st, p.uniform ? stage_ws : nullptr);
+  PickPlan pick{};
+  uint8_t* pick_ws = static_cast<uint8_t*>(p.pick);
+  if (p.pick) pick = pick_plan(idx, Q, p.pmax, L, p.lin_rows, topk);
   if (p.uniform) qmode = nprobe_q = nullptr;  // (one branch for all queries; every query's lists are p.pmax then)
-  else k_plan<<<(Q + 255) / 256, 256, 0, st>>>(target_offsets, idx->N, Q, idx->theta, K, L, p.pmax, qmode, nprobe_q);
+  else k_plan<<<(Q + 255) / 256, 256, 0, st>>>(target_offsets, idx->N, Q, idx->theta, K, L, p.pmax, qmode, nprobe_q,
+                                               p.pick ? reinterpret_cast<uint32_t*>(pick_ws + pick.few_ws) : nullptr,
+                                               (int)(align_up((size_t)Q * 4, 256) / 4));
   int rc = RII_OK;
+  if (p.pick) {
+    if (!pick.joint) {
+      rc = launch_scan(idx, idx->d_codes_rows, idx->plane_rows, idx->N, lut, Q, kSubset, target_ids, target_offsets, p.lin_rows, topk,
+                       ids, dist, topk, qmode, 0, stage_ws, st, false, p.tight);
+      if (rc) return rc;
+    }
+    rc = coarse_rank(idx, lut, Q, p.pmax, probe, nullptr, p.pmax, qmode, 1, stage_ws, st, p.tight);
+    if (rc) return rc;
+    FewArgs f{};
+    rc = launch_pick(idx, pick, Q, probe, p.pmax, p.pmax, nprobe_q, target_ids, target_offsets, L, qmode, p.pick, &f, st);
+    if (rc) return rc;
+    f.codes = idx->d_codes_rows; f.plane = idx->plane_rows; f.M = idx->M; f.lut = lut; f.N = idx->N;
+    f.k = topk; f.ids = ids; f.dist = dist; f.out_stride = topk; f.qmode = qmode;
+    if (pick.joint) {  // both branches in one scan by identifiers: the target sets (mode 0), their first L members in the lists (mode 1)
+      f.target_ids = target_ids; f.target_offsets = target_offsets; f.want_mode = -1;
+      return launch_few<kFewSubset>(f, pick.few, Q, pick_ws + pick.few_ws, true, st);
+    }
+    f.want_mode = 1;
+    return launch_few<kFewListed>(f, pick.few, Q, pick_ws + pick.few_ws, true, st);
+  }
   // linear-scan branch (mode 0)
   const bool all_linear = !target_ids && (!has_lists || idx->N < idx->theta);
   if (target_ids) {
@@ -1559,6 +1644,8 @@ int rii_query(const rii_index_t* idx, const float* q, int Q, int topk, const int
     p.products = matrix_scratch(idx, Q, topk, p.lut_b + 2 * p.plan_b + p.probe_b, reserved, static_cast<hipStream_t>(stream));
   else if (!target_ids)
     p.lists = list_scratch(idx, Q, p.pmax, L, topk, p.total, reserved, static_cast<hipStream_t>(stream));
+  else if (idx->K > 0 && pick_applies(idx, Q, p.pmax, L, topk))
+    p.pick = extra_scratch(idx, pick_plan(idx, Q, p.pmax, L, p.lin_rows, topk).total, p.total, reserved, static_cast<hipStream_t>(stream));
   return run_query(idx, p, q, Q, topk, target_ids, target_offsets, L, ids, dist, idx->ws, static_cast<hipStream_t>(stream));
 }
 

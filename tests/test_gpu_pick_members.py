@@ -1,0 +1,97 @@
+"""Lists with a target set and a candidate cap: the first L members of the set, found in front of the scan, against the definition in numpy,
+and whole queries against the form that does both at once (rii_query_noalloc, which has no room for the other)."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import t2n
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rii():
+    import paper_1808_03969_amd as r
+    r.load_library()
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    return r
+
+
+def make(rii, M, Ds, N, K, seed):
+    """Lists of very different lengths, one empty and one of a single member."""
+    rng = np.random.default_rng(seed)
+    index = rii.Index(rng.standard_normal((M, 256, Ds)).astype(np.float32))
+    codes = rng.integers(0, 256, (N, M), dtype=np.uint8)
+    index.add(codes)
+    share = rng.random(K) ** 2 + 0.05
+    share[K // 2] = 0.0
+    lengths = np.floor(share / share.sum() * (N - 1)).astype(np.int64)
+    lengths[K - 1] += 1
+    lengths[0] += N - lengths.sum()
+    a = rng.permutation(np.repeat(np.arange(K), lengths))
+    order = np.argsort(a, kind="stable").astype(np.int32)
+    off = np.zeros(K + 1, np.int64)
+    off[1:] = np.cumsum(lengths)
+    index.set_lists(rng.integers(0, 256, (K, M), dtype=np.uint8), off, order)
+    return index, codes, off, order, rng
+
+
+def target_sets(rng, N, sizes):
+    sets = [np.sort(rng.permutation(N)[:s]).astype(np.int32) for s in sizes]
+    off = np.zeros(len(sets) + 1, np.int64)
+    off[1:] = np.cumsum([len(s) for s in sets])
+    return sets, torch.from_numpy(np.concatenate(sets)).cuda(), torch.from_numpy(off).cuda()
+
+
+# a bit map with a bit an identifier, two and four identifiers a bit (the latter beside many lists), samples of sets that are far larger than
+# the lists; sets of none, of one, of less than a wave, that end inside and at the edge of what is read at a time, of everything; caps
+# that cut the first list, that are met in a later round and never; rounds that end inside a list
+CASES = [
+    (16, 4, 50_000, 50, 7, 3_000, 100, [0, 1, 2, 63, 4096, 4097, 25_000, 32_768, 49_999, 50_000]),
+    (12, 4, 3_000, 10, 10, 2_999, 20, [0, 1, 31, 1_500, 3_000]),
+    (8, 4, 1_048_576, 64, 30, 20_000, 50, [5, 70_000, 600_000, 1_048_576]),
+    (8, 4, 1_048_577, 64, 30, 20_000, 50, [5, 70_000, 600_000, 1_048_577]),
+    (32, 2, 1_300_000, 300, 2, 100, 100, [0, 10, 131_072, 900_000, 1_300_000]),
+    (64, 2, 1_300_000, 300, 40, 4_000, 1, [40_000, 1_000_001]),
+    (16, 4, 1_500_000, 2_000, 1_200, 9_000, 100, [0, 300, 20_000, 1_500_000]),
+]
+
+
+@pytest.mark.parametrize("M,Ds,N,K,nprobe,L,topk,sizes", CASES)
+def test_against_the_definition(rii, M, Ds, N, K, nprobe, L, topk, sizes):
+    index, codes, off, order, rng = make(rii, M, Ds, N, K, N + nprobe)
+    Q = 3 * len(sizes)
+    sets, tids, toff = target_sets(rng, N, sizes * 3)
+    q = torch.from_numpy(rng.standard_normal((Q, M * Ds)).astype(np.float32)).cuda()
+    lut = rii.rii_build_lut(index, q)
+    probe = np.stack([rng.permutation(K)[:nprobe] for _ in range(Q)]).astype(np.int32)
+    probe[1, :] = probe[1, 0]  # a list named again and again
+    ids, dist = rii.rii_adc_scan_ivf(index, lut, torch.from_numpy(probe).cuda(), topk, tids, toff, L=L)
+    A, ids, dist = t2n(lut), t2n(ids), t2n(dist)
+    for i in range(Q):
+        rows = np.concatenate([order[off[l]:off[l + 1]] for l in probe[i]])
+        member = np.zeros(N, bool)
+        member[sets[i]] = True
+        rows = rows[member[rows]][:L]
+        d = np.zeros(len(rows), np.float32)
+        for m in range(M):
+            d += A[i, m][codes[rows, m]]
+        best = np.lexsort((rows, d))[:topk]
+        n = len(best)
+        assert np.array_equal(ids[i, :n], rows[best]) and np.array_equal(dist[i, :n], d[best]), i
+        assert np.all(ids[i, n:] == -1) and np.all(np.isinf(dist[i, n:]))
+
+
+# both branches in one launch, and target sets that are too many for a small scan
+@pytest.mark.parametrize("N,K,Q,L,theta,most", [(60_000, 60, 200, 900, 5_000, 60_000), (300_000, 40, 120, 2_000, 25_000, 200_000),
+                                                 (60_000, 60, 33, 700, 1, 60_000)])
+def test_whole_queries(rii, N, K, Q, L, theta, most):
+    index, codes, off, order, rng = make(rii, 16, 4, N, K, Q)
+    index.set_threshold(theta)
+    sizes = np.exp(rng.uniform(np.log(10), np.log(most), Q)).astype(int)
+    sizes[:3] = 0, theta, max(theta - 1, 0)
+    _, tids, toff = target_sets(rng, N, sizes)
+    q = torch.from_numpy(rng.standard_normal((Q, 64)).astype(np.float32)).cuda()
+    out = rii.rii_query(index, q, 100, tids, toff, int(sizes.max()), L=L)
+    ref = rii.rii_query_noalloc(index, q, 100, tids, toff, int(sizes.max()), L=L)
+    assert torch.equal(out[0], ref[0]) and torch.equal(out[1], ref[1])
