@@ -95,3 +95,26 @@ def test_whole_queries(rii, N, K, Q, L, theta, most):
     out = rii.rii_query(index, q, 100, tids, toff, int(sizes.max()), L=L)
     ref = rii.rii_query_noalloc(index, q, 100, tids, toff, int(sizes.max()), L=L)
     assert torch.equal(out[0], ref[0]) and torch.equal(out[1], ref[1])
+
+
+# target sets around the cap: up to it all lists are asked for and all of the set is scored, whatever the threshold says
+@pytest.mark.parametrize("M,Ds,L,theta", [(16, 4, 700, 0), (16, 4, 700, 100), (8, 8, 1, 1), (64, 2, 4_000, 50), (12, 4, 300, 301)])
+def test_sets_up_to_the_cap(rii, oracle_lib, M, Ds, L, theta):
+    N, K = 4_000, 20
+    rng = np.random.default_rng(L + M)
+    cb = rng.standard_normal((M, 256, Ds)).astype(np.float32)
+    codes = rng.integers(0, 256, (N, M), dtype=np.uint8)
+    index = rii.Index(cb)
+    index.add(codes)
+    index.build_lists(codes[rng.permutation(N)[:K]].copy())
+    coarse, off, lids, _ = index.get_lists()
+    index.set_threshold(theta)
+    sizes = [0, 1, max(L - 1, 0), L, min(L + 1, N), min(2 * L, N), 99, 100, 301, N]
+    sets, tids, toff = target_sets(rng, N, sizes)
+    q = rng.standard_normal((len(sizes), M * Ds)).astype(np.float32)
+    for call in (rii.rii_query, rii.rii_query_noalloc):
+        ids, dist = call(index, torch.from_numpy(q).cuda(), 50, tids, toff, N, L=L)
+        ids, dist = t2n(ids), t2n(dist)
+        for i in range(len(sizes)):
+            ref = oracle_lib.query(cb, q[i], codes, coarse, off, lids, 50, L, theta, sets[i])
+            assert np.array_equal(ids[i], ref[0]) and np.array_equal(dist[i], ref[1]), (call, i)
