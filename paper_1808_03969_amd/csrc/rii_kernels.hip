@@ -1332,7 +1332,8 @@ static size_t coarse_ws_bytes(const rii_index* idx, int Q, int nprobe, bool tigh
 }
 
 static int coarse_rank(const rii_index* idx, const float* lut, int Q, int nprobe, int32_t* list_ids, float* list_d0,
-                       int out_stride, const int* qmode, int want_mode, void* ws, hipStream_t st, bool tight = false) {
+                       int out_stride, const int* qmode, int want_mode, void* ws, hipStream_t st, bool tight = false,
+                       const RankTables& tables = RankTables{}) {
   const int M = idx->M, K = idx->K;
   const bool in_lds = coarse_in_lds(K, nprobe);
   if (nprobe <= RII_MAX_TOPK && !in_lds) {
@@ -1349,16 +1350,18 @@ static int coarse_rank(const rii_index* idx, const float* lut, int Q, int nprobe
   }
   if (in_lds) {
     const size_t lds = rank_lds(M, K, nprobe, !split);
-    // one block per query: small blocks, several to a CU, when the queries fill the chip
-    const int threads = Q < kWantBlocks ? 1024 : K <= 2048 ? 256 : 512;
+    // one block per query: small blocks, several to a CU, when the queries fill the chip, of as many threads
+    // as fill it however few the LDS leaves room for (M = 64: 777 queries, K = 1000, 36 us with 256)
+    const int per_cu = (int)(160 * 1024 / lds);
+    const int threads = Q < kWantBlocks || per_cu <= 2 ? 1024 : per_cu <= 4 || K > 2048 ? 512 : 256;
     if (split) {
       int rc = set_lds(k_rank_lists<0, true>, lds);
       if (rc) return rc;
-      k_rank_lists<0, true><<<Q, threads, lds, st>>>(nullptr, K, M, nullptr, d0, nprobe, out_stride, list_ids, list_d0, qmode, want_mode);
+      k_rank_lists<0, true><<<Q, threads, lds, st>>>(nullptr, K, M, nullptr, d0, nprobe, out_stride, list_ids, list_d0, qmode, want_mode, tables);
     } else {
       DISPATCH_M(M, { int rc = set_lds(k_rank_lists<MT, false>, lds); if (rc) return rc;
                       k_rank_lists<MT, false><<<Q, threads, lds, st>>>(idx->d_coarse, K, M, lut, nullptr, nprobe, out_stride,
-                                                                       list_ids, list_d0, qmode, want_mode); });
+                                                                       list_ids, list_d0, qmode, want_mode, tables); });
     }
     RII_HIP(hipGetLastError());
     return RII_OK;
@@ -1580,7 +1583,11 @@ static int run_query(const rii_index* idx, const QueryPlan& p, const float* q, i
   int32_t* probe = reinterpret_cast<int32_t*>(w); w += p.probe_b;
   void* stage_ws = w;
 
-  launch_build_lut(idx, q, Q, lut, st, p.uniform ? stage_ws : nullptr);
+  // One branch for all queries, and that the lists: the ranking makes the tables where it reads them in LDS (with few queries a block's 16,384
+  // entries of M = 64 take a microsecond longer than the launch that they save).
+  const bool untouched = has_lists && coarse_in_lds(K, p.pmax) && !coarse_split(Q, K);  // (the ranking leaves the stage scratch alone then)
+  const bool by_rank = p.uniform && untouched && idx->N >= idx->theta && idx->Ds <= kRankTableDs && (idx->M <= 32 || Q > 32);
+  if (!by_rank) launch_build_lut(idx, q, Q, lut, st, p.uniform ? stage_ws : nullptr);
   PickPlan pick{};
   uint8_t* pick_ws = static_cast<uint8_t*>(p.pick);
   if (p.pick) pick = pick_plan(idx, Q, p.pmax, L, p.lin_rows, topk);
@@ -1623,9 +1630,10 @@ static int run_query(const rii_index* idx, const QueryPlan& p, const float* q, i
   if (rc) return rc;
   // inverted-index branch (mode 1); the scratch of the scan stage is reused in stream order
   if (has_lists && !all_linear) {
-    rc = coarse_rank(idx, lut, Q, p.pmax, probe, nullptr, p.pmax, qmode, 1, stage_ws, st, p.tight);
+    RankTables tables{};
+    if (by_rank) tables = RankTables{q, idx->d_cb, idx->D, idx->Ds, lut, static_cast<uint32_t*>(stage_ws), (int)(align_up((size_t)Q * 4, 256) / 4)};
+    rc = coarse_rank(idx, lut, Q, p.pmax, probe, nullptr, p.pmax, qmode, 1, stage_ws, st, p.tight, tables);
     if (rc) return rc;
-    const bool untouched = coarse_in_lds(K, p.pmax) && !coarse_split(Q, K);  // the ranking leaves the stage scratch alone
     rc = launch_ivf(idx, lut, Q, probe, p.pmax, p.pmax, nprobe_q, target_ids, target_offsets, L, topk, ids, dist, qmode,
                     1, stage_ws, st, p.uniform && untouched, p.tight, p.lists);
     if (rc) return rc;
