@@ -248,7 +248,8 @@ int rii_query(const rii_index_t* index, const float* q, int Q, int topk, const i
 /* rii_query for callers that cannot allocate device memory while they search: code that runs
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments,
  * same results as rii_query, by the same kernels but for large batches without target sets, which always go by table
- * look-ups here (the matrix products want more scratch); the scratch (distance tables, per-query plan, probed
+ * look-ups here, and lists with candidate cap and target set, which one kernel does here (matrix products and lists of
+ * picked members want more scratch); the scratch (distance tables, per-query plan, probed
  * lists, candidate lists, bounds and counters) is not the handle's but one array of
  * RII_NOALLOC_SCRATCH_BYTES in the library's own device image, which every GPU the library runs
  * on holds until the process ends.  The call makes no hipMalloc / hipFree and no other allocating
