@@ -26,7 +26,8 @@ struct rii_index {
   float* mx_fit = nullptr;  // [M][mx_dsp][256] -1/2 of the centred code words' pseudo-inverse
   float* mx_ch = nullptr;   // [M][mx_dsp][256] the fp16 code words as floats
   float* mx_scale = nullptr;      // what the coordinates and the distances are multiplied with
-  float* mx_b = nullptr;    // [M][256] |c|^2 of the fp16 code words
+  float* mx_b = nullptr;    // [M][256] |c|^2 of the code words
+  float* mx_bh = nullptr;   // [M][256] the same of the fp16 code words (posting lists)
   float* d_sym = nullptr;         // [M][256][256] code-word-to-code-word squared distances (lazy)
   // "Stored" code arrays (d_codes, d_codes_list, d_coarse_st) keep row r rotated by r bytes when
   // M is 8, 16 or 32 (stored[r][t] = code[r][(t + r) % M]), plain otherwise; see rii_kernels.hip.

@@ -845,7 +845,7 @@ void launch_fit(const rii_index* idx, const float* lut, int Q, int Qp, int nf, b
   // groups of 16 queries a wave goes through: one round of blocks (three a CU by their registers)
   const int per = std::max(1, (int)(((int64_t)(Qp / 16) * M + 12 * kWantBlocks - 1) / (12 * kWantBlocks)));
   const dim3 grid((unsigned)((Qp / 16 + 4 * per - 1) / (4 * per)), (unsigned)M);
-#define RII_FIT(DSP) k_fit_tables<DSP><<<grid, 256, 0, st>>>(lut, idx->mx_fit, idx->mx_ch, idx->mx_b, idx->mx_scale, M, idx->Ds, nf, Q, Qp, per, by_query, qfrag, part, left_n)
+#define RII_FIT(DSP) k_fit_tables<DSP><<<grid, 256, 0, st>>>(lut, idx->mx_fit, idx->mx_ch, by_query ? idx->mx_bh : idx->mx_b, idx->mx_scale, M, idx->Ds, nf, Q, Qp, per, by_query, qfrag, part, left_n)
   switch (idx->mx_dsp) {
     case 4: RII_FIT(4); break;
     case 8: RII_FIT(8); break;
@@ -957,7 +957,7 @@ int matrix_books(const rii_index* idx, hipStream_t st) {
   const bool known = hipStreamIsCapturing(st, &capture) == hipSuccess;
   if (!known) (void)hipGetLastError();
   k_matrix_scale<<<1, 1024, 0, st>>>(idx->d_cb, idx->M, idx->Ds, idx->mx_scale);
-  k_matrix_books<<<idx->M, 256, 0, st>>>(idx->d_cb, idx->mx_scale, idx->Ds, idx->mx_dsp, idx->mx_book, idx->mx_fit, idx->mx_ch, idx->mx_b);
+  k_matrix_books<<<idx->M, 256, 0, st>>>(idx->d_cb, idx->mx_scale, idx->Ds, idx->mx_dsp, idx->mx_book, idx->mx_fit, idx->mx_ch, idx->mx_b, idx->mx_bh);
   RII_HIP(hipGetLastError());
   idx->mx_ready = known && capture == hipStreamCaptureStatusNone;
   return RII_OK;
@@ -1801,7 +1801,7 @@ int rii_rotate(const float* R, int D, const float* x, int64_t n, float* y, void*
 static int matrix_dsp(int Ds) { return Ds <= 4 ? 4 : Ds <= 8 ? 8 : Ds <= 16 ? 16 : 32; }
 size_t rii_internal_matrix_bytes(int M, int Ds) {
   if (!m_supported(M) || M * Ds > kMxMaxD || Ds > kMxMaxDs) return 0;
-  return (size_t)M * 256 * (mx_entry_bytes(Ds) + 2 * matrix_dsp(Ds) * 4 + 4) + 256;
+  return (size_t)M * 256 * (mx_entry_bytes(Ds) + 2 * matrix_dsp(Ds) * 4 + 8) + 256;
 }
 int rii_internal_matrix_books(rii_index* idx, void* where) {
   const int M = idx->M, Ds = idx->Ds;
@@ -1810,7 +1810,8 @@ int rii_internal_matrix_books(rii_index* idx, void* where) {
   idx->mx_fit = reinterpret_cast<float*>(idx->mx_book + (size_t)M * 256 * mx_entry_bytes(Ds));
   idx->mx_ch = idx->mx_fit + (size_t)M * idx->mx_dsp * 256;
   idx->mx_b = idx->mx_ch + (size_t)M * idx->mx_dsp * 256;
-  idx->mx_scale = idx->mx_b + (size_t)M * 256;
+  idx->mx_bh = idx->mx_b + (size_t)M * 256;
+  idx->mx_scale = idx->mx_bh + (size_t)M * 256;
   return RII_OK;
 }
 
