@@ -36,7 +36,7 @@ int rii_index_set_scan_events(rii_index_t* index, void* start_event, void* stop_
  *       only when its first 16 look-ups leave it within the bound)
  *   scan by matrix products:
  *   [5] queries it left to the look-up kernels: tables that no query made, lists that ran over (what those kernels
- *       look up for them is not counted)
+ *       look up for them is not counted); those of a batch through posting lists by matrix products included
  *   [6] blocks that multiplied: tiles of 512 rows by groups of query tiles
  *   [7] unused (zero). */
 int rii_index_read_scan_counters(rii_index_t* index, uint64_t* counters_out);

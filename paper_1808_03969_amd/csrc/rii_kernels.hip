@@ -1020,7 +1020,8 @@ ListPlan list_plan(const rii_index* idx, int Q, int nprobe) {
   p.groups = take((size_t)Q * kLpGroups * 4);
   // (an eighth of the scratch there may be)
   p.cap = (int)std::min<int64_t>(std::max<int64_t>((int64_t)kMatrixScratch / 8 / 4 / Q, kLpLeast), kLpMost);
-  p.cand = take((size_t)Q * p.cap * 4);
+  // (scored before what is left of the batch needs its candidates there: topk a block)
+  p.cand = take(std::max((size_t)Q * p.cap * 4, (size_t)std::max(Q, kWantBlocks) * kWaveK * 8));
   p.total = at;
   return p;
 }
@@ -1054,9 +1055,14 @@ int launch_list_round(const ListProductsArgs& a, hipStream_t st) {
   k_list_products<M, DS, SEED><<<kWantBlocks, 64 * kLpWaves, lp_lds(M, DS), st>>>(a);
   return RII_OK;
 }
-// All but the queries that are left: their mode is 1 afterwards, the others' 0.
+// All but the queries that are left: their mode is 1 afterwards.
+struct ListLeft {
+  int* mode;
+  LeftOut out;
+  uint64_t* cand;  // for k_ivf_w
+};
 int launch_list_products(const rii_index* idx, const float* lut, int Q, const int32_t* probe, int probe_stride, int nprobe, int64_t L,
-                         int topk, int32_t* ids, float* dist, void* scratch, int** mode_out, hipStream_t st) {
+                         int topk, int32_t* ids, float* dist, void* scratch, ListLeft* left_out, hipStream_t st) {
   int rc = matrix_books(idx, st);
   if (rc) return rc;
   const int M = idx->M, K = idx->K;
@@ -1069,6 +1075,7 @@ int launch_list_products(const rii_index* idx, const float* lut, int Q, const in
   LeftOut left{};
   left.n = words(p.left); left.q = reinterpret_cast<int32_t*>(w + p.left + 256);
   left.arrays = words(p.left + 256) + p.Qp; left.stride = p.Qp;
+  left.counters = idx->ev_start && idx->ev_stop ? idx->d_scan_counters : nullptr;
   launch_fit(idx, lut, Q, p.Qp, p.nf, true, reinterpret_cast<uint16_t*>(w + p.query), part, left.n, st);
   uint32_t* counts = words(p.counts);
   k_fit_sums<<<(p.Qp + 255) / 256, 256, 0, st>>>(part, M, p.nf, Q, p.Qp, floats(p.cq), floats(p.lo), floats(p.hi), mode, words(p.cnt), left, counts, K + 2);
@@ -1091,12 +1098,12 @@ int launch_list_products(const rii_index* idx, const float* lut, int Q, const in
 #define RII_LIST_ROUND(MT, DS) if (M == MT && idx->Ds == DS) rc = launch_list_round<MT, DS, false>(a, st);
   RII_LIST_SHAPES(RII_SEED_ROUND)
   if (rc) return rc;
-  k_list_bound<<<(Q + 3) / 4, 256, 0, st>>>(a.groups, words(p.groups_n), Q, topk, floats(p.lo), floats(p.hi), mode, floats(p.cq), left.n, a.left_most);
+  k_list_bound<<<(Q + 3) / 4, 256, 0, st>>>(a.groups, words(p.groups_n), Q, topk, floats(p.lo), floats(p.hi), mode, floats(p.cq), left, a.left_most);
   RII_LIST_SHAPES(RII_LIST_ROUND)
 #undef RII_SEED_ROUND
 #undef RII_LIST_ROUND
   if (rc) return rc;
-  DISPATCH_M(M, k_list_score<MT><<<Q, kLpRanked, 0, st>>>(idx->d_codes_rows, idx->plane_rows, M, lut, a.cnt, a.cand, p.cap, topk, ids, dist, mode));
+  DISPATCH_M(M, k_list_score<MT><<<Q, kLpRanked, 0, st>>>(idx->d_codes_rows, idx->plane_rows, M, lut, a.cnt, a.cand, p.cap, topk, ids, dist, mode, left));
   FewArgs f{};
   f.codes = idx->d_codes_rows; f.plane = idx->plane_rows; f.M = M; f.lut = lut; f.N = idx->N;
   f.listed = a.cand; f.listed_cnt = a.cnt; f.listed_cap = p.cap; f.listed_cnt_stride = kMxCntStride;
@@ -1104,7 +1111,7 @@ int launch_list_products(const rii_index* idx, const float* lut, int Q, const in
   FewShape shape = few_shape(M, Q, p.cap, topk, FewRows::targets, false);
   shape.split = 1;
   rc = launch_few<kFewListed>(f, shape, Q, nullptr, true, st);
-  *mode_out = mode;
+  *left_out = ListLeft{mode, left, reinterpret_cast<uint64_t*>(w + p.cand)};
   return rc;
 }
 
@@ -1417,21 +1424,39 @@ static size_t ivf_ws_bytes(const rii_index* idx, int Q, int nprobe, int64_t L, i
   return std::max(few, kScanArrays * align_up((size_t)Q * 4, 256) + (size_t)Q * ivf_split(Q, nprobe) * topk * 8 + 256);
 }
 
+constexpr int64_t kLeftFewRows = 32768;
+constexpr uint32_t kLeftFewQueries = 64;
 static int launch_ivf(const rii_index* idx, const float* lut, int Q, const int32_t* probe, int probe_stride,
                       int nprobe, const int* nprobe_q, const int32_t* target_ids, const int64_t* target_offsets,
                       int64_t L, int topk, int32_t* ids, float* dist, const int* qmode, int want_mode, void* ws,
                       hipStream_t st, bool cleared = false, bool tight = false, void* products = nullptr) {
   const int M = idx->M;
   const bool capped = L > 0 && target_ids;
-  int* left = nullptr;
+  const int64_t rows = list_rows(idx, nprobe, capped ? 0 : L);
+  const bool few = nprobe <= kIvfMaxProbe && Q <= 65535 && (capped || topk > kWaveK || few_lists(M, Q, topk, rows));
   if (products) {  // (no target sets, one branch and one number of lists for all queries); below: what it leaves
-    const int rc = launch_list_products(idx, lut, Q, probe, probe_stride, nprobe, L, topk, ids, dist, products, &left, st);
+    ListLeft left;
+    int rc = launch_list_products(idx, lut, Q, probe, probe_stride, nprobe, L, topk, ids, dist, products, &left, st);
     if (rc) return rc;
-    qmode = left;
+    // Many members: queries that are left share the chip, where k_few would take them up to kLeftFewQueries of them (so many that each
+    // has four blocks; all others by k_few).  Few members: a block of k_few has done them as soon.
+    if (!few || rows > kLeftFewRows) {
+      IvfArgs a{};
+      a.codes_list = idx->d_codes_list; a.plane = idx->plane_list; a.list_ids = idx->d_list_ids; a.list_off = idx->d_list_off; a.M = M;
+      a.lut = lut; a.probe = probe; a.probe_stride = probe_stride; a.nprobe = nprobe; a.Lcap = L; a.k = topk; a.ids = ids; a.dist = dist;
+      a.tau_g = left.out.arrays; a.cand_cnt = left.out.arrays + left.out.stride; a.done_cnt = left.out.arrays + 3 * left.out.stride; a.cand = left.cand;
+      a.left_n = left.out.n; a.left_q = left.out.q; a.left_most = few ? kLeftFewQueries : 0xFFFFFFFFu; a.left_mode = left.mode;
+      const size_t lds = ivf_w_lds(M, nprobe);
+      const unsigned blocks = (unsigned)(few ? kWantBlocks : std::max(Q, kWantBlocks));
+      DISPATCH_M(M, { rc = set_lds0(k_ivf_w<MT, true>, lds); if (rc) return rc;
+                      k_ivf_w<MT, true><<<blocks, kScanThreads, lds, st>>>(a); });
+      RII_HIP(hipGetLastError());
+      if (!few) return RII_OK;
+    }
+    qmode = left.mode;
     want_mode = 1;
   }
-  const int64_t rows = list_rows(idx, nprobe, capped ? 0 : L);
-  if (nprobe <= kIvfMaxProbe && Q <= 65535 && (capped || topk > kWaveK || few_lists(M, Q, topk, rows))) {
+  if (few) {
     FewArgs f{};
     f.codes = idx->d_codes_list; f.plane = idx->plane_list; f.M = M; f.lut = lut; f.N = idx->N;
     f.target_ids = target_ids; f.target_offsets = target_offsets; f.list_ids = idx->d_list_ids; f.list_off = idx->d_list_off;
@@ -1876,6 +1901,7 @@ void rii_internal_matrix_room(rii_index* idx, size_t most) {
 int64_t rii_internal_left_chunks(int per, int64_t groups, int64_t rows, int64_t big) { return left_chunks(per, groups, rows, big); }
 int64_t rii_internal_left_blocks(int per, int64_t Q, int64_t big) { return left_blocks(per, Q, big); }
 int64_t rii_internal_left_lists(int64_t Q, int64_t big) { return left_lists(Q, big); }
+int64_t rii_internal_ivf_left_parts(int64_t n) { return ivf_left_parts((uint32_t)n); }
 
 int rii_internal_assign_matrix(const rii_index* idx, const uint8_t* codes, int64_t n, int64_t rot_base, int64_t plane,
                                const uint8_t* coarse, int K, int32_t* assign_out, void* scratch, const uint32_t** open_out,

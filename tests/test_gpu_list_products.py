@@ -173,3 +173,35 @@ def test_query_and_graph(rii):
         eager = rii.rii_adc_scan_ivf(index, lut, probe, 100)
         torch.cuda.synchronize()
         assert torch.equal(eager[0], out[0])
+
+
+# Queries that the products leave share the chip: none, one, some, as many as k_few does not take, more, all of them; lists of so many members that
+# the streaming kernel would have the batch, and fewer of them (k_few's); a cap inside a list
+@pytest.mark.parametrize("M,Ds,N,K,Q,nprobe,topk,L", [(16, 4, 1_200_003, 8, 300, 2, 10, 0), (8, 8, 1_200_000, 8, 420, 2, 128, 290_001), (32, 3, 900_000, 6, 300, 2, 10, 0),
+                                                      (64, 2, 600_000, 5, 150, 2, 10, 0), (12, 8, 600_001, 5, 200, 2, 20, 0),
+                                                      (16, 8, 400_000, 16, 800, 2, 100, 0), (32, 4, 320_000, 16, 700, 2, 100, 39_990),
+                                                      (12, 8, 400_000, 16, 500, 2, 64, 0)])
+def test_left_queries_share_the_chip(rii, M, Ds, N, K, Q, nprobe, topk, L):
+    from paper_1808_03969_amd import binding
+    lengths = np.full(K, N // K)
+    lengths[0] += N - lengths.sum()
+    index, codes, off, order, rng = make(rii, M, Ds, N, lengths, "normal", Q)
+    lut = rii.rii_build_lut(index, torch.from_numpy(rng.standard_normal((Q, M * Ds)).astype(np.float32)).cuda())
+    foreign = torch.from_numpy(rng.random((Q, M, 256)).astype(np.float32)).cuda() * lut.mean() * 2
+    probe = torch.from_numpy(np.stack([rng.permutation(K)[:nprobe] for _ in range(Q)]).astype(np.int32)).cuda()
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    for e in ev:
+        e.record()
+    binding.rii_index_set_scan_events(index, ev[0].cuda_event, ev[1].cuda_event)
+    for left in (0, 1, 3, 33, 64, 65, Q * 3 // 8, Q):
+        mixed = lut.clone()
+        at = torch.from_numpy(np.sort(rng.permutation(Q)[:left])).cuda()
+        mixed[at] = foreign[at]
+        parts = [rii.rii_adc_scan_ivf(index, mixed[i:i + 10].contiguous(), probe[i:i + 10].contiguous(), topk, L=L) for i in range(0, Q, 10)]
+        binding.rii_index_read_scan_counters(index)
+        ids, dist = rii.rii_adc_scan_ivf(index, mixed, probe, topk, L=L)
+        torch.cuda.synchronize()
+        # (with more than three eighths of the tables foreign nothing is multiplied)
+        assert binding.rii_index_read_scan_counters(index)[5] == (left if left <= Q * 3 // 8 else Q)
+        assert torch.equal(ids, torch.cat([p[0] for p in parts])) and torch.equal(dist, torch.cat([p[1] for p in parts])), left
+    binding.rii_index_set_scan_events(index, None, None)

@@ -29,3 +29,14 @@ def test_blocks_and_lists_fit(per, rows, Q, big):
             c = -(-rows // step)
             assert 1 <= c and groups * c <= grid
             assert n * c <= places or (c == 1 and n <= places)
+
+
+def test_parts_of_left_list_queries_fit():
+    """Blocks that queries left by the lists' products get: within the grid (one a query of the batch, 256 at least; 256 where k_few
+    takes more than 64 of them), which is also what their candidates have room for."""
+    parts = binding.load_library().rii_internal_ivf_left_parts
+    parts.restype, parts.argtypes = ctypes.c_int64, [ctypes.c_int64]
+    for n in list(range(1, 600)) + [4095, 4096, 65_535]:
+        assert 1 <= parts(n) and n * parts(n) <= max(n, 256)
+        assert n <= 256 or parts(n) == 1
+    assert parts(1) >= 16 and parts(64) == 4
