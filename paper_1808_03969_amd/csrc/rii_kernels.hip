@@ -986,7 +986,8 @@ int launch_matrix_batches(const rii_index* idx, const float* lut, int Q, const M
 struct ListPlan {
   int nf, Qp, cap;
   int64_t items;  // most work items
-  size_t query, cq, lo, hi, mode, cnt, left, part, counts, starts, groups_n, pairs, by_list, items_at, groups, cand, total;
+  FewShape few;   // for long lists of candidates
+  size_t query, cq, lo, hi, mode, cnt, left, part, counts, starts, groups_n, pairs, by_list, items_at, groups, cand, few_ws, total;
 };
 bool list_shape(int M, int Ds) {
 #define RII_SHAPE(MT, DS) if (M == MT && Ds == DS) return true;
@@ -994,7 +995,7 @@ bool list_shape(int M, int Ds) {
 #undef RII_SHAPE
   return false;
 }
-ListPlan list_plan(const rii_index* idx, int Q, int nprobe) {
+ListPlan list_plan(const rii_index* idx, int Q, int nprobe, int topk) {
   const int M = idx->M, K = idx->K;
   ListPlan p;
   p.nf = lp_frags(M, idx->Ds);
@@ -1022,6 +1023,8 @@ ListPlan list_plan(const rii_index* idx, int Q, int nprobe) {
   p.cap = (int)std::min<int64_t>(std::max<int64_t>((int64_t)kMatrixScratch / 8 / 4 / Q, kLpLeast), kLpMost);
   // (scored before what is left of the batch needs its candidates there: topk a block)
   p.cand = take(std::max((size_t)Q * p.cap * 4, (size_t)std::max(Q, kWantBlocks) * kWaveK * 8));
+  p.few = few_shape(M, Q, p.cap, topk, FewRows::targets, false);
+  p.few_ws = take(few_ws_bytes(p.few, Q));
   p.total = at;
   return p;
 }
@@ -1046,7 +1049,7 @@ bool list_products_apply(const rii_index* idx, int Q, int nprobe, int64_t L, int
 // Their scratch; NULL: query by query.
 void* list_scratch(const rii_index* idx, int Q, int nprobe, int64_t L, int topk, size_t lead, bool reserved, hipStream_t st) {
   if (!list_products_apply(idx, Q, nprobe, L, topk)) return nullptr;
-  return extra_scratch(idx, list_plan(idx, Q, nprobe).total, lead, reserved, st);
+  return extra_scratch(idx, list_plan(idx, Q, nprobe, topk).total, lead, reserved, st);
 }
 template <int M, int DS, bool SEED>
 int launch_list_round(const ListProductsArgs& a, hipStream_t st) {
@@ -1066,7 +1069,7 @@ int launch_list_products(const rii_index* idx, const float* lut, int Q, const in
   int rc = matrix_books(idx, st);
   if (rc) return rc;
   const int M = idx->M, K = idx->K;
-  const ListPlan p = list_plan(idx, Q, nprobe);
+  const ListPlan p = list_plan(idx, Q, nprobe, topk);
   uint8_t* w = static_cast<uint8_t*>(scratch);
   auto floats = [&](size_t o) { return reinterpret_cast<float*>(w + o); };
   auto words = [&](size_t o) { return reinterpret_cast<uint32_t*>(w + o); };
@@ -1103,14 +1106,13 @@ int launch_list_products(const rii_index* idx, const float* lut, int Q, const in
 #undef RII_SEED_ROUND
 #undef RII_LIST_ROUND
   if (rc) return rc;
-  DISPATCH_M(M, k_list_score<MT><<<Q, kLpRanked, 0, st>>>(idx->d_codes_rows, idx->plane_rows, M, lut, a.cnt, a.cand, p.cap, topk, ids, dist, mode, left));
+  DISPATCH_M(M, k_list_score<MT><<<Q, kLpRanked, 0, st>>>(idx->d_codes_rows, idx->plane_rows, M, lut, a.cnt, a.cand, p.cap, topk, ids, dist, mode, left,
+                                                        p.few.split > 1 ? words(p.few_ws) : nullptr, (int)(align_up((size_t)Q * 4, 256) / 4)));
   FewArgs f{};
   f.codes = idx->d_codes_rows; f.plane = idx->plane_rows; f.M = M; f.lut = lut; f.N = idx->N;
   f.listed = a.cand; f.listed_cnt = a.cnt; f.listed_cap = p.cap; f.listed_cnt_stride = kMxCntStride;
   f.k = topk; f.ids = ids; f.dist = dist; f.out_stride = topk; f.qmode = mode; f.want_mode = 2;
-  FewShape shape = few_shape(M, Q, p.cap, topk, FewRows::targets, false);
-  shape.split = 1;
-  rc = launch_few<kFewListed>(f, shape, Q, nullptr, true, st);
+  rc = launch_few<kFewListed>(f, p.few, Q, w + p.few_ws, true, st);
   *left_out = ListLeft{mode, left, reinterpret_cast<uint64_t*>(w + p.cand)};
   return rc;
 }

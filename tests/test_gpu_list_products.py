@@ -205,3 +205,40 @@ def test_left_queries_share_the_chip(rii, M, Ds, N, K, Q, nprobe, topk, L):
         assert binding.rii_index_read_scan_counters(index)[5] == (left if left <= Q * 3 // 8 else Q)
         assert torch.equal(ids, torch.cat([p[0] for p in parts])) and torch.equal(dist, torch.cat([p[1] for p in parts])), left
     binding.rii_index_set_scan_events(index, None, None)
+
+
+# Queries whose bound thousands of members share (copies of one code): more listed than are scored one a thread, up to what a list of candidates
+# holds and past it, in batches of few queries (several blocks for such a list) and of many
+@pytest.mark.parametrize("M,Ds,N,K,Q,topk,copies", [(16, 4, 200_000, 5, 300, 10, 250), (16, 4, 200_000, 5, 300, 10, 12_000), (16, 8, 200_000, 5, 340, 100, 16_000),
+                                                    (16, 8, 200_000, 5, 340, 100, 17_000), (8, 8, 200_000, 5, 700, 10, 5_000), (32, 3, 200_000, 5, 300, 128, 9_000),
+                                                    (64, 2, 200_000, 5, 200, 1, 15_000), (12, 8, 200_000, 5, 200, 100, 8_000), (16, 4, 200_000, 5, 2_600, 10, 7_000)])
+def test_long_lists_of_candidates(rii, M, Ds, N, K, Q, topk, copies):
+    from paper_1808_03969_amd import binding
+    rng = np.random.default_rng(M + copies)
+    cb = rng.standard_normal((M, 256, Ds)).astype(np.float32)
+    codes = rng.integers(0, 256, (N, M), dtype=np.uint8)
+    a = rng.permutation(np.repeat(np.arange(K), N // K))
+    codes[rng.permutation(np.nonzero(a == 0)[0])[:copies]] = codes[0]
+    off = np.arange(K + 1, dtype=np.int64) * (N // K)
+    index = rii.Index(cb)
+    index.add(codes)
+    index.set_lists(codes[:K].copy(), off, np.argsort(a, kind="stable").astype(np.int32))
+    q = rng.standard_normal((Q, M * Ds)).astype(np.float32)
+    q[::7] = np.concatenate([cb[m][codes[0][m]] for m in range(M)]) + 0.01 * q[::7]
+    lut = rii.rii_build_lut(index, torch.from_numpy(q).cuda())
+    probe = torch.from_numpy(np.stack([np.append(0, 1 + rng.permutation(K - 1)[:1]) for _ in range(Q)]).astype(np.int32)).cuda()
+    parts = [rii.rii_adc_scan_ivf(index, lut[i:i + 10].contiguous(), probe[i:i + 10].contiguous(), topk) for i in range(0, Q, 10)]
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    for e in ev:
+        e.record()
+    binding.rii_index_set_scan_events(index, ev[0].cuda_event, ev[1].cuda_event)
+    before = bytes_held(index)
+    for _ in range(2):
+        binding.rii_index_read_scan_counters(index)
+        ids, dist = rii.rii_adc_scan_ivf(index, lut, probe, topk)
+        torch.cuda.synchronize()
+        left = binding.rii_index_read_scan_counters(index)[5]
+        assert 0 <= left - (len(q[::7]) if copies > 16_384 else 0) <= 8  # (others that happen to be near the copies)
+        assert bytes_held(index) > before
+        assert torch.equal(ids, torch.cat([p[0] for p in parts])) and torch.equal(dist, torch.cat([p[1] for p in parts]))
+    binding.rii_index_set_scan_events(index, None, None)
