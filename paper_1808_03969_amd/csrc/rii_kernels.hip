@@ -1028,23 +1028,36 @@ ListPlan list_plan(const rii_index* idx, int Q, int nprobe, int topk) {
   p.total = at;
   return p;
 }
-// Which batches: from so many members on, all queries together, as pay for the launches (90 us) and for decoding the lists twice.
-// Microseconds query by query / here (lists of 1000 and nprobe 8 unless said; mixture: rows in 1000 clusters):
-//   M = 16, N = 10^6, 1500 queries 107 / 109, 4000 top-10 210 / 153, top-100 244 / 178, mixture 251 / 234 and 290 / 264, 4000 with 32
-//   lists 769 / 251 and 732 / 330;  N = 100,000, 4000 queries 164 / 122;  D = 96, N = 4 x 10^6, 2048 lists of 1953, 4000 queries 241 / 264,
-//   1500 with 32 lists 322 / 262;  M = 32, D = 96, N = 10^6, 4000 queries 249 / 176 and 272 / 220
-//   M = 8, where clusters share few codes and their members are listed by thousands:  10^6, 4000 queries 199 / 147, mixture 232 / 229;
-//   8 x 10^6, 500 lists, mixture, 32 of them, 500 queries 1227 / 1403, 1500 2935 / 2165
-//   kernels of two blocks a CU or less lose earlier:  M = 64, N = 500,000, 500 queries 142 / 142, 1500 339 / 167, N = 10^6, mixture, 1500
-//   182 / 202, 4000 457 / 335;  M = 12, N = 500,000, 1500 queries 243 / 146
+// Which batches: from so many members on, all queries together, as pay for the launches (90 us), for decoding the lists twice and for what
+// the filter lists.  The line lies where it no longer loses on rows in clusters that share codes (they list most, and their members
+// look alike to the bound), measured over the shapes that there are kernels for, 100,000 to 16 x 10^6 rows, 20 to 4096 lists, 4 to 100 of
+// them, top-10 and top-100.  Microseconds query by query / here, the lists in parentheses; "mixture": rows in clusters.
+//   at the line, mixture, top-100:  M = 8, N = 10^6 (8 of 1000) 399 / 359, 4 x 10^6 (16 of 2048) 536 / 522;  M = 16, 10^6 (8 of 1000) 310 / 286,
+//   4 x 10^6 (16 of 2048) 433 / 421;  M = 32, 10^6 (8 of 1000) 289 / 232;  M = 12, 100,000 (4 of 20) 102 / 100;  M = 64, 10^6 (8 of
+//   1000) 449 / 426, with 0.7 times the queries 319 / 366
+//   many short lists (the term with K):  M = 16, 10^6 (100 of 4096), 2653 queries top-10 303 / 248, top-100 239 / 274, 4421 368 / 348,
+//   4 x 10^6 (64 of 4096) 1818 queries top-100 354 / 383, 2160 437 / 401;  M = 8, 10^6 (100 of 4096) 2959 queries top-100 286 / 310, 4181 406 /
+//   370;  M = 12, 10^6 (100 of 4096) 704 queries top-10 146 / 174
+//   top-10 and rows that share little are ahead by 1.1 to 4 at the same points, M = 64 in long lists by 2 to 4
+//   lists of more than 12,000 (the bound is taken of the nearest 18,432 members only; M = 8 and 16 were ahead of the products for longer):  M = 8, 8 x
+//   10^6 (8 of 100), 383 queries top-100 1670 / 1620, 607 2190 / 2136, (32 of 250) 240 queries 1243 / 1342, 469 2277 / 1869;  M = 16, 300,000 (4 of
+//   20), 463 queries 149 / 165, 10^6 (16 of 60), 193 queries 282 / 295
+//   below the line, left to the look-ups:  M = 16, N = 10^6 (8 of 1000), 1500 queries 107 / 109;  D = 96, 4 x 10^6 (8 of 2048), 4000
+//   queries 241 / 264;  M = 64, 500,000, 500 queries 142 / 142, N = 10^6, mixture, 1500 182 / 202.  And, ahead by the products on rows that
+//   share little, 1500 queries (8 lists of 1000), M = 64, N = 500,000 339 / 167, M = 12 243 / 146, 4000 queries, N = 10^6, M = 16 210 / 153,
+//   M = 32 249 / 176, M = 8 199 / 147: what the rows are like is not known here.
 bool list_products_apply(const rii_index* idx, int Q, int nprobe, int64_t L, int topk) {
   const int M = idx->M;
   if (!idx->mx_book || !list_shape(M, idx->Ds) || topk > kWaveK || nprobe > kIvfMaxProbe || idx->K > kLpMaxLists || Q > 65535) return false;
   int64_t rows = idx->N / idx->K * nprobe;
   if (L > 0 && L < rows) rows = L;
   if (rows < 32 * (int64_t)topk) return false;  // (a bound is taken of groups of four and more members)
-  const double share = M == 8 ? 1.5 : rot_m(M) ? 1.0 : M == 64 ? 0.6 : 0.5;
-  return (double)Q * (double)rows >= share * (16e6 + 18.0 * (double)idx->N);
+  const bool lengthy = idx->N / idx->K > 12000;
+  const double share = M == 8 ? (lengthy ? 2.6 : 1.5) : M == 16 ? (lengthy ? 1.6 : 1.0) : M == 32 ? 1.0 : M == 64 || lengthy ? 0.6 : 0.5;
+  const bool many = topk >= kFewManyResults;
+  const double lists = M == 64 ? 8000.0 : M == 16 ? (many ? 12000.0 : 4500.0) : M == 8 ? (many ? 8000.0 : 0.0) : M == 12 ? 2500.0 : 0.0;
+  const double more = lists * idx->K + (M == 16 ? 1.5 * (double)idx->N : 0.0);
+  return (double)Q * (double)rows >= share * (16e6 + 18.0 * (double)idx->N) + more;
 }
 // Their scratch; NULL: query by query.
 void* list_scratch(const rii_index* idx, int Q, int nprobe, int64_t L, int topk, size_t lead, bool reserved, hipStream_t st) {

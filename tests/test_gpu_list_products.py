@@ -209,8 +209,8 @@ def test_left_queries_share_the_chip(rii, M, Ds, N, K, Q, nprobe, topk, L):
 
 # Queries whose bound thousands of members share (copies of one code): more listed than are scored one a thread, up to what a list of candidates
 # holds and past it, in batches of few queries (several blocks for such a list) and of many
-@pytest.mark.parametrize("M,Ds,N,K,Q,topk,copies", [(16, 4, 200_000, 5, 300, 10, 250), (16, 4, 200_000, 5, 300, 10, 12_000), (16, 8, 200_000, 5, 340, 100, 16_000),
-                                                    (16, 8, 200_000, 5, 340, 100, 17_000), (8, 8, 200_000, 5, 700, 10, 5_000), (32, 3, 200_000, 5, 300, 128, 9_000),
+@pytest.mark.parametrize("M,Ds,N,K,Q,topk,copies", [(16, 4, 200_000, 5, 420, 10, 250), (16, 4, 200_000, 5, 420, 10, 12_000), (16, 8, 200_000, 5, 430, 100, 16_000),
+                                                    (16, 8, 200_000, 5, 430, 100, 17_000), (8, 8, 200_000, 5, 700, 10, 5_000), (32, 3, 200_000, 5, 300, 128, 9_000),
                                                     (64, 2, 200_000, 5, 200, 1, 15_000), (12, 8, 200_000, 5, 200, 100, 8_000), (16, 4, 200_000, 5, 2_600, 10, 7_000)])
 def test_long_lists_of_candidates(rii, M, Ds, N, K, Q, topk, copies):
     from paper_1808_03969_amd import binding
@@ -242,3 +242,25 @@ def test_long_lists_of_candidates(rii, M, Ds, N, K, Q, topk, copies):
         assert bytes_held(index) > before
         assert torch.equal(ids, torch.cat([p[0] for p in parts])) and torch.equal(dist, torch.cat([p[1] for p in parts]))
     binding.rii_index_set_scan_events(index, None, None)
+
+
+# both sides of the line from which a batch goes by products: long lists (M = 8 and 16 take more queries there), many short ones (M = 16, M = 64)
+@pytest.mark.parametrize("M,Ds,N,K,nprobe,below,above", [(8, 8, 260_000, 20, 4, 1000, 1070), (16, 4, 260_000, 20, 4, 630, 670),
+                                                         (64, 2, 100_000, 1000, 50, 3600, 3850), (16, 4, 100_000, 1000, 50, 4300, 4600)])
+def test_line_of_the_rule(rii, M, Ds, N, K, nprobe, below, above):
+    index, codes, off, order, rng = make(rii, M, Ds, N, np.full(K, N // K), "normal", K)
+    lut = rii.rii_build_lut(index, torch.from_numpy(rng.standard_normal((above, M * Ds)).astype(np.float32)).cuda())
+    probe = torch.from_numpy(np.stack([rng.permutation(K)[:nprobe] for _ in range(above)]).astype(np.int32)).cuda()
+    small = rii.rii_adc_scan_ivf(index, lut[:below].contiguous(), probe[:below].contiguous(), 10)
+    torch.cuda.synchronize()
+    before = bytes_held(index)
+    ids, dist = rii.rii_adc_scan_ivf(index, lut, probe, 10)
+    torch.cuda.synchronize()
+    assert bytes_held(index) > before + above * 8192
+    assert torch.equal(ids[:below], small[0]) and torch.equal(dist[:below], small[1])
+    index.close()
+    index, *_ = make(rii, M, Ds, N, np.full(K, N // K), "normal", K)
+    before = bytes_held(index)
+    rii.rii_adc_scan_ivf(index, lut[:below].contiguous(), probe[:below].contiguous(), 10)
+    torch.cuda.synchronize()
+    assert bytes_held(index) < before + below * 8192  # (scratch of the look-ups)
