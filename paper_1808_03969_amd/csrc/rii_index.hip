@@ -369,6 +369,10 @@ void rii_index_destroy(rii_index_t* idx) {
   idx->d_codes_rows = nullptr;  // part of the same allocation
   if (idx->ws) (void)hipFree(idx->ws);
   if (idx->mx_ws) (void)hipFree(idx->mx_ws);
+  for (rii_extra* e : {&idx->lists_extra, &idx->pick_extra}) {
+    if (e->at) (void)hipFree(e->at);
+    for (int i = 0; i < e->n_kept; ++i) (void)hipFree(e->kept[i]);
+  }
   if (idx->d_scan_counters) (void)hipFree(idx->d_scan_counters);
   delete idx;
 }
@@ -504,6 +508,7 @@ int rii_index_info(const rii_index_t* idx, int64_t* info) {
   info[0] = N; info[1] = idx->D; info[2] = M; info[3] = idx->Ks; info[4] = K; info[5] = idx->theta;
   info[6] = (N + K) * M + 4 * N;
   int64_t dev = (int64_t)M * 256 * idx->Ds * 4 + (int64_t)rii_internal_matrix_bytes(M, idx->Ds) + idx->cap * M * (idx->d_codes_rows != idx->d_codes ? 2 : 1) + (int64_t)idx->ws_bytes + (int64_t)idx->mx_ws_bytes;
+  for (const rii_extra* e : {&idx->lists_extra, &idx->pick_extra}) dev += (int64_t)(e->bytes + e->kept_bytes);
   if (idx->d_sym) dev += M * 256 * 256 * 4;
   if (K > 0) dev += 2 * K * M + (K + 1) * 8 + N * 4 /*ids*/ + N * M /*list-ordered codes*/;
   info[7] = dev;

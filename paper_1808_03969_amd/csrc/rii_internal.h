@@ -8,6 +8,17 @@
 
 #include "rii.h"
 
+// Scratch that one kind of call can do without.
+struct rii_extra {
+  void* at = nullptr;
+  size_t bytes = 0;
+  bool held = false;          // a captured graph holds it: it stays, a larger one is put beside it
+  int wait = 0;               // calls that go without before the device is asked again
+  void* kept[64];             // smaller ones that captured graphs hold
+  int n_kept = 0;
+  size_t kept_bytes = 0;
+};
+
 struct rii_index {
   int D = 0, M = 0, Ks = 0, Ds = 0;
   int device = 0;
@@ -62,6 +73,9 @@ struct rii_index {
   mutable bool mx_held = false;   // a captured graph holds it: it stays
   mutable int mx_wait = 0;        // calls that go without before the device is asked again
   size_t mx_most = SIZE_MAX;      // more than that the device has no room for
+  // the same of lists by matrix products and of lists with target set and cap (see extra_scratch): what one of the three is refused,
+  // or a captured graph of it holds, is nothing to the others
+  mutable rii_extra lists_extra, pick_extra;
 
   bool bench_half_table = false;  // set around one launch by rii_bench_scan_linear_half only
   // optional measurement aid: events recorded right before / after the linear-scan kernel

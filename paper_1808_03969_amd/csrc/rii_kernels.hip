@@ -802,33 +802,40 @@ MatrixScratch matrix_scratch(const rii_index* idx, int Q, int topk, size_t lead,
   return s;
 }
 
-// Scratch that a call can do without: behind the `lead` bytes of the handle's, else an allocation of its own, the one that the
-// linear scan's products have (see matrix_scratch for when it is asked for); NULL: there is none.
-void* extra_scratch(const rii_index* idx, size_t need, size_t lead, bool reserved, hipStream_t st) {
+// Scratch that a call can do without: behind the `lead` bytes of the handle's, else an allocation of its kind's own (`own`; see
+// matrix_scratch for when it is asked for); NULL: there is none.  One that a captured graph holds stays as it is, a larger call gets a
+// second one: a small captured call must not send all later ones the slower way.
+void* extra_scratch(const rii_index* idx, rii_extra& own, size_t need, size_t lead, bool reserved, hipStream_t st) {
   if (need > kMatrixScratch) return nullptr;
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   const bool capturing = hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
   if (capturing) (void)hipGetLastError();
   const size_t behind = idx->ws_bytes > lead ? idx->ws_bytes - lead : 0;
   if (need <= behind) return static_cast<uint8_t*>(idx->ws) + lead;
-  if (need > idx->mx_ws_bytes) {
-    if (reserved || capturing || idx->mx_held) return nullptr;
-    if (idx->mx_wait > 0) {
-      --idx->mx_wait;
+  if (need > own.bytes) {
+    if (reserved || capturing || (own.held && own.n_kept == 64)) return nullptr;
+    if (own.wait > 0) {
+      --own.wait;
       return nullptr;
     }
     void* bigger = nullptr;
     if (need > idx->mx_most || hipMalloc(&bigger, need) != hipSuccess) {
       (void)hipGetLastError();
-      idx->mx_wait = kMatrixPatience;
+      own.wait = kMatrixPatience;
       return nullptr;
     }
-    if (idx->mx_ws) (void)hipFree(idx->mx_ws);  // (waits for the device)
-    idx->mx_ws = bigger;
-    idx->mx_ws_bytes = need;
+    if (own.held) {
+      own.kept[own.n_kept++] = own.at;
+      own.kept_bytes += own.bytes;
+      own.held = false;
+    } else if (own.at) {
+      (void)hipFree(own.at);  // (waits for the device)
+    }
+    own.at = bigger;
+    own.bytes = need;
   }
-  if (capturing) idx->mx_held = true;
-  return idx->mx_ws;
+  if (capturing) own.held = true;
+  return own.at;
 }
 
 // Whether rii_adc_scan_linear takes the products for such a batch (a device that has not refused is taken to have room).
@@ -1062,7 +1069,7 @@ bool list_products_apply(const rii_index* idx, int Q, int nprobe, int64_t L, int
 // Their scratch; NULL: query by query.
 void* list_scratch(const rii_index* idx, int Q, int nprobe, int64_t L, int topk, size_t lead, bool reserved, hipStream_t st) {
   if (!list_products_apply(idx, Q, nprobe, L, topk)) return nullptr;
-  return extra_scratch(idx, list_plan(idx, Q, nprobe, topk).total, lead, reserved, st);
+  return extra_scratch(idx, idx->lists_extra, list_plan(idx, Q, nprobe, topk).total, lead, reserved, st);
 }
 template <int M, int DS, bool SEED>
 int launch_list_round(const ListProductsArgs& a, hipStream_t st) {
@@ -1525,7 +1532,7 @@ int rii_adc_scan_ivf(const rii_index_t* idx, const float* lut, int Q, const int3
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (target_ids && L > 0 && pick_applies(idx, Q, nprobe, L, topk)) {
     const PickPlan p = pick_plan(idx, Q, nprobe, L, 0, topk);
-    if (void* pick = extra_scratch(idx, p.total, align_up(need, 256), reserved, st)) {
+    if (void* pick = extra_scratch(idx, idx->pick_extra, p.total, align_up(need, 256), reserved, st)) {
       FewArgs f{};
       rc = launch_pick(idx, p, Q, probe_lists, nprobe, nprobe, nullptr, target_ids, target_offsets, L, nullptr, pick, &f, st);
       if (rc) return rc;
@@ -1701,7 +1708,7 @@ int rii_query(const rii_index_t* idx, const float* q, int Q, int topk, const int
   else if (!target_ids)
     p.lists = list_scratch(idx, Q, p.pmax, L, topk, p.total, reserved, static_cast<hipStream_t>(stream));
   else if (idx->K > 0 && pick_applies(idx, Q, p.pmax, L, topk))
-    p.pick = extra_scratch(idx, pick_plan(idx, Q, p.pmax, L, p.lin_rows, topk).total, p.total, reserved, static_cast<hipStream_t>(stream));
+    p.pick = extra_scratch(idx, idx->pick_extra, pick_plan(idx, Q, p.pmax, L, p.lin_rows, topk).total, p.total, reserved, static_cast<hipStream_t>(stream));
   return run_query(idx, p, q, Q, topk, target_ids, target_offsets, L, ids, dist, idx->ws, static_cast<hipStream_t>(stream));
 }
 
@@ -1909,7 +1916,7 @@ float rii_internal_matrix_margin(int M, int Ds) { return mx_margin((M * Ds + 31)
 // What the device is taken to have room for at the most, for the products' scratch (tests of a full device).
 void rii_internal_matrix_room(rii_index* idx, size_t most) {
   idx->mx_most = most;
-  idx->mx_wait = 0;
+  idx->mx_wait = idx->lists_extra.wait = idx->pick_extra.wait = 0;
 }
 
 // What the launches for left-over queries ask for (see left_chunks).
