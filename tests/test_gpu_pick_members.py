@@ -118,3 +118,21 @@ def test_sets_up_to_the_cap(rii, oracle_lib, M, Ds, L, theta):
         for i in range(len(sizes)):
             ref = oracle_lib.query(cb, q[i], codes, coarse, off, lids, 50, L, theta, sets[i])
             assert np.array_equal(ids[i], ref[0]) and np.array_equal(dist[i], ref[1]), (call, i)
+
+
+# Numbers that are no identifier (against the precondition) are in no list: beside a bit map with a bit an identifier and with four, in sets that are
+# read in whole pieces and not, the result is that of the sets without them.
+@pytest.mark.parametrize("N", [50_000, 2_100_000])
+def test_numbers_that_are_no_identifier(rii, N):
+    index, codes, off, order, rng = make(rii, 16, 4, N, 50, N)
+    top = 2 ** 31 - 1
+    stray = [[-top - 1, -5, -1], [N, N + 1, N + 31, 1 << 20, 1 << 22, 1 << 25, top - 32, top], list(range(-3000, 0)), list(range(top - 5000, top))]
+    sizes = [10, 1000, 20_000, 49_999]
+    sets, tids, toff = target_sets(rng, N, sizes)
+    dirty = [np.unique(np.concatenate([t, np.array([x for x in more if not 0 <= x < N], np.int64)])).astype(np.int32) for t, more in zip(sets, stray)]
+    doff = torch.from_numpy(np.cumsum([0] + [len(t) for t in dirty])).cuda()
+    lut = rii.rii_build_lut(index, torch.from_numpy(rng.standard_normal((4, 64)).astype(np.float32)).cuda())
+    probe = torch.from_numpy(np.stack([rng.permutation(50)[:20] for _ in range(4)]).astype(np.int32)).cuda()
+    want = rii.rii_adc_scan_ivf(index, lut, probe, 100, tids, toff, L=3_000)
+    got = rii.rii_adc_scan_ivf(index, lut, probe, 100, torch.from_numpy(np.concatenate(dirty)).cuda(), doff, L=3_000)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
