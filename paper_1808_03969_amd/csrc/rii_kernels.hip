@@ -818,11 +818,17 @@ void* extra_scratch(const rii_index* idx, rii_extra& own, size_t need, size_t le
       --own.wait;
       return nullptr;
     }
+    // (a quarter more than needed, as in ensure_ws: calls that vary a little would wait for the device again and again)
     void* bigger = nullptr;
-    if (need > idx->mx_most || hipMalloc(&bigger, need) != hipSuccess) {
+    size_t ask = std::min(need + need / 4, kMatrixScratch);
+    if (ask > idx->mx_most || hipMalloc(&bigger, ask) != hipSuccess) {
       (void)hipGetLastError();
-      own.wait = kMatrixPatience;
-      return nullptr;
+      ask = need;
+      if (ask > idx->mx_most || hipMalloc(&bigger, ask) != hipSuccess) {
+        (void)hipGetLastError();
+        own.wait = kMatrixPatience;
+        return nullptr;
+      }
     }
     if (own.held) {
       own.kept[own.n_kept++] = own.at;
@@ -832,7 +838,7 @@ void* extra_scratch(const rii_index* idx, rii_extra& own, size_t need, size_t le
       (void)hipFree(own.at);  // (waits for the device)
     }
     own.at = bigger;
-    own.bytes = need;
+    own.bytes = ask;
   }
   if (capturing) own.held = true;
   return own.at;

@@ -116,3 +116,15 @@ def test_refusals_are_apart(rii):
     got, blocks = multiplied(rii, index, lambda: rii.rii_adc_scan_linear(index, part, 100))
     assert blocks > 0 and index.info()["device_bytes"] > refused
     assert torch.equal(got[0], torch.cat([w[0] for w in want])) and torch.equal(got[1], torch.cat([w[1] for w in want]))
+
+
+def test_calls_that_vary_a_little(rii):
+    """Filter calls of slowly growing caps ask the device for scratch now and then, not each time."""
+    index, rng = make(rii)
+    lut = tables(rii, index, rng, 300)
+    probe, tids, toff = filters(rng, 300_000, 20, 300, 6, 10_000)
+    held = set()
+    for L in range(1000, 1500, 10):
+        rii.rii_adc_scan_ivf(index, lut, probe, 20, tids, toff, L=L)
+        held.add(index.info()["device_bytes"])
+    assert len(held) <= 6
