@@ -1172,7 +1172,7 @@ int launch_pick(const rii_index* idx, const PickPlan& p, int Q, const int32_t* p
   uint8_t* w = static_cast<uint8_t*>(scratch);
   PickArgs a{};
   a.list_ids = idx->d_list_ids; a.list_off = idx->d_list_off; a.probe = probe; a.probe_stride = probe_stride; a.nprobe = nprobe;
-  a.nprobe_q = nprobe_q; a.target_ids = target_ids; a.target_offsets = target_offsets; a.qmode = qmode; a.Lcap = L;
+  a.nprobe_q = nprobe_q; a.target_ids = target_ids; a.target_offsets = target_offsets; a.qmode = qmode; a.Lcap = L; a.N = idx->N;
   a.cand = reinterpret_cast<int32_t*>(w); a.cnt = reinterpret_cast<uint32_t*>(w + p.cnt); a.cap = p.cap;
   // as many bits as there are identifiers, 128 KB of them at most, half of it where more than 1000 lists want their place in LDS
   const int64_t bits = std::min<int64_t>((idx->N + 127) / 128 * 128, nprobe <= 1000 ? 1 << 20 : 1 << 19);

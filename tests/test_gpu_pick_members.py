@@ -60,8 +60,12 @@ CASES = [
 @pytest.mark.parametrize("M,Ds,N,K,nprobe,L,topk,sizes", CASES)
 def test_against_the_definition(rii, M, Ds, N, K, nprobe, L, topk, sizes):
     index, codes, off, order, rng = make(rii, M, Ds, N, K, N + nprobe)
-    Q = 3 * len(sizes)
-    sets, tids, toff = target_sets(rng, N, sizes * 3)
+    check(rii, index, codes, off, order, rng, nprobe, L, topk, *target_sets(rng, N, sizes * 3))
+
+
+def check(rii, index, codes, off, order, rng, nprobe, L, topk, sets, tids, toff):
+    Q, (N, M), K = len(sets), codes.shape, len(off) - 1
+    Ds = index.info()["D"] // M
     q = torch.from_numpy(rng.standard_normal((Q, M * Ds)).astype(np.float32)).cuda()
     lut = rii.rii_build_lut(index, q)
     probe = np.stack([rng.permutation(K)[:nprobe] for _ in range(Q)]).astype(np.int32)
@@ -136,3 +140,19 @@ def test_numbers_that_are_no_identifier(rii, N):
     want = rii.rii_adc_scan_ivf(index, lut, probe, 100, tids, toff, L=3_000)
     got = rii.rii_adc_scan_ivf(index, lut, probe, 100, torch.from_numpy(np.concatenate(dirty)).cuda(), doff, L=3_000)
     assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+# Sets that are looked up member by member: everything, runs and clumps of identifiers, sets that thin out, all of a list and none of it, so that guesses of
+# a member's place are right and far off; fewer members wanted than a wave, than a block and than a round has, and more of them than
+# expected to look at.  Beside a bit map with several identifiers a bit, without samples: sets of fewer than the eight that are read at a time, and of a few more.
+@pytest.mark.parametrize("N,K,nprobe,L", [(600_000, 300, 1, 30), (600_000, 300, 3, 1_500), (600_000, 60, 1, 5_900), (600_000, 60, 9, 50_000), (2_100_000, 100, 3, 9_000)])
+def test_sets_of_every_kind(rii, N, K, nprobe, L):
+    index, codes, off, order, rng = make(rii, 8, 4, N, K, N + L)
+    every = np.arange(N)
+    first = np.sort(order[off[0]:off[1]])
+    kinds = [every, every[:-1], every[1:], every[N // 3:], every[:N // 2], every[(every // 1000) % 2 == 0], every[::3], every[(every * 7919) % 10 < 8],
+             np.unique((np.arange(N // 2) / (N // 2)) ** 3 * N // 1), np.setdiff1d(every, first), np.concatenate([first, every[-N // 4:]]),
+             first, every[:5], every[-7:], every[N // 2:N // 2 + 8], every[::N // 9], every[::N // 17]]
+    sets = [np.unique(s).astype(np.int32) for s in kinds] * 2
+    toff = torch.from_numpy(np.cumsum([0] + [len(s) for s in sets])).cuda()
+    check(rii, index, codes, off, order, rng, nprobe, L, 100, sets, torch.from_numpy(np.concatenate(sets)).cuda(), toff)
