@@ -1163,7 +1163,17 @@ PickPlan pick_plan(const rii_index* idx, int Q, int nprobe, int64_t L, int64_t l
   p.total = p.few_ws + few_ws_bytes(p.few, Q);
   return p;
 }
-bool pick_applies(const rii_index* idx, int Q, int nprobe, int64_t L, int topk) {
+// Lists of so few members and sets so small that k_few's capped form is done in the time that two kernels take (12 us of one query where these
+// take 15), up to a round of blocks.  What the sets' size is only the device knows: `largest` may be a guess.  Microseconds of rii_adc_scan_ivf
+// in the capped form / members first:  M = 32, 300,000 codes in lists of 1000, one list, L = 20, 20 queries with sets of 24,000 12.4 / 16.0, 300,000 13.1 / 16.0, 200 queries 13.1 / 17.0 and 31 / 17;  M = 16, 10^6 codes, one
+// query, L = 5, sets of 10,000 12.6 / 14.8, 160,000 15.0 / 14.7;  M = 64, 20 queries, two lists, L = 50, 40,000 16.9 / 18.5, three
+// lists, 20,000 24.2 / 16.9;  M = 8, 100,000 codes, two lists, L = 50, 4000 13.6 / 15.1, five lists, 2000, L = 100 21.4 / 15.5.
+bool pick_small(int M, int Q, int64_t members, int64_t L, double largest) {
+  return Q <= kWantBlocks && members + 10 * std::min<int64_t>(L, 1 << 20) <= (M == 8 || M == 16 ? 5000 : 3000) &&
+         Q * largest <= (M >= 32 ? 6e6 : 2e6) && largest <= (M >= 32 ? 3e5 : 1e5);
+}
+bool pick_applies(const rii_index* idx, int Q, int nprobe, int64_t L, int topk, double largest) {
+  if (pick_small(idx->M, Q, idx->N / idx->K * nprobe, L, largest)) return false;
   return nprobe <= kIvfMaxProbe && Q <= 65535 && few_scan(kSubset, idx->M, Q, topk, std::min(L, idx->N));
 }
 int launch_pick(const rii_index* idx, const PickPlan& p, int Q, const int32_t* probe, int probe_stride, int nprobe, const int* nprobe_q,
@@ -1536,7 +1546,10 @@ int rii_adc_scan_ivf(const rii_index_t* idx, const float* lut, int Q, const int3
   int rc = ensure_ws(idx, need);
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (target_ids && L > 0 && pick_applies(idx, Q, nprobe, L, topk)) {
+  // (the largest set for which Alg. 3 asks for so many lists; for a single one half-way, by their logarithms, from the smallest to everything)
+  const double all = (double)idx->N, one = std::min(all, (double)idx->K * (double)L);
+  const double largest = nprobe > 1 ? std::min(all, one / (nprobe - 1)) : std::sqrt(one * all);
+  if (target_ids && L > 0 && pick_applies(idx, Q, nprobe, L, topk, largest)) {
     const PickPlan p = pick_plan(idx, Q, nprobe, L, 0, topk);
     if (void* pick = extra_scratch(idx, idx->pick_extra, p.total, align_up(need, 256), reserved, st)) {
       FewArgs f{};
@@ -1713,7 +1726,7 @@ int rii_query(const rii_index_t* idx, const float* q, int Q, int topk, const int
     p.products = matrix_scratch(idx, Q, topk, p.lut_b + 2 * p.plan_b + p.probe_b, reserved, static_cast<hipStream_t>(stream));
   else if (!target_ids)
     p.lists = list_scratch(idx, Q, p.pmax, L, topk, p.total, reserved, static_cast<hipStream_t>(stream));
-  else if (idx->K > 0 && pick_applies(idx, Q, p.pmax, L, topk))
+  else if (idx->K > 0 && pick_applies(idx, Q, p.pmax, L, topk, (double)std::min(max_targets, idx->N)))
     p.pick = extra_scratch(idx, idx->pick_extra, pick_plan(idx, Q, p.pmax, L, p.lin_rows, topk).total, p.total, reserved, static_cast<hipStream_t>(stream));
   return run_query(idx, p, q, Q, topk, target_ids, target_offsets, L, ids, dist, idx->ws, static_cast<hipStream_t>(stream));
 }

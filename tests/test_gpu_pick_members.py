@@ -156,3 +156,13 @@ def test_sets_of_every_kind(rii, N, K, nprobe, L):
     sets = [np.unique(s).astype(np.int32) for s in kinds] * 2
     toff = torch.from_numpy(np.cumsum([0] + [len(s) for s in sets])).cuda()
     check(rii, index, codes, off, order, rng, nprobe, L, 100, sets, torch.from_numpy(np.concatenate(sets)).cuda(), toff)
+
+
+# Calls of few members and small sets on both sides of the lines between the two forms: members and cap, identifiers of all queries' sets, those of
+# one, a round of queries
+@pytest.mark.parametrize("M,N,K,nprobe,L,Q,sizes", [(16, 50_000, 50, 4, 99, 3, [1_000, 600]), (16, 50_000, 50, 4, 101, 3, [1_000, 600]), (32, 60_000, 60, 1, 199, 2, [6_000]),
+                                                    (32, 60_000, 60, 1, 201, 2, [6_000]), (64, 40_000, 40, 2, 10, 256, [390]), (64, 40_000, 40, 2, 10, 257, [390]),
+                                                    (8, 300_000, 300, 1, 5, 100, [1_500, 9_000]), (12, 20_000, 20, 3, 5, 20, [40]), (8, 300_000, 300, 1, 5, 40, [300_000, 1_500])])
+def test_few_members(rii, M, N, K, nprobe, L, Q, sizes):
+    index, codes, off, order, rng = make(rii, M, 4 if M < 32 else 2, N, K, N + L)
+    check(rii, index, codes, off, order, rng, nprobe, L, 20, *target_sets(rng, N, (sizes * Q)[:Q]))
