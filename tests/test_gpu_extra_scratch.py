@@ -128,3 +128,21 @@ def test_calls_that_vary_a_little(rii):
         rii.rii_adc_scan_ivf(index, lut, probe, 20, tids, toff, L=L)
         held.add(index.info()["device_bytes"])
     assert len(held) <= 6
+
+
+def test_no_set_reaches_the_lists(rii):
+    """No target set is as large as the threshold: nothing is asked for that only lists with target sets need (400 MB for 4000 queries
+    with a cap of 25,000), and the result is that of smaller batches."""
+    index, rng = make(rii)
+    index.set_threshold(30_000)
+    Q, size = 4000, 20
+    q = torch.from_numpy(rng.standard_normal((Q, 32)).astype(np.float32)).cuda()
+    _, tids, toff = filters(rng, 300_000, 20, Q, 1, size)
+    parts = [rii.rii_query(index, q[i:i + 50].contiguous(), 10, tids[i * size:(i + 50) * size].contiguous(), toff[:51].contiguous(), size, L=25_000)
+             for i in range(0, Q, 50)]
+    before = index.info()["device_bytes"]
+    out = rii.rii_query(index, q, 10, tids, toff, size, L=25_000)
+    torch.cuda.synchronize()
+    # (tables, plan, probed lists and the scan's own scratch, a quarter more)
+    assert index.info()["device_bytes"] < before + 1.25 * Q * (16 * 1024 + 8 + 20 * 4) + (64 << 20)
+    assert torch.equal(out[0], torch.cat([p[0] for p in parts])) and torch.equal(out[1], torch.cat([p[1] for p in parts]))
