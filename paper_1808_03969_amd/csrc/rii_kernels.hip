@@ -1676,8 +1676,8 @@ static int run_query(const rii_index* idx, const QueryPlan& p, const float* q, i
     f.codes = idx->d_codes_rows; f.plane = idx->plane_rows; f.M = idx->M; f.lut = lut; f.N = idx->N;
     f.k = topk; f.ids = ids; f.dist = dist; f.out_stride = topk; f.qmode = qmode;
     if (pick.joint) {  // both branches in one scan by identifiers: the target sets (mode 0), their first L members in the lists (mode 1)
-      f.target_ids = target_ids; f.target_offsets = target_offsets; f.want_mode = -1;
-      return launch_few<kFewSubset>(f, pick.few, Q, pick_ws + pick.few_ws, true, st);
+      f.target_ids = target_ids; f.target_offsets = target_offsets;
+      return launch_few<kFewJoint>(f, pick.few, Q, pick_ws + pick.few_ws, true, st);
     }
     f.want_mode = 1;
     return launch_few<kFewListed>(f, pick.few, Q, pick_ws + pick.few_ws, true, st);

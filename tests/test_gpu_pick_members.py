@@ -90,12 +90,22 @@ def check(rii, index, codes, off, order, rng, nprobe, L, topk, sets, tids, toff)
 @pytest.mark.parametrize("N,K,Q,L,theta,most", [(60_000, 60, 200, 900, 5_000, 60_000), (300_000, 40, 120, 2_000, 25_000, 200_000),
                                                  (60_000, 60, 33, 700, 1, 60_000)])
 def test_whole_queries(rii, N, K, Q, L, theta, most):
-    index, codes, off, order, rng = make(rii, 16, 4, N, K, Q)
+    whole_queries(rii, 16, N, K, Q, L, theta, most)
+
+
+# the same for every other kernel of the joint scan
+@pytest.mark.parametrize("M", [8, 12, 32, 64])
+def test_whole_queries_of_every_shape(rii, M):
+    whole_queries(rii, M, 60_000, 60, 200, 900, 5_000, 60_000)
+
+
+def whole_queries(rii, M, N, K, Q, L, theta, most):
+    index, codes, off, order, rng = make(rii, M, 64 // M, N, K, Q)
     index.set_threshold(theta)
     sizes = np.exp(rng.uniform(np.log(10), np.log(most), Q)).astype(int)
     sizes[:3] = 0, theta, max(theta - 1, 0)
     _, tids, toff = target_sets(rng, N, sizes)
-    q = torch.from_numpy(rng.standard_normal((Q, 64)).astype(np.float32)).cuda()
+    q = torch.from_numpy(rng.standard_normal((Q, index.info()["D"])).astype(np.float32)).cuda()
     out = rii.rii_query(index, q, 100, tids, toff, int(sizes.max()), L=L)
     ref = rii.rii_query_noalloc(index, q, 100, tids, toff, int(sizes.max()), L=L)
     assert torch.equal(out[0], ref[0]) and torch.equal(out[1], ref[1])
