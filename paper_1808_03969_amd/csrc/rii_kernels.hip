@@ -1404,9 +1404,13 @@ static int coarse_rank(const rii_index* idx, const float* lut, int Q, int nprobe
       if (rc) return rc;
       k_rank_lists<0, true><<<Q, threads, lds, st>>>(nullptr, K, M, nullptr, d0, nprobe, out_stride, list_ids, list_d0, qmode, want_mode, tables);
     } else {
-      DISPATCH_M(M, { int rc = set_lds(k_rank_lists<MT, false>, lds); if (rc) return rc;
-                      k_rank_lists<MT, false><<<Q, threads, lds, st>>>(idx->d_coarse, K, M, lut, nullptr, nprobe, out_stride,
-                                                                       list_ids, list_d0, qmode, want_mode, tables); });
+      // (two kernels: the choice in one cost calls that have their tables)
+#define RII_RANK(TABLES) DISPATCH_M(M, { int rc = set_lds(k_rank_lists<MT, false, TABLES>, lds); if (rc) return rc; \
+                                         k_rank_lists<MT, false, TABLES><<<Q, threads, lds, st>>>(idx->d_coarse, K, M, lut, nullptr, nprobe, out_stride, \
+                                                                                                  list_ids, list_d0, qmode, want_mode, tables); })
+      if (tables.q) { RII_RANK(true); }
+      else { RII_RANK(false); }
+#undef RII_RANK
     }
     RII_HIP(hipGetLastError());
     return RII_OK;
