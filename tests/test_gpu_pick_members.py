@@ -176,3 +176,30 @@ def test_sets_of_every_kind(rii, N, K, nprobe, L):
 def test_few_members(rii, M, N, K, nprobe, L, Q, sizes):
     index, codes, off, order, rng = make(rii, M, 4 if M < 32 else 2, N, K, N + L)
     check(rii, index, codes, off, order, rng, nprobe, L, 20, *target_sets(rng, N, (sizes * Q)[:Q]))
+
+
+# Every way through the kernel -- a bit map with a bit an identifier and with two, look-ups -- is taken (its lists are there afterwards) and agrees with
+# the form that has no lists, on a device without room for them.
+@pytest.mark.parametrize("M", [8, 12, 16, 32, 64])
+@pytest.mark.parametrize("N,sizes", [(60_000, [6_000, 59_000]), (1_100_000, [20_000, 900])])
+def test_lists_of_members_and_without(rii, M, N, sizes):
+    import ctypes
+    room = rii.load_library().rii_internal_matrix_room
+    room.restype, room.argtypes = None, [ctypes.c_void_p, ctypes.c_size_t]
+    K, Q, nprobe, L = 30, 400, 8, 2_900
+    index, codes, off, order, rng = make(rii, M, 64 // M, N, K, N + M)
+    other = rii.Index(np.zeros((M, 256, 64 // M), np.float32))
+    other.add(codes)
+    other.set_lists(index.get_lists()[0], off, order)
+    room(other.handle, 0)
+    _, tids, toff = target_sets(rng, N, sizes * (Q // 2))
+    lut = rii.rii_build_lut(index, torch.from_numpy(rng.standard_normal((Q, index.info()["D"])).astype(np.float32)).cuda())
+    probe = torch.from_numpy(np.stack([rng.permutation(K)[:nprobe] for _ in range(Q)]).astype(np.int32)).cuda()
+    out, grown = [], []
+    for i in (index, other):
+        before = i.info()["device_bytes"]
+        out.append(rii.rii_adc_scan_ivf(i, lut, probe, 100, tids, toff, L=L))
+        torch.cuda.synchronize()
+        grown.append(i.info()["device_bytes"] - before)
+    assert grown[0] >= grown[1] + Q * L * 4
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
