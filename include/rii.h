@@ -25,10 +25,13 @@
  *     scratch memory that the online calls reuse, so calls on one handle must be issued on
  *     one stream at a time.  A call that needs more scratch than the handle holds frees and
  *     re-allocates it first, which waits for the device; rii_index_reserve_workspace sizes it
- *     ahead of time.  Large batches over the whole database (from 64 to 512 queries on, 2^18 codes and more) are faster
- *     with up to 1 GB beside it, which the first such call asks the device for: not in a handle that was reserved, not
- *     while its stream is being captured, nor once a captured graph holds it, and a refusal is no error (the call then
- *     makes do with the scratch there is).
+ *     ahead of time.  Three kinds of calls are faster with more, up to 1 GB each beside it: large batches over the whole
+ *     database (from 64 to 512 queries on, 2^18 codes and more), large batches through posting lists without target
+ *     sets, and lists with target sets and a candidate cap (4 bytes a query and candidate, any number of queries).  The first
+ *     such call, and now and then a larger one, asks the device for it: not in a handle that was reserved and not
+ *     while its stream is being captured, and a refusal is no error (the call then makes do with the scratch there
+ *     is).  What a captured graph holds stays: batches over the whole database then make do with it, the other two kinds get
+ *     a second allocation beside it for a larger call.
  *   - Results are ordered by (distance, identifier) ascending; distances are squared
  *     (Eq. (2)), fp32, accumulated over sub-spaces in ascending order.  When fewer than R
  *     candidates exist the tail is filled with identifier -1 and distance +infinity.
@@ -127,7 +130,9 @@ int rii_index_build_lists(rii_index_t* index, const uint8_t* coarse, int K);
  * its code.  Deterministic for fixed (K, iters, seed).  Synchronous. */
 int rii_index_reconfigure(rii_index_t* index, int K, int iters, uint64_t seed);
 
-/* The threshold theta of Alg. 3 (default 0: always the inverted index when lists exist). */
+/* The threshold theta of Alg. 3 (default 0: always the inverted index when lists exist; target sets of no more
+ * than L members, which ask for all lists and never meet the cap, are scored by the linear scan whatever it is:
+ * the result is the same). */
 int rii_index_set_threshold(rii_index_t* index, int64_t theta);
 
 /* Options of a handle (rii_index_set_option).  None of them changes any result.
@@ -236,7 +241,7 @@ int rii_topk(const float* cand_dist, const int32_t* cand_ids, const int64_t* can
              int64_t max_segment, int topk, int32_t* ids, float* dist, void* stream);
 
 /* Alg. 3 for a batch: build the tables, then per query PQ-linear-scan over its target
- * identifiers when |S| < theta, else the inverted index over ceil(K L / |S|) lists (at most
+ * identifiers when |S| < theta (or |S| <= L: the same result), else the inverted index over ceil(K L / |S|) lists (at most
  * K) stopping after L candidates.  target_ids == NULL means the whole database (|S| = N).
  * An index without posting lists always takes the linear scan.
  *   q device [Q][D]; target_ids / target_offsets device (or both NULL); L >= 1;
