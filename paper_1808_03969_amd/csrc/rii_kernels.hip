@@ -1136,7 +1136,7 @@ int launch_list_products(const rii_index* idx, const float* lut, int Q, const in
                                                         p.few.split > 1 ? words(p.few_ws) : nullptr, (int)(align_up((size_t)Q * 4, 256) / 4)));
   FewArgs f{};
   f.codes = idx->d_codes_rows; f.plane = idx->plane_rows; f.M = M; f.lut = lut; f.N = idx->N;
-  f.listed = a.cand; f.listed_cnt = a.cnt; f.listed_cap = p.cap; f.listed_cnt_stride = kMxCntStride;
+  f.listed = a.cand; f.listed_cnt = a.cnt; f.listed_cap = p.cap; f.listed_cnt_stride = kMxCntStride; f.listed_alone = kLpAlone;
   f.k = topk; f.ids = ids; f.dist = dist; f.out_stride = topk; f.qmode = mode; f.want_mode = 2;
   rc = launch_few<kFewListed>(f, p.few, Q, w + p.few_ws, true, st);
   *left_out = ListLeft{mode, left, reinterpret_cast<uint64_t*>(w + p.cand)};

@@ -264,3 +264,9 @@ def test_line_of_the_rule(rii, M, Ds, N, K, nprobe, below, above):
     rii.rii_adc_scan_ivf(index, lut[:below].contiguous(), probe[:below].contiguous(), 10)
     torch.cuda.synchronize()
     assert bytes_held(index) < before + below * 8192  # (scratch of the look-ups)
+
+
+# Lists of candidates of as many rounds of a block as one does by itself, one more, and none more than the first
+@pytest.mark.parametrize("M,Ds,copies", [(16, 4, 5_900), (16, 4, 6_400), (16, 4, 900), (32, 3, 6_000), (32, 3, 6_400), (12, 8, 2_900), (12, 8, 3_300)])
+def test_lists_of_candidates_for_one_block(rii, M, Ds, copies):
+    test_long_lists_of_candidates(rii, M, Ds, 200_000, 5, 420, 10, copies)
