@@ -1008,7 +1008,11 @@ bool list_shape(int M, int Ds) {
 #undef RII_SHAPE
   return false;
 }
-ListPlan list_plan(const rii_index* idx, int Q, int nprobe, int topk) {
+int64_t list_members(const rii_index* idx, int nprobe, int64_t L) {  // that a query probes, in lists of the mean length
+  const int64_t rows = idx->N / idx->K * nprobe;
+  return L > 0 && L < rows ? L : rows;
+}
+ListPlan list_plan(const rii_index* idx, int Q, int nprobe, int64_t L, int topk) {
   const int M = idx->M, K = idx->K;
   ListPlan p;
   p.nf = lp_frags(M, idx->Ds);
@@ -1032,8 +1036,12 @@ ListPlan list_plan(const rii_index* idx, int Q, int nprobe, int topk) {
   p.by_list = take((size_t)pairs * sizeof(ListPair));
   p.items_at = take((size_t)p.items * sizeof(ListItem));
   p.groups = take((size_t)Q * kLpGroups * 4);
-  // (an eighth of the scratch there may be)
+  // An eighth of the scratch there may be.  More for members that a bound of the nearest kLpSeen of them will list: four times as many as there
+  // would be if the others were no farther away (clusters that share codes list three times that), up to half of the scratch.
   p.cap = (int)std::min<int64_t>(std::max<int64_t>((int64_t)kMatrixScratch / 8 / 4 / Q, kLpLeast), kLpMost);
+  const int64_t more = std::min<int64_t>(4 * topk * (list_members(idx, nprobe, L) / kLpSeen), kLpMostSeen);
+  const int64_t room = std::min<int64_t>((int64_t)kMatrixScratch / 2, (int64_t)kMatrixScratch * 3 / 4 - (int64_t)at) / 4 / Q;
+  p.cap = (int)std::max<int64_t>(p.cap, std::min(more, room));
   // (scored before what is left of the batch needs its candidates there: topk a block)
   p.cand = take(std::max((size_t)Q * p.cap * 4, (size_t)std::max(Q, kWantBlocks) * kWaveK * 8));
   p.few = few_shape(M, Q, p.cap, topk, FewRows::targets, false);
@@ -1052,9 +1060,11 @@ ListPlan list_plan(const rii_index* idx, int Q, int nprobe, int topk) {
 //   4 x 10^6 (64 of 4096) 1818 queries top-100 354 / 383, 2160 437 / 401;  M = 8, 10^6 (100 of 4096) 2959 queries top-100 286 / 310, 4181 406 /
 //   370;  M = 12, 10^6 (100 of 4096) 704 queries top-10 146 / 174
 //   top-10 and rows that share little are ahead by 1.1 to 4 at the same points, M = 64 in long lists by 2 to 4
-//   lists of more than 12,000 (the bound is taken of the nearest 18,432 members only; M = 8 and 16 were ahead of the products for longer):  M = 8, 8 x
-//   10^6 (8 of 100), 383 queries top-100 1670 / 1620, 607 2190 / 2136, (32 of 250) 240 queries 1243 / 1342, 469 2277 / 1869;  M = 16, 300,000 (4 of
-//   20), 463 queries 149 / 165, 10^6 (16 of 60), 193 queries 282 / 295
+//   lists of more than 12,000, mixture, top-100 (the bound is taken of the nearest 18,432 members only, which M = 8 lists most by):  M = 8, 6.5 x 10^6
+//   (8 of 72) 291 queries 1359 / 1320, 489 1600 / 1580, (27 of 72) 86 queries 873 / 1330, 145 1568 / 1490, 8 x 10^6 (8 of 100) 395 queries
+//   1635 / 1663, (32 of 250) 416 2151 / 1780;  top-10 and M = 16 are ahead from where shorter lists are:  M = 8, (27 of 72) 83 queries 769 / 749,
+//   (32 of 250) 239 1030 / 970;  M = 16, 6.5 x 10^6 (8 of 72) 202 queries top-100 937 / 715, (27 of 72) 60 873 / 730, 8 x 10^6 (32 of 250) 174
+//   1159 / 980;  M = 12, (8 of 72) 94 986 / 796.  Under 250,000 members a query:  M = 12, 300,000 (4 of 20) 182 queries top-100 121 / 124
 //   below the line, left to the look-ups:  M = 16, N = 10^6 (8 of 1000), 1500 queries 107 / 109;  D = 96, 4 x 10^6 (8 of 2048), 4000
 //   queries 241 / 264;  M = 64, 500,000, 500 queries 142 / 142, N = 10^6, mixture, 1500 182 / 202.  And, ahead by the products on rows that
 //   share little, 1500 queries (8 lists of 1000), M = 64, N = 500,000 339 / 167, M = 12 243 / 146, 4000 queries, N = 10^6, M = 16 210 / 153,
@@ -1062,12 +1072,11 @@ ListPlan list_plan(const rii_index* idx, int Q, int nprobe, int topk) {
 bool list_products_apply(const rii_index* idx, int Q, int nprobe, int64_t L, int topk) {
   const int M = idx->M;
   if (!idx->mx_book || !list_shape(M, idx->Ds) || topk > kWaveK || nprobe > kIvfMaxProbe || idx->K > kLpMaxLists || Q > 65535) return false;
-  int64_t rows = idx->N / idx->K * nprobe;
-  if (L > 0 && L < rows) rows = L;
+  const int64_t rows = list_members(idx, nprobe, L);
   if (rows < 32 * (int64_t)topk) return false;  // (a bound is taken of groups of four and more members)
-  const bool lengthy = idx->N / idx->K > 12000;
-  const double share = M == 8 ? (lengthy ? 2.6 : 1.5) : M == 16 ? (lengthy ? 1.6 : 1.0) : M == 32 ? 1.0 : M == 64 || lengthy ? 0.6 : 0.5;
   const bool many = topk >= kFewManyResults;
+  const bool lengthy = idx->N / idx->K > 12000 && (rows < 250000 || (M == 8 && many));
+  const double share = M == 8 ? (lengthy ? 2.6 : 1.5) : M == 16 ? (lengthy ? 1.6 : 1.0) : M == 32 ? 1.0 : M == 64 || lengthy ? 0.6 : 0.5;
   const double lists = M == 64 ? 8000.0 : M == 16 ? (many ? 12000.0 : 4500.0) : M == 8 ? (many ? 8000.0 : 0.0) : M == 12 ? 2500.0 : 0.0;
   const double more = lists * idx->K + (M == 16 ? 1.5 * (double)idx->N : 0.0);
   return (double)Q * (double)rows >= share * (16e6 + 18.0 * (double)idx->N) + more;
@@ -1075,7 +1084,7 @@ bool list_products_apply(const rii_index* idx, int Q, int nprobe, int64_t L, int
 // Their scratch; NULL: query by query.
 void* list_scratch(const rii_index* idx, int Q, int nprobe, int64_t L, int topk, size_t lead, bool reserved, hipStream_t st) {
   if (!list_products_apply(idx, Q, nprobe, L, topk)) return nullptr;
-  return extra_scratch(idx, idx->lists_extra, list_plan(idx, Q, nprobe, topk).total, lead, reserved, st);
+  return extra_scratch(idx, idx->lists_extra, list_plan(idx, Q, nprobe, L, topk).total, lead, reserved, st);
 }
 template <int M, int DS, bool SEED>
 int launch_list_round(const ListProductsArgs& a, hipStream_t st) {
@@ -1095,7 +1104,7 @@ int launch_list_products(const rii_index* idx, const float* lut, int Q, const in
   int rc = matrix_books(idx, st);
   if (rc) return rc;
   const int M = idx->M, K = idx->K;
-  const ListPlan p = list_plan(idx, Q, nprobe, topk);
+  const ListPlan p = list_plan(idx, Q, nprobe, L, topk);
   uint8_t* w = static_cast<uint8_t*>(scratch);
   auto floats = [&](size_t o) { return reinterpret_cast<float*>(w + o); };
   auto words = [&](size_t o) { return reinterpret_cast<uint32_t*>(w + o); };

@@ -266,6 +266,28 @@ def test_line_of_the_rule(rii, M, Ds, N, K, nprobe, below, above):
     assert bytes_held(index) < before + below * 8192  # (scratch of the look-ups)
 
 
+# Probes so long that the members the bound is taken of are a small part: without places for what it lists all queries would be left
+@pytest.mark.parametrize("M,Ds,K,nprobe,Q,topk,L", [(16, 4, 20, 20, 60, 128, 0), (8, 8, 16, 16, 120, 100, 0), (32, 2, 40, 40, 50, 128, 3_900_001)])
+def test_bound_of_a_small_part(rii, M, Ds, K, nprobe, Q, topk, L):
+    from paper_1808_03969_amd import binding
+    index, codes, off, order, rng = make(rii, M, Ds, 4_000_000, np.full(K, 4_000_000 // K), "normal", K)
+    lut = rii.rii_build_lut(index, torch.from_numpy(rng.standard_normal((Q, M * Ds)).astype(np.float32)).cuda())
+    probe = torch.from_numpy(np.stack([rng.permutation(K)[:nprobe] for _ in range(Q)]).astype(np.int32)).cuda()
+    parts = [rii.rii_adc_scan_ivf(index, lut[i:i + 10].contiguous(), probe[i:i + 10].contiguous(), topk, L=L) for i in range(0, Q, 10)]
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    for e in ev:
+        e.record()
+    binding.rii_index_set_scan_events(index, ev[0].cuda_event, ev[1].cuda_event)
+    before = bytes_held(index)
+    binding.rii_index_read_scan_counters(index)
+    ids, dist = rii.rii_adc_scan_ivf(index, lut, probe, topk, L=L)
+    torch.cuda.synchronize()
+    assert binding.rii_index_read_scan_counters(index)[5] <= Q // 10
+    binding.rii_index_set_scan_events(index, None, None)
+    assert bytes_held(index) > before + Q * 65_536
+    assert torch.equal(ids, torch.cat([p[0] for p in parts])) and torch.equal(dist, torch.cat([p[1] for p in parts]))
+
+
 # Lists of candidates of as many rounds of a block as one does by itself, one more, and none more than the first
 @pytest.mark.parametrize("M,Ds,copies", [(16, 4, 5_900), (16, 4, 6_400), (16, 4, 900), (32, 3, 6_000), (32, 3, 6_400), (12, 8, 2_900), (12, 8, 3_300)])
 def test_lists_of_candidates_for_one_block(rii, M, Ds, copies):
