@@ -1589,6 +1589,7 @@ struct QueryPlan {
   // the per-query modes fall away, which also lets a batch into the batched scan.
   bool uniform = false;
   bool tight = false;  // small scans get the least scratch (see few_shape)
+  bool no_lists = false;  // all target sets are below theta
   MatrixScratch products;  // of the linear scan by matrix products, where it goes that way
   void* lists = nullptr;   // the same of the inverted index
   void* pick = nullptr;    // of lists with target sets, whose members are found first
@@ -1613,6 +1614,7 @@ static int plan_query(const rii_index* idx, int Q, int topk, bool targets, int64
     if (lists(idx->theta) > RII_MAX_TOPK && K > RII_MAX_SORT) return RII_ERR_UNSUPPORTED;
     p->pmax = lists(p->theta);
   }
+  p->no_lists = targets && has_lists && max_targets < p->theta;
   // linear-scan queries have |S| < theta (and at most max_targets, N)
   int64_t lin_rows = targets ? std::min<int64_t>(max_targets, idx->N) : idx->N;
   if (has_lists && p->theta > 0) lin_rows = std::min<int64_t>(lin_rows, p->theta - 1);
@@ -1667,6 +1669,11 @@ static int run_query(const rii_index* idx, const QueryPlan& p, const float* q, i
   const bool untouched = has_lists && coarse_in_lds(K, p.pmax) && !coarse_split(Q, K);  // (the ranking leaves the stage scratch alone then)
   const bool by_rank = p.uniform && untouched && idx->N >= idx->theta && idx->Ds <= kRankTableDs && (idx->M <= 32 || Q > 32);
   if (!by_rank) launch_build_lut(idx, q, Q, lut, st, p.uniform ? stage_ws : nullptr);
+  // No set is as large as those that go through the lists: the ranking and the lists' scan would find no query of theirs (138 sets
+  // of up to 1844 identifiers, 28 lists of 184, M = 32: they took 10 of 41 us).
+  if (has_lists && p.no_lists)
+    return launch_scan(idx, idx->d_codes_rows, idx->plane_rows, idx->N, lut, Q, kSubset, target_ids, target_offsets, p.lin_rows, topk, ids, dist,
+                       topk, nullptr, 0, stage_ws, st, false, p.tight);
   PickPlan pick{};
   uint8_t* pick_ws = static_cast<uint8_t*>(p.pick);
   if (p.pick) pick = pick_plan(idx, Q, p.pmax, L, p.lin_rows, topk);
@@ -1739,7 +1746,7 @@ int rii_query(const rii_index_t* idx, const float* q, int Q, int topk, const int
     p.products = matrix_scratch(idx, Q, topk, p.lut_b + 2 * p.plan_b + p.probe_b, reserved, static_cast<hipStream_t>(stream));
   else if (!target_ids)
     p.lists = list_scratch(idx, Q, p.pmax, L, topk, p.total, reserved, static_cast<hipStream_t>(stream));
-  else if (idx->K > 0 && max_targets >= p.theta) {
+  else if (idx->K > 0 && !p.no_lists) {
     const PickPlan pick = pick_plan(idx, Q, p.pmax, L, p.lin_rows, topk);
     // (joint: the members are found in a kernel more and the sets of both branches scanned in one less, which few members earn as well: M = 8,
     // four sets of 85 to 1839, 95 lists of 160, L = 160 34.7 us in the capped form, 26.5 here)

@@ -203,3 +203,25 @@ def test_lists_of_members_and_without(rii, M, N, sizes):
         grown.append(i.info()["device_bytes"] - before)
     assert grown[0] >= grown[1] + Q * L * 4
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+# Batches none of whose sets reaches the lists: the linear scan of the sets, whatever the threshold and the cap, empty sets and the largest one among them
+@pytest.mark.parametrize("M,theta,L,largest", [(16, 0, 700, 700), (16, 701, 5, 700), (8, 30_001, 40, 30_000), (32, 2_000, 1, 1_999), (64, 501, 100, 500),
+                                               (12, 0, 40_000, 40_000)])
+def test_no_set_reaches_the_lists(rii, M, theta, L, largest):
+    N, K, Q, topk, Ds = 40_000, 60, 37, 20, 2
+    rng = np.random.default_rng(M + largest)
+    index = rii.Index(rng.standard_normal((M, 256, Ds)).astype(np.float32))
+    index.add(rng.integers(0, 256, (N, M), dtype=np.uint8))
+    index.reconfigure(K, iters=1, seed=3)
+    index.set_threshold(theta)
+    sizes = rng.integers(0, largest + 1, Q)
+    sizes[:3] = 0, 1, largest
+    ids = np.concatenate([np.sort(rng.permutation(N)[:s]) for s in sizes]).astype(np.int32)
+    off = np.zeros(Q + 1, np.int64)
+    off[1:] = np.cumsum(sizes)
+    q = torch.from_numpy(rng.standard_normal((Q, M * Ds)).astype(np.float32)).cuda()
+    tids, toff = torch.from_numpy(ids).cuda(), torch.from_numpy(off).cuda()
+    want = rii.rii_adc_scan_subset(index, rii.rii_build_lut(index, q), tids, toff, largest, topk)
+    got = rii.rii_query(index, q, topk, tids, toff, largest, L=L)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
